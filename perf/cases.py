@@ -13,6 +13,7 @@ import torch
 import paper_2505_23725_amd as mlc
 
 DEV = "cuda:0"
+COEFFS = (3.4445, -4.7750, 2.0315)      # of the Newton-Schulz polynomial
 PARAM_STD, GRAD_STD, DELTA_STD = 0.02, 1e-3, 1e-2        # as in synth_inputs.py
 NS_ITERS = 5
 DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
@@ -242,6 +243,111 @@ def run(state):
                    [[ts[k] for k in two] for ts in (g.worker_params, g.codes, g.scales, g.offsets, g.residuals)
                     if ts is not None])
     return out
+
+
+# ---- the same in 64 bits --------------------------------------------------------------
+def _orthogonalise(u):
+    a, b, c = COEFFS
+    x = u / (u.norm() + 1e-7)
+    wide = x.shape[0] <= x.shape[1]
+    for _ in range(NS_ITERS):
+        g = x @ x.T if wide else x.T @ x
+        p = b * g + c * (g @ g)
+        x = a * x + (p @ x if wide else x @ p)
+    return x
+
+
+def _levels(v, bits, offset, per_matrix):
+    """(dequantised values, scale, lower end) of [c][m][n] fp32 values.  Which level a value falls
+    on is defined in 32 bits (a tensor by a tensor: a true division); everything after that is in
+    64."""
+    r = v.reshape(v.shape[0], 1, -1) if per_matrix else v
+    if offset:
+        lo, levels = r.amin(-1, keepdim=True), 2 ** bits - 1
+        scale = (r.amax(-1, keepdim=True) - lo) / torch.full_like(lo, levels)
+        q = ((r - lo) / scale).round_().clamp_(0, levels)
+    else:
+        lo, levels = torch.zeros_like(r[..., :1]), 2 ** (bits - 1) - 1
+        scale = r.abs().amax(-1, keepdim=True) / torch.full_like(lo, levels)
+        q = (r / scale).round_().clamp_(-levels, levels)
+    sent = q.double() * scale.double() + lo.double()
+    return sent.reshape(v.shape), scale.reshape(-1).double(), lo.reshape(-1).double()
+
+
+def _exact_outer(state):
+    hp, fraction = state["hp"], state.get("fraction")
+    out = []
+    for g in state["groups"]:
+        theta = g.global_param
+        c = theta.shape[0]
+        mean = torch.zeros(theta.shape, dtype=torch.float64, device=DEV)
+        scales, offsets, residuals = [], [], []
+        for k, w in enumerate(g.worker_params):
+            if not hp.quant_bits and fraction is None:
+                mean += theta.double() - w.double()
+                continue
+            v = theta.float() - w.float()
+            if hp.error_feedback:
+                v = g.residuals[k] * hp.ef_beta + v
+            if fraction is None:
+                sent, scale, lo = _levels(v, hp.quant_bits, hp.quant_offset, hp.quant_per_matrix)
+                scales.append(scale)
+                offsets.append(lo)
+            else:
+                per = v[0].numel()
+                kept = min(per, max(1, math.ceil(fraction * per)))
+                tau = torch.stack([m.abs().flatten().sort(descending=True).values[kept - 1] for m in v])
+                sent = torch.where(v.abs() >= tau[:, None, None], v, torch.zeros_like(v)).double()
+                scales.append(tau.double())
+            residuals.append(v.double() - sent)
+            mean += sent
+        psi = mean / hp.K
+        u = hp.mu * g.outer_momentum.double() + hp.eta_out * psi
+        new = theta.double() - hp.mu * u - hp.eta_out * psi
+        two = range(0, hp.K, max(1, hp.K - 1))
+        rows = [[new if hp.write_back else w.double() for w in g.worker_params]]
+        if g.codes is not None:
+            rows.append([None] * hp.K)                    # whole numbers
+        if g.scales is not None:
+            rows.append(scales)
+        if g.offsets is not None:
+            rows.append(offsets)
+        if g.residuals is not None:
+            rows.append(residuals)
+        out.append([new, u] + [[r[k] for k in two] for r in rows])
+    return out
+
+
+def exact(case, seed):
+    state = prepare(case, seed)
+    kind, hp = state["kind"], state.get("hp")
+    if kind == "ns":
+        return torch.stack([_orthogonalise(x.double()) for x in state["x"]])
+    if kind == "inner":
+        out = []
+        for g in state["groups"]:
+            w, m = g.param.double(), g.momentum.double()
+            for i in range(w.shape[0]):
+                grad = g.grad[i].double()
+                m[i] = hp.beta * m[i] + grad
+                o = _orthogonalise(grad + hp.beta * m[i])
+                w[i] -= hp.eta * hp.weight_decay * w[i] + hp.eta * g.lr_scale * o
+            out.append((w, m))
+        return out
+    if kind == "adamw":
+        theta, grad, m, v = [t.double() for t in state["flat"]]
+        new = [theta.clone(), m.clone(), v.clone()]
+        ends = 0
+        for n in [t[0].numel() for t in state["tensors"]]:
+            s = slice(ends, ends + n)
+            new[1][s] = hp.beta1 * m[s] + (1 - hp.beta1) * grad[s]
+            new[2][s] = hp.beta2 * v[s] + (1 - hp.beta2) * grad[s] ** 2
+            mh = new[1][s] / (1 - hp.beta1 ** hp.step)
+            vh = new[2][s] / (1 - hp.beta2 ** hp.step)
+            new[0][s] -= hp.lr * mh / (vh.sqrt() + hp.eps) + hp.lr * hp.weight_decay * theta[s]
+            ends += (n + 15) // 16 * 16
+        return new
+    return _exact_outer(state)
 
 
 def work(case):
