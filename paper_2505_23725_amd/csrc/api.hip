@@ -144,6 +144,22 @@ static bool can_fuse_update(const NsPlan& p, int param_dtype, int iters) {
 }
 constexpr int MAX_NS_JOBS = 16;
 
+// The products work on X with its short side as rows, [sp][lp]: a tall matrix is stored
+// transposed when its input is laid out (the iteration commutes with transposition), and its
+// last product writes the result the other way round again.  Every Gram product then reads
+// both operands along K, and tall and wide matrices of one shape share launches.  Without
+// iterations, and in the one-launch chain, X keeps the caller's orientation.
+static bool store_transposed(const NsPlan& p, int iters) {
+  return iters >= 1 && p.mp > p.np && !ns_chain_small_fits(p.mp, p.np);
+}
+struct XLayout { int64_t sp, lp, ld, stride; };
+static XLayout x_layout(const NsPlan& p) {
+  const int64_t lp = p.mp > p.np ? p.mp : p.np;
+  return XLayout{p.sp, lp, lp + PITCH_SKEW, p.sp * (lp + PITCH_SKEW)};     // never larger than mp * ldx
+}
+
+static int64_t x_pitch(const NsPlan& p, int iters) { return store_transposed(p, iters) ? x_layout(p).ld : p.ldx; }
+
 // The three products of one iteration of job j (X = current buffer, Xn = the other one).
 //
 // The polynomial is folded before the last product: B' = a I + b A + c A^2, X <- B' X,
@@ -151,15 +167,14 @@ constexpr int MAX_NS_JOBS = 16;
 // folded into the first iteration's scalars: A_0 = s^2 U U^T, X_1 = s B' U.
 static GemmDesc gram_desc(const NsJob& j, const bf16_t* X, bool first) {
   const NsPlan& p = j.p;
-  const bool wide = p.mp <= p.np;
-  const int64_t xs = p.mp * p.ldx, ss = p.sp * p.lds;
+  const XLayout x = x_layout(p);
   GemmDesc g{};
-  // Gram matrix: A = X X^T (wide) or X^T X (tall)
-  g.A = X; g.lda = p.ldx; g.strideA = xs; g.a_kstrided = wide ? 0 : 1;
-  g.B = X; g.ldb = p.ldx; g.strideB = xs; g.b_kstrided = wide ? 0 : 1;
-  g.D = j.w.A; g.ldd = p.lds; g.strideD = ss;
+  // Gram matrix: A = X X^T
+  g.A = X; g.lda = x.ld; g.strideA = x.stride;
+  g.B = X; g.ldb = x.ld; g.strideB = x.stride;
+  g.D = j.w.A; g.ldd = p.lds; g.strideD = p.sp * p.lds;
   g.C = nullptr;
-  g.M = (int)p.sp; g.N = (int)p.sp; g.K = (int)(wide ? p.np : p.mp); g.batch = (int)j.chunk;
+  g.M = (int)p.sp; g.N = (int)p.sp; g.K = (int)x.lp; g.batch = (int)j.chunk;
   g.alpha = 1.f; g.beta = 0.f; g.gamma = 0.f;
   g.bscale = first ? j.w.scale : nullptr; g.bscale_pow = 2;
   g.symmetric = 1;     // only the lower triangle of tiles is computed, then mirrored
@@ -168,11 +183,10 @@ static GemmDesc gram_desc(const NsJob& j, const bf16_t* X, bool first) {
 static GemmDesc poly_desc(const NsJob& j, float a, float b, float c) {
   const NsPlan& p = j.p;
   const int64_t ss = p.sp * p.lds;
-  // Polynomial: B' = c A A + b A + a I.  A is symmetric, so either operand may be read
-  // along rows or along columns; the K-contiguous LDS path is the faster one.
+  // Polynomial: B' = c A A + b A + a I.  A is symmetric and is read along rows for both operands.
   GemmDesc g{};
-  g.A = j.w.A; g.lda = p.lds; g.strideA = ss; g.a_kstrided = 0;
-  g.B = j.w.A; g.ldb = p.lds; g.strideB = ss; g.b_kstrided = 0;
+  g.A = j.w.A; g.lda = p.lds; g.strideA = ss;
+  g.B = j.w.A; g.ldb = p.lds; g.strideB = ss;
   g.D = j.w.B; g.ldd = p.lds; g.strideD = ss;
   g.C = j.w.A; g.ldc = p.lds; g.strideC = ss;
   g.M = g.N = g.K = (int)p.sp; g.batch = (int)j.chunk;
@@ -180,22 +194,19 @@ static GemmDesc poly_desc(const NsJob& j, float a, float b, float c) {
   g.symmetric = 1;
   return g;
 }
-static GemmDesc apply_desc(const NsJob& j, const bf16_t* X, bf16_t* Xn, bool first) {
+static GemmDesc apply_desc(const NsJob& j, const bf16_t* X, bf16_t* Xn, bool first, bool last) {
   const NsPlan& p = j.p;
-  const bool wide = p.mp <= p.np;
-  const int64_t xs = p.mp * p.ldx, ss = p.sp * p.lds;
-  // Apply: X <- B' X (wide) or X B' (tall; B' symmetric)
+  const XLayout x = x_layout(p);
+  // Apply: X <- B' X; X has k as its slow index
   GemmDesc g{};
-  if (wide) {     // B' symmetric: read along rows (K-contiguous); X has k as its slow index
-    g.A = j.w.B; g.lda = p.lds; g.strideA = ss; g.a_kstrided = 0;
-    g.B = X; g.ldb = p.ldx; g.strideB = xs; g.b_kstrided = 1;
-    g.M = (int)p.mp; g.N = (int)p.np; g.K = (int)p.mp;
-  } else {
-    g.A = X; g.lda = p.ldx; g.strideA = xs; g.a_kstrided = 0;
-    g.B = j.w.B; g.ldb = p.lds; g.strideB = ss; g.b_kstrided = 0;
-    g.M = (int)p.mp; g.N = (int)p.np; g.K = (int)p.np;
+  g.A = j.w.B; g.lda = p.lds; g.strideA = p.sp * p.lds;
+  g.B = X; g.ldb = x.ld; g.strideB = x.stride; g.b_kstrided = 1;
+  g.M = (int)p.sp; g.N = (int)x.lp; g.K = (int)p.sp;
+  g.D = Xn; g.ldd = x.ld; g.strideD = x.stride;
+  if (last) {          // back to the caller's orientation
+    g.ldd = p.ldx; g.strideD = p.mp * p.ldx;
+    g.transposed = p.mp > p.np;
   }
-  g.D = Xn; g.ldd = p.ldx; g.strideD = xs;
   g.C = nullptr; g.batch = (int)j.chunk;
   g.alpha = 1.f; g.beta = 0.f; g.gamma = 0.f;
   g.bscale = first ? j.w.scale : nullptr; g.bscale_pow = 1;
@@ -203,7 +214,7 @@ static GemmDesc apply_desc(const NsJob& j, const bf16_t* X, bf16_t* Xn, bool fir
 }
 // The same product with the parameter update as its epilogue: D = decay * W - step * (B' X).
 static GemmDesc apply_update_desc(const NsJob& j, const bf16_t* X, bool first) {
-  GemmDesc g = apply_desc(j, X, j.fuse_W, first);
+  GemmDesc g = apply_desc(j, X, j.fuse_W, first, true);
   g.ldd = j.p.n; g.strideD = j.p.m * j.p.n;
   g.C = j.fuse_W; g.ldc = g.ldd; g.strideC = g.strideD;
   g.alpha = -j.fuse_step; g.beta = j.fuse_decay;
@@ -245,7 +256,7 @@ int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float 
     const bool last = it + 1 == iters;
     for (int i = 0; i < nbig; ++i)
       d[i] = (last && big[i]->fuse_W) ? apply_update_desc(*big[i], big[i]->w.X[cur], it == 0)
-                                      : apply_desc(*big[i], big[i]->w.X[cur], big[i]->w.X[cur ^ 1], it == 0);
+                                      : apply_desc(*big[i], big[i]->w.X[cur], big[i]->w.X[cur ^ 1], it == 0, last);
     rc = launch_ns_gemm_set(d, nbig, stream);
     if (rc != MLC_OK) return rc;
     cur ^= 1;
@@ -324,7 +335,8 @@ static int newton_schulz_in(const void* in, void* out, int io_dtype, int64_t cou
     const NsBuffers w = carve(p, workspace, chunk);
     const unsigned char* src = (const unsigned char*)in + (size_t)c0 * m * n * es;
     unsigned char* dst = (unsigned char*)out + (size_t)c0 * m * n * es;
-    rc = launch_ns_load(src, io_dtype, w.X[0], w.partials, p.nblk, cc, m, n, p.mp, p.np, p.ldx, stream);
+    rc = launch_ns_load(src, io_dtype, w.X[0], w.partials, p.nblk, cc, m, n, p.mp, p.np, x_pitch(p, iters),
+                        store_transposed(p, iters), stream);
     if (rc != MLC_OK) return rc;
     int res = 0;
     rc = run_ns_chunk(p, w, cc, iters, a, b, c, eps, stream, &res);
@@ -462,7 +474,8 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
       }
       base += jobs[gi].p.per_matrix * (size_t)g.count;
       rc = launch_momentum(g.grad, g.grad_dtype, g.momentum, jobs[gi].w.X[0], jobs[gi].w.partials,
-                           jobs[gi].p.nblk, g.count, g.m, g.n, jobs[gi].p.mp, jobs[gi].p.np, jobs[gi].p.ldx,
+                           jobs[gi].p.nblk, g.count, g.m, g.n, jobs[gi].p.mp, jobs[gi].p.np,
+                           x_pitch(jobs[gi].p, hp->ns_iters), store_transposed(jobs[gi].p, hp->ns_iters),
                            hp->beta, hp->nesterov, stream);
       if (rc != MLC_OK) return rc;
     }
@@ -491,7 +504,8 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
       unsigned char* param = (unsigned char*)g.param + c0 * mat * elem_size(g.param_dtype);
       float* mom = g.momentum + c0 * mat;
       rc = launch_momentum(grad, g.grad_dtype, mom, w.X[0], w.partials, p.nblk, cc, g.m, g.n, p.mp,
-                           p.np, p.ldx, hp->beta, hp->nesterov, stream);
+                           p.np, x_pitch(p, hp->ns_iters), store_transposed(p, hp->ns_iters), hp->beta,
+                           hp->nesterov, stream);
       if (rc != MLC_OK) return rc;
       int res = 0;
       const bool fuse = can_fuse_update(p, g.param_dtype, hp->ns_iters);

@@ -137,13 +137,13 @@ struct LaunchScope {
 };
 
 // ---- batched bf16 GEMM of Newton-Schulz (ns_gemm.hip) ------------------------------
-// D[b] = alpha_b * op(A[b]) * op(B[b])^T + beta * C[b] + gamma * I, all bf16, fp32 accum.
-// Operand A is M x K, operand B is N x K.  An operand is either K-contiguous (element
-// (i,k) at ptr[i*ld + k]) or K-strided (element (i,k) at ptr[k*ld + i]).
+// D[b] = alpha_b * A[b] * op(B[b])^T + beta * C[b] + gamma * I, all bf16, fp32 accum.
+// Operand A is M x K, operand B is N x K.  A is K-contiguous (element (i,k) at
+// ptr[i*ld + k]); B is that or K-strided (element (i,k) at ptr[k*ld + i]).
 // M, N and K must be multiples of 128; all leading dimensions and batch
 // strides multiples of 8 elements.
 struct GemmDesc {
-  const bf16_t* A; int64_t lda, strideA; int a_kstrided;
+  const bf16_t* A; int64_t lda, strideA;
   const bf16_t* B; int64_t ldb, strideB; int b_kstrided;
   bf16_t* D; int64_t ldd, strideD;
   const bf16_t* C; int64_t ldc, strideC;   // may be null (beta ignored)
@@ -153,11 +153,10 @@ struct GemmDesc {
   int bscale_pow;        // alpha_b = alpha * bscale[b]^bscale_pow (pow in {1,2})
   int symmetric;         // the result is symmetric (M == N): compute the lower triangle of
                          // tiles and store each off-diagonal tile twice
+  int transposed;        // D and C are N x M in memory: element (i,j) at ptr[j*ld + i]
 };
-int launch_ns_gemm(const GemmDesc& d, hipStream_t stream);
-// n independent products (n <= 64).  Those of equal depth K that use the large tile and the
-// same kind of epilogue share launches, up to three at a time; each result is what
-// launch_ns_gemm gives for that product, bit for bit.
+// n independent products (n <= 64).  Those of equal depth K, tile and layout share launches, up
+// to three at a time.
 int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream);
 
 // ---- whole Newton-Schulz chain of a small matrix in one workgroup (ns_chain_small.hip) ----
@@ -171,12 +170,13 @@ int launch_ns_chain_small(const bf16_t* in, bf16_t* out, int64_t ld, int64_t str
                           int iters, float a, float b, float c, hipStream_t stream);
 
 // ---- elementwise kernels of the inner step (inner_elementwise.hip) ----------------
+// U has row pitch ldx and is mp x np per matrix, or np x mp with `transposed`.
 int launch_momentum(const void* grad, int grad_dtype, float* mom, bf16_t* U, float* partials,
                     int nblk, int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np,
-                    int64_t ldx, float beta, int nesterov, hipStream_t stream);
+                    int64_t ldx, bool transposed, float beta, int nesterov, hipStream_t stream);
 int launch_ns_load(const void* in, int dtype, bf16_t* U, float* partials, int nblk,
                    int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t ldx,
-                   hipStream_t stream);
+                   bool transposed, hipStream_t stream);
 int launch_norm_finalize(const float* partials, int nblk, float* scale, int64_t count,
                          float eps, hipStream_t stream);
 int launch_param_update(void* W, int dtype, const bf16_t* O, const float* oscale,

@@ -85,6 +85,85 @@ __global__ __launch_bounds__(EW_THREADS) void muon_momentum_kernel(
   if (threadIdx.x == 0) partials[(long)b * gridDim.x + blockIdx.x] = tot;
 }
 
+// The same with U stored transposed, [np][mp].  A workgroup takes 128 x 64 blocks through the LDS:
+// rows are read 64 columns at a time (whole lines), and 128 adjacent values of a column leave as
+// 256 bytes.  LDS chunk x (8 values of a column) of column c sits at position x ^ ((c / 8) % 8),
+// which spreads a wavefront's 2-byte stores over the banks.
+constexpr int TR_M = 128, TR_N = 64;
+template <typename GT, bool WITH_MOM, bool VEC>
+__global__ __launch_bounds__(EW_THREADS) void muon_momentum_t_kernel(
+    const GT* __restrict__ grad, float* __restrict__ mom, bf16_t* __restrict__ U,
+    float* __restrict__ partials, int m, int n, int mp, int np, int ldx, float beta, int nesterov) {
+  __shared__ __attribute__((aligned(16))) bf16_t tile[TR_N * TR_M];
+  const int b = blockIdx.y;
+  const long mat = (long)b * m * n;
+  const GT* g = grad + mat;
+  float* mo = WITH_MOM ? mom + mat : nullptr;
+  bf16_t* u = U + (long)b * np * ldx;
+  const int blocks_n = np / TR_N;
+  const int blocks = (mp / TR_M) * blocks_n;
+  const int r0 = threadIdx.x >> 3, c8 = threadIdx.x & 7;      // this thread's row and 8-column chunk
+  float ss = 0.f;
+  for (int blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+    const int row0 = blk / blocks_n * TR_M, col0 = blk % blocks_n * TR_N;
+    const int col = col0 + c8 * 8;
+#pragma unroll
+    for (int pass = 0; pass < TR_M / 32; ++pass) {
+      const int lr = pass * 32 + r0, row = row0 + lr;
+      float uv[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) uv[j] = 0.f;
+      if (row < m && col < n) {
+        const long off = (long)row * n + col;
+        float gv[8], mv[8];
+        if (VEC) {
+          Vec8<GT>::load(g + off, gv);
+          if (WITH_MOM) Vec8<float>::load(mo + off, mv);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const bool in = col + j < n;
+            gv[j] = in ? Vec8<GT>::load1(g + off + j) : 0.f;
+            mv[j] = (WITH_MOM && in) ? mo[off + j] : 0.f;
+          }
+        }
+        if (WITH_MOM) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            mv[j] = beta * mv[j] + gv[j];
+            uv[j] = nesterov ? gv[j] + beta * mv[j] : mv[j];
+          }
+          if (VEC) {
+            Vec8<float>::store(mo + off, mv);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              if (col + j < n) mo[off + j] = mv[j];
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) uv[j] = gv[j];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ss += uv[j] * uv[j];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        tile[(c8 * 8 + j) * TR_M + (((lr >> 3) ^ c8) << 3) + (lr & 7)] = f32_to_bf16(uv[j]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < TR_N / 16; ++pass) {
+      const int c = pass * 16 + (threadIdx.x >> 4), x = threadIdx.x & 15;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(tile + c * TR_M + ((x ^ ((c >> 3) & 7)) << 3));
+      *reinterpret_cast<u32x4*>(u + (long)(col0 + c) * ldx + row0 + x * 8) = v;
+    }
+    __syncthreads();
+  }
+  const float tot = block_sum(ss);
+  if (threadIdx.x == 0) partials[(long)b * gridDim.x + blockIdx.x] = tot;
+}
+
 // scale[b] = 1 / (sqrt(sum_b) + eps); an all-zero matrix gets 0, also when eps = 0
 __global__ __launch_bounds__(EW_THREADS) void muon_norm_kernel(const float* __restrict__ partials,
                                                                int nblk, float* __restrict__ scale,
@@ -213,17 +292,20 @@ int grid_blocks(long items, int cap) {
 template <typename GT, bool WITH_MOM>
 int launch_momentum_t(const GT* grad, float* mom, bf16_t* U, float* partials, int nblk,
                       int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t ldx,
-                      float beta, int nesterov, hipStream_t stream, int family) {
+                      bool transposed, float beta, int nesterov, hipStream_t stream, int family) {
   const dim3 grid(nblk, (unsigned)count), block(EW_THREADS);
   const double elems = (double)count * m * n;
   const double bytes = elems * (sizeof(GT) + (WITH_MOM ? 8 : 0)) + (double)count * mp * np * 2;
   LaunchScope scope(family, stream, 0.0, bytes);
-  if (n % 8 == 0)
-    hipLaunchKernelGGL((muon_momentum_kernel<GT, WITH_MOM, true>), grid, block, 0, stream, grad, mom,
-                       U, partials, (int)m, (int)n, (int)mp, (int)np, (int)ldx, beta, nesterov);
-  else
-    hipLaunchKernelGGL((muon_momentum_kernel<GT, WITH_MOM, false>), grid, block, 0, stream, grad, mom,
-                       U, partials, (int)m, (int)n, (int)mp, (int)np, (int)ldx, beta, nesterov);
+#define MLC_MOM(KERNEL, V)                                                                          \
+  hipLaunchKernelGGL((KERNEL<GT, WITH_MOM, V>), grid, block, 0, stream, grad, mom, U, partials, (int)m, \
+                     (int)n, (int)mp, (int)np, (int)ldx, beta, nesterov)
+  if (transposed) {
+    if (n % 8 == 0) MLC_MOM(muon_momentum_t_kernel, true); else MLC_MOM(muon_momentum_t_kernel, false);
+  } else {
+    if (n % 8 == 0) MLC_MOM(muon_momentum_kernel, true); else MLC_MOM(muon_momentum_kernel, false);
+  }
+#undef MLC_MOM
   return check_launch();
 }
 
@@ -231,21 +313,22 @@ int launch_momentum_t(const GT* grad, float* mom, bf16_t* U, float* partials, in
 
 int launch_momentum(const void* grad, int grad_dtype, float* mom, bf16_t* U, float* partials,
                     int nblk, int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np,
-                    int64_t ldx, float beta, int nesterov, hipStream_t stream) {
+                    int64_t ldx, bool transposed, float beta, int nesterov, hipStream_t stream) {
   if (grad_dtype == MLC_F32)
     return launch_momentum_t<float, true>((const float*)grad, mom, U, partials, nblk, count, m, n,
-                                          mp, np, ldx, beta, nesterov, stream, MLC_KERNEL_MOMENTUM);
+                                          mp, np, ldx, transposed, beta, nesterov, stream, MLC_KERNEL_MOMENTUM);
   return launch_momentum_t<bf16_t, true>((const bf16_t*)grad, mom, U, partials, nblk, count, m, n,
-                                         mp, np, ldx, beta, nesterov, stream, MLC_KERNEL_MOMENTUM);
+                                         mp, np, ldx, transposed, beta, nesterov, stream, MLC_KERNEL_MOMENTUM);
 }
 
 int launch_ns_load(const void* in, int dtype, bf16_t* U, float* partials, int nblk, int64_t count,
-                   int64_t m, int64_t n, int64_t mp, int64_t np, int64_t ldx, hipStream_t stream) {
+                   int64_t m, int64_t n, int64_t mp, int64_t np, int64_t ldx, bool transposed,
+                   hipStream_t stream) {
   if (dtype == MLC_F32)
     return launch_momentum_t<float, false>((const float*)in, nullptr, U, partials, nblk, count, m,
-                                           n, mp, np, ldx, 0.f, 0, stream, MLC_KERNEL_CONVERT);
+                                           n, mp, np, ldx, transposed, 0.f, 0, stream, MLC_KERNEL_CONVERT);
   return launch_momentum_t<bf16_t, false>((const bf16_t*)in, nullptr, U, partials, nblk, count, m,
-                                          n, mp, np, ldx, 0.f, 0, stream, MLC_KERNEL_CONVERT);
+                                          n, mp, np, ldx, transposed, 0.f, 0, stream, MLC_KERNEL_CONVERT);
 }
 
 int launch_norm_finalize(const float* partials, int nblk, float* scale, int64_t count, float eps,

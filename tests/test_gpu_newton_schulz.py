@@ -127,6 +127,19 @@ def test_more_small_tiles_than_compute_units(cnt, m, n):
         assert_ns_close(to_f64(a[i]), muon.newton_schulz(to_f64(x[i]), 5), f"matrix {i} of {cnt} x {m} x {n}")
 
 
+@pytest.mark.parametrize("cnt,m,n", [
+    (70, 128, 640), (70, 640, 128),      # K = 128: two K tiles, the short ring; tall: transposed result
+    (40, 256, 640), (40, 640, 250),      # K = 256: as many K tiles as the long ring holds ahead; ragged tall
+    (90, 512, 768), (90, 768, 512),      # 256 x 256 tiles, a second output tile for some workgroups
+])
+def test_ring_across_output_tiles(cnt, m, n):
+    x = S.normal((cnt, m, n), S.GRAD_STD, seed=9, stream=cnt + m, dtype=torch.bfloat16)
+    a = _run(x)
+    assert torch.equal(a.view(torch.int16), _run(x).view(torch.int16))
+    for i in (0, cnt // 2, cnt - 1):
+        assert_ns_close(to_f64(a[i]), muon.newton_schulz(to_f64(x[i]), 5), f"matrix {i} of {cnt} x {m} x {n}")
+
+
 def test_singular_values_land_in_the_band():
     x = S.normal((1, 256, 512), S.GRAD_STD, seed=5, stream=0, dtype=torch.bfloat16)
     out = _run(x)
