@@ -1,5 +1,6 @@
 // C-ABI entry points, host-side argument validation, launch planning and the optional
 // timing recorder.  Nothing here allocates device memory or synchronises the stream.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <mutex>
@@ -753,6 +754,24 @@ int muloco_topk_outer_step(const mlc_outer_group* groups, int n_groups, const ml
   return MLC_OK;
 }
 
+// Do any two of the memory ranges that these tensors name overlap?  (Such tensors are updated one
+// launch after the other.)
+static bool adamw_overlap(const mlc_adamw_group* g, int n) {
+  struct Span { uintptr_t lo, hi; } s[4 * ADAMW_MAX_SEG];
+  for (int i = 0; i < n; ++i) {
+    const void* p[4] = {g[i].param, g[i].grad, g[i].exp_avg, g[i].exp_avg_sq};
+    const size_t es[4] = {elem_size(g[i].param_dtype), elem_size(g[i].grad_dtype), 4, 4};
+    for (int x = 0; x < 4; ++x) {
+      const uintptr_t lo = (uintptr_t)p[x];
+      s[4 * i + x] = Span{lo, lo + (size_t)g[i].count * es[x]};
+    }
+  }
+  std::sort(s, s + 4 * n, [](const Span& a, const Span& b) { return a.lo < b.lo; });
+  for (int i = 1; i < 4 * n; ++i)
+    if (s[i].lo < s[i - 1].hi) return true;
+  return false;
+}
+
 int muloco_adamw_step(const mlc_adamw_group* groups, int n_groups, const mlc_adamw_hparams* hp,
                       void* stream_) {
   if (!groups || !hp) return MLC_ERR_NULL;
@@ -776,12 +795,17 @@ int muloco_adamw_step(const mlc_adamw_group* groups, int n_groups, const mlc_ada
     c2 = (float)(1.0 / std::sqrt(1.0 - std::pow((double)hp->beta2, (double)hp->step)));
   }
   hipStream_t stream = (hipStream_t)stream_;
-  for (int i = 0; i < n_groups; ++i) {
-    const mlc_adamw_group& g = groups[i];
-    const int rc = launch_adamw(g.param, g.param_dtype, g.grad, g.grad_dtype, g.exp_avg, g.exp_avg_sq,
-                                g.count, hp->lr, hp->beta1, hp->beta2, hp->eps,
+  for (int i = 0; i < n_groups;) {
+    // consecutive tensors of one dtype pair share a launch, as long as no two of them overlap
+    int run = 1;
+    while (i + run < n_groups && run < ADAMW_MAX_SEG && groups[i + run].param_dtype == groups[i].param_dtype &&
+           groups[i + run].grad_dtype == groups[i].grad_dtype)
+      ++run;
+    if (run > 1 && adamw_overlap(groups + i, run)) run = 1;
+    const int rc = launch_adamw(groups + i, run, hp->lr, hp->beta1, hp->beta2, hp->eps,
                                 hp->lr * hp->weight_decay, c1, c2, stream);
     if (rc != MLC_OK) return rc;
+    i += run;
   }
   return MLC_OK;
 }

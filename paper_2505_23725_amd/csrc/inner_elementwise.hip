@@ -245,37 +245,52 @@ __global__ __launch_bounds__(EW_THREADS) void ns_store_kernel(
 //   theta <- theta - lr * (m * c1) / (sqrt(v) * c2 + eps) - lr * lambda * theta
 // c1 = 1 / (1 - b1^t), c2 = 1 / sqrt(1 - b2^t) with bias correction, else 1.
 // (Plain loads and stores: non-temporal ones measured 6 % slower here.)
-template <typename WT, typename GT, bool VEC>
-__global__ __launch_bounds__(EW_THREADS) void adamw_kernel(
-    WT* __restrict__ theta, const GT* __restrict__ grad, float* __restrict__ m, float* __restrict__ v,
-    long n, float lr, float b1, float b2, float eps, float decay, float c1, float c2) {
-  constexpr int W = VEC ? 8 : 1;
-  const long items = (n + W - 1) / W;
-  const long per_blk = (items + gridDim.x - 1) / gridDim.x;
-  const long it_end = min(items, (long)(blockIdx.x + 1) * per_blk);
-  for (long it = (long)blockIdx.x * per_blk + threadIdx.x; it < it_end; it += EW_THREADS) {
-    const long off = it * W;
-    float th[8], g[8], mv[8], vv[8];
-    if (VEC) {
-      Vec8<WT>::load(theta + off, th); Vec8<GT>::load(grad + off, g);
-      Vec8<float>::load(m + off, mv); Vec8<float>::load(v + off, vv);
-    } else {
-      th[0] = Vec8<WT>::load1(theta + off); g[0] = Vec8<GT>::load1(grad + off);
-      mv[0] = m[off]; vv[0] = v[off];
-    }
+//
+// Bound by the memory stream.  One launch covers up to ADAMW_MAX_SEG tensors (their table
+// travels in the kernel arguments): most tensors that Muon leaves over are a few KB, and a
+// launch for each of them cost more than the whole stream (a 32000 x 2048 embedding with 72
+// vectors beside it: 568 us in 73 launches, 282 in two).  A workgroup takes ADAMW_CHUNK elements
+// of one tensor, found by counting the first workgroups at or below its own index.
+constexpr int ADAMW_CHUNK = EW_THREADS * 8 * 4;
+struct AdamWSeg { void* theta; const void* grad; float* m; float* v; long n; };
+struct AdamWTable { AdamWSeg s[ADAMW_MAX_SEG]; unsigned int blk0[ADAMW_MAX_SEG]; };
+struct AdamWScalars { float lr, b1, b2, eps, decay, c1, c2; };
+
+__device__ __forceinline__ void adamw_element(float& th, float g, float& m, float& v, const AdamWScalars& h) {
+  m = h.b1 * m + (1.0f - h.b1) * g;
+  v = h.b2 * v + (1.0f - h.b2) * g * g;
+  const float step = (m * h.c1) / (sqrtf(v) * h.c2 + h.eps);
+  th = th - h.lr * step - h.decay * th;
+}
+
+template <typename WT, typename GT>
+__global__ __launch_bounds__(EW_THREADS) void adamw_kernel(AdamWTable tab, AdamWScalars h) {
+  static_assert(ADAMW_MAX_SEG == 64, "one lane per tensor");
+  const bool below = blockIdx.x >= tab.blk0[threadIdx.x & 63];      // 0xffffffff beyond the last tensor
+  const int si = __builtin_amdgcn_readfirstlane(__popcll(__ballot(below)) - 1);
+  const AdamWSeg sg = tab.s[si];
+  WT* const theta = (WT*)sg.theta;
+  const GT* const grad = (const GT*)sg.grad;
+  const long first = (long)(blockIdx.x - tab.blk0[si]) * ADAMW_CHUNK;
+  const long end = min(sg.n, first + ADAMW_CHUNK);
 #pragma unroll
-    for (int j = 0; j < W; ++j) {
-      mv[j] = b1 * mv[j] + (1.0f - b1) * g[j];
-      vv[j] = b2 * vv[j] + (1.0f - b2) * g[j] * g[j];
-      const float step = (mv[j] * c1) / (sqrtf(vv[j]) * c2 + eps);
-      th[j] = th[j] - lr * step - decay * th[j];
-    }
-    if (VEC) {
+  for (int u = 0; u < ADAMW_CHUNK / (EW_THREADS * 8); ++u) {
+    const long off = first + (u * EW_THREADS + (int)threadIdx.x) * 8;
+    if (off + 8 <= end) {
+      float th[8], g[8], mv[8], vv[8];
+      Vec8<WT>::load(theta + off, th); Vec8<GT>::load(grad + off, g);
+      Vec8<float>::load(sg.m + off, mv); Vec8<float>::load(sg.v + off, vv);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) adamw_element(th[j], g[j], mv[j], vv[j], h);
       Vec8<WT>::store(theta + off, th);
-      Vec8<float>::store(m + off, mv); Vec8<float>::store(v + off, vv);
+      Vec8<float>::store(sg.m + off, mv); Vec8<float>::store(sg.v + off, vv);
     } else {
-      Vec8<WT>::store1(theta + off, th[0]);
-      m[off] = mv[0]; v[off] = vv[0];
+      for (long e = off; e < end; ++e) {          // fewer than 8, the tensor's last ones
+        float th = Vec8<WT>::load1(theta + e), mv = sg.m[e], vv = sg.v[e];
+        adamw_element(th, Vec8<GT>::load1(grad + e), mv, vv, h);
+        Vec8<WT>::store1(theta + e, th);
+        sg.m[e] = mv; sg.v[e] = vv;
+      }
     }
   }
 }
@@ -373,23 +388,28 @@ int launch_ns_store(const bf16_t* X, const float* oscale, void* out, int dtype, 
   return check_launch();
 }
 
-int launch_adamw(void* theta, int param_dtype, const void* grad, int grad_dtype, float* m, float* v,
-                 int64_t n, float lr, float b1, float b2, float eps, float decay, float c1, float c2,
-                 hipStream_t stream) {
-  const bool vec = n % 8 == 0;
-  const long items = vec ? n / 8 : n;
-  const dim3 grid(grid_blocks(items, 256 * 16)), block(EW_THREADS);
-  const double bytes = (double)n * (2 * (param_dtype == MLC_F32 ? 4 : 2) + (grad_dtype == MLC_F32 ? 4 : 2) + 16);
+int launch_adamw(const mlc_adamw_group* gs, int n, float lr, float b1, float b2, float eps, float decay,
+                 float c1, float c2, hipStream_t stream) {
+  AdamWTable tab;
+  const int wd = gs[0].param_dtype, gd = gs[0].grad_dtype;
+  double bytes = 0.0;
+  unsigned long blk = 0;
+  for (int i = 0; i < ADAMW_MAX_SEG; ++i) {
+    if (i >= n) { tab.s[i] = tab.s[0]; tab.blk0[i] = 0xffffffffu; continue; }
+    tab.s[i] = AdamWSeg{gs[i].param, gs[i].grad, gs[i].exp_avg, gs[i].exp_avg_sq, (long)gs[i].count};
+    tab.blk0[i] = (unsigned int)blk;
+    blk += (unsigned long)((gs[i].count + ADAMW_CHUNK - 1) / ADAMW_CHUNK);
+    if (blk > 0x7fffffffUL) return MLC_ERR_SHAPE;
+    bytes += (double)gs[i].count * (2 * (wd == MLC_F32 ? 4 : 2) + (gd == MLC_F32 ? 4 : 2) + 16);
+  }
+  const AdamWScalars h{lr, b1, b2, eps, decay, c1, c2};
   LaunchScope scope(MLC_KERNEL_ADAMW, stream, 0.0, bytes);
-#define MLC_AW(WT, GT, V)                                                                         \
-  hipLaunchKernelGGL((adamw_kernel<WT, GT, V>), grid, block, 0, stream, (WT*)theta, (const GT*)grad, m, v, \
-                     (long)n, lr, b1, b2, eps, decay, c1, c2)
-#define MLC_AW_V(WT, GT) do { if (vec) MLC_AW(WT, GT, true); else MLC_AW(WT, GT, false); } while (0)
-  if (param_dtype == MLC_F32 && grad_dtype == MLC_F32) MLC_AW_V(float, float);
-  else if (param_dtype == MLC_F32) MLC_AW_V(float, bf16_t);
-  else if (grad_dtype == MLC_F32) MLC_AW_V(bf16_t, float);
-  else MLC_AW_V(bf16_t, bf16_t);
-#undef MLC_AW_V
+#define MLC_AW(WT, GT) \
+  hipLaunchKernelGGL((adamw_kernel<WT, GT>), dim3((unsigned)blk), dim3(EW_THREADS), 0, stream, tab, h)
+  if (wd == MLC_F32 && gd == MLC_F32) MLC_AW(float, float);
+  else if (wd == MLC_F32) MLC_AW(float, bf16_t);
+  else if (gd == MLC_F32) MLC_AW(bf16_t, float);
+  else MLC_AW(bf16_t, bf16_t);
 #undef MLC_AW
   return check_launch();
 }

@@ -52,3 +52,28 @@ def test_adamw_several_tensors_in_one_call_and_zero_gradient():
     for p, q in zip(ps, p0):          # zero gradient: pure decoupled decay
         assert_fp32_close(p.cpu(), to_f64(q) * (1 - 0.05), "decay only")
     assert all(torch.count_nonzero(x) == 0 for x in ms + vs)
+
+
+@pytest.mark.parametrize("pd,gd", [(torch.bfloat16, torch.bfloat16), (torch.float32, torch.bfloat16)])
+def test_adamw_many_tensors_share_launches(pd, gd):
+    """More tensors than one launch holds, sizes around the chunk of a workgroup (8192) and off the
+    8-element vector, a change of dtype in between, and a tensor that appears twice: the same
+    bits as one call per tensor."""
+    sizes = [8192, 8191, 8193, 1, 7, 8, 16384 + 5] + [40 + i for i in range(70)]
+    hp = mlc.AdamWHParams(lr=3e-3, weight_decay=0.1, bias_correction=True, step=3)
+
+    def state():
+        out = []
+        for i, n in enumerate(sizes):
+            d = torch.float32 if i == 30 else pd
+            out.append((S.normal((n,), 1.0, 7, i, dtype=d).to(DEV), S.normal((n,), 1.0, 8, i, dtype=gd).to(DEV),
+                        S.normal((n,), 1.0, 9, i).to(DEV), S.normal((n,), 1.0, 10, i).abs().to(DEV)))
+        return out + [out[3], out[0]]
+    one, many = state(), state()
+    for t in one:
+        mlc.muloco_adamw_step([t], hp)
+    mlc.muloco_adamw_step(many, hp)
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(one, many)):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y), f"tensor {i} of {len(one)}"
