@@ -645,7 +645,8 @@ int muloco_outer_step(const mlc_outer_group* groups, int n_groups, const mlc_out
     // is three small groups: one launch instead of three fills the chip for longer).
     int run = 0;
     while (i + run < n_groups && run < OUTER_MAX_SEG && groups[i + run].worker_dtype == groups[i].worker_dtype &&
-           groups[i + run].global_dtype == groups[i].global_dtype && multi_launch_covers(groups[i + run], *hp))
+           groups[i + run].global_dtype == groups[i].global_dtype && multi_launch_covers(groups[i + run], *hp) &&
+           (hp->quant_bits == 0 || quant_ragged(groups[i + run].n) == quant_ragged(groups[i].n)))
       ++run;
     if (run >= 2) {
       OuterGroupArgs args[OUTER_MAX_SEG];

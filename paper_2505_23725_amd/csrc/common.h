@@ -101,6 +101,58 @@ template <> struct Vec8<bf16_t> {
   static __device__ __forceinline__ float round(float v) { return bf16_to_f32(f32_to_bf16(v)); }
 };
 
+// The same accesses at addresses aligned to the element only (global memory takes them unaligned),
+// and of the first `cnt` (1 .. 8) of 8 elements; elements beyond come back as 0.
+template <typename T> struct Vec8U;
+template <> struct Vec8U<float> {
+  typedef f32x4 __attribute__((aligned(4))) vec_t;
+  typedef Vec8<float>::raw_t raw_t;
+  static __device__ __forceinline__ raw_t load_raw(const float* p) {
+    raw_t r;
+    r.a = *reinterpret_cast<const vec_t*>(p);
+    r.b = *reinterpret_cast<const vec_t*>(p + 4);
+    return r;
+  }
+  static __device__ __forceinline__ raw_t load_raw(const float* p, int cnt) {
+    if (cnt >= 8) return load_raw(p);
+    raw_t r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { r.a[j] = j < cnt ? p[j] : 0.f; r.b[j] = j + 4 < cnt ? p[j + 4] : 0.f; }
+    return r;
+  }
+  static __device__ __forceinline__ void store(float* p, const float (&v)[8], int cnt) {
+    if (cnt >= 8) {
+      f32x4 a, b;
+      a.x = v[0]; a.y = v[1]; a.z = v[2]; a.w = v[3]; b.x = v[4]; b.y = v[5]; b.z = v[6]; b.w = v[7];
+      *reinterpret_cast<vec_t*>(p) = a;
+      *reinterpret_cast<vec_t*>(p + 4) = b;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) if (j < cnt) p[j] = v[j];
+    }
+  }
+};
+template <> struct Vec8U<bf16_t> {
+  typedef u32x4 __attribute__((aligned(2))) vec_t;
+  typedef u32x4 raw_t;
+  static __device__ __forceinline__ raw_t load_raw(const bf16_t* p) { return *reinterpret_cast<const vec_t*>(p); }
+  static __device__ __forceinline__ raw_t load_raw(const bf16_t* p, int cnt) {
+    if (cnt >= 8) return load_raw(p);
+    raw_t r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      r[j] = (2 * j < cnt ? (unsigned int)p[2 * j] : 0u) | (2 * j + 1 < cnt ? (unsigned int)p[2 * j + 1] << 16 : 0u);
+    return r;
+  }
+  static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8], int cnt) {
+    const u32x4 w = Vec8<bf16_t>::pack(v);
+    if (cnt >= 8) *reinterpret_cast<vec_t*>(p) = w;
+    else
+#pragma unroll
+      for (int j = 0; j < 8; ++j) if (j < cnt) p[j] = (bf16_t)(w[j / 2] >> (16 * (j & 1)));
+  }
+};
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -212,6 +264,8 @@ struct OuterGroupArgs {
 // (configurations 0 .. QUANT_MULTI_MAX_CFG) can share a launch with other groups, longer ones
 // need so many registers per thread that they would halve the occupancy of the whole launch.
 int quant_reg_cfg(int64_t n);
+// Rows whose length is a multiple of 8 start on 16 bytes (8 for codes) whatever their index.
+static inline bool quant_ragged(int64_t n) { return n % 8 != 0; }
 constexpr int QUANT_MULTI_MAX_CFG = 4;
 struct QuantForm;
 int launch_outer_fused_multi(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K,

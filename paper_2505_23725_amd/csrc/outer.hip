@@ -131,6 +131,24 @@ __device__ __forceinline__ void store_codes8(uint8_t* crow, int c, const int (&q
   }
 }
 
+// The first cnt of 8 levels at an address aligned to a byte only (cnt * bits is a multiple of 8).
+__device__ __forceinline__ void store_codes8_part(uint8_t* crow, int c, const int (&q)[8], int bits, int bias,
+                                                  int cnt) {
+  typedef unsigned short u16_u __attribute__((aligned(1)));
+  typedef unsigned int u32_u __attribute__((aligned(1)));
+  unsigned long p = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) p |= (unsigned long)(unsigned int)(q[j] + bias) << (bits * j);
+  uint8_t* const at = crow + c * bits / 8;
+  if (cnt >= 8) {
+    if (bits == 2) *reinterpret_cast<u16_u*>(at) = (unsigned short)p;
+    else *reinterpret_cast<u32_u*>(at) = (unsigned int)p;
+    if (bits == 8) *reinterpret_cast<u32_u*>(at + 4) = (unsigned int)(p >> 32);
+  } else {
+    for (int j = 0; j < cnt * bits / 8; ++j) at[j] = (uint8_t)(p >> (8 * j));
+  }
+}
+
 __device__ __forceinline__ void load_levels8(const uint8_t* crow, int c, int (&q)[8], int bits, int bias) {
   if (bits == 4) {
     const unsigned int p = *reinterpret_cast<const unsigned int*>(crow + c / 2);
@@ -318,6 +336,19 @@ __global__ __launch_bounds__(OT_THREADS) void quantize_rows_kernel(
   }
 }
 
+// 8 elements of a row from column c on, `left` of them before its end (RAG: perhaps fewer than 8,
+// and at any alignment).
+template <typename T, bool RAG>
+__device__ __forceinline__ void load8(const T* p, int left, float (&v)[8]) {
+  if constexpr (RAG) Vec8<T>::unpack(Vec8U<T>::load_raw(p, left), v);
+  else Vec8<T>::load(p, v);
+}
+template <typename T, bool RAG>
+__device__ __forceinline__ void store8(T* p, const float (&v)[8], int left) {
+  if constexpr (RAG) Vec8U<T>::store(p, v, left);
+  else Vec8<T>::store(p, v);
+}
+
 // Single-pass variant: a group of G threads (a wavefront or the whole workgroup) owns a row
 // and keeps it in registers (NV vectors of 8 elements per thread), so theta_g is read once
 // for all K workers and every theta_k exactly once.  Same arithmetic as above.  With
@@ -326,7 +357,10 @@ __global__ __launch_bounds__(OT_THREADS) void quantize_rows_kernel(
 // `blk` is the index of the workgroup among those that share these arguments; the pointer sets
 // may be the 32-wide ones of a single-group launch or the narrow ones of a launch that covers
 // several groups.
-template <typename WT, typename GT, int NV, int G, bool OUTER, typename PW, typename PC, typename PS,
+// RAG: rows of any length, so neither the rows nor their codes are aligned and the last vector of
+// a row may be a part of one (24 / 6 / 6 matrices of 1001 x 1001, 1001 x 2730 and 2730 x 1001, two
+// workers, 8 bits with error feedback: 1500 us element by element in two passes, 516 like this).
+template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG, typename PW, typename PC, typename PS,
           typename PO, typename PE>
 __device__ __forceinline__ void quantize_rows_reg_body(
     const PW& w, GT* __restrict__ theta_g, float* __restrict__ u, const PC& codes, const PS& scales,
@@ -348,7 +382,7 @@ __device__ __forceinline__ void quantize_rows_reg_body(
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int c = (t + i * G) * 8;
-    if (live && c < n) Vec8<GT>::load(theta_g + rbase + c, tg[i]);
+    if (live && c < n) load8<GT, RAG>(theta_g + rbase + c, n - c, tg[i]);
     else
 #pragma unroll
       for (int j = 0; j < 8; ++j) tg[i][j] = 0.f;
@@ -365,7 +399,10 @@ __device__ __forceinline__ void quantize_rows_reg_body(
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int c = (t + i * G) * 8;
-      if (live && c < n) ahead[i] = Vec8<WT>::load_raw(tk + c);
+      if (live && c < n) {
+        if constexpr (RAG) ahead[i] = Vec8U<WT>::load_raw(tk + c, n - c);
+        else ahead[i] = Vec8<WT>::load_raw(tk + c);
+      }
     }
   };
   request(0);
@@ -387,12 +424,13 @@ __device__ __forceinline__ void quantize_rows_reg_body(
         for (int j = 0; j < 8; ++j) d[i][j] = tg[i][j] - b[j];
         if (res) {
           float e[8];
-          Vec8<float>::load(res + c, e);
+          load8<float, RAG>(res + c, n - c, e);
 #pragma unroll
           for (int j = 0; j < 8; ++j) d[i][j] = ef_input(d[i][j], e[j], form.ef_beta);
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { mn = fminf(mn, d[i][j]); mx = fmaxf(mx, d[i][j]); }
+        for (int j = 0; j < 8; ++j)
+          if (!RAG || c + j < n) { mn = fminf(mn, d[i][j]); mx = fmaxf(mx, d[i][j]); }
       } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) d[i][j] = 0.f;
@@ -429,8 +467,9 @@ __device__ __forceinline__ void quantize_rows_reg_body(
           e[j] = __fsub_rn(d[i][j], sent);
           if constexpr (OUTER) acc[i][j] += sent;
         }
-        store_codes8(crow, c, q, bits, form.code_bias);
-        if (res) Vec8<float>::store(res + c, e);
+        if constexpr (RAG) store_codes8_part(crow, c, q, bits, form.code_bias, n - c);
+        else store_codes8(crow, c, q, bits, form.code_bias);
+        if (res) store8<float, RAG>(res + c, e, n - c);
       }
     }
   }
@@ -439,7 +478,7 @@ __device__ __forceinline__ void quantize_rows_reg_body(
     for (int i = 0; i < NV; ++i)
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[i][j] = __fmul_rn(acc[i][j], inv_k);     // Psi
-    if (requant) {
+    if (!RAG && requant) {
       // Second quantisation (the dequantise-reduce-quantise step between the two modelled
       // collectives): Psi is quantised row-wise again and its dequantised value is used.
       float mn = INFINITY, mx = -INFINITY;
@@ -481,13 +520,13 @@ __device__ __forceinline__ void quantize_rows_reg_body(
       const int c = (t + i * G) * 8;
       if (live && c < n) {
         float uv[8];
-        Vec8<float>::load(u + rbase + c, uv);
+        load8<float, RAG>(u + rbase + c, n - c, uv);
 #pragma unroll
         for (int j = 0; j < 8; ++j) outer_update<GT>(tg[i][j], uv[j], acc[i][j], eta, mu, nesterov);
-        Vec8<GT>::store(theta_g + rbase + c, tg[i]);
-        Vec8<float>::store(u + rbase + c, uv);
+        store8<GT, RAG>(theta_g + rbase + c, tg[i], n - c);
+        store8<float, RAG>(u + rbase + c, uv, n - c);
         if (write_back)
-          for (int k = 0; k < K; ++k) Vec8<WT>::store(reinterpret_cast<WT*>(w.p[k]) + rbase + c, tg[i]);
+          for (int k = 0; k < K; ++k) store8<WT, RAG>(reinterpret_cast<WT*>(w.p[k]) + rbase + c, tg[i], n - c);
       }
     }
   }
@@ -500,13 +539,13 @@ constexpr int quant_min_waves(int nv, bool outer) {
   return outer ? (nv <= 1 ? 6 : nv <= 2 ? 4 : nv <= 4 ? 3 : 1) : (nv <= 1 ? 7 : nv <= 2 ? 5 : nv <= 4 ? 3 : 1);
 }
 
-template <typename WT, typename GT, int NV, int G, bool OUTER>
+template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG>
 __global__ __launch_bounds__(OT_THREADS, quant_min_waves(NV, OUTER)) void quantize_rows_reg_kernel(
     WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, CodePtrs codes, ScalePtrs scales,
     OffsetPtrs offsets, ResidualPtrs ef, long rows, int n, int K, QuantForm form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
     float* mean_offsets) {
-  quantize_rows_reg_body<WT, GT, NV, G, OUTER>(w, theta_g, u, codes, scales, offsets, ef, rows, n, K, form,
+  quantize_rows_reg_body<WT, GT, NV, G, OUTER, RAG>(w, theta_g, u, codes, scales, offsets, ef, rows, n, K, form,
                                                eta, mu, inv_k, nesterov, write_back, requant, mean_codes,
                                                mean_scales, mean_offsets, (long)blockIdx.x);
 }
@@ -538,7 +577,7 @@ __host__ __device__ constexpr RegCfg reg_cfg(int idx) {
        : idx == 6 ? RegCfg{8, 256} : RegCfg{12, 256};
 }
 
-template <typename WT, typename GT>
+template <typename WT, typename GT, bool RAG>
 __global__ __launch_bounds__(OT_THREADS, 3) void quantize_outer_multi_kernel(
     QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
   int si = 0;
@@ -548,7 +587,7 @@ __global__ __launch_bounds__(OT_THREADS, 3) void quantize_outer_multi_kernel(
   const QuantSeg& sg = tab.s[si];
   const long blk = (long)(blockIdx.x - sg.blk0);
 #define MLC_SEG_BODY(IDX)                                                                              \
-  quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true>(                               \
+  quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG>(                             \
       sg.w, (GT*)sg.theta_g, sg.u, sg.codes, sg.scales, sg.offsets, sg.ef, sg.rows, sg.n, K, form, eta, \
       mu, inv_k, nesterov, write_back, 0, nullptr, nullptr, nullptr, blk)
   switch (sg.cfg) {      // uniform over the workgroup
@@ -914,18 +953,20 @@ int launch_quantize(const WorkerPtrs& w, int worker_dtype, const void* theta_g, 
   LaunchScope scope(MLC_KERNEL_QUANTIZE, stream, 0.0, bytes);
   const bool vec = n % 8 == 0;
   // single-pass register kernel: a wavefront per row up to 2048 columns, a workgroup per row
-  // up to 24576; otherwise (or for odd row lengths) the two-pass kernel
-  if (vec && n <= 24576 && !(worker_dtype == MLC_F32 && global_dtype == MLC_BF16)) {
+  // up to 24576; otherwise the two-pass kernel
+  if (n <= 24576 && !(worker_dtype == MLC_F32 && global_dtype == MLC_BF16)) {
     const int g = n <= 2048 ? 64 : OT_THREADS;
     const int need = (int)((n + g * 8 - 1) / (g * 8));
     const int nv = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 8 ? 8 : 12;
     const long rpb = OT_THREADS / g;
     const long nblk = (rows + rpb - 1) / rpb;
-#define MLC_QR(WT, GT, NV, G)                                                                     \
-  hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, false>), dim3((unsigned)nblk),       \
+#define MLC_QR_R(WT, GT, NV, G, RAG)                                                              \
+  hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, false, RAG>), dim3((unsigned)nblk),  \
                      dim3(OT_THREADS), 0, stream, w, (GT*)const_cast<void*>(theta_g), (float*)nullptr, \
                      codes, scales, offsets, ef, (long)rows, (int)n, K, form, 0.f, 0.f, 0.f, 0, 0, 0, \
                      (uint8_t*)nullptr, (float*)nullptr, (float*)nullptr)
+#define MLC_QR(WT, GT, NV, G)                                                                     \
+  do { if (vec) MLC_QR_R(WT, GT, NV, G, false); else MLC_QR_R(WT, GT, NV, G, true); } while (0)
 #define MLC_QR_NV(WT, GT)                                                                         \
   do {                                                                                            \
     if (g == 64) { if (nv == 1) MLC_QR(WT, GT, 1, 64); else if (nv == 2) MLC_QR(WT, GT, 2, 64);   \
@@ -938,6 +979,7 @@ int launch_quantize(const WorkerPtrs& w, int worker_dtype, const void* theta_g, 
     else MLC_QR_NV(float, float);
 #undef MLC_QR_NV
 #undef MLC_QR
+#undef MLC_QR_R
     return check_launch();
   }
 #define MLC_CALL(WT, GT)                                                                          \
@@ -994,8 +1036,8 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
                                 int64_t n, int K, const QuantForm& form, float eta_out, float mu,
                                 int nesterov, int write_back, int requant, uint8_t* mean_codes,
                                 float* mean_scales, float* mean_offsets, hipStream_t stream) {
-  if (n % 8 || n > 24576 || (worker_dtype == MLC_F32 && global_dtype == MLC_BF16))
-    return MLC_ERR_UNSUPPORTED;
+  if (n > 24576 || (worker_dtype == MLC_F32 && global_dtype == MLC_BF16)) return MLC_ERR_UNSUPPORTED;
+  if (requant && quant_ragged(n)) return MLC_ERR_UNSUPPORTED;
   const int g = n <= 2048 ? 64 : OT_THREADS;
   const int need = (int)((n + g * 8 - 1) / (g * 8));
   // Vectors per thread.  The row, its running mean and the current worker's delta all live in
@@ -1012,11 +1054,13 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
                                            2 * esize(global_dtype) + 8) + (double)rows * 4 * K;
   LaunchScope scope(MLC_KERNEL_DEQUANT_OUTER, stream, 0.0, bytes);
   const float inv_k = 1.0f / (float)K;
-#define MLC_QO(WT, GT, NV, G)                                                                     \
-  hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, true>), dim3((unsigned)nblk),        \
+#define MLC_QO_R(WT, GT, NV, G, RAG)                                                              \
+  hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, true, RAG>), dim3((unsigned)nblk),   \
                      dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, codes, scales, offsets, ef,  \
                      (long)rows, (int)n, K, form, eta_out, mu, inv_k, nesterov, write_back, requant, \
                      mean_codes, mean_scales, mean_offsets)
+#define MLC_QO(WT, GT, NV, G)                                                                     \
+  do { if (quant_ragged(n)) MLC_QO_R(WT, GT, NV, G, true); else MLC_QO_R(WT, GT, NV, G, false); } while (0)
 #define MLC_QO_NV(WT, GT)                                                                         \
   do {                                                                                            \
     if (g == 64) { if (nv == 1) MLC_QO(WT, GT, 1, 64); else if (nv == 2) MLC_QO(WT, GT, 2, 64);   \
@@ -1030,6 +1074,7 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
   else MLC_QO_NV(float, float);
 #undef MLC_QO_NV
 #undef MLC_QO
+#undef MLC_QO_R
   return check_launch();
 }
 
@@ -1075,7 +1120,7 @@ int launch_outer_fused_multi(const OuterGroupArgs* gs, int ng, int worker_dtype,
 // Index of the (vectors per thread, threads per row) pair of the one-pass kernel for rows of
 // length n, or -1 when the one-pass kernel does not cover them.
 int quant_reg_cfg(int64_t n) {
-  if (n % 8 || n > 24576) return -1;
+  if (n > 24576) return -1;
   const int g = n <= 2048 ? 64 : OT_THREADS;
   const int need = (int)((n + g * 8 - 1) / (g * 8));
   if (g == 64) return need <= 1 ? 0 : need <= 2 ? 1 : 2;
@@ -1098,7 +1143,8 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     QuantSeg& sg = tab.s[i];
     if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
     const int cfg = quant_reg_cfg(gs[i].n);
-    if (cfg < 0 || cfg > QUANT_MULTI_MAX_CFG) return MLC_ERR_UNSUPPORTED;
+    if (cfg < 0 || cfg > QUANT_MULTI_MAX_CFG || quant_ragged(gs[i].n) != quant_ragged(gs[0].n))
+      return MLC_ERR_UNSUPPORTED;
     for (int k = 0; k < OUTER_MAX_SEG_K; ++k) {
       sg.w.p[k] = k < K ? gs[i].w.p[k] : nullptr;
       sg.codes.p[k] = k < K ? gs[i].codes.p[k] : nullptr;
@@ -1122,13 +1168,15 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
   }
   LaunchScope scope(MLC_KERNEL_DEQUANT_OUTER, stream, 0.0, bytes);
   const float inv_k = 1.0f / (float)K;
-#define MLC_QM(WT, GT)                                                                             \
-  hipLaunchKernelGGL((quantize_outer_multi_kernel<WT, GT>), dim3((unsigned)blk), dim3(OT_THREADS), 0, \
-                     stream, tab, K, form, eta_out, mu, inv_k, nesterov, write_back)
+#define MLC_QM_R(WT, GT, RAG)                                                                      \
+  hipLaunchKernelGGL((quantize_outer_multi_kernel<WT, GT, RAG>), dim3((unsigned)blk), dim3(OT_THREADS), \
+                     0, stream, tab, K, form, eta_out, mu, inv_k, nesterov, write_back)
+#define MLC_QM(WT, GT) do { if (quant_ragged(gs[0].n)) MLC_QM_R(WT, GT, true); else MLC_QM_R(WT, GT, false); } while (0)
   if (worker_dtype == MLC_BF16 && global_dtype == MLC_F32) MLC_QM(bf16_t, float);
   else if (worker_dtype == MLC_BF16) MLC_QM(bf16_t, bf16_t);
   else MLC_QM(float, float);
 #undef MLC_QM
+#undef MLC_QM_R
   return check_launch();
 }
 

@@ -277,3 +277,51 @@ def test_quantiser_forms_bit_exact(cnt, m, n, K, wd, gd, bits, offset, per_matri
     assert_stored_close(tg.cpu().reshape(-1, n), ref["theta"], "global parameters")
     for k in range(K):
         assert torch.equal(ws[k].cpu(), tg.cpu().to(wd)), f"worker {k} write-back differs from theta_g"
+
+
+BF16, F32 = torch.bfloat16, torch.float32
+RAGGED_CASES = [
+    # rows that are not a multiple of 8: ends of a wavefront's and a workgroup's vectors, one
+    # element more or less, the longest that registers hold, and one beyond
+    # (count, m, n, K, workers, global, bits, offset, per matrix, error feedback)
+    (2, 5, 1, 1, BF16, F32, 8, False, False, False),
+    (1, 7, 513, 2, BF16, F32, 8, True, False, True),
+    (2, 9, 1001, 2, BF16, BF16, 8, True, False, True),
+    (1, 6, 1022, 4, BF16, F32, 4, False, False, False),
+    (1, 3, 2047, 1, F32, F32, 8, False, True, True),
+    (1, 3, 2050, 2, BF16, F32, 4, True, False, True),
+    (2, 3, 4100, 2, BF16, F32, 2, False, False, True),
+    (1, 2, 12292, 2, F32, F32, 2, True, False, False),
+    (1, 2, 24575, 1, BF16, F32, 8, False, False, True),
+    (1, 2, 24580, 1, BF16, F32, 4, False, False, True),
+    (1, 3, 1001, 1, F32, BF16, 8, False, False, False),
+]
+
+
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,bits,offset,per_matrix,ef", RAGGED_CASES)
+def test_ragged_rows_bit_exact(cnt, m, n, K, wd, gd, bits, offset, per_matrix, ef):
+    test_quantiser_forms_bit_exact(cnt, m, n, K, wd, gd, bits, offset, per_matrix, ef, False)
+
+
+def test_ragged_and_aligned_groups_in_one_call_equal_one_call_per_group():
+    shapes = [(3, 50, 1001), (2, 9, 2730), (2, 40, 1000), (1, 12, 4099), (2, 5, 77)]
+    hp = mlc.OuterHParams(K=2, eta_out=0.9, mu=0.8, quant_bits=8, error_feedback=True, ef_beta=0.9, quant_offset=True)
+
+    def groups():
+        out = []
+        for cnt, m, n in shapes:
+            tg0, ws0, u0 = _inputs(cnt, m, n, 2, BF16, F32, n)
+            codes, scales = _alloc(cnt, m, n, 2, 8)
+            out.append(mlc.OuterGroup([w.to(DEV) for w in ws0], tg0.to(DEV), u0.to(DEV), codes, scales,
+                                      [S.normal((cnt, m, n), 1e-3, n, 40 + k).to(DEV) for k in range(2)], None, None,
+                                      [torch.zeros(cnt * m, device=DEV) for _ in range(2)]))
+        return out
+    one, many = groups(), groups()
+    for g in one:
+        mlc.muloco_outer_step([g], hp)
+    mlc.muloco_outer_step(many, hp)
+    torch.cuda.synchronize()
+    for a, b in zip(one, many):
+        for x, y in zip([a.global_param, a.outer_momentum, *a.worker_params, *a.codes, *a.scales, *a.residuals, *a.offsets],
+                        [b.global_param, b.outer_momentum, *b.worker_params, *b.codes, *b.scales, *b.residuals, *b.offsets]):
+            assert torch.equal(x, y)
