@@ -84,6 +84,23 @@ def test_inner_step_matches_oracle(cnt, m, n, pd, gd, nesterov):
     _check_group(W0, g, mom0, W.cpu(), mom.cpu(), hp, lr_scale, f"{cnt}x{m}x{n} {dtype_name(W0)}")
 
 
+# rows that end in a part of a vector: shorter than one, one element over or short of a multiple
+# of 8, wide and tall (stored transposed), each combination of stored types
+TAIL_CASES = [
+    (2, 130, 5, torch.bfloat16, torch.bfloat16),
+    (1, 5, 1, torch.float32, torch.float32),
+    (2, 257, 129, torch.float32, torch.bfloat16),
+    (2, 140, 641, torch.bfloat16, torch.float32),
+    (1, 647, 263, torch.bfloat16, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("cnt,m,n,pd,gd", TAIL_CASES)
+def test_ragged_row_tails_match_oracle(cnt, m, n, pd, gd):
+    test_inner_step_matches_oracle(cnt, m, n, pd, gd, True)
+
+
+
 def test_several_groups_one_call_and_small_work_space():
     hp = mlc.MuonHParams(eta=0.05, weight_decay=0.01, beta=0.9)
     shapes = [(4, 128, 128), (2, 128, 512), (2, 512, 128)]
