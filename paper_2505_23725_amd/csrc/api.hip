@@ -229,21 +229,26 @@ static GemmDesc apply_update_desc(const NsJob& j, const bf16_t* X, bool first) {
 int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float eps, hipStream_t stream) {
   if (n < 1 || n > MAX_NS_JOBS) return MLC_ERR_ARG;
   NsJob* big[MAX_NS_JOBS];
-  int nbig = 0;
+  ChainDesc chain[MAX_CHAINS];
+  static_assert(MAX_CHAINS >= MAX_NS_JOBS, "every job may be a chain");
+  int nbig = 0, nchain = 0;
   for (int i = 0; i < n; ++i) {
     NsJob& j = jobs[i];
     if (iters >= 1 && ns_chain_small_fits(j.p.mp, j.p.np)) {
       // small matrices: norm and all iterations in one launch, X and A resident in LDS
       j.result_buf = 1;
-      const int rc = launch_ns_chain_small(j.w.X[0], j.w.X[1], j.p.ldx, j.p.mp * j.p.ldx, j.p.mp, j.p.np,
-                                           j.w.partials, j.p.nblk, eps, j.chunk, iters, a, b, c, stream);
-      if (rc != MLC_OK) return rc;
+      chain[nchain++] = ChainDesc{j.w.X[0], j.w.X[1], j.p.ldx, j.p.mp * j.p.ldx, j.p.mp, j.p.np,
+                                  j.w.partials, j.p.nblk, j.chunk};
       continue;
     }
     const int rc = launch_norm_finalize(j.w.partials, j.p.nblk, j.w.scale, j.chunk, eps, stream);
     if (rc != MLC_OK) return rc;
     j.result_buf = 0;
     big[nbig++] = &j;
+  }
+  if (nchain) {
+    const int rc = launch_ns_chain_small(chain, nchain, eps, iters, a, b, c, stream);
+    if (rc != MLC_OK) return rc;
   }
   GemmDesc d[MAX_NS_JOBS];
   int cur = 0;

@@ -217,9 +217,16 @@ bool ns_chain_small_fits(int64_t mp, int64_t np);
 // in/out: [count] padded mp x np bf16 matrices, row pitch ld, batch stride `stride`
 // (elements); partials: per matrix nblk partial sums of squares of the input, from which the
 // kernel forms 1 / (norm + eps); iters >= 1.  in == out is allowed.
-int launch_ns_chain_small(const bf16_t* in, bf16_t* out, int64_t ld, int64_t stride, int64_t mp,
-                          int64_t np, const float* partials, int nblk, float eps, int64_t count,
-                          int iters, float a, float b, float c, hipStream_t stream);
+struct ChainDesc {
+  const bf16_t* in; bf16_t* out;
+  int64_t ld, stride, mp, np;
+  const float* partials; int nblk;
+  int64_t count;
+};
+constexpr int MAX_CHAINS = 16;
+// n (1 .. MAX_CHAINS) batches, side by side in one launch where the chip holds them all at once.
+int launch_ns_chain_small(const ChainDesc* d, int n, float eps, int iters, float a, float b, float c,
+                          hipStream_t stream);
 
 // ---- elementwise kernels of the inner step (inner_elementwise.hip) ----------------
 // U has row pitch ldx and is mp x np per matrix, or np x mp with `transposed`.

@@ -34,6 +34,7 @@ namespace {
 constexpr int S = 128;                 // padded short side
 constexpr int A_PITCH = S * 2;         // bytes per row of A
 
+constexpr int64_t CHAIN_SHARE_MAX = 256;     // compute units of the chip
 struct ChainArgs {
   const bf16_t* in;        // [batch] matrices, row pitch ld, batch stride `stride` (elements)
   bf16_t* out;             // same layout
@@ -65,8 +66,9 @@ __device__ __forceinline__ f32x16 mfma(const u32x4& a, const u32x4& b, const f32
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// The whole chain of matrix `mat` of a batch, by one workgroup.
 template <int TT>
-__global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
+__device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   constexpr int LP = 128 * TT;
   constexpr int X_PITCH = LP * 2;
   constexpr int X_BYTES = S * X_PITCH;
@@ -78,13 +80,13 @@ __global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lg = lane >> 5;
-  const bf16_t* in = g.in + (long)blockIdx.x * g.stride;
-  bf16_t* out = g.out + (long)blockIdx.x * g.stride;
+  const bf16_t* in = g.in + mat * g.stride;
+  bf16_t* out = g.out + mat * g.stride;
   const int L = g.L;
   // 1 / (|U| + eps) from the partial sums the pass that wrote U left behind (every wavefront
   // adds them up for itself, in the same order)
   float tot = 0.f;
-  for (int i = lane; i < g.nblk; i += 64) tot += g.partials[(long)blockIdx.x * g.nblk + i];
+  for (int i = lane; i < g.nblk; i += 64) tot += g.partials[mat * g.nblk + i];
   const float sumsq = wave_sum(tot);
   const float s = sumsq > 0.f ? 1.0f / (sqrtf(sumsq) + g.eps) : 0.f;   // all-zero matrix: 0, also when eps = 0
 
@@ -340,23 +342,59 @@ __global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
 }
 
 template <int TT>
-int launch_tt(const ChainArgs& g, int64_t count, hipStream_t stream) {
-  constexpr size_t lds = (size_t)S * 128 * TT * 2 + (size_t)S * A_PITCH;
-  auto kern = ns_chain_small_kernel<TT>;
-  // raised once per instantiation and device; the call is idempotent
-  static std::atomic<bool> attr_set[MAX_DEVICES];
+__global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
+  ns_chain_body<TT>(g, (long)blockIdx.x);
+}
+
+// Batches of several shapes in one launch.  A chain is a serial walk of one workgroup (32 us for
+// 128 x 128, 60 us for 128 x 512) that leaves the other compute units idle, so batches that fit
+// the chip together go side by side: 8 / 2 / 2 matrices of 128 x 128, 128 x 512 and 512 x 128 take
+// 60 us instead of 150 one after the other.
+struct ChainTable { ChainArgs s[MAX_CHAINS]; unsigned int blk0[MAX_CHAINS]; int n; };
+__global__ __launch_bounds__(256) void ns_chain_multi_kernel(ChainTable tab) {
+  int si = 0;
+  for (int i = 1; i < tab.n; ++i)
+    if (blockIdx.x >= tab.blk0[i]) si = i;
+  const ChainArgs g = tab.s[si];
+  const long mat = (long)(blockIdx.x - tab.blk0[si]);
+  if (g.L <= 128) ns_chain_body<1>(g, mat);
+  else if (g.L <= 256) ns_chain_body<2>(g, mat);
+  else ns_chain_body<4>(g, mat);
+}
+
+constexpr size_t chain_lds(int tt) { return (size_t)S * 128 * tt * 2 + (size_t)S * A_PITCH; }
+int chain_tt(const ChainArgs& g) { return g.L <= 128 ? 1 : g.L <= 256 ? 2 : 4; }
+// executed: the full Gram matrix and square (no triangle saving), all LP columns of X
+double chain_flops(const ChainArgs& g) {
+  return (2.0 * S * S * (double)g.L + 2.0 * S * S * S + 2.0 * S * S * (128.0 * chain_tt(g))) * g.iters;
+}
+// raised once per kernel and device; the call is idempotent
+int raise_lds_limit(const void* kern, std::atomic<bool>* done, size_t lds) {
   const int slot = device_slot();
-  if (slot < 0 || !attr_set[slot].load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+  if (slot < 0 || !done[slot].load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return MLC_ERR_LAUNCH;
-    if (slot >= 0) attr_set[slot].store(true, std::memory_order_release);
+    if (slot >= 0) done[slot].store(true, std::memory_order_release);
   }
-  // executed: the full Gram matrix and square (no triangle saving), all LP columns of X
-  const double per_iter = 2.0 * S * S * (double)g.L + 2.0 * S * S * S + 2.0 * S * S * (128.0 * TT);
-  LaunchScope scope(MLC_KERNEL_NS_GEMM, stream, per_iter * g.iters * (double)count, 0.0);
-  hipLaunchKernelGGL(kern, dim3((unsigned int)count), dim3(256), lds, stream, g);
+  return MLC_OK;
+}
+
+template <int TT>
+int launch_tt(const ChainArgs& g, int64_t count, hipStream_t stream) {
+  auto kern = ns_chain_small_kernel<TT>;
+  static std::atomic<bool> attr_set[MAX_DEVICES];
+  const int rc = raise_lds_limit(reinterpret_cast<const void*>(kern), attr_set, chain_lds(TT));
+  if (rc != MLC_OK) return rc;
+  LaunchScope scope(MLC_KERNEL_NS_GEMM, stream, chain_flops(g) * (double)count, 0.0);
+  hipLaunchKernelGGL(kern, dim3((unsigned int)count), dim3(256), chain_lds(TT), stream, g);
   return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH;
+}
+
+int launch_one(const ChainArgs& g, int64_t count, hipStream_t stream) {
+  const int tt = chain_tt(g);
+  if (tt == 1) return launch_tt<1>(g, count, stream);
+  if (tt == 2) return launch_tt<2>(g, count, stream);
+  return launch_tt<4>(g, count, stream);
 }
 
 }  // namespace
@@ -366,24 +404,50 @@ bool ns_chain_small_fits(int64_t mp, int64_t np) {
   return sp == S && lp <= 512;
 }
 
-int launch_ns_chain_small(const bf16_t* in, bf16_t* out, int64_t ld, int64_t stride, int64_t mp,
-                          int64_t np, const float* partials, int nblk, float eps, int64_t count,
-                          int iters, float a, float b, float c, hipStream_t stream) {
-  if (!ns_chain_small_fits(mp, np) || mp % 128 || np % 128) return MLC_ERR_SHAPE;
-  if (!in || !out || !partials) return MLC_ERR_NULL;
-  if (iters < 1 || count < 1 || count > 0x7fffffff || nblk < 1) return MLC_ERR_ARG;
-  const bool tall = mp > np;
-  // every 16-byte access stays inside a row of the padded matrix
-  if (ld % 8 || stride % 8 || ld < np || stride < mp * ld) return MLC_ERR_SHAPE;
-  ChainArgs g;
-  g.in = in; g.out = out; g.ld = ld; g.stride = stride;
-  g.tall = tall ? 1 : 0;
-  g.L = (int)(tall ? mp : np);
-  g.partials = partials; g.nblk = nblk; g.eps = eps;
-  g.iters = iters; g.a = a; g.b = b; g.c = c;
-  if (g.L <= 128) return launch_tt<1>(g, count, stream);
-  if (g.L <= 256) return launch_tt<2>(g, count, stream);
-  return launch_tt<4>(g, count, stream);
+int launch_ns_chain_small(const ChainDesc* d, int n, float eps, int iters, float a, float b, float c,
+                          hipStream_t stream) {
+  if (n < 1 || n > MAX_CHAINS || iters < 1) return MLC_ERR_ARG;
+  ChainTable tab;
+  tab.n = n;
+  int64_t total = 0;
+  int tt = 1;
+  double flops = 0.0;
+  for (int i = 0; i < MAX_CHAINS; ++i) {
+    const ChainDesc& c_ = d[i < n ? i : 0];
+    if (!ns_chain_small_fits(c_.mp, c_.np) || c_.mp % 128 || c_.np % 128) return MLC_ERR_SHAPE;
+    if (!c_.in || !c_.out || !c_.partials) return MLC_ERR_NULL;
+    if (c_.count < 1 || c_.count > 0x7fffffff || c_.nblk < 1) return MLC_ERR_ARG;
+    // every 16-byte access stays inside a row of the padded matrix
+    if (c_.ld % 8 || c_.stride % 8 || c_.ld < c_.np || c_.stride < c_.mp * c_.ld) return MLC_ERR_SHAPE;
+    const bool tall = c_.mp > c_.np;
+    ChainArgs& g = tab.s[i];
+    g.in = c_.in; g.out = c_.out; g.ld = c_.ld; g.stride = c_.stride;
+    g.tall = tall ? 1 : 0;
+    g.L = (int)(tall ? c_.mp : c_.np);
+    g.partials = c_.partials; g.nblk = c_.nblk; g.eps = eps;
+    g.iters = iters; g.a = a; g.b = b; g.c = c;
+    tab.blk0[i] = i < n ? (unsigned int)total : 0xffffffffu;
+    if (i >= n) continue;
+    total += c_.count;
+    if (chain_tt(g) > tt) tt = chain_tt(g);
+    flops += chain_flops(g) * (double)c_.count;
+  }
+  // Side by side as long as every matrix finds a compute unit of its own.  Beyond that a launch of
+  // its own is better for each batch: it asks for no more LDS than its shape needs, and two
+  // workgroups of the narrow shapes fit a compute unit.
+  if (n == 1 || total > CHAIN_SHARE_MAX) {
+    for (int i = 0; i < n; ++i) {
+      const int rc = launch_one(tab.s[i], d[i].count, stream);
+      if (rc != MLC_OK) return rc;
+    }
+    return MLC_OK;
+  }
+  static std::atomic<bool> attr_set[MAX_DEVICES];
+  const int rc = raise_lds_limit(reinterpret_cast<const void*>(ns_chain_multi_kernel), attr_set, chain_lds(4));
+  if (rc != MLC_OK) return rc;
+  LaunchScope scope(MLC_KERNEL_NS_GEMM, stream, flops, 0.0);
+  hipLaunchKernelGGL(ns_chain_multi_kernel, dim3((unsigned int)total), dim3(256), chain_lds(tt), stream, tab);
+  return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH;
 }
 
 }  // namespace mlc

@@ -233,3 +233,26 @@ def test_groups_of_different_kinds_side_by_side():
         sl = slice(c - 2, c)
         _check_group(W0[sl], g[sl], m0[sl], grp.param[sl].cpu(), grp.momentum[sl].cpu(), hp, math.sqrt(n / m),
                      f"group {m}x{n} {dtype_name(W0)}")
+
+
+@pytest.mark.parametrize("counts", [(3, 1, 2, 5), (200, 40, 10, 6), (250, 30, 1, 1)])
+def test_small_batches_side_by_side_equal_one_call_each(counts):
+    """Shapes of the one-workgroup chain in one call: their batches share a launch while all matrices
+    fit the chip at once (256), and go one after the other beyond."""
+    shapes = [(128, 128), (100, 250), (512, 128), (128, 384)]
+    hp = mlc.MuonHParams(eta=6.25e-2, weight_decay=1.25e-3)
+
+    def groups():
+        return [mlc.InnerGroup(*[t.to(DEV) for t in _make_group(c, m, n, torch.float32, torch.float32, 31 + i)], 1.0)
+                for i, (c, (m, n)) in enumerate(zip(counts, shapes))]
+
+    def step(gs):
+        ws = torch.empty(mlc.muloco_inner_workspace_bytes(gs), dtype=torch.uint8, device=DEV)
+        mlc.muloco_inner_step(gs, hp, ws)
+        torch.cuda.synchronize()
+    one, many = groups(), groups()
+    for g in one:
+        step([g])
+    step(many)
+    for a, b in zip(one, many):
+        assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
