@@ -53,7 +53,6 @@ constexpr int BK = 64;           // K depth of one LDS buffer
 constexpr int NTHREADS = 256;
 constexpr int NUM_XCD = 8;
 constexpr int GROUP_M = 8;        // most tile rows per group of the tile order
-constexpr long MIN_TILES_256 = 160;   // fewest 256 x 256 tiles of a product for which that tile is used
 
 struct GemmArgs {
   const bf16_t* A; long lda, strideA;
@@ -129,6 +128,8 @@ __device__ __forceinline__ void acc_settle(const f32x4 (&acc)[TI][TJ]) {
     if constexpr (TJ == 8)
       asm volatile("" :: "a"(acc[i][0]), "a"(acc[i][1]), "a"(acc[i][2]), "a"(acc[i][3]),
                          "a"(acc[i][4]), "a"(acc[i][5]), "a"(acc[i][6]), "a"(acc[i][7]));
+    else if constexpr (TJ == 2)
+      asm volatile("" :: "a"(acc[i][0]), "a"(acc[i][1]));
     else
       asm volatile("" :: "a"(acc[i][0]), "a"(acc[i][1]), "a"(acc[i][2]), "a"(acc[i][3]));
   }
@@ -147,6 +148,8 @@ __device__ __forceinline__ void store_words(const unsigned int (&w)[TI / 2], __a
     u32x4 v;
     v.x = w[0]; v.y = w[1]; v.z = w[2]; v.w = w[3];
     __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, 0);
+  } else if constexpr (TI == 2) {
+    __builtin_amdgcn_raw_buffer_store_b32(w[0], r, voff, soff, 0);
   } else {
     u32x2 v;
     v.x = w[0]; v.y = w[1];
@@ -198,6 +201,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
     auto load_c = [&](int J, int e) {
       const unsigned int soff = (unsigned int)(32 * J + e) * ldc2;
       if constexpr (TI == 8) c[e] = __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c, soff, 0);
+      else if constexpr (TI == 2) c[e].x = __builtin_amdgcn_raw_buffer_load_b32(rc, voff_c, soff, 0);
       else {
         const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rc, voff_c, soff, 0);
         c[e].x = v.x;
@@ -249,15 +253,16 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
     const int diag = col0 - row0;         // i - (32 J + e) of the lane's elements on the diagonal
     wait_vmcnt<HAS_C ? TI : 0>();
     acc_settle(acc);
+    constexpr int NH = NJ > 1 ? 2 : 1;      // 32-column blocks handled together
 #pragma unroll
-    for (int P = 0; P < NJ / 2; ++P) {
+    for (int P = 0; P < NJ / NH; ++P) {
       __builtin_amdgcn_sched_barrier(0);
-      u32x4 packed[TI][2];
+      u32x4 packed[TI][NH];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < NH; ++h)
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
-          const int J = 2 * P + h;
+          const int J = NH * P + h;
 #pragma unroll
           for (int e = 0; e < 8; e += 2) {
             float v0 = value(i, J, e), v1 = value(i, J, e + 1);
@@ -273,12 +278,18 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
           }
           if (HAS_C && J + 1 < NJ) load_c(J + 1, i);
         }
+      if constexpr (NH == 1) {      // a wavefront's rows are 64 bytes: nothing to gather
+        const unsigned int voff_n = (unsigned int)(((long)row0 * g.ldd + col0) * 2);
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
+        for (int i = 0; i < TI; ++i)
+          __builtin_amdgcn_raw_buffer_store_b128(packed[i][0], rd, voff_n + 64u * P, (unsigned int)i * ldd2, 0);
+      }
+#pragma unroll
+      for (int half = 0; half < (NH == 2 ? 2 : 0); ++half) {
 #pragma unroll
         for (int i = 0; i < TI / 2; ++i)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
+          for (int h = 0; h < NH; ++h)
             *reinterpret_cast<u32x4*>(put + i * 8192 + (((unsigned int)(4 * h + lg) ^ put_x) << 4)) =
                 packed[half * (TI / 2) + i][h];
 #pragma unroll
@@ -291,7 +302,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
       if constexpr (MIRROR) {
         // column col0 + 32 J + e of this tile becomes a row of the mirrored tile
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             unsigned int w[TI / 2];
@@ -299,7 +310,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
             for (int i = 0; i < TI; i += 2)
               w[i / 2] = (e & 1) ? pair_hi(packed[i][h][e / 2], packed[i + 1][h][e / 2])
                                  : pair_lo(packed[i][h][e / 2], packed[i + 1][h][e / 2]);
-            store_words<TI>(w, rd, voff_m, (unsigned int)(32 * (2 * P + h) + e) * ldd2);
+            store_words<TI>(w, rd, voff_m, (unsigned int)(32 * (NH * P + h) + e) * ldd2);
           }
       }
     }
@@ -365,7 +376,9 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   // slot's row at position x ^ ((slot / 2) % 8): the LDS serves a 128-bit read 16 lanes at a
   // time over 64 banks, and the 16 lanes of one k chunk then meet 16 different 16-byte columns.
   // K-strided buffer: [k][BN], chunk x of row k at position x ^ 4 (k % 4), for the same reason
-  // (a transposing read takes 4 chunks of each of 4 consecutive k).
+  // (a transposing read takes 4 chunks of each of 4 consecutive k); with BN = 64 two rows share
+  // the 256 bytes of a bank line and the position is x ^ 4 (k / 2 % 2).
+  auto ks_swizzle = [](int k) { return BN == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); };
   const int slot = tid >> 3;
   const unsigned int kc_chunk = (unsigned int)(((tid & 7) ^ ((tid >> 4) & 7)) * 16);
   const unsigned int lda2 = (unsigned int)(g.lda * 2), ldb2 = (unsigned int)(g.ldb * 2);
@@ -373,7 +386,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   unsigned int voffB;
   if constexpr (BKS) {
     constexpr int CPR = BN / 8;
-    voffB = (unsigned int)(tid / CPR) * ldb2 + (unsigned int)(((tid % CPR) ^ (4 * ((tid / CPR) & 3))) * 16);
+    voffB = (unsigned int)(tid / CPR) * ldb2 + (unsigned int)(((tid % CPR) ^ ks_swizzle(tid / CPR)) * 16);
   } else {
     voffB = (unsigned int)(8 * ((slot & 15) >> 2) + 4 * (slot >> 4) + (slot & 3)) * ldb2 + kc_chunk;
   }
@@ -391,7 +404,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
     const int k4 = idx >> 2, q = idx & 3;
 #pragma unroll
     for (int J = 0; J < TJ / 2; ++J)
-      fragB[J] = (unsigned int)(8 * lg + k4) * (BN * 2) + (unsigned int)(((wbase_n / 8 + 4 * J + q) ^ (4 * k4)) * 16);
+      fragB[J] = (unsigned int)(8 * lg + k4) * (BN * 2) + (unsigned int)(((wbase_n / 8 + 4 * J + q) ^ ks_swizzle(k4)) * 16);
   } else {
     fragB[0] = (unsigned int)(wbase_n + idx) * 128 + (((unsigned int)lg ^ swz) * 16);
   }
@@ -399,7 +412,8 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   u32x4 fa[2][TI], fb[2][TJ];
   f32x4 acc[TI][TJ];
   constexpr int NR = TI + (BKS ? 2 * TJ : TJ);       // LDS reads per slice
-  constexpr int RSTEP = NM / 2 / NR > 0 ? NM / 2 / NR : 1;
+  constexpr int RSTEP = NM / 2 / NR > 0 ? NM / 2 / NR : 1;      // MFMAs between reads ...
+  constexpr int RPER = (NR + NM - 1) / NM;                      // ... and reads at a time
   constexpr int DSTEP = NM / NCH;                    // MFMAs between transfers
 
   // LDS read r of a slice: A0, all of B, the rest of A.
@@ -459,8 +473,8 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
     switch (n) {
       case 0: f(I<0>{}); break;
       case 1: f(I<1>{}); break;
-      case 2: f(I<2>{}); break;
-      case 3: f(I<3>{}); break;
+      case 2: if constexpr (NCH > 2) f(I<2 % NCH>{}); break;
+      case 3: if constexpr (NCH > 2) f(I<3 % NCH>{}); break;
       case 4: if constexpr (NCH > 4) f(I<4 % NCH>{}); break;
       case 5: if constexpr (NCH > 4) f(I<5 % NCH>{}); break;
       case 6: if constexpr (NCH > 4) f(I<6 % NCH>{}); break;
@@ -480,7 +494,9 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
       if constexpr (ZERO) c = f32x4{0.f, 0.f, 0.f, 0.f};
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
           __builtin_bit_cast(bf16x8, fb[S][j]), __builtin_bit_cast(bf16x8, fa[S][i]), c, 0, 0, 0);
-      if (n % RSTEP == 0 && n / RSTEP < NR) read_one(1 - S, n / RSTEP);
+#pragma unroll
+      for (int r = 0; r < RPER; ++r)
+        if (n % RSTEP == 0 && n / RSTEP * RPER + r < NR) read_one(1 - S, n / RSTEP * RPER + r);
       if (n % DSTEP == 1) dma_n(n / DSTEP, issue);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -720,12 +736,56 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
 }
 
 template <bool BKS>
-int launch_tiles(const GemmDesc* const* d, int n, bool tile256, hipStream_t stream) {
-  if (tile256) return launch_cfg<256, 256, BKS, 5>(d, n, stream);
-  // The small tile leaves room for a ring of nine buffers, four K tiles ahead; a product of two
+int launch_tiles(const GemmDesc* const* d, int n, int tile, hipStream_t stream) {
+  if (tile == 256) return launch_cfg<256, 256, BKS, 5>(d, n, stream);
+  // The small tiles leave room for a ring of nine buffers, four K tiles ahead; a product of two
   // or three K tiles has no use for it.
-  if (d[0]->K >= 256) return launch_cfg<128, 128, BKS, 9>(d, n, stream);
-  return launch_cfg<128, 128, BKS, 5>(d, n, stream);
+  if (d[0]->K < 256) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
+  if (tile == 128) return launch_cfg<128, 128, BKS, 9>(d, n, stream);
+  return launch_cfg<64, 64, BKS, 9>(d, n, stream);
+}
+
+long tiles_of(const GemmDesc& d, int tile) {
+  const long tm = d.M / tile, tn = d.N / tile;
+  return (d.symmetric ? tm * (tm + 1) / 2 : tm * tn) * d.batch;
+}
+
+// Microseconds that a launch of `tiles` output tiles takes, from kernel traces over 1 to 64
+// matrices of 256 to 4096 (within 15 % of them): a fixed part, and for every round of one tile
+// per compute unit the K tiles and the epilogue.  The 256 x 256 tile runs faster in a round that
+// leaves compute units idle (the chip is power-limited), and pays for the transposed copy that
+// a symmetric result takes.
+double estimate_us(int tile, long tiles, int kt, bool symmetric, int cus) {
+  const double launch = 3.5;
+  const long full = tiles / cus, rest = tiles - full * cus;
+  if (tile == 256) {
+    const double epi = symmetric ? 12.0 : 9.0;
+    return launch + full * (kt * 1.40 + epi) + (rest ? kt * (1.02 + 0.38 * (double)rest / cus) + epi - 1.0 : 0.0);
+  }
+  const double per_round = tile == 128 ? kt * 0.47 + 3.2 : kt * 0.22 + 1.2;
+  return launch + (full + (rest ? 1 : 0)) * per_round;
+}
+
+// The tile for a launch of these products.  One large tile moves half the operand bytes per FLOP
+// of a 128 x 128 one (1.25 against 0.9 PFLOP/s where both fill the chip), but products with few
+// tiles leave most of the chip idle: one 1024 x 1024 matrix takes 27 us a product in 16 tiles of
+// 256, 13 in 64 of 128, 9 in 256 of 64; six of 1024 x 3072 take 54, 48 and 81 for the last product
+// of an iteration.  A smaller tile has to be clearly ahead: the estimate is not exact, and it is
+// optimistic for small tiles over sets of matrices that no longer fit the caches (32 Gram
+// products of 1024 x 1024: estimated 0.86 of the large tile's time, measured 1.2).
+int pick_tile(const GemmDesc* const* d, int n, int cus) {
+  long tiles[3] = {0, 0, 0};
+  bool divides = true;
+  for (int j = 0; j < n; ++j) {
+    divides = divides && d[j]->M % 256 == 0 && d[j]->N % 256 == 0;
+    for (int t = 0; t < 3; ++t) tiles[t] += tiles_of(*d[j], 256 >> t);
+  }
+  const int kt = d[0]->K / BK;
+  const bool sym = d[0]->symmetric != 0;
+  const double e128 = estimate_us(128, tiles[1], kt, sym, cus), e64 = estimate_us(64, tiles[2], kt, sym, cus);
+  const int small = e64 < 0.95 * e128 ? 64 : 128;
+  if (!divides) return small;
+  return (small == 64 ? e64 : e128) < 0.85 * estimate_us(256, tiles[0], kt, sym, cus) ? small : 256;
 }
 
 }  // namespace
@@ -735,7 +795,7 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   bool done[64] = {};
   for (int i = 0; i < n; ++i)
     if (!valid_desc(d[i])) return MLC_ERR_SHAPE;
-  auto tiles = [](const GemmDesc& g) { return (long)(g.M / 256) * (g.N / 256) * g.batch; };
+  const int cus = cus_per_xcd(device_slot()) * NUM_XCD;
   auto divides = [](const GemmDesc& g) { return g.M % 256 == 0 && g.N % 256 == 0; };
   for (int i = 0; i < n; ++i) {
     if (done[i]) continue;
@@ -744,20 +804,16 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
     const GemmDesc* pick[MAX_MULTI] = {&d[i], nullptr, nullptr};
     int idx[MAX_MULTI] = {i, -1, -1};
     int np = 1;
-    long total = tiles(d[i]);
     for (int j = i + 1; j < n && np < MAX_MULTI; ++j) {
       if (done[j] || d[j].K != d[i].K || divides(d[j]) != divides(d[i]) ||
           (d[j].b_kstrided != 0) != (d[i].b_kstrided != 0))
         continue;
       pick[np] = &d[j];
       idx[np++] = j;
-      total += tiles(d[j]);
     }
-    // The large tile as soon as it occupies most of the chip for one round: the small tile moves
-    // twice the operand bytes per FLOP and needs four times the tiles.
-    const bool tile256 = divides(d[i]) && total >= MIN_TILES_256;
-    const int rc = d[i].b_kstrided ? launch_tiles<true>(pick, np, tile256, stream)
-                                   : launch_tiles<false>(pick, np, tile256, stream);
+    const int tile = pick_tile(pick, np, cus);
+    const int rc = d[i].b_kstrided ? launch_tiles<true>(pick, np, tile, stream)
+                                   : launch_tiles<false>(pick, np, tile, stream);
     if (rc != MLC_OK) return rc;
     for (int k = 0; k < np; ++k) done[idx[k]] = true;
   }

@@ -131,6 +131,9 @@ def test_more_small_tiles_than_compute_units(cnt, m, n):
     (70, 128, 640), (70, 640, 128),      # K = 128: two K tiles, the short ring; tall: transposed result
     (40, 256, 640), (40, 640, 250),      # K = 256: as many K tiles as the long ring holds ahead; ragged tall
     (90, 512, 768), (90, 768, 512),      # 256 x 256 tiles, a second output tile for some workgroups
+    (1, 384, 1152), (1, 1152, 384),      # 64 x 64 tiles, fewer than compute units
+    (9, 256, 1300), (9, 1300, 256),      # 64 x 64 tiles, more than compute units in the last product
+    (1, 128, 1000),                      # K = 128 again: too short for the small tile's ring
 ])
 def test_ring_across_output_tiles(cnt, m, n):
     x = S.normal((cnt, m, n), S.GRAD_STD, seed=9, stream=cnt + m, dtype=torch.bfloat16)
