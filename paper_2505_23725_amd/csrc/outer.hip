@@ -24,6 +24,19 @@ __device__ __forceinline__ void outer_update(float& theta, float& u, float psi, 
   theta = Vec8<GT>::round(nesterov ? theta - mu * u - step : theta - u);
 }
 
+// 8 elements, `left` of them before the end of the row or matrix (RAG: perhaps fewer than 8, and at
+// any alignment).
+template <typename T, bool RAG>
+__device__ __forceinline__ void load8(const T* p, int left, float (&v)[8]) {
+  if constexpr (RAG) Vec8<T>::unpack(Vec8U<T>::load_raw(p, left), v);
+  else Vec8<T>::load(p, v);
+}
+template <typename T, bool RAG>
+__device__ __forceinline__ void store8(T* p, const float (&v)[8], int left) {
+  if constexpr (RAG) Vec8U<T>::store(p, v, left);
+  else Vec8<T>::store(p, v);
+}
+
 // ---- unquantised fused outer step ---------------------------------------------------
 // Workgroup blk of nblk walks over its share of the n_elems elements.
 template <typename WT, typename GT, typename PW>
@@ -207,23 +220,18 @@ __global__ __launch_bounds__(OT_THREADS) void matrix_range_kernel(
   const GT* tg = theta_g + b * elems;
   const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
   const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
-  constexpr int W = VEC ? 8 : 1;
   float mn = INFINITY, mx = -INFINITY;
-  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * W; i < elems;
-       i += (long)gridDim.x * OT_THREADS * W) {
+  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)gridDim.x * OT_THREADS * 8) {
     float a[8], c[8], e[8];
-    if (VEC) {
-      Vec8<GT>::load(tg + i, a); Vec8<WT>::load(tk + i, c);
-      if (res) Vec8<float>::load(res + i, e);
-    } else {
-      a[0] = Vec8<GT>::load1(tg + i); c[0] = Vec8<WT>::load1(tk + i);
-      if (res) e[0] = res[i];
-    }
+    const int left = (int)min(elems - i, 8L);
+    load8<GT, !VEC>(tg + i, left, a); load8<WT, !VEC>(tk + i, left, c);
+    if (res) load8<float, !VEC>(res + i, left, e);
 #pragma unroll
-    for (int j = 0; j < W; ++j) {
+    for (int j = 0; j < 8; ++j) {
       const float d = a[j] - c[j];
       const float v = res ? ef_input(d, e[j], form.ef_beta) : d;
-      mn = fminf(mn, v); mx = fmaxf(mx, v);
+      if (VEC || j < left) { mn = fminf(mn, v); mx = fmaxf(mx, v); }
     }
   }
   mn = wave_min(mn); mx = wave_max(mx);
@@ -334,19 +342,6 @@ __global__ __launch_bounds__(OT_THREADS) void quantize_rows_kernel(
       }
     }
   }
-}
-
-// 8 elements of a row from column c on, `left` of them before its end (RAG: perhaps fewer than 8,
-// and at any alignment).
-template <typename T, bool RAG>
-__device__ __forceinline__ void load8(const T* p, int left, float (&v)[8]) {
-  if constexpr (RAG) Vec8<T>::unpack(Vec8U<T>::load_raw(p, left), v);
-  else Vec8<T>::load(p, v);
-}
-template <typename T, bool RAG>
-__device__ __forceinline__ void store8(T* p, const float (&v)[8], int left) {
-  if constexpr (RAG) Vec8U<T>::store(p, v, left);
-  else Vec8<T>::store(p, v);
 }
 
 // Single-pass variant: a group of G threads (a wavefront or the whole workgroup) owns a row
@@ -686,7 +681,11 @@ __global__ void topk_init_kernel(TopkState* st, unsigned int kcount) {
   if (threadIdx.x == 0) { s.prefix = 0u; s.mask = 0u; s.rank = kcount; s.pad = 0u; }
 }
 
-template <typename WT, typename GT, bool VEC>
+// FIRST: the pass that computes v = beta E + (theta_g - theta_k).  With error feedback it leaves v
+// in E, where it ends up anyway unless it is sent: the later passes then read 4 bytes an element
+// instead of 10, and the update needs no worker parameters (six layers of 2048 / 8192, K = 1:
+// 3300 -> 2880 us).
+template <typename WT, typename GT, bool VEC, bool FIRST>
 __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
     WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count,
     int shift, int nbins, float ef_beta) {
@@ -702,27 +701,40 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
   unsigned int* mine = lh[threadIdx.x >> 6];
   const GT* tg = theta_g + b * elems;
   const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
-  const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
-  constexpr int W = VEC ? 8 : 1;
-  unsigned int cur = 0xffffffffu, run = 0u;       // run-length of the current digit
-  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * W; i < elems;
-       i += (long)gridDim.x * OT_THREADS * W) {
-    float a[8], c[8], e[8];
-    if (VEC) {
-      Vec8<GT>::load(tg + i, a); Vec8<WT>::load(tk + i, c);
-      if (res) Vec8<float>::load(res + i, e);
+  float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
+  unsigned int cur = FIRST ? 0u : 0xffffffffu, run = 0u;       // run-length of the current digit
+  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)gridDim.x * OT_THREADS * 8) {
+    float vals[8];
+    const int left = (int)min(elems - i, 8L);
+    if (!FIRST && res) {
+      load8<float, !VEC>(res + i, left, vals);
     } else {
-      a[0] = Vec8<GT>::load1(tg + i); c[0] = Vec8<WT>::load1(tk + i);
-      if (res) e[0] = res[i];
+      float a[8], c[8];
+      load8<GT, !VEC>(tg + i, left, a); load8<WT, !VEC>(tk + i, left, c);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) vals[j] = a[j] - c[j];
+      if (res) {
+        float e[8];
+        load8<float, !VEC>(res + i, left, e);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) vals[j] = ef_input(vals[j], e[j], ef_beta);
+        store8<float, !VEC>(res + i, vals, left);
+      }
     }
 #pragma unroll
-    for (int j = 0; j < W; ++j) {
-      const float d = a[j] - c[j];
-      const float v = res ? ef_input(d, e[j], ef_beta) : d;
+    for (int j = 0; j < 8; ++j) {
+      if (!VEC && j >= left) break;
+      const float v = vals[j];
       const unsigned int key = __float_as_uint(fabsf(v));
       if ((key & mask) == prefix) {
         const unsigned int bin = (key >> shift) & digit_mask;
-        if (bin == cur) {
+        // The first digit changes from element to element (counting runs there took 335 us a pass
+        // instead of 290); zeros, of which a step that moved little has many, are kept apart.
+        if (FIRST) {
+          if (key == 0u) ++run;
+          else atomicAdd(&mine[bin], 1u);
+        } else if (bin == cur) {
           ++run;
         } else {
           if (run) atomicAdd(&mine[cur], run);
@@ -796,8 +808,8 @@ __global__ __launch_bounds__(256) void topk_pick_kernel(TopkState* st, int shift
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
     WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
-    const TopkState* st, long elems, int count, int K, float ef_beta, float eta, float mu, float inv_k,
-    int nesterov, int write_back) {
+    const TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov,
+    int write_back) {
   __shared__ unsigned int tau[MLC_MAX_WORKERS];
   const long b = blockIdx.y;
   if (threadIdx.x < K) {
@@ -808,51 +820,37 @@ __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
   __syncthreads();
   GT* tg = theta_g + b * elems;
   float* ub = u + b * elems;
-  constexpr int W = VEC ? 8 : 1;
-  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * W; i < elems;
-       i += (long)gridDim.x * OT_THREADS * W) {
+  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)gridDim.x * OT_THREADS * 8) {
     float a[8], uv[8], acc[8];
-    if (VEC) { Vec8<GT>::load(tg + i, a); Vec8<float>::load(ub + i, uv); }
-    else { a[0] = Vec8<GT>::load1(tg + i); uv[0] = ub[i]; }
+    const int left = (int)min(elems - i, 8L);
+    load8<GT, !VEC>(tg + i, left, a); load8<float, !VEC>(ub + i, left, uv);
 #pragma unroll
-    for (int j = 0; j < W; ++j) acc[j] = 0.f;
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     for (int k = 0; k < K; ++k) {
-      const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
       float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
-      float c[8], e[8];
-      if (VEC) {
-        Vec8<WT>::load(tk + i, c);
-        if (res) Vec8<float>::load(res + i, e);
+      float v[8];
+      if (res) {                       // v is already there
+        load8<float, !VEC>(res + i, left, v);
       } else {
-        c[0] = Vec8<WT>::load1(tk + i);
-        if (res) e[0] = res[i];
+        load8<WT, !VEC>(reinterpret_cast<const WT*>(w.p[k]) + b * elems + i, left, v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = a[j] - v[j];
       }
 #pragma unroll
-      for (int j = 0; j < W; ++j) {
-        const float d = a[j] - c[j];
-        const float v = res ? ef_input(d, e[j], ef_beta) : d;
-        const bool keep = __float_as_uint(fabsf(v)) >= tau[k];
-        acc[j] += keep ? v : 0.f;
-        e[j] = keep ? 0.f : v;           // what was not sent
+      for (int j = 0; j < 8; ++j) {
+        const bool keep = __float_as_uint(fabsf(v[j])) >= tau[k];
+        acc[j] += keep ? v[j] : 0.f;
+        v[j] = keep ? 0.f : v[j];           // what was not sent
       }
-      if (res) {
-        if (VEC) Vec8<float>::store(res + i, e);
-        else res[i] = e[0];
-      }
+      if (res) store8<float, !VEC>(res + i, v, left);
     }
 #pragma unroll
-    for (int j = 0; j < W; ++j) outer_update<GT>(a[j], uv[j], __fmul_rn(acc[j], inv_k), eta, mu, nesterov);
-    if (VEC) {
-      Vec8<GT>::store(tg + i, a);
-      Vec8<float>::store(ub + i, uv);
-      if (write_back)
-        for (int k = 0; k < K; ++k) Vec8<WT>::store(reinterpret_cast<WT*>(w.p[k]) + b * elems + i, a);
-    } else {
-      Vec8<GT>::store1(tg + i, a[0]);
-      ub[i] = uv[0];
-      if (write_back)
-        for (int k = 0; k < K; ++k) Vec8<WT>::store1(reinterpret_cast<WT*>(w.p[k]) + b * elems + i, a[0]);
-    }
+    for (int j = 0; j < 8; ++j) outer_update<GT>(a[j], uv[j], __fmul_rn(acc[j], inv_k), eta, mu, nesterov);
+    store8<GT, !VEC>(tg + i, a, left);
+    store8<float, !VEC>(ub + i, uv, left);
+    if (write_back)
+      for (int k = 0; k < K; ++k) store8<WT, !VEC>(reinterpret_cast<WT*>(w.p[k]) + b * elems + i, a, left);
   }
 }
 
@@ -915,7 +913,7 @@ int launch_matrix_ranges(const WorkerPtrs& w, int worker_dtype, const void* thet
   if (count > 65535 || K > 65535) return MLC_ERR_SHAPE;
   const long elems = m * n;
   const bool vec = elems % 8 == 0;
-  const int nblk = cap_blocks((elems / (vec ? 8 : 1) + OT_THREADS - 1) / OT_THREADS, 512);
+  const int nblk = cap_blocks(((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, 512);
   const double bytes = (double)count * elems * (K * esize(worker_dtype) + K * esize(global_dtype) +
                                                 (has_residuals(ef) ? 4.0 * K : 0.0));
   LaunchScope scope(MLC_KERNEL_QUANTIZE, stream, 0.0, bytes);
@@ -1190,32 +1188,32 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
   TopkState* st = (TopkState*)workspace;
   const long elems = m * n;
   const bool vec = elems % 8 == 0;
-  const int nblk = cap_blocks((elems / (vec ? 8 : 1) + OT_THREADS - 1) / OT_THREADS, 256);
+  const int nblk = cap_blocks(((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, 256);
   const int n_states = (int)(count * K);
-  const double pass_bytes = (double)count * elems * (K * esize(worker_dtype) + K * esize(global_dtype) +
-                                                     (has_residuals(ef) ? 4.0 * K : 0.0));
-  const double last_bytes = (double)count * elems * (K * esize(worker_dtype) * (write_back ? 2 : 1) +
-                                                     (has_residuals(ef) ? 8.0 * K : 0.0) +
-                                                     2 * esize(global_dtype) + 8);
-  LaunchScope scope(MLC_KERNEL_TOPK, stream, 0.0, 3 * pass_bytes + last_bytes);
+  const bool fb = has_residuals(ef);
+  const double inputs = K * (esize(worker_dtype) + esize(global_dtype));
+  // three passes over the values (with error feedback: the inputs once, then the residuals), the update
+  const double passes = fb ? inputs + 8.0 * K + 2 * 4.0 * K : 3 * inputs;
+  const double last = (fb ? 8.0 * K : K * esize(worker_dtype)) + (write_back ? K * esize(worker_dtype) : 0.0) +
+                      2 * esize(global_dtype) + 8;
+  LaunchScope scope(MLC_KERNEL_TOPK, stream, 0.0, (double)count * elems * (passes + last));
   hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
   // digits of 11, 10 and 10 bits cover bits 30 .. 0 of |v|
   const int shifts[3] = {20, 10, 0}, bins[3] = {2048, 1024, 1024};
   for (int pass = 0; pass < 3; ++pass) {
     const int shift = shifts[pass], nbins = bins[pass];
+#define MLC_HIST(WT, GT, V, F)                                                                    \
+  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(nblk, (unsigned)count, K),             \
+                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, \
+                     shift, nbins, ef_beta)
 #define MLC_CALL(WT, GT)                                                                          \
   do {                                                                                            \
-    if (vec)                                                                                      \
-      hipLaunchKernelGGL((topk_hist_kernel<WT, GT, true>), dim3(nblk, (unsigned)count, K),         \
-                         dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems,       \
-                         (int)count, shift, nbins, ef_beta);                                      \
-    else                                                                                          \
-      hipLaunchKernelGGL((topk_hist_kernel<WT, GT, false>), dim3(nblk, (unsigned)count, K),        \
-                         dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems,       \
-                         (int)count, shift, nbins, ef_beta);                                      \
+    if (vec) { if (pass == 0) MLC_HIST(WT, GT, true, true); else MLC_HIST(WT, GT, true, false); } \
+    else { if (pass == 0) MLC_HIST(WT, GT, false, true); else MLC_HIST(WT, GT, false, false); }   \
   } while (0)
     MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
+#undef MLC_HIST
     hipLaunchKernelGGL(topk_pick_kernel, dim3(n_states), dim3(256), 0, stream, st, shift, nbins);
   }
   const float inv_k = 1.0f / (float)K;
@@ -1224,11 +1222,11 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
     if (vec)                                                                                      \
       hipLaunchKernelGGL((topk_outer_kernel<WT, GT, true>), dim3(nblk, (unsigned)count),           \
                          dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, ef, thresholds, st, elems, \
-                         (int)count, K, ef_beta, eta_out, mu, inv_k, nesterov, write_back);       \
+                         (int)count, K, eta_out, mu, inv_k, nesterov, write_back);       \
     else                                                                                          \
       hipLaunchKernelGGL((topk_outer_kernel<WT, GT, false>), dim3(nblk, (unsigned)count),          \
                          dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, ef, thresholds, st, elems, \
-                         (int)count, K, ef_beta, eta_out, mu, inv_k, nesterov, write_back);       \
+                         (int)count, K, eta_out, mu, inv_k, nesterov, write_back);       \
   } while (0)
   MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL

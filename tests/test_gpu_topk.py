@@ -78,3 +78,16 @@ def test_topk_second_call_reuses_the_workspace():
         torch.cuda.synchronize()
         outs.append((tg.cpu(), u.cpu()))
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+# sizes that no vector of 8 divides (shorter than one, one over, one short), with the residual
+# holding v between the passes and without a residual
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef", [
+    (3, 1, 5, 2, torch.bfloat16, torch.float32, 0.3, True),
+    (2, 3, 3, 1, torch.float32, torch.float32, 0.5, False),
+    (2, 77, 1001, 3, torch.bfloat16, torch.bfloat16, 0.05, True),
+    (1, 411, 271, 2, torch.bfloat16, torch.float32, 0.02, False),
+    (2, 511, 513, 1, torch.float32, torch.bfloat16, 0.01, True),
+])
+def test_topk_sizes_off_the_vector(cnt, m, n, K, wd, gd, frac, ef):
+    test_topk_outer_step_matches_oracle(cnt, m, n, K, wd, gd, frac, ef)
