@@ -32,7 +32,7 @@
 // Measured (batches of 2048-wide matrices, executed FLOP): the K loop alone runs at 1.49 PFLOP/s,
 // whole launches at 1.18-1.41 depending on their depth; the kernel this one replaced (32x32x16
 // MFMAs, 32-deep half-line stages requested in bursts) ran at 1.09.  What is left on top of the
-// K loop is the epilogue: 7 us per 256 x 256 tile, 10 with the transposed copy, against 47 us of
+// K loop is the epilogue: 7 us per 256 x 256 tile, 9 with the transposed copy, against 47 us of
 // K loop at K = 2048, of which 2 to 3 us are the conversions and the rest the stores.
 #include <atomic>
 #include <type_traits>
