@@ -466,6 +466,7 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
   const size_t all = (n_groups >= 2 && n_groups <= MAX_NS_JOBS) ? inner_workspace_all(groups, n_groups) : 0;
   if (all && workspace_bytes >= all) {
     NsJob jobs[MAX_NS_JOBS];
+    MomentumDesc mom[MAX_NS_JOBS];
     unsigned char* base = (unsigned char*)workspace;
     for (int gi = 0; gi < n_groups; ++gi) {
       const mlc_inner_group& g = groups[gi];
@@ -479,12 +480,12 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
         jobs[gi].fuse_step = hp->eta * g.lr_scale;
       }
       base += jobs[gi].p.per_matrix * (size_t)g.count;
-      rc = launch_momentum(g.grad, g.grad_dtype, g.momentum, jobs[gi].w.X[0], jobs[gi].w.partials,
-                           jobs[gi].p.nblk, g.count, g.m, g.n, jobs[gi].p.mp, jobs[gi].p.np,
-                           x_pitch(jobs[gi].p, hp->ns_iters), store_transposed(jobs[gi].p, hp->ns_iters),
-                           hp->beta, hp->nesterov, stream);
-      if (rc != MLC_OK) return rc;
+      mom[gi] = MomentumDesc{g.grad, g.grad_dtype, g.momentum, jobs[gi].w.X[0], jobs[gi].w.partials,
+                             jobs[gi].p.nblk, g.count, g.m, g.n, jobs[gi].p.mp, jobs[gi].p.np,
+                             x_pitch(jobs[gi].p, hp->ns_iters), store_transposed(jobs[gi].p, hp->ns_iters)};
     }
+    rc = launch_momentum(mom, n_groups, hp->beta, hp->nesterov, stream);
+    if (rc != MLC_OK) return rc;
     rc = run_ns_jobs(jobs, n_groups, hp->ns_iters, hp->ns_a, hp->ns_b, hp->ns_c, hp->ns_eps, stream);
     if (rc != MLC_OK) return rc;
     for (int gi = 0; gi < n_groups; ++gi) {
@@ -509,9 +510,9 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
       const unsigned char* grad = (const unsigned char*)g.grad + c0 * mat * elem_size(g.grad_dtype);
       unsigned char* param = (unsigned char*)g.param + c0 * mat * elem_size(g.param_dtype);
       float* mom = g.momentum + c0 * mat;
-      rc = launch_momentum(grad, g.grad_dtype, mom, w.X[0], w.partials, p.nblk, cc, g.m, g.n, p.mp,
-                           p.np, x_pitch(p, hp->ns_iters), store_transposed(p, hp->ns_iters), hp->beta,
-                           hp->nesterov, stream);
+      const MomentumDesc md{grad, g.grad_dtype, mom, w.X[0], w.partials, p.nblk, cc, g.m, g.n, p.mp, p.np,
+                            x_pitch(p, hp->ns_iters), store_transposed(p, hp->ns_iters)};
+      rc = launch_momentum(&md, 1, hp->beta, hp->nesterov, stream);
       if (rc != MLC_OK) return rc;
       int res = 0;
       const bool fuse = can_fuse_update(p, g.param_dtype, hp->ns_iters);

@@ -230,9 +230,12 @@ int launch_ns_chain_small(const ChainDesc* d, int n, float eps, int iters, float
 
 // ---- elementwise kernels of the inner step (inner_elementwise.hip) ----------------
 // U has row pitch ldx and is mp x np per matrix, or np x mp with `transposed`.
-int launch_momentum(const void* grad, int grad_dtype, float* mom, bf16_t* U, float* partials,
-                    int nblk, int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np,
-                    int64_t ldx, bool transposed, float beta, int nesterov, hipStream_t stream);
+constexpr int INNER_MAX_SEG = 4;       // groups of one launch
+struct MomentumDesc {
+  const void* grad; int grad_dtype; float* mom; bf16_t* U; float* partials; int nblk;
+  int64_t count, m, n, mp, np, ldx; bool transposed;
+};
+int launch_momentum(const MomentumDesc* d, int n, float beta, int nesterov, hipStream_t stream);
 int launch_ns_load(const void* in, int dtype, bf16_t* U, float* partials, int nblk,
                    int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t ldx,
                    bool transposed, hipStream_t stream);

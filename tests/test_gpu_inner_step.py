@@ -256,3 +256,27 @@ def test_small_batches_side_by_side_equal_one_call_each(counts):
     step(many)
     for a, b in zip(one, many):
         assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
+
+
+def test_more_groups_than_one_momentum_launch_holds():
+    """Seven groups of one kind (a launch holds four) between groups of other kinds: transposed,
+    ragged, another gradient type."""
+    shapes = [(128, 128)] * 3 + [(640, 256), (130, 77)] + [(128, 256)] * 4 + [(256, 384)]
+    hp = mlc.MuonHParams(eta=6.25e-2, weight_decay=1.25e-3)
+
+    def groups():
+        return [mlc.InnerGroup(*[t.to(DEV) for t in _make_group(
+                    2, m, n, torch.float32, torch.bfloat16 if i == 9 else torch.float32, 51 + i)], 1.0)
+                for i, (m, n) in enumerate(shapes)]
+
+    def step(gs):
+        ws = torch.empty(mlc.muloco_inner_workspace_bytes(gs), dtype=torch.uint8, device=DEV)
+        mlc.muloco_inner_step(gs, hp, ws)
+        torch.cuda.synchronize()
+    one, many = groups(), groups()
+    for g in one:
+        step([g])
+    step(many)
+    for i, (a, b) in enumerate(zip(one, many)):
+        assert torch.equal(a.momentum, b.momentum), f"group {i}"
+        assert torch.equal(a.param, b.param), f"group {i}"
