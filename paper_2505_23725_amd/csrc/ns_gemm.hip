@@ -53,6 +53,7 @@ constexpr int BK = 64;           // K depth of one LDS buffer
 constexpr int NTHREADS = 256;
 constexpr int NUM_XCD = 8;
 constexpr int GROUP_M = 8;        // most tile rows per group of the tile order
+constexpr size_t CU_LDS = 160 * 1024;
 
 struct GemmArgs {
   const bf16_t* A; long lda, strideA;
@@ -704,10 +705,12 @@ template <int BM, int BN, bool BKS, int NB>
 int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   MultiArgs m;
   m.nseg = n;
-  // One workgroup per CU, always: every ring is given more than half of the LDS.  With two
-  // workgroups of an earlier 128 x 128 kernel on one CU the second one's tiles came out wrong, from
-  // run to run on different tiles.  (Suspected, not established: the LDS address of
-  // `buffer_load ... lds`, taken from m0, when an LDS allocation does not start at 0.)
+  // Every launch asks for the whole LDS of a CU, however small its ring, so that its workgroups
+  // share a CU with no other workgroup that holds LDS, neither of this kernel nor of one that runs on
+  // another stream: an earlier 128 x 128 kernel gave wrong tiles when two of its workgroups were on
+  // one CU, and why is not known.  (Not the LDS address of the transfers: `buffer_load ... lds`
+  // lands where it should in allocations of 20, 40 and 80 KiB that do not start at 0, measured on
+  // 7600 workgroups.)  The schedule wants one workgroup per CU anyway.
   const int slot = device_slot();
   int W = cus_per_xcd(slot);
   double flops = 0.0;
@@ -724,14 +727,13 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
     W = most;
     for (GemmArgs& g : m.seg) g.wg_per_xcd = W;
   }
-  constexpr size_t lds = (size_t)NB * BM * BK * 2;
+  static_assert((size_t)NB * BM * BK * 2 <= CU_LDS, "the ring fits a CU");
   auto kern = ns_gemm_bf16_kernel<BM, BN, BKS, NB>;
   static std::atomic<bool> attr_set[MAX_DEVICES];
-  constexpr size_t ask = lds > 96 * 1024 ? lds : (size_t)96 * 1024;
-  const int rc = raise_lds_limit(kern, attr_set, slot, ask);
+  const int rc = raise_lds_limit(kern, attr_set, slot, CU_LDS);
   if (rc != MLC_OK) return rc;
   LaunchScope scope(MLC_KERNEL_NS_GEMM, stream, flops, 0.0);
-  hipLaunchKernelGGL(kern, dim3(W * NUM_XCD), dim3(NTHREADS), ask, stream, m);
+  hipLaunchKernelGGL(kern, dim3(W * NUM_XCD), dim3(NTHREADS), CU_LDS, stream, m);
   return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH;
 }
 

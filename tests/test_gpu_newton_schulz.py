@@ -143,6 +143,35 @@ def test_ring_across_output_tiles(cnt, m, n):
         assert_ns_close(to_f64(a[i]), muon.newton_schulz(to_f64(x[i]), 5), f"matrix {i} of {cnt} x {m} x {n}")
 
 
+def test_products_beside_lds_kernels_of_another_stream():
+    """Newton-Schulz of small tiles (which leave most of the LDS unused) on one stream while kernels
+    that hold LDS (top-k selection, small chains) keep the compute units busy on another: the bits of
+    a run alone."""
+    x = S.normal((60, 256, 640), S.GRAD_STD, seed=12, stream=0, dtype=torch.bfloat16).to(DEV)
+    y = S.normal((900, 128, 128), S.GRAD_STD, seed=12, stream=1, dtype=torch.bfloat16).to(DEV)
+    out, yout = torch.empty_like(x), torch.empty_like(y)
+    ws = torch.empty(mlc.newton_schulz_workspace_bytes(*x.shape), dtype=torch.uint8, device=DEV)
+    ws2 = torch.empty(mlc.newton_schulz_workspace_bytes(*y.shape), dtype=torch.uint8, device=DEV)
+    mlc.newton_schulz(x, out, ws)
+    torch.cuda.synchronize()
+    alone = out.clone()
+    theta = S.normal((8, 1024, 1024), S.PARAM_STD, seed=12, stream=2).to(DEV)
+    grp = mlc.OuterGroup([theta + 0.01], theta, torch.zeros_like(theta))
+    hp = mlc.OuterHParams(K=1, eta_out=0.0, mu=0.0, write_back=False)
+    wsp = torch.empty(mlc.muloco_topk_workspace_bytes([grp], 1), dtype=torch.uint8, device=DEV)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for _ in range(5):
+        with torch.cuda.stream(side):
+            for _ in range(4):
+                mlc.muloco_topk_outer_step([grp], hp, 0.05, wsp)
+                mlc.newton_schulz(y, yout, ws2)
+        for _ in range(4):
+            mlc.newton_schulz(x, out, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), alone.view(torch.int16))
+
+
 def test_singular_values_land_in_the_band():
     x = S.normal((1, 256, 512), S.GRAD_STD, seed=5, stream=0, dtype=torch.bfloat16)
     out = _run(x)
