@@ -57,18 +57,19 @@ def test_adamw_several_tensors_in_one_call_and_zero_gradient():
 @pytest.mark.parametrize("pd,gd", [(torch.bfloat16, torch.bfloat16), (torch.float32, torch.bfloat16)])
 def test_adamw_many_tensors_share_launches(pd, gd):
     """More tensors than one launch holds, sizes around the chunk of a workgroup (8192) and off the
-    8-element vector, a change of dtype in between, and a tensor that appears twice: the same
-    bits as one call per tensor."""
+    8-element vector, a change of dtype in between, and in the last launch's run a tensor that
+    appears twice and two overlapping slices of one: the same bits as one call per tensor."""
     sizes = [8192, 8191, 8193, 1, 7, 8, 16384 + 5] + [40 + i for i in range(70)]
     hp = mlc.AdamWHParams(lr=3e-3, weight_decay=0.1, bias_correction=True, step=3)
+    other = torch.bfloat16 if pd == torch.float32 else torch.float32
 
     def state():
         out = []
         for i, n in enumerate(sizes):
-            d = torch.float32 if i == 30 else pd
+            d = other if i == 30 else pd
             out.append((S.normal((n,), 1.0, 7, i, dtype=d).to(DEV), S.normal((n,), 1.0, 8, i, dtype=gd).to(DEV),
                         S.normal((n,), 1.0, 9, i).to(DEV), S.normal((n,), 1.0, 10, i).abs().to(DEV)))
-        return out + [out[3], out[0]]
+        return out + [out[70], out[0], tuple(t[:48] for t in out[75]), tuple(t[16:] for t in out[75])]
     one, many = state(), state()
     for t in one:
         mlc.muloco_adamw_step([t], hp)
@@ -77,3 +78,25 @@ def test_adamw_many_tensors_share_launches(pd, gd):
     for i, (a, b) in enumerate(zip(one, many)):
         for x, y in zip(a, b):
             assert torch.equal(x, y), f"tensor {i} of {len(one)}"
+
+
+@pytest.mark.parametrize("count", [2, 3, 4, 5, 9, 64])
+def test_adamw_launches(count):
+    """Tensors of one dtype pair go out in one launch; one that shares memory with a later one goes
+    out before it, alone."""
+    ts = [tuple(torch.ones(24 + 8 * i, device=DEV) for _ in range(4)) for i in range(count)]
+    hp = mlc.AdamWHParams(lr=1e-3)
+
+    def launches(tensors):
+        mlc.muloco_timing_enable(True)
+        mlc.muloco_timing_read()
+        mlc.muloco_adamw_step(tensors, hp)
+        torch.cuda.synchronize()
+        n = mlc.muloco_timing_read()["adamw"]["launches"]
+        mlc.muloco_timing_enable(False)
+        return n
+    assert launches(ts) == 1
+    twice = ts[:-1] + [ts[0]]
+    assert launches(twice) == 2
+    part = ts[:-1] + [tuple(t[8:] for t in ts[0])]
+    assert launches(part) == 2
