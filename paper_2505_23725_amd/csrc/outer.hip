@@ -681,6 +681,47 @@ __global__ void topk_init_kernel(TopkState* st, unsigned int kcount) {
   if (threadIdx.x == 0) { s.prefix = 0u; s.mask = 0u; s.rank = kcount; s.pad = 0u; }
 }
 
+// The first digits (bits from `shift` up) of a lane's first cnt of 8 values.  They mostly change
+// from element to element, so each is counted by itself (counting runs took 335 us a pass instead
+// of 290); zeros, of which a step that moved little has many, are left to the lane's `zeros`.  Where
+// a quarter of the wavefront starts with one digit (replicas that all moved by about the same amount),
+// that digit and the next one met are counted for the wavefront by one lane: the LDS takes atomics
+// on one counter one after the other (24 matrices of 2048 x 2048, all magnitudes equal: 875 us a
+// call without this, 683 with it; normal values: 700 either way).
+__device__ __forceinline__ void count_first_digit(unsigned int* hist, const float (&vals)[8], int cnt, int shift,
+                                                  unsigned int& zeros) {
+  unsigned int key[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) key[j] = __float_as_uint(fabsf(vals[j]));
+  const unsigned int mine = key[0] >> shift;
+  const unsigned int d0 = (unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
+  if (__popcll(__ballot(mine == d0)) < 16) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j >= cnt) break;
+      if (key[j] == 0u) ++zeros;
+      else atomicAdd(&hist[key[j] >> shift], 1u);
+    }
+    return;
+  }
+  const unsigned long other = __ballot(mine != d0);
+  const unsigned int d1 =
+      other ? (unsigned int)__builtin_amdgcn_readlane((int)mine, __builtin_ctzl(other)) : 0xffffffffu;
+  unsigned int n0 = 0u, n1 = 0u;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const unsigned int d = key[j] >> shift;
+    const bool in = j < cnt;
+    n0 += (unsigned int)__popcll(__ballot(in && d == d0));
+    n1 += (unsigned int)__popcll(__ballot(in && d == d1));
+    if (in && d != d0 && d != d1) atomicAdd(&hist[d], 1u);
+  }
+  if ((int)(threadIdx.x & 63) == __builtin_ctzl(__ballot(true))) {
+    atomicAdd(&hist[d0], n0);
+    if (n1) atomicAdd(&hist[d1], n1);
+  }
+}
+
 // FIRST: the pass that computes v = beta E + (theta_g - theta_k).  With error feedback it leaves v
 // in E, where it ends up anyway unless it is sent: the later passes then read 4 bytes an element
 // instead of 10, and the update needs no worker parameters (six layers of 2048 / 8192, K = 1:
@@ -722,19 +763,17 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
         store8<float, !VEC>(res + i, vals, left);
       }
     }
+    if constexpr (FIRST) {
+      count_first_digit(mine, vals, VEC ? 8 : left, shift, run);
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (!VEC && j >= left) break;
-      const float v = vals[j];
-      const unsigned int key = __float_as_uint(fabsf(v));
+      const unsigned int key = __float_as_uint(fabsf(vals[j]));
       if ((key & mask) == prefix) {
         const unsigned int bin = (key >> shift) & digit_mask;
-        // The first digit changes from element to element (counting runs there took 335 us a pass
-        // instead of 290); zeros, of which a step that moved little has many, are kept apart.
-        if (FIRST) {
-          if (key == 0u) ++run;
-          else atomicAdd(&mine[bin], 1u);
-        } else if (bin == cur) {
+        if (bin == cur) {
           ++run;
         } else {
           if (run) atomicAdd(&mine[cur], run);

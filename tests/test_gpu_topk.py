@@ -91,3 +91,32 @@ def test_topk_second_call_reuses_the_workspace():
 ])
 def test_topk_sizes_off_the_vector(cnt, m, n, K, wd, gd, frac, ef):
     test_topk_outer_step_matches_oracle(cnt, m, n, K, wd, gd, frac, ef)
+
+
+@pytest.mark.parametrize("cnt,m,n,ef", [(2, 64, 64, True), (1, 77, 1001, False), (1, 3, 5, False), (1, 200, 333, True)])
+@pytest.mark.parametrize("steps", [(1.0,), (1.0, 16.0), (1.0, 4.0, 64.0, 0.0), (1.0, 1.0, 1.0, 1.0, 1.0, 0.0)])
+def test_topk_few_distinct_magnitudes(cnt, m, n, ef, steps):
+    """Values whose first digits agree over most of a wavefront (counted together) or fall on two or
+    more of them, in sizes that leave lanes idle: thresholds, residuals and update as the oracle."""
+    gen = np.random.default_rng(m * n + len(steps))
+    mag = np.float32(2.0 ** -8) * np.asarray(steps, np.float32)[gen.integers(0, len(steps), (cnt, m, n))]
+    d = torch.from_numpy(mag * gen.choice(np.float32([-1, 1]), (cnt, m, n)))
+    tg0 = torch.zeros(cnt, m, n)
+    w0 = (tg0 - d).to(torch.bfloat16)           # powers of two: exact
+    u0 = S.normal((cnt, m, n), 1e-3, 3, 5)
+    tg, w, u = tg0.to(DEV), w0.to(DEV), u0.to(DEV)
+    res0 = torch.zeros(cnt, m, n)
+    res = res0.to(DEV)
+    taus = [torch.full((cnt,), -1.0, device=DEV)]
+    grp = mlc.OuterGroup([w], tg, u, None, taus, [res] if ef else None)
+    hp = mlc.OuterHParams(K=1, eta_out=0.9, mu=0.8, error_feedback=ef, ef_beta=0.9)
+    wsp = torch.empty(mlc.muloco_topk_workspace_bytes([grp], 1), dtype=torch.uint8, device=DEV)
+    mlc.muloco_topk_outer_step([grp], hp, 0.3, wsp)
+    torch.cuda.synchronize()
+    ref = diloco.outer_step(to_f64(tg0).reshape(-1, n), to_f64(u0).reshape(-1, n), [to_f64(w0).reshape(-1, n)],
+                            eta_out=0.9, mu=0.8, residuals=[res0.numpy().reshape(-1, n)] if ef else None,
+                            ef_beta=0.9, topk_fraction=0.3, rows_per_matrix=m)
+    assert np.array_equal(taus[0].cpu().numpy().view(np.uint32), ref["thresholds"][0].view(np.uint32))
+    if ef:
+        assert np.array_equal(res.cpu().numpy().reshape(-1, n).view(np.uint32), ref["residuals"][0].view(np.uint32))
+    assert_fp32_close(u.cpu().reshape(-1, n), ref["u"], "outer momentum")
