@@ -276,6 +276,14 @@ struct OuterGroupArgs {
 int quant_reg_cfg(int64_t n);
 // Rows whose length is a multiple of 8 start on 16 bytes (8 for codes) whatever their index.
 static inline bool quant_ragged(int64_t n) { return n % 8 != 0; }
+// Ragged rows of fewer than 64 with a code a byte keep the two-pass kernels, whose wavefront then has
+// one element per lane, where the one-pass kernel's has eight in a few lanes and loads the last,
+// partial eight one by one (rows of 7 / 15 / 47 / 63, two workers: 0.81 / 0.82 / 0.92 / 0.90 of the
+// two-pass speed, from 65 on 1.2 to 4.5; narrower codes are faster in one pass at every length).  Up
+// to 8000 rows one launch instead of two decides (1.00 to 1.19 of the two-pass speed).
+static inline bool quant_two_pass(int64_t rows, int64_t n, int bits) {
+  return bits == 8 && n < 64 && quant_ragged(n) && rows >= 8192;
+}
 constexpr int QUANT_MULTI_MAX_CFG = 4;
 struct QuantForm;
 int launch_outer_fused_multi(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K,

@@ -991,7 +991,7 @@ int launch_quantize(const WorkerPtrs& w, int worker_dtype, const void* theta_g, 
   const bool vec = n % 8 == 0;
   // single-pass register kernel: a wavefront per row up to 2048 columns, a workgroup per row
   // up to 24576; otherwise the two-pass kernel
-  if (n <= 24576 && !(worker_dtype == MLC_F32 && global_dtype == MLC_BF16)) {
+  if (n <= 24576 && !quant_two_pass(rows, n, bits) && !(worker_dtype == MLC_F32 && global_dtype == MLC_BF16)) {
     const int g = n <= 2048 ? 64 : OT_THREADS;
     const int need = (int)((n + g * 8 - 1) / (g * 8));
     const int nv = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 8 ? 8 : 12;
@@ -1073,7 +1073,8 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
                                 int64_t n, int K, const QuantForm& form, float eta_out, float mu,
                                 int nesterov, int write_back, int requant, uint8_t* mean_codes,
                                 float* mean_scales, float* mean_offsets, hipStream_t stream) {
-  if (n > 24576 || (worker_dtype == MLC_F32 && global_dtype == MLC_BF16)) return MLC_ERR_UNSUPPORTED;
+  if (n > 24576 || quant_two_pass(rows, n, form.bits) || (worker_dtype == MLC_F32 && global_dtype == MLC_BF16))
+    return MLC_ERR_UNSUPPORTED;
   if (requant && quant_ragged(n)) return MLC_ERR_UNSUPPORTED;
   const int g = n <= 2048 ? 64 : OT_THREADS;
   const int need = (int)((n + g * 8 - 1) / (g * 8));
@@ -1180,7 +1181,8 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     QuantSeg& sg = tab.s[i];
     if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
     const int cfg = quant_reg_cfg(gs[i].n);
-    if (cfg < 0 || cfg > QUANT_MULTI_MAX_CFG || quant_ragged(gs[i].n) != quant_ragged(gs[0].n))
+    if (cfg < 0 || cfg > QUANT_MULTI_MAX_CFG || quant_two_pass(gs[i].rows, gs[i].n, form.bits) ||
+        quant_ragged(gs[i].n) != quant_ragged(gs[0].n))
       return MLC_ERR_UNSUPPORTED;
     for (int k = 0; k < OUTER_MAX_SEG_K; ++k) {
       sg.w.p[k] = k < K ? gs[i].w.p[k] : nullptr;

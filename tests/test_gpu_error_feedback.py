@@ -285,6 +285,12 @@ RAGGED_CASES = [
     # element more or less, the longest that registers hold, and one beyond
     # (count, m, n, K, workers, global, bits, offset, per matrix, error feedback)
     (2, 5, 1, 1, BF16, F32, 8, False, False, False),
+    # ... and on both sides of the lengths and numbers of rows that take two passes
+    (1, 8191, 63, 2, BF16, F32, 8, True, False, True),
+    (1, 8192, 63, 2, BF16, F32, 8, True, False, True),
+    (1, 70, 65, 2, BF16, F32, 8, True, False, True),
+    (2, 9, 62, 3, BF16, BF16, 4, False, False, True),
+    (1, 8193, 47, 2, F32, F32, 8, False, True, False),
     (1, 7, 513, 2, BF16, F32, 8, True, False, True),
     (2, 9, 1001, 2, BF16, BF16, 8, True, False, True),
     (1, 6, 1022, 4, BF16, F32, 4, False, False, False),
@@ -304,7 +310,7 @@ def test_ragged_rows_bit_exact(cnt, m, n, K, wd, gd, bits, offset, per_matrix, e
 
 
 def test_ragged_and_aligned_groups_in_one_call_equal_one_call_per_group():
-    shapes = [(3, 50, 1001), (2, 9, 2730), (2, 40, 1000), (1, 12, 4099), (2, 5, 77)]
+    shapes = [(3, 50, 1001), (2, 9, 2730), (2, 40, 1000), (1, 12, 4099), (2, 4100, 63), (2, 5, 77)]
     hp = mlc.OuterHParams(K=2, eta_out=0.9, mu=0.8, quant_bits=8, error_feedback=True, ef_beta=0.9, quant_offset=True)
 
     def groups():
