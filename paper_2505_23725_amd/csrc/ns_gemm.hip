@@ -742,7 +742,7 @@ template <bool BKS>
 int launch_tiles(const GemmDesc* const* d, int n, int tile, hipStream_t stream) {
   if (tile == 256) return launch_cfg<256, 256, BKS, 5>(d, n, stream);
   // The small tiles leave room for a ring of nine buffers, four K tiles ahead; a product of two
-  // or three K tiles has no use for it.
+  // K tiles has no use for it.
   if (d[0]->K < 256) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
   if (tile == 128) return launch_cfg<128, 128, BKS, 9>(d, n, stream);
   return launch_cfg<64, 64, BKS, 9>(d, n, stream);
@@ -753,29 +753,34 @@ long tiles_of(const GemmDesc& d, int tile) {
   return (d.symmetric ? tm * (tm + 1) / 2 : tm * tn) * d.batch;
 }
 
-// Microseconds that a launch of `tiles` output tiles takes, from kernel traces over 1 to 64
-// matrices of 256 to 4096 (within 15 % of them): a fixed part, and for every round of one tile
-// per compute unit the K tiles and the epilogue.  The 256 x 256 tile runs faster in a round that
-// leaves compute units idle (the chip is power-limited), and pays for the transposed copy that
-// a symmetric result takes.
-double estimate_us(int tile, long tiles, int kt, bool symmetric, int cus) {
-  const double launch = 3.5;
+// Microseconds that a launch of `tiles` output tiles of kt K tiles takes, from kernel traces of 142
+// batches (1 to 200 matrices of 128 to 2048, K to 4096): a first round of one tile per compute unit,
+// and further ones that overlap its ends.  Nine in ten launches lie between 0.85 and 1.12 of it, the
+// others being sets of matrices that fit no cache.  The 256 x 256 tile runs faster in a round that
+// leaves compute units idle (the chip is power-limited).  Symmetric results pay for the transposed
+// copy, the polynomial for its C operand too.
+enum { FORM_GRAM, FORM_POLY, FORM_APPLY };
+double estimate_us(int tile, int form, long tiles, int kt, int cus) {
   const long full = tiles / cus, rest = tiles - full * cus;
   if (tile == 256) {
-    const double epi = symmetric ? 12.0 : 9.0;
-    return launch + full * (kt * 1.40 + epi) + (rest ? kt * (1.02 + 0.38 * (double)rest / cus) + epi - 1.0 : 0.0);
+    constexpr double E[3] = {8.7, 14.8, 6.9}, R[3] = {4.8, 8.9, 4.4}, F[3] = {3.3, 7.3, 3.2};
+    const double f = (double)rest / cus;
+    return 3.5 + full * (kt * 1.40 + E[form]) + (rest ? kt * (1.02 + 0.38 * f) + R[form] + F[form] * f : 0.0);
   }
-  const double per_round = tile == 128 ? kt * 0.47 + 3.2 : kt * 0.22 + 1.2;
-  return launch + (full + (rest ? 1 : 0)) * per_round;
+  struct Fit { double base, first, more, epi; };
+  constexpr Fit F128[3] = {{6.2, 0.36, 0.47, 2.9}, {5.3, 0.50, 0.38, 4.1}, {5.4, 0.44, 0.44, 2.3}};
+  constexpr Fit F64[3] = {{4.8, 0.19, 0.18, 1.3}, {4.6, 0.21, 0.18, 1.4}, {4.7, 0.21, 0.16, 1.3}};
+  const Fit& x = tile == 128 ? F128[form] : F64[form];
+  return x.base + x.first * kt + (double)(full + (rest ? 1 : 0) - 1) * (x.more * kt + x.epi);
 }
 
 // The tile for a launch of these products.  One large tile moves half the operand bytes per FLOP
 // of a 128 x 128 one (1.25 against 0.9 PFLOP/s where both fill the chip), but products with few
 // tiles leave most of the chip idle: one 1024 x 1024 matrix takes 27 us a product in 16 tiles of
-// 256, 13 in 64 of 128, 9 in 256 of 64; six of 1024 x 3072 take 54, 48 and 81 for the last product
-// of an iteration.  A smaller tile has to be clearly ahead: the estimate is not exact, and it is
-// optimistic for small tiles over sets of matrices that no longer fit the caches (32 Gram
-// products of 1024 x 1024: estimated 0.86 of the large tile's time, measured 1.2).
+// 256, 12 in 64 of 128, 9 in 256 of 64; 200 of 256 x 256 take 17 / 23 / 20 in tiles of 256 and
+// 16 / 18 / 21 in tiles of 128.  A smaller tile has to be ahead by 5 %: the estimate is optimistic for
+// small tiles over sets that no longer fit the caches.  Over the traced batches this takes 1.004 of
+// the time of the best tile for each.  The 64 x 64 tile's ring needs four K tiles.
 int pick_tile(const GemmDesc* const* d, int n, int cus) {
   long tiles[3] = {0, 0, 0};
   bool divides = true;
@@ -784,11 +789,13 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
     for (int t = 0; t < 3; ++t) tiles[t] += tiles_of(*d[j], 256 >> t);
   }
   const int kt = d[0]->K / BK;
-  const bool sym = d[0]->symmetric != 0;
-  const double e128 = estimate_us(128, tiles[1], kt, sym, cus), e64 = estimate_us(64, tiles[2], kt, sym, cus);
-  const int small = e64 < 0.95 * e128 ? 64 : 128;
+  const int form = !d[0]->symmetric ? FORM_APPLY : d[0]->C ? FORM_POLY : FORM_GRAM;
+  int small = 128;
+  double us = estimate_us(128, form, tiles[1], kt, cus);
+  const double e64 = estimate_us(64, form, tiles[2], kt, cus);
+  if (kt >= 4 && e64 < 0.95 * us) { small = 64; us = e64; }
   if (!divides) return small;
-  return (small == 64 ? e64 : e128) < 0.85 * estimate_us(256, tiles[0], kt, sym, cus) ? small : 256;
+  return us < 0.95 * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
 }
 
 }  // namespace
