@@ -738,16 +738,6 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH;
 }
 
-template <bool BKS>
-int launch_tiles(const GemmDesc* const* d, int n, int tile, hipStream_t stream) {
-  if (tile == 256) return launch_cfg<256, 256, BKS, 5>(d, n, stream);
-  // The small tiles leave room for a ring of nine buffers, four K tiles ahead; a product of two
-  // K tiles has no use for it.
-  if (d[0]->K < 256) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
-  if (tile == 128) return launch_cfg<128, 128, BKS, 9>(d, n, stream);
-  return launch_cfg<64, 64, BKS, 9>(d, n, stream);
-}
-
 long tiles_of(const GemmDesc& d, int tile) {
   const long tm = d.M / tile, tn = d.N / tile;
   return (d.symmetric ? tm * (tm + 1) / 2 : tm * tn) * d.batch;
@@ -768,8 +758,8 @@ double estimate_us(int tile, int form, long tiles, int kt, int cus) {
     return 3.5 + full * (kt * 1.40 + E[form]) + (rest ? kt * (1.02 + 0.38 * f) + R[form] + F[form] * f : 0.0);
   }
   struct Fit { double base, first, more, epi; };
-  constexpr Fit F128[3] = {{6.2, 0.36, 0.47, 2.9}, {5.3, 0.50, 0.38, 4.1}, {5.4, 0.44, 0.44, 2.3}};
-  constexpr Fit F64[3] = {{4.8, 0.19, 0.18, 1.3}, {4.6, 0.21, 0.18, 1.4}, {4.7, 0.21, 0.16, 1.3}};
+  constexpr Fit F128[3] = {{5.8, 0.38, 0.47, 3.1}, {5.1, 0.50, 0.39, 4.1}, {5.1, 0.45, 0.44, 2.5}};
+  constexpr Fit F64[3] = {{5.0, 0.18, 0.19, 1.2}, {4.8, 0.21, 0.18, 1.3}, {4.8, 0.22, 0.16, 1.3}};
   const Fit& x = tile == 128 ? F128[form] : F64[form];
   return x.base + x.first * kt + (double)(full + (rest ? 1 : 0) - 1) * (x.more * kt + x.epi);
 }
@@ -778,13 +768,17 @@ double estimate_us(int tile, int form, long tiles, int kt, int cus) {
 // of a 128 x 128 one (1.25 against 0.9 PFLOP/s where both fill the chip), but products with few
 // tiles leave most of the chip idle: one 1024 x 1024 matrix takes 27 us a product in 16 tiles of
 // 256, 12 in 64 of 128, 9 in 256 of 64; 200 of 256 x 256 take 17 / 23 / 20 in tiles of 256 and
-// 16 / 18 / 21 in tiles of 128.  A smaller tile has to be ahead by 5 %: the estimate is optimistic for
-// small tiles over sets that no longer fit the caches.  Over the traced batches this takes 1.004 of
-// the time of the best tile for each.  The 64 x 64 tile's ring needs four K tiles.
+// 16 / 18 / 21 in tiles of 128.  A smaller tile has to be ahead by 5 %, and by 15 % over operands of
+// more than 64 MB, of which X, its next iterate, A and B' fill the 256 MB memory-side cache: the operand
+// bytes then decide (Gram products of 32 x 1024 x 1024 beside 16 of 1024 x 2816: 62 us in tiles of
+// 256, 68 in tiles of 128; alone 59 and 54).  Over the traced batches this takes 1.004 of the time
+// of the best tile for each.  The 64 x 64 tile's ring needs four K tiles.
 int pick_tile(const GemmDesc* const* d, int n, int cus) {
   long tiles[3] = {0, 0, 0};
   bool divides = true;
+  double bytes = 0.0;
   for (int j = 0; j < n; ++j) {
+    bytes += 2.0 * d[j]->batch * d[j]->K * (d[j]->M + (d[j]->symmetric ? 0.0 : (double)d[j]->N));
     divides = divides && d[j]->M % 256 == 0 && d[j]->N % 256 == 0;
     for (int t = 0; t < 3; ++t) tiles[t] += tiles_of(*d[j], 256 >> t);
   }
@@ -795,7 +789,25 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
   const double e64 = estimate_us(64, form, tiles[2], kt, cus);
   if (kt >= 4 && e64 < 0.95 * us) { small = 64; us = e64; }
   if (!divides) return small;
-  return us < 0.95 * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
+  return us < (bytes > 64e6 ? 0.85 : 0.95) * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
+}
+
+template <bool BKS>
+int launch_tiles(const GemmDesc* const* d, int n, hipStream_t stream) {
+  const int cus = cus_per_xcd(device_slot()) * NUM_XCD;
+  const int tile = pick_tile(d, n, cus);
+  if (tile == 256) return launch_cfg<256, 256, BKS, 5>(d, n, stream);
+  if (tile == 64) return launch_cfg<64, 64, BKS, 9>(d, n, stream);
+  // The small tiles leave room for a ring of nine buffers, four K tiles ahead.  Up to ten K tiles
+  // two are better while a launch is short: a wavefront has requested all that its ring holds ahead
+  // before its first MFMA, and a CU takes 64 bytes a cycle (15 products of 32 / 64 matrices of
+  // 256 x 256: 113 / 126 us instead of 120 / 135, of 8 / 16 of 640 x 640 152 / 208 instead of 157 / 211).
+  // Where workgroups take more than two tiles the longer ring is ahead again from six K tiles on
+  // (400 matrices of 384 x 384: 1273 us, with the short one 1320; 96 of 640 x 640 977, 1022).
+  long tiles = 0;
+  for (int j = 0; j < n; ++j) tiles += tiles_of(*d[j], 128);
+  if (d[0]->K <= 256 || (d[0]->K <= 640 && tiles <= 2 * cus)) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
+  return launch_cfg<128, 128, BKS, 9>(d, n, stream);
 }
 
 }  // namespace
@@ -805,7 +817,6 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   bool done[64] = {};
   for (int i = 0; i < n; ++i)
     if (!valid_desc(d[i])) return MLC_ERR_SHAPE;
-  const int cus = cus_per_xcd(device_slot()) * NUM_XCD;
   auto divides = [](const GemmDesc& g) { return g.M % 256 == 0 && g.N % 256 == 0; };
   for (int i = 0; i < n; ++i) {
     if (done[i]) continue;
@@ -821,9 +832,7 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
       pick[np] = &d[j];
       idx[np++] = j;
     }
-    const int tile = pick_tile(pick, np, cus);
-    const int rc = d[i].b_kstrided ? launch_tiles<true>(pick, np, tile, stream)
-                                   : launch_tiles<false>(pick, np, tile, stream);
+    const int rc = d[i].b_kstrided ? launch_tiles<true>(pick, np, stream) : launch_tiles<false>(pick, np, stream);
     if (rc != MLC_OK) return rc;
     for (int k = 0; k < np; ++k) done[idx[k]] = true;
   }
