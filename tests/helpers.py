@@ -16,6 +16,9 @@ Comparison rules (derived from the arithmetic):
   largest error of 1.7e7 elements sits near 10 x the rms error on a correct result).
 * quantiser codes and scales: exact equality.
 """
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -133,3 +136,77 @@ def assert_update_elements(W_gpu_t: torch.Tensor, W_ref: np.ndarray, O_ref: np.n
     assert worst <= 1.0, (f"{what}: {int((ratio > 1).sum())} of {ratio.size} elements off by more than the "
                           f"element bound, worst {worst:.2f}x")
     return worst
+
+
+# ---- which output tile a Newton-Schulz product runs ------------------------------------
+def _tile_constants():
+    """The fitted constants of the tile estimate, from the kernel source."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    text = open(os.path.join(root, "paper_2505_23725_amd", "csrc", "ns_gemm.hip")).read()
+
+    def numbers(name):
+        m = re.search(r"\b%s\[3\] = (\{.*?\})[;,] ?(?:R|F|$|\n|constexpr)" % name, text)
+        return [float(x) for x in re.findall(r"\d+\.?\d*", m.group(1))]
+    return {"E": numbers("E"), "R": numbers("R"), "F": numbers("F"), 128: numbers("F128"), 64: numbers("F64")}
+
+
+def ns_tiles(groups, cus=256):
+    """[(gram, polynomial, apply) tile width per group] that one call of the library over these
+    groups (count, m, n) uses, by the rule of csrc/ns_gemm.hip; None for a group on the
+    one-workgroup chain.  test_gpu_newton_schulz.py checks it against the executed FLOP."""
+    k = _tile_constants()
+    jobs = []
+    for i, (c, m, n) in enumerate(groups):
+        mp, np_ = -(-m // 128) * 128, -(-n // 128) * 128
+        s, l = min(mp, np_), max(mp, np_)
+        if not (s == 128 and l <= 512):
+            jobs.append((i, c, s, l))
+    out = [None if i not in [j[0] for j in jobs] else [0, 0, 0] for i in range(len(groups))]
+    for form in range(3):
+        todo = list(jobs)
+        while todo:
+            def shape(j):
+                _, c, s, l = j
+                return c, s, (l if form == 2 else s), (l if form == 0 else s)       # batch, M, N, K
+            first = shape(todo[0])
+            divides = first[1] % 256 == 0 and first[2] % 256 == 0
+            some = [j for j in todo if shape(j)[3] == first[3] and
+                    (shape(j)[1] % 256 == 0 and shape(j)[2] % 256 == 0) == divides][:3]
+            todo = [j for j in todo if j not in some]
+            kt = first[3] // 64
+            tiles, nbytes = {}, 0
+            for t in (64, 128, 256):
+                tiles[t] = sum(c * ((M // t) * (M // t + 1) // 2 if form < 2 else (M // t) * (N // t))
+                               for c, M, N, K in map(shape, some))
+            for c, M, N, K in map(shape, some):
+                nbytes += 2 * c * K * (M + (N if form == 2 else 0))
+
+            def estimate(t):
+                full, rest = divmod(tiles[t], cus)
+                if t == 256:
+                    f = rest / cus
+                    return 3.5 + full * (kt * 1.40 + k["E"][form]) + (
+                        kt * (1.02 + 0.38 * f) + k["R"][form] + k["F"][form] * f if rest else 0.0)
+                base, one, more, epi = k[t][4 * form:4 * form + 4]
+                return base + one * kt + (full + (rest > 0) - 1) * (more * kt + epi)
+            tile, us = 128, estimate(128)
+            if kt >= 4 and estimate(64) < 0.95 * us:
+                tile, us = 64, estimate(64)
+            if divides and not us < (0.85 if nbytes > 64e6 else 0.95) * estimate(256):
+                tile = 256
+            for j in some:
+                out[j[0]][form] = tile
+    return [None if o is None else tuple(o) for o in out]
+
+
+def ns_executed_flops(groups, iters=5):
+    """Matrix-core FLOP that the library's recorder counts for groups off the one-workgroup chain."""
+    total = 0.0
+    for (c, m, n), (gram, poly, _) in zip(groups, ns_tiles(groups)):
+        mp, np_ = -(-m // 128) * 128, -(-n // 128) * 128
+        s, l = min(mp, np_), max(mp, np_)
+
+        def sym(t):
+            return (s // t) * (s // t + 1) // 2 * t * t
+        total += iters * c * 2.0 * (sym(gram) * l + sym(poly) * s + s * l * s)
+    return total

@@ -8,8 +8,8 @@ import torch
 import paper_2505_23725_amd as mlc
 import synth_inputs as S
 from oracle import muon, storage
-from helpers import (EW_TOL, NS_TOL, assert_fp32_close, assert_update_elements, dtype_name, rel_fro, to_f64,
-                     update_error_bf16)
+from helpers import (EW_TOL, NS_TOL, assert_fp32_close, assert_update_elements, dtype_name, ns_tiles, rel_fro,
+                     to_f64, update_error_bf16)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -64,7 +64,7 @@ CASES = [
     # bf16 weights of a shape the products work on unpadded: the last product writes the update
     (2, 768, 3072, torch.bfloat16, torch.bfloat16),
     (2, 3072, 768, torch.bfloat16, torch.float32),
-    (70, 256, 512, torch.bfloat16, torch.bfloat16),    # enough tiles for the 256 x 256 tile
+    (70, 256, 512, torch.bfloat16, torch.bfloat16),    # its apply products run the 256 x 256 tile
 ]
 
 
@@ -160,20 +160,27 @@ def test_zero_iterations_uses_normalised_direction():
     assert rel_fro(upd, Wr - to_f64(W0)) <= 4e-3      # bf16 rounding of the direction only
 
 
-@pytest.mark.parametrize("shapes", [
+# (groups of one call, their tiles for the Gram, polynomial and apply products when side by side)
+SIDE_BY_SIDE = [
     # 150M-like proportions, scaled down: the Gram products of the wide and the tall group share a
-    # launch (depth 1024, K-contiguous next to K-strided), all three polynomial products share one,
-    # and the three apply products (depth 256) share one; a shared launch needs 256 tiles in all
-    [(230, 256, 256), (130, 256, 1024), (130, 1024, 256)],
-    # two groups of one shape and a group that runs the small tile: only some products can share
-    [(50, 512, 512), (50, 512, 512), (3, 384, 640)],
+    # launch (depth 1024; the tall one is held transposed), all three polynomial products share one,
+    # and the three apply products (depth 256) share one
+    ([(230, 256, 256), (130, 256, 1024), (130, 1024, 256)], [(256, 128, 256), (128, 128, 256), (128, 128, 256)]),
+    # two groups of one shape and a group whose width 256 does not divide: only some products can share
+    ([(50, 512, 512), (50, 512, 512), (3, 384, 640)], [(128, 128, 256), (128, 128, 256), (64, 64, 64)]),
     # a group that takes the one-workgroup chain beside two that do not
-    [(9, 128, 512), (140, 256, 512), (140, 512, 256)],
-])
-def test_groups_side_by_side_give_the_bits_of_one_group_after_the_other(shapes):
+    ([(9, 128, 512), (140, 256, 512), (140, 512, 256)], [None, (128, 128, 256), (128, 128, 256)]),
+    # large tiles throughout
+    ([(40, 768, 768), (30, 768, 768)], [(256, 256, 256)] * 2),
+]
+
+
+@pytest.mark.parametrize("shapes,tiles", SIDE_BY_SIDE)
+def test_groups_side_by_side_give_the_bits_of_one_group_after_the_other(shapes, tiles):
     """With a work space that holds all groups at once, products of equal depth share launches;
     with the smaller one each group runs alone.  Both must give the same bits, and one group
     of each call is checked against the oracle."""
+    assert ns_tiles(shapes) == tiles
     hp = mlc.MuonHParams(eta=0.05, weight_decay=0.01, beta=0.9)
 
     def build():
@@ -199,6 +206,28 @@ def test_groups_side_by_side_give_the_bits_of_one_group_after_the_other(shapes):
         sl = slice(c - 1, c)        # the last matrix of every group
         _check_group(W0[sl], g[sl], m0[sl], grp.param[sl].cpu(), grp.momentum[sl].cpu(), hp, math.sqrt(n / m),
                      f"group {m}x{n}")
+
+
+# bf16 weights of few, unpadded matrices: the last product writes the update from 64 x 64 tiles,
+# transposed for the tall ones
+SMALL_TILE_UPDATES = [
+    ([(1, 384, 256)], [(64, 64, 64)]),
+    ([(4, 256, 256), (1, 256, 1024), (1, 1024, 256)], [(64, 64, 64)] * 3),
+    ([(1, 640, 384), (1, 384, 640)], [(64, 64, 64)] * 2),
+]
+
+
+@pytest.mark.parametrize("shapes,tiles", SMALL_TILE_UPDATES)
+def test_update_from_small_tiles(shapes, tiles):
+    assert ns_tiles(shapes) == tiles
+    hp = mlc.MuonHParams(eta=6.25e-2, weight_decay=1.25e-3, beta=0.9)
+    host = [_make_group(c, m, n, torch.bfloat16, torch.bfloat16, seed=90 + i) for i, (c, m, n) in enumerate(shapes)]
+    grps = [mlc.InnerGroup(*[t.to(DEV) for t in h], math.sqrt(n / m)) for h, (_, m, n) in zip(host, shapes)]
+    ws = torch.empty(mlc.muloco_inner_workspace_bytes(grps), dtype=torch.uint8, device=DEV)
+    mlc.muloco_inner_step(grps, hp, ws)
+    torch.cuda.synchronize()
+    for (W0, g, m0), grp, (c, m, n) in zip(host, grps, shapes):
+        _check_group(W0, g, m0, grp.param.cpu(), grp.momentum.cpu(), hp, math.sqrt(n / m), f"group {c}x{m}x{n}")
 
 
 def test_groups_of_different_kinds_side_by_side():

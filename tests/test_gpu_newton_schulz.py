@@ -7,7 +7,7 @@ import torch
 import paper_2505_23725_amd as mlc
 import synth_inputs as S
 from oracle import muon
-from helpers import NS_TOL, assert_ns_close, to_f64
+from helpers import NS_TOL, assert_ns_close, ns_executed_flops, ns_tiles, to_f64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -112,14 +112,51 @@ def test_zero_matrix_with_eps_zero_stays_zero():
             assert_ns_close(to_f64(o[1]), ref, f"{shape} eps=0 iters={iters}", 4e-3 if iters == 0 else NS_TOL)
 
 
-@pytest.mark.parametrize("cnt,m,n", [(100, 256, 256), (230, 256, 256), (70, 384, 384), (45, 256, 512), (45, 512, 256)])
-def test_more_small_tiles_than_compute_units(cnt, m, n):
-    """Batches whose products run the 128 x 128 tile with more tiles than compute units (a CU must
-    never hold two of these workgroups: the second one's tiles once came out as garbage): every
-    matrix finite, two runs bit-identical, and matrices from the end of the batch, where the
-    workgroups beyond the first 256 work, match the oracle."""
+# (count, m, n, tile widths of the Gram, polynomial and apply products): more output tiles than
+# compute units at every width, tall and wide
+MANY_TILES = [
+    (100, 256, 256, (64, 64, 128)),       # 1000 tiles of 64, 400 of 128
+    (230, 256, 256, (256, 128, 256)),
+    (70, 384, 384, (128, 128, 128)),      # 420 and 630
+    (45, 256, 512, (128, 128, 128)),
+    (45, 512, 256, (128, 128, 128)),      # 360 whose result is stored transposed
+    (130, 512, 1024, (256, 256, 256)),    # 390 and 1040
+    (130, 1024, 512, (256, 256, 256)),
+]
+# the ring of operand tiles: products of few K tiles, and a workgroup's second output tile
+RING = [
+    (70, 128, 640, (64, 128, 128)), (70, 640, 128, (64, 128, 128)),      # K = 128: two K tiles; tall: transposed result
+    (40, 256, 640, (128, 128, 128)), (40, 640, 250, (128, 128, 128)),    # K = 256: the short ring; ragged tall
+    (90, 512, 768, (128, 128, 256)), (90, 768, 512, (128, 128, 256)),    # the long ring, several tiles a workgroup
+    (1, 384, 1152, (64, 64, 64)), (1, 1152, 384, (64, 64, 64)),          # fewer tiles than compute units
+    (1, 256, 1024, (64, 64, 64)), (1, 1024, 256, (64, 64, 64)),          # ... with as many K tiles as the ring holds ahead
+    (9, 256, 1300, (64, 64, 128)), (9, 1300, 256, (64, 64, 128)),
+    (1, 128, 1000, (64, 128, 128)),                                      # K = 128 again: too short for the 64 tile's ring
+    (24, 640, 640, (128, 128, 128)), (60, 640, 640, (128, 128, 128)),    # K = 640: the short ring up to two rounds, and the long one
+]
+
+
+def _run_recorded(x, shape):
+    """The result, after checking that the call executed the FLOP of the tiles it is said to use."""
+    mlc.muloco_timing_enable(True)
+    mlc.muloco_timing_read()
+    out = _run(x)
+    t = mlc.muloco_timing_read()["ns_gemm"]
+    mlc.muloco_timing_enable(False)
+    assert t["launches"] == 15
+    assert abs(t["flops"] / ns_executed_flops([shape]) - 1) < 1e-9
+    return out
+
+
+@pytest.mark.parametrize("cnt,m,n,tiles", MANY_TILES)
+def test_more_small_tiles_than_compute_units(cnt, m, n, tiles):
+    """Batches with more output tiles than compute units (an earlier kernel put two workgroups on a CU
+    then, and the second one's tiles came out as garbage): every matrix finite, two runs
+    bit-identical, and matrices from the end of the batch, where the workgroups' later tiles are,
+    match the oracle."""
+    assert ns_tiles([(cnt, m, n)]) == [tiles]
     x = S.normal((cnt, m, n), S.GRAD_STD, seed=8, stream=cnt + n, dtype=torch.bfloat16)
-    a = _run(x)
+    a = _run_recorded(x, (cnt, m, n))
     b = _run(x)
     assert torch.isfinite(a.float()).all()
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
@@ -127,20 +164,36 @@ def test_more_small_tiles_than_compute_units(cnt, m, n):
         assert_ns_close(to_f64(a[i]), muon.newton_schulz(to_f64(x[i]), 5), f"matrix {i} of {cnt} x {m} x {n}")
 
 
-@pytest.mark.parametrize("cnt,m,n", [
-    (70, 128, 640), (70, 640, 128),      # K = 128: two K tiles, the short ring; tall: transposed result
-    (40, 256, 640), (40, 640, 250),      # K = 256: as many K tiles as the long ring holds ahead; ragged tall
-    (90, 512, 768), (90, 768, 512),      # 256 x 256 tiles, a second output tile for some workgroups
-    (1, 384, 1152), (1, 1152, 384),      # 64 x 64 tiles, fewer than compute units
-    (9, 256, 1300), (9, 1300, 256),      # 64 x 64 tiles, more than compute units in the last product
-    (1, 128, 1000),                      # K = 128 again: too short for the small tile's ring
-])
-def test_ring_across_output_tiles(cnt, m, n):
+@pytest.mark.parametrize("cnt,m,n,tiles", RING)
+def test_ring_across_output_tiles(cnt, m, n, tiles):
+    assert ns_tiles([(cnt, m, n)]) == [tiles]
     x = S.normal((cnt, m, n), S.GRAD_STD, seed=9, stream=cnt + m, dtype=torch.bfloat16)
-    a = _run(x)
+    a = _run_recorded(x, (cnt, m, n))
     assert torch.equal(a.view(torch.int16), _run(x).view(torch.int16))
     for i in (0, cnt // 2, cnt - 1):
         assert_ns_close(to_f64(a[i]), muon.newton_schulz(to_f64(x[i]), 5), f"matrix {i} of {cnt} x {m} x {n}")
+
+
+# (m, n, counts that take different tiles for one product or another)
+SAME_BITS = [
+    (512, 512, {1: (64, 64, 64), 9: (128, 128, 128), 64: (256, 128, 256)}),
+    (1024, 256, {1: (64, 64, 64), 8: (64, 64, 128), 48: (128, 128, 256)}),
+    (256, 1024, {1: (64, 64, 64), 8: (64, 64, 128), 48: (128, 128, 256)}),
+    (768, 768, {1: (64, 64, 64), 8: (128, 128, 128), 64: (256, 256, 256)}),
+]
+
+
+@pytest.mark.parametrize("m,n,counts", SAME_BITS)
+def test_every_tile_gives_the_same_bits(m, n, counts):
+    """What lets a call with a small work space give the bits of one with a large one: the first
+    matrix of the batch, orthogonalised in batches that run different tiles."""
+    x = S.normal((max(counts), m, n), S.GRAD_STD, seed=13, stream=m + n, dtype=torch.bfloat16)
+    first = None
+    for c, tiles in counts.items():
+        assert ns_tiles([(c, m, n)]) == [tiles], f"batch of {c}"
+        out = _run_recorded(x[:c].contiguous(), (c, m, n))[0].view(torch.int16)
+        assert first is None or torch.equal(out, first), f"batch of {c}"
+        first = out
 
 
 def test_products_beside_lds_kernels_of_another_stream():
