@@ -444,6 +444,8 @@ def main() -> int:
         for line in open(tpath):
             if line.startswith("traffic_bytes_per_launch"):
                 traffic = float(line.split()[1])
+    # shapes of at most 128 x 512 run the whole chain in one launch instead
+    chain = max(wl.d_model, wl.d_ffn) <= 512 and wl.d_model <= 128
     out = {
         "metric": METRIC,
         "value": ns_tflops,
@@ -466,9 +468,7 @@ def main() -> int:
                      "traffic_source": (None if traffic is None else
                                         f"profiles/ns_gemm_bf16_kernel_{wl.name}_traffic.txt (rocprofv3 --pmc runs of this "
                                         "command; read from the file, not measured in this run)"),
-                     # shapes of at most 128 x 512 run the whole chain in one launch instead
-                     "kernel": ("ns_chain_small_kernel" if max(wl.d_model, wl.d_ffn) <= 512 and wl.d_model <= 128
-                                else "ns_gemm_bf16_kernel"),
+                     "kernel": "ns_chain_small_kernel" if chain else "ns_gemm_bf16_kernel",
                      "avg_launch_ms": gemm["total_ms"] / max(1, gemm["launches"])},
         "breakdown": breakdown,
     }
@@ -478,8 +478,10 @@ def main() -> int:
         from paper_2505_23725_amd.build import MICROBENCH_PATH
         res = subprocess.run([MICROBENCH_PATH], capture_output=True, text=True, timeout=120)
         out["achievable"] = json.loads(res.stdout.strip().splitlines()[-1])
-        # operands drawn like the workload's; the random-bit-pattern figure is the worst case
-        ach = out["achievable"]["mfma_bf16_tflops_gaussian_operands"]
+        # operands drawn like the workload's (the random-bit-pattern figure is the worst case), the
+        # instruction of the kernel that runs: 32x32x16 in the one-launch chain, else 16x16x32
+        ach = out["achievable"]["mfma_bf16_tflops_gaussian_operands" if chain else
+                                "mfma16x16x32_bf16_tflops_gaussian_operands"]
         out["roofline"]["frac_of_achievable"] = ns_tflops / ach if ach > 0 else None
         # every GB/s figure also against what a plain in-place read-modify-write stream reaches
         # on this machine (all of the elementwise kernels are such streams)

@@ -1,8 +1,9 @@
 // Achievable-peak microbenchmarks for one MI355X (not part of the method): the sustained
 // v_mfma_f32_32x32x16_bf16 rate of a register-resident loop with constant operands, with
 // random bit patterns (the most switching activity the datapath can see) and with operands
-// drawn like the workload's (bf16 roundings of 1e-3 * N(0, 1); accumulators stay finite):
-// the chip is power-limited, so the sustained rate depends on the data.  Also the HBM
+// drawn like the workload's (bf16 roundings of 1e-3 * N(0, 1); accumulators stay finite), and the
+// v_mfma_f32_16x16x32_bf16 rate (the instruction of the large products) on the same operands: the
+// chip is power-limited, so the sustained rate depends on the data and on the instruction.  Also the HBM
 // bandwidth of a plain 16-byte copy, of a pure read (plain and non-temporal), of a pure write
 // and of an in-place read-modify-write stream.  Prints one JSON line.
 #include <hip/hip_runtime.h>
@@ -32,6 +33,29 @@ __global__ __launch_bounds__(256) void mfma_loop(const u32x4* in, float* out, in
   }
   float s = 0;
   for (int i = 0; i < 16; ++i) for (int r = 0; r < 16; ++r) s += acc[i][r];
+  if (s == 12345.f) out[0] = s;
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256, 1) void mfma16_loop(const u32x4* in, float* out, int iters) {
+  f32x4 acc[8][8];
+  for (int i = 0; i < 8; ++i)
+    for (int j = 0; j < 8; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[i][j]));      // one register set from here on, no copies in the loop
+    }
+  u32x4 a[8], b[8];      // every lane 16 fragments, as the large tile's slice has
+  for (int i = 0; i < 8; ++i) { a[i] = in[threadIdx.x * 8 + i]; b[i] = in[(threadIdx.x ^ 1) * 8 + i]; }
+  for (int it = 0; it < iters; ++it) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
+  }
+  float s = 0;
+  for (int i = 0; i < 8; ++i) for (int j = 0; j < 8; ++j) for (int r = 0; r < 4; ++r) s += acc[i][j][r];
   if (s == 12345.f) out[0] = s;
 }
 
@@ -99,7 +123,7 @@ int main() {
     u += 0x7fffu + ((u >> 16) & 1u);         // round to nearest even
     return u >> 16;
   };
-  double tf[3];
+  double tf[3], tf16[3];
   for (int mode = 0; mode < 3; ++mode) {
     std::vector<unsigned> h(256 * 8 * 4);
     srand(1);
@@ -115,6 +139,11 @@ int main() {
     hipLaunchKernelGGL(mfma_loop, dim3(blocks), dim3(256), 0, 0, in, d, iters);
     CK(hipEventRecord(e1, 0)); CK(hipEventSynchronize(e1)); CK(hipEventElapsedTime(&ms, e0, e1));
     tf[mode] = 2.0 * 32 * 32 * 16 * 16.0 * iters * 4 * blocks / ms * 1e-9;
+    hipLaunchKernelGGL(mfma16_loop, dim3(blocks), dim3(256), 0, 0, in, d, 100);
+    CK(hipEventRecord(e0, 0));
+    hipLaunchKernelGGL(mfma16_loop, dim3(blocks), dim3(256), 0, 0, in, d, iters / 2);
+    CK(hipEventRecord(e1, 0)); CK(hipEventSynchronize(e1)); CK(hipEventElapsedTime(&ms, e0, e1));
+    tf16[mode] = 2.0 * 16 * 16 * 32 * 64.0 * (iters / 2) * 4 * blocks / ms * 1e-9;
   }
   const size_t bytes = (size_t)2 << 30;
   u32x4 *a, *b; CK(hipMalloc(&a, bytes)); CK(hipMalloc(&b, bytes));
@@ -148,8 +177,10 @@ int main() {
   CK(hipEventRecord(e1, 0)); CK(hipEventSynchronize(e1)); CK(hipEventElapsedTime(&ms, e0, e1));
   rmw_gbs = 2.0 * bytes / (ms / 5 * 1e-3) * 1e-9;
   printf("{\"mfma_bf16_tflops_constant_operands\": %.1f, \"mfma_bf16_tflops_random_operands\": %.1f, "
-         "\"mfma_bf16_tflops_gaussian_operands\": %.1f, \"hbm_copy_GBps\": %.0f, \"hbm_read_GBps\": %.0f, "
+         "\"mfma_bf16_tflops_gaussian_operands\": %.1f, "
+         "\"mfma16x16x32_bf16_tflops_constant_operands\": %.1f, \"mfma16x16x32_bf16_tflops_random_operands\": %.1f, "
+         "\"mfma16x16x32_bf16_tflops_gaussian_operands\": %.1f, \"hbm_copy_GBps\": %.0f, \"hbm_read_GBps\": %.0f, "
          "\"hbm_read_nontemporal_GBps\": %.0f, \"hbm_write_GBps\": %.0f, \"hbm_rmw_in_place_GBps\": %.0f}\n",
-         tf[0], tf[1], tf[2], copy_gbs, read_gbs, read_nt_gbs, write_gbs, rmw_gbs);
+         tf[0], tf[1], tf[2], tf16[0], tf16[1], tf16[2], copy_gbs, read_gbs, read_nt_gbs, write_gbs, rmw_gbs);
   return 0;
 }

@@ -4,8 +4,8 @@
 // One workgroup = 256 threads = 4 wavefronts in a 2 x 2 arrangement; each wavefront owns a
 // (BM/2) x (BN/2) block of the output tile as TI x TJ accumulators of v_mfma_f32_16x16x32_bf16.
 // The 16x16x32 shape moves half the accumulator traffic per FLOP of the 32x32x16 one, and this
-// part is power-limited under matrix-core load: register-only loops on N(0, 1) operands run at
-// 2.05 PFLOP/s with it and 1.80 with the other.
+// part is power-limited under matrix-core load: register-only loops on normally distributed
+// operands run at 1.84 PFLOP/s with it and 1.75 with the other (microbench.hip).
 //
 // Operand tiles travel HBM -> LDS directly (buffer_load ... lds): no staging registers, no LDS
 // store instructions.  One LDS buffer holds one operand of one 64-deep K tile, so that a
