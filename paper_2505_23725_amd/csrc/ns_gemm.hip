@@ -803,10 +803,12 @@ int launch_tiles(const GemmDesc* const* d, int n, hipStream_t stream) {
   // before its first MFMA, and a CU takes 64 bytes a cycle (15 products of 32 / 64 matrices of
   // 256 x 256: 113 / 126 us instead of 120 / 135, of 8 / 16 of 640 x 640 152 / 208 instead of 157 / 211).
   // Where workgroups take more than two tiles the longer ring is ahead again from six K tiles on
-  // (400 matrices of 384 x 384: 1273 us, with the short one 1320; 96 of 640 x 640 977, 1022).
+  // (400 matrices of 384 x 384: 1273 us, with the short one 1320; 96 of 640 x 640 977, 1022), and with
+  // four from about eight tiles on (400 of 256 x 256 491, short 481; 101 of 2088 x 178 623, short 638).
   long tiles = 0;
   for (int j = 0; j < n; ++j) tiles += tiles_of(*d[j], 128);
-  if (d[0]->K <= 256 || (d[0]->K <= 640 && tiles <= 2 * cus)) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
+  const int64_t K = d[0]->K;
+  if (K < 256 || tiles <= (K == 256 ? 8 : K <= 640 ? 2 : 0) * cus) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
   return launch_cfg<128, 128, BKS, 9>(d, n, stream);
 }
 
