@@ -196,6 +196,19 @@ def test_every_tile_gives_the_same_bits(m, n, counts):
         first = out
 
 
+@pytest.mark.parametrize("cnt,m,n", [(1, 384, 256), (2, 1000, 333), (6, 1536, 512), (48, 1024, 256), (12, 2048, 1024)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_tall_is_the_wide_result_transposed(cnt, m, n, dtype):
+    """A tall matrix is held transposed while it is iterated on, so its result is the transposed result of
+    its transpose, bit for bit, wherever the norm is the same: elements of one magnitude have an exact
+    sum of squares in any order.  (Other values may differ in the sum's last bit, and through it in
+    roundings of the iteration.)"""
+    x = torch.sign(S.normal((cnt, m, n), 1.0, seed=14, stream=m + n)) * 2.0 ** -10
+    x = x.to(dtype)
+    tall, wide = _run(x), _run(x.transpose(1, 2).contiguous())
+    assert torch.equal(tall, wide.transpose(1, 2))
+
+
 def test_products_beside_lds_kernels_of_another_stream():
     """Newton-Schulz of small tiles (which leave most of the LDS unused) on one stream while kernels
     that hold LDS (top-k selection, small chains) keep the compute units busy on another: the bits of
