@@ -711,7 +711,7 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   // another stream: an earlier 128 x 128 kernel gave wrong tiles when two of its workgroups were on
   // one CU, and why is not known.  (Not the LDS address of the transfers: `buffer_load ... lds`
   // lands where it should in allocations of 20, 40 and 80 KiB that do not start at 0, measured on
-  // 7600 workgroups.)  The schedule wants one workgroup per CU anyway.
+  // 5600 such workgroups.)  The schedule wants one workgroup per CU anyway.
   const int slot = device_slot();
   int W = cus_per_xcd(slot);
   double flops = 0.0;
