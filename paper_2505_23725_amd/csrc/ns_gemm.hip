@@ -16,8 +16,11 @@
 // between MFMAs: a burst fills the vector-memory queue, and a wavefront issues in order.  One
 // barrier per K tile, in its middle, publishes the next K tile and frees both of its own
 // buffers.  The ring does not drain between output tiles.  The compiler does not model these
-// transfers, so their completion is awaited explicitly (s_waitcnt vmcnt(n): a wavefront's
-// vector-memory loads complete in issue order).
+// transfers, so their completion is awaited explicitly (s_waitcnt vmcnt(n): completion of a
+// wavefront's vector-memory operations, loads and stores alike, is reported in the order in which they
+// were issued, as the public gfx9 memory model has it and as the compiler's own waits assume).  The n
+// of a wait is the number of operations certain to have been issued after what is awaited, stores
+// included, so that no wait is one for stores that are still on their way.
 //
 // An operand whose K index is the slow one in memory ("K-strided": X in B'X) is never
 // transposed in HBM.  Its tile is stored in LDS as it is in memory ([k][row]) and read with the
@@ -29,11 +32,13 @@
 // operand order is swapped (the N operand is the MFMA's first), so that a lane owns 8 adjacent
 // columns in two tiles.  Both the tile and its transposed copy then leave as 16-byte stores.
 //
-// Measured (batches of 2048-wide matrices, executed FLOP): the K loop alone runs at 1.49 PFLOP/s,
-// whole launches at 1.18-1.41 depending on their depth; the kernel this one replaced (32x32x16
-// MFMAs, 32-deep half-line stages requested in bursts) ran at 1.09.  What is left on top of the
-// K loop is the epilogue: 7 us per 256 x 256 tile, 9 with the transposed copy, against 47 us of
-// K loop at K = 2048, of which 2 to 3 us are the conversions and the rest the stores.
+// Between two output tiles the matrix cores stand still only while the accumulators are rounded and
+// half of the tile is stored; the other half waits in registers and leaves during the next tile's
+// first K tiles.  256 x 256 tile, cycles at K = 2048: 32 K tiles of 2470 (2048 are MFMAs), 3460 of
+// epilogue, about 3000 that the stores behind it cost the first K tiles.  Before this (one epilogue
+// of 7 us that also waited for all its stores, staged through the LDS) the same work took 1.04 (2048
+// wide) to 1.06 (768 wide) times as long.  Cycles are not time here: the part runs at its power limit,
+// 1.7 GHz in these launches, and 16 % fewer cycles at 768 gave 5 %.
 #include <atomic>
 #include <type_traits>
 
@@ -92,6 +97,30 @@ __device__ __forceinline__ void dma16(const i32x4& rsrc, unsigned voff, unsigned
                "buffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "n"(OFF) : "memory", "m0", "scc");
 }
+// One MFMA of the 256 x 256 tile: acc = b a (+ acc).  Written out so that the accumulator stays where it
+// is: left to choose, the compiler moves accumulators about where code paths meet.
+template <bool ZERO>
+__device__ __forceinline__ void mfma(f32x4& acc, const u32x4& b, const u32x4& a) {
+  if constexpr (ZERO) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
+// The same with a transfer (see dma16): the MFMA stands between the write of m0 and its use.
+template <bool ZERO, int OFF>
+__device__ __forceinline__ void mfma_dma(f32x4& acc, const u32x4& b, const u32x4& a, const i32x4& rsrc,
+                                         unsigned voff, unsigned soff, unsigned lds_base) {
+  if constexpr (ZERO)
+    asm volatile("s_add_u32 m0, %3, %7\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0\n\t"
+                 "buffer_load_dwordx4 %4, %5, %6 offen lds"
+                 : "=&a"(acc) : "v"(b), "v"(a), "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "n"(OFF)
+                 : "memory", "m0", "scc");
+  else
+    asm volatile("s_add_u32 m0, %3, %7\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\t"
+                 "buffer_load_dwordx4 %4, %5, %6 offen lds"
+                 : "+a"(acc) : "v"(b), "v"(a), "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "n"(OFF)
+                 : "memory", "m0", "scc");
+}
 #pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -111,13 +140,12 @@ __device__ __forceinline__ unsigned int pair_hi(unsigned int x, unsigned int y) 
   return __builtin_amdgcn_perm(y, x, 0x07060302u);
 }
 
-// One accumulator element, read where it is needed: the statement keeps the accumulators in
-// their accumulation registers until then (left to itself the compiler copies all of them to
-// ordinary registers first, and from there to scratch memory).
-__device__ __forceinline__ float acc_read(float a) {
-  float x;
-  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(a));
-  return x;
+// Four accumulator elements, moved to ordinary registers here: the statement keeps the accumulators
+// in their accumulation registers until then (left to itself the compiler copies all of them first,
+// and from there to scratch memory).
+__device__ __forceinline__ f32x4 acc_read(f32x4 a) {
+  asm volatile("" : "+v"(a));
+  return a;
 }
 // The wait states between the last MFMA and the first acc_read of its result (the compiler
 // does not see into either statement); the operands tie the statements to every accumulator.
@@ -138,8 +166,22 @@ __device__ __forceinline__ void acc_settle(const f32x4 (&acc)[TI][TJ]) {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// In the accumulator layout the 16 lanes of a store meet 16 rows, 64 bytes of each: half a line.  Lanes
+// whose rows are neighbours therefore swap: x and y are 16 bytes each of a lane's row, 32 columns
+// apart; a becomes 16 bytes of the even lane's row, b of the odd lane's, and a store covers 8 rows of
+// 128 bytes (a store costs the address path about five cycles a line).
+__device__ __forceinline__ void pair_rows(const u32x4& x, const u32x4& y, bool odd, u32x4& a, u32x4& b) {
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const unsigned int xs = (unsigned int)__builtin_amdgcn_mov_dpp((int)x[w], 0xb1, 0xf, 0xf, true);   // from the neighbour
+    const unsigned int ys = (unsigned int)__builtin_amdgcn_mov_dpp((int)y[w], 0xb1, 0xf, 0xf, true);
+    a[w] = odd ? ys : x[w];
+    b[w] = odd ? y[w] : xs;
+  }
+}
+
 // Position of an output tile.
-struct TileCoord { int b, m0, n0; bool mirror; };
+struct TileCoord { int b, m0, n0, mirror; };
 
 // TI adjacent bf16 values of a row <-> TI / 2 words.
 template <int TI>
@@ -163,17 +205,20 @@ __device__ __forceinline__ void store_words(const unsigned int (&w)[TI / 2], __a
 // tiles).  TOUT: only the transposed tile is stored, and C is read transposed.  DIAG: the
 // diagonal may cross the tile.  UNIT: alpha_b is 1.
 //
-// In the accumulator layout a store covers 16 rows x 64 bytes, half a line each.  The tile
-// therefore goes through the ring buffer that is free between two tiles, 64 columns at a time
-// and half of the rows, and leaves as 128-byte lines (64 matrices of 2048 x 2048: Gram products
-// 1.17 -> 1.25 PFLOP/s, polynomial 1.10 -> 1.18, apply 1.25 -> 1.27).
-// stage + wave * 1024 + 4096 x, 1 KiB each, x < TI, is the part of that buffer which this
-// wavefront's own next transfers overwrite, so no other wavefront is involved.  (The transposed
-// tile needs no such detour: its stores are 256 bytes wide as they are.)
+// Of the 256 x 256 tile only the first 64 of a wavefront's 128 columns leave here; the others are
+// left packed in `pend`, and run_tiles stores them between the MFMAs of the next tile's first K
+// tiles.  (All 128 columns at once would not fit beside the next tile's fragments.)  What bounds this
+// is the stores: a CU sends about one line in five cycles, so a row is rounded while the one before it
+// is on its way (one row after the other 3460 cycles, all rows before the first store 4500; with rows
+// gathered to whole lines through the LDS instead of pair_rows 4600, and as half lines 6400).
+constexpr int epilogue_stores(int ti, bool mirror) {      // what store_tile leaves in flight, at least
+  const int plain = ti == 8 ? 16 : ti == 4 ? 8 : 2, transposed = ti == 2 ? 8 : 16;
+  return mirror ? plain + transposed : plain;
+}
 template <int TI, int TJ, bool HAS_C, bool MIRROR, bool TOUT, bool DIAG, bool UNIT>
 __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)[TI][TJ],
                                            const TileCoord& tc, float alpha, int wbase_m, int wbase_n,
-                                           int lane, unsigned char* stage) {
+                                           int lane, u32x4 (&pend)[TI == 8 ? 16 : 1]) {
   // what follows from the lane is computed here, not kept in registers through the K loop
   asm volatile("" : "+v"(lane));
   // lane's first row and column; its element (i, J, e) is row row0 + i, column col0 + 32 J + e.
@@ -183,6 +228,9 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   const int row0 = tc.m0 + wbase_m + TI * idx;
   const int col0 = tc.n0 + wbase_n + 8 * lg;
   constexpr int NJ = TJ / 2;
+  constexpr int NH = NJ > 1 ? 2 : 1;      // 32-column blocks handled together
+  constexpr int NP = NJ / NH;             // the second of two such groups is the one left in `pend`
+  static_assert(NP == (TI == 8 ? 2 : 1), "which columns are stored when");
   const __amdgpu_buffer_rsrc_t rd =
       __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, 0xffffffff, 0x00020000);
   __amdgpu_buffer_rsrc_t rc = rd;
@@ -193,127 +241,120 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   const unsigned int voff_m = (unsigned int)(((long)col0 * g.ldd + row0) * 2);   // transposed
   const unsigned int voff_c =
       HAS_C ? (unsigned int)(((TOUT ? (long)col0 * g.ldc + row0 : (long)row0 * g.ldc + col0)) * 2) : 0u;
-  auto value = [&](int i, int J, int e) {
-    const float v = acc_read(acc[i][2 * J + e / 4][e % 4]);
-    return UNIT ? v : alpha * v;
-  };
+  auto value = [&](float v) { return UNIT ? v : alpha * v; };
+  // All of C is requested before the first store: vector-memory operations count down in order, so
+  // a wait for a later load would be one for the stores before it.
   if constexpr (TOUT) {
-    u32x4 c[8];
-    auto load_c = [&](int J, int e) {
-      const unsigned int soff = (unsigned int)(32 * J + e) * ldc2;
-      if constexpr (TI == 8) c[e] = __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c, soff, 0);
-      else if constexpr (TI == 2) c[e].x = __builtin_amdgcn_raw_buffer_load_b32(rc, voff_c, soff, 0);
-      else {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rc, voff_c, soff, 0);
-        c[e].x = v.x;
-        c[e].y = v.y;
-      }
-    };
+    constexpr int NX = 8 * NH;            // columns of a group
+    u32x4 c[NP][NX];
     if constexpr (HAS_C)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) load_c(0, e);
-    wait_vmcnt<HAS_C ? 8 : 0>();
+      for (int x = 0; x < NP * NX; ++x) {
+        const unsigned int soff = (unsigned int)(32 * (x / 8) + x % 8) * ldc2;
+        u32x4& d = c[x / NX][x % NX];
+        if constexpr (TI == 8) d = __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c, soff, 0);
+        else if constexpr (TI == 2) d.x = __builtin_amdgcn_raw_buffer_load_b32(rc, voff_c, soff, 0);
+        else {
+          const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rc, voff_c, soff, 0);
+          d.x = v.x;
+          d.y = v.y;
+        }
+      }
     acc_settle(acc);
 #pragma unroll
-    for (int J = 0; J < NJ; ++J) {
-      // keep the scheduler from pulling the next columns' accumulator reads up here: all
-      // accumulators in VGPRs at once do not fit
-      __builtin_amdgcn_sched_barrier(0);
+    for (int x4 = 0; x4 < NX; x4 += 4)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        unsigned int w[TI / 2];
+      for (int P = 0; P < NP; ++P) {
+        // keep the scheduler from pulling later accumulator reads up here: all accumulators in
+        // VGPRs at once do not fit
+        __builtin_amdgcn_sched_barrier(0);
+        unsigned int w[4][TI / 2];
 #pragma unroll
         for (int i = 0; i < TI; i += 2) {
-          float v0 = value(i, J, e), v1 = value(i + 1, J, e);
-          if constexpr (HAS_C) {
-            v0 += g.beta * bf16lo(c[e][i / 2]);
-            v1 += g.beta * bf16hi(c[e][i / 2]);
+          const f32x4 lo = acc_read(acc[i][2 * NH * P + x4 / 4]), hi = acc_read(acc[i + 1][2 * NH * P + x4 / 4]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float v0 = value(lo[e]), v1 = value(hi[e]);
+            if constexpr (HAS_C) {
+              v0 += g.beta * bf16lo(c[P][x4 + e][i / 2]);
+              v1 += g.beta * bf16hi(c[P][x4 + e][i / 2]);
+            }
+            w[e][i / 2] = pack_bf16x2(v0, v1);
           }
-          w[i / 2] = pack_bf16x2(v0, v1);
         }
-        if (HAS_C && J + 1 < NJ) load_c(J + 1, e);
-        store_words<TI>(w, rd, voff_m, (unsigned int)(32 * J + e) * ldd2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int x = x4 + e;
+          if constexpr (TI == 8) {
+            if (P > 0) { pend[x] = u32x4{w[e][0], w[e][1], w[e][2], w[e][3]}; continue; }
+          }
+          store_words<TI>(w[e], rd, voff_m, (unsigned int)(32 * (x / 8) + x % 8) * ldd2);
+        }
       }
-    }
   } else {
-    u32x4 c[TI];
-    auto load_c = [&](int J, int i) {
-      c[i] = __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c + 64u * J, (unsigned int)i * ldc2, 0);
-    };
+    u32x4 c[NP][NH][TI];
     if constexpr (HAS_C)
 #pragma unroll
-      for (int i = 0; i < TI; ++i) load_c(0, i);
-    // staging: row 16 (i % (TI/2)) + idx of 128 bytes, 16-byte chunk x at position x ^ (idx / 2 % 8)
-    // (conflict-free both ways); read back 8 rows at a time, row 8 x + lane / 8, chunk lane % 8
-    unsigned char* const put = stage + (idx >> 3) * 4096 + (idx & 7) * 128;
-    const unsigned int put_x = (unsigned int)((idx >> 1) & 7);
-    const unsigned char* const get0 = stage + (lane >> 3) * 128 + (((lane & 7) ^ ((lane >> 4) & 7)) * 16);
-    const unsigned char* const get1 = stage + (lane >> 3) * 128 + (((lane & 7) ^ ((lane >> 4) + 4)) * 16);
-    const unsigned int voff_d = (unsigned int)(((long)(tc.m0 + wbase_m + TI * (lane >> 3)) * g.ldd +
-                                                tc.n0 + wbase_n + 8 * (lane & 7)) * 2);
+      for (int x = 0; x < NJ * TI; ++x)
+        c[x / TI / NH][x / TI % NH][x % TI] =
+            __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c + 64u * (x / TI), (unsigned int)(x % TI) * ldc2, 0);
+    const bool odd = idx & 1;
+    const unsigned int voff_n =
+        (unsigned int)(((long)(row0 - (NH == 2 && odd ? TI : 0)) * g.ldd + col0 + (NH == 2 && odd ? 32 : 0)) * 2);
     const int diag = col0 - row0;         // i - (32 J + e) of the lane's elements on the diagonal
-    wait_vmcnt<HAS_C ? TI : 0>();
     acc_settle(acc);
-    constexpr int NH = NJ > 1 ? 2 : 1;      // 32-column blocks handled together
+    u32x4 first[TI][NH];
 #pragma unroll
-    for (int P = 0; P < NJ / NH; ++P) {
-      __builtin_amdgcn_sched_barrier(0);
-      u32x4 packed[TI][NH];
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int h = 0; h < NH; ++h)
+      for (int P = 0; P < NP; ++P) {
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4 packed[NH];
 #pragma unroll
-        for (int i = 0; i < TI; ++i) {
+        for (int h = 0; h < NH; ++h) {
           const int J = NH * P + h;
+          const f32x4 lo = acc_read(acc[i][2 * J]), hi = acc_read(acc[i][2 * J + 1]);
 #pragma unroll
           for (int e = 0; e < 8; e += 2) {
-            float v0 = value(i, J, e), v1 = value(i, J, e + 1);
+            float v0 = value(e < 4 ? lo[e % 4] : hi[e % 4]), v1 = value(e < 4 ? lo[e % 4 + 1] : hi[e % 4 + 1]);
             if constexpr (HAS_C) {
-              v0 += g.beta * bf16lo(c[i][e / 2]);
-              v1 += g.beta * bf16hi(c[i][e / 2]);
+              v0 += g.beta * bf16lo(c[P][h][i][e / 2]);
+              v1 += g.beta * bf16hi(c[P][h][i][e / 2]);
             }
             if constexpr (DIAG) {
               if (i - (32 * J + e) == diag) v0 += g.gamma;
               if (i - (32 * J + e + 1) == diag) v1 += g.gamma;
             }
-            packed[i][h][e / 2] = pack_bf16x2(v0, v1);
+            packed[h][e / 2] = pack_bf16x2(v0, v1);
           }
-          if (HAS_C && J + 1 < NJ) load_c(J + 1, i);
         }
-      if constexpr (NH == 1) {      // a wavefront's rows are 64 bytes: nothing to gather
-        const unsigned int voff_n = (unsigned int)(((long)row0 * g.ldd + col0) * 2);
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-          __builtin_amdgcn_raw_buffer_store_b128(packed[i][0], rd, voff_n + 64u * P, (unsigned int)i * ldd2, 0);
-      }
-#pragma unroll
-      for (int half = 0; half < (NH == 2 ? 2 : 0); ++half) {
-#pragma unroll
-        for (int i = 0; i < TI / 2; ++i)
-#pragma unroll
-          for (int h = 0; h < NH; ++h)
-            *reinterpret_cast<u32x4*>(put + i * 8192 + (((unsigned int)(4 * h + lg) ^ put_x) << 4)) =
-                packed[half * (TI / 2) + i][h];
-#pragma unroll
-        for (int x = 0; x < TI; ++x) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(((x & 1) ? get1 : get0) + x * 4096);
-          __builtin_amdgcn_raw_buffer_store_b128(
-              v, rd, voff_d + 128u * P, (unsigned int)(8 * TI * (x & 1) + half * (TI / 2) + (x >> 1)) * ldd2, 0);
+        if constexpr (TI == 8) {
+          if (P > 0) { pend[2 * i] = packed[0]; pend[2 * i + 1] = packed[1]; continue; }
         }
+        if constexpr (NH == 1) {          // a wavefront's rows are 64 bytes: nothing to gather
+          __builtin_amdgcn_raw_buffer_store_b128(packed[0], rd, voff_n, (unsigned int)i * ldd2, 0);
+        } else {
+          u32x4 x, y;
+          pair_rows(packed[0], packed[1], odd, x, y);
+          __builtin_amdgcn_raw_buffer_store_b128(x, rd, voff_n, (unsigned int)i * ldd2, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(y, rd, voff_n, (unsigned int)(TI + i) * ldd2, 0);
+        }
+#pragma unroll
+        for (int h = 0; h < NH; ++h) first[i][h] = packed[h];
       }
-      if constexpr (MIRROR) {
-        // column col0 + 32 J + e of this tile becomes a row of the mirrored tile
+    if constexpr (MIRROR) {
+      // column col0 + 32 J + e of this tile becomes a row of the mirrored tile
 #pragma unroll
-        for (int h = 0; h < NH; ++h)
+      for (int h = 0; h < NH; ++h)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            unsigned int w[TI / 2];
+        for (int e = 0; e < 8; ++e) {
+          unsigned int w[TI / 2];
 #pragma unroll
-            for (int i = 0; i < TI; i += 2)
-              w[i / 2] = (e & 1) ? pair_hi(packed[i][h][e / 2], packed[i + 1][h][e / 2])
-                                 : pair_lo(packed[i][h][e / 2], packed[i + 1][h][e / 2]);
-            store_words<TI>(w, rd, voff_m, (unsigned int)(32 * (NH * P + h) + e) * ldd2);
-          }
-      }
+          for (int i = 0; i < TI; i += 2)
+            w[i / 2] = (e & 1) ? pair_hi(first[i][h][e / 2], first[i + 1][h][e / 2])
+                               : pair_lo(first[i][h][e / 2], first[i + 1][h][e / 2]);
+          store_words<TI>(w, rd, voff_m, (unsigned int)(32 * h + e) * ldd2);
+        }
     }
   }
 }
@@ -362,7 +403,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
     tc.m0 = __builtin_amdgcn_readfirstlane(tm * BM);
     tc.n0 = __builtin_amdgcn_readfirstlane(tn * BN);
     tc.b = __builtin_amdgcn_readfirstlane(tc.b);
-    tc.mirror = g.symmetric && tm != tn;
+    tc.mirror = g.symmetric && tm != tn ? 1 : 0;
     return tc;
   };
 
@@ -460,15 +501,18 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
     left = KT;
   };
   unsigned int runA = 0, runB = 0;    // offsets of the next transfer
+  // what transfer `it` of an operand's buffer is followed by
+  auto next_a = [&](int it) { runA += it == TI / 2 - 1 ? jumpA : stepA; };
+  auto next_b = [&](int) { runB += stepB; };
   auto dma_a = [&](auto it_tag, unsigned int dst) {
     constexpr int it = decltype(it_tag)::value;
     dma16<it * 4096>(rsA, voffA, runA, dst);
-    runA += it == TI / 2 - 1 ? jumpA : stepA;
+    next_a(it);
   };
   auto dma_b = [&](auto it_tag, unsigned int dst) {
     constexpr int it = decltype(it_tag)::value;
     dma16<it * 4096>(rsB, voffB, runB, dst);
-    runB += stepB;
+    next_b(it);
   };
   auto dma_n = [&](int n, auto&& f) {        // f(I<n>): n is a constant after unrolling
     switch (n) {
@@ -485,20 +529,68 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
 
   // One slice: NM MFMAs on fragment set `set`, with the reads of the next slice into the other
   // set and the NCH transfers `issue` between them.
-  auto slice = [&](auto set_tag, auto zero_tag, auto&& issue) {
+  // The second half of the last output tile (64 of each wavefront's 128 columns) waits in `pend` and
+  // leaves during the first eight K tiles, two stores (four with a transposed copy) each in its first
+  // slice: they then have a K tile's time before a wait can reach them.  (In the second slice they had
+  // half of that: 2600 cycles more a K tile.)
+  constexpr bool DEFER = TI == 8;
+  u32x4 pend[DEFER ? 16 : 1];
+  bool stored = false, mirrored = false;      // this workgroup's last tile: is there one, has it a transposed copy
+  __amdgpu_buffer_rsrc_t pend_rd;
+  unsigned int pend_n = 0, pend_m = 0, pend_ld = 0;      // lane offsets, plain and transposed; row pitch
+  auto drain = [&](int i) {          // row i of a lane's eight (transposed: columns 2 i and 2 i + 1 of its 16)
+    u32x4 x = pend[2 * i], y = pend[2 * i + 1];
+    unsigned int at = (unsigned int)i * pend_ld, step = TI * pend_ld;
+    if (BKS && g.transposed) {
+      at = (unsigned int)(32 * (i / 4) + 2 * (i % 4)) * pend_ld;
+      step = pend_ld;
+    } else {
+      pair_rows(pend[2 * i], pend[2 * i + 1], lane & 1, x, y);
+    }
+    __builtin_amdgcn_raw_buffer_store_b128(x, pend_rd, pend_n, at, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(y, pend_rd, pend_n, at + step, 0);
+  };
+  auto drain_mirror = [&](int q) {   // column q of a lane's 16
+    const int h = q / 8, e = q % 8;
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 8; i += 2)
+      w[i / 2] = (e & 1) ? pair_hi(pend[2 * i + h][e / 2], pend[2 * i + 2 + h][e / 2])
+                         : pair_lo(pend[2 * i + h][e / 2], pend[2 * i + 2 + h][e / 2]);
+    __builtin_amdgcn_raw_buffer_store_b128(w, pend_rd, pend_m, (unsigned int)(32 * h + e) * pend_ld, 0);
+  };
+  auto slice = [&](auto set_tag, auto zero_tag, auto drain_tag, auto b_tag, unsigned int dst) {
+    constexpr int DR = decltype(drain_tag)::value;
+    constexpr bool OPB = decltype(b_tag)::value;       // operand of the transfers
     constexpr int S = decltype(set_tag)::value;
     constexpr bool ZERO = decltype(zero_tag)::value;
 #pragma unroll
     for (int n = 0; n < NM; ++n) {
-      const int i = n / TJ, j = n % TJ;
-      f32x4 c = acc[i][j];
-      if constexpr (ZERO) c = f32x4{0.f, 0.f, 0.f, 0.f};
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-          __builtin_bit_cast(bf16x8, fb[S][j]), __builtin_bit_cast(bf16x8, fa[S][i]), c, 0, 0, 0);
+      const int i = n / TJ, j = (i & 1) ? TJ - 1 - n % TJ : n % TJ;   // back and forth: one operand changes at a time
+      if constexpr (!DEFER) {
+        f32x4 c = acc[i][j];
+        if constexpr (ZERO) c = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, fb[S][j]), __builtin_bit_cast(bf16x8, fa[S][i]), c, 0, 0, 0);
+        if (n % DSTEP == 1)
+          dma_n(n / DSTEP, [&](auto it) { if constexpr (OPB) dma_b(it, dst); else dma_a(it, dst); });
+      } else if (n % DSTEP == 1) {
+        dma_n(n / DSTEP, [&](auto it) {
+          mfma_dma<ZERO, decltype(it)::value * 4096>(acc[i][j], fb[S][j], fa[S][i], OPB ? rsB : rsA, OPB ? voffB : voffA,
+                                                     OPB ? runB : runA, dst);
+        });
+      } else {
+        mfma<ZERO>(acc[i][j], fb[S][j], fa[S][i]);
+        if (n % DSTEP == 2) { if constexpr (OPB) next_b(n / DSTEP); else next_a(n / DSTEP); }
+      }
 #pragma unroll
       for (int r = 0; r < RPER; ++r)
         if (n % RSTEP == 0 && n / RSTEP * RPER + r < NR) read_one(1 - S, n / RSTEP * RPER + r);
-      if (n % DSTEP == 1) dma_n(n / DSTEP, issue);
+      if constexpr (DR >= 0) {
+        if (n == 12 && stored) drain(DR);
+        if constexpr (!BKS)
+          if (n % 32 == 28 && mirrored) drain_mirror(2 * DR + n / 32);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -524,57 +616,77 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   // instead of 134.8, six of 3001 x 1000 513 instead of 501.)
   wait_vmcnt<(D - 1) * 2 * NCH>();
   block_sync();
-  point_at(0u, BUF, 0);
-#pragma unroll
-  for (int r = 0; r < NR; ++r) read_one(0, r);
   unsigned int p = 0;                 // buffer of operand A of the current K tile
 
   using T = std::true_type;
   using F = std::false_type;
   // Transfers that may be in flight at a K tile's barrier, which publishes the next K tile: all
-  // requested after it.  The first barrier of a later output tile waits for nothing: what it
-  // publishes had landed before the previous tile's epilogue.
+  // requested after it.
   constexpr int STEADY = (NB - 4) * NCH;
-  bool landed = false;
   while (true) {
+    point_at(p, wrap(p + BUF), 0);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read_one(0, r);
     // The next output tile of this workgroup; after the last one the same requests go to this
     // tile's own first K tiles again (in bounds, never read).
     const int next = logical + g.wg_per_xcd;
     const bool more = next < range_end;
     const TileCoord tn = more ? decode(next) : tc;
-    auto step = [&](auto first_tag) {
+    auto step = [&](auto first_tag, auto drain_tag) {
       if (left == 0) aim(tn);
       runA = soA;
       runB = soB;
       const unsigned int pb = wrap(p + BUF), pa1 = wrap(p + 2 * BUF), pb1 = wrap(p + 3 * BUF);
       const unsigned int free0 = lds_wave + (p == 0 ? RING - BUF : p - BUF), free1 = lds_wave + p;
       point_at(p, pb, 1);
-      slice(I<0>{}, first_tag, [&](auto n) { dma_a(n, free0); });
-      if (!decltype(first_tag)::value || !landed) wait_vmcnt<STEADY>();
+      slice(I<0>{}, first_tag, drain_tag, F{}, free0);
+      // in flight behind what has to be there now: this slice's transfers and stores and, on the first
+      // K tile, the last epilogue's stores
+      constexpr int DR = decltype(drain_tag)::value >= 0 ? 2 : 0;
+      constexpr bool FIRST = decltype(first_tag)::value;
+      if (DR + FIRST == 0 || !stored) wait_vmcnt<STEADY>();
+      else if (!BKS && mirrored) wait_vmcnt<STEADY + 2 * DR + (FIRST ? epilogue_stores(TI, true) : 0)>();
+      else wait_vmcnt<STEADY + DR + (FIRST ? epilogue_stores(TI, false) : 0)>();
       block_sync();
       point_at(pa1, pb1, 0);
-      slice(I<1>{}, F{}, [&](auto n) { dma_b(n, free1); });
+      slice(I<1>{}, F{}, I<-1>{}, T{}, free1);
       soA += advA;
       soB += advB;
       --left;
       p = pa1;
     };
-    step(T{});
-    landed = true;
+    if constexpr (DEFER) {
+      step(T{}, I<0>{});
+      step(F{}, I<1>{});
+      step(F{}, I<2>{});
+      step(F{}, I<3>{});
+      if (KT >= 8) {
+        step(F{}, I<4>{});
+        step(F{}, I<5>{});
+        step(F{}, I<6>{});
+        step(F{}, I<7>{});
+      } else if (stored) {
+#pragma unroll
+        for (int i = 4; i < 8; ++i) drain(i);
+        if (!BKS && mirrored)
+#pragma unroll
+          for (int q = 8; q < 16; ++q) drain_mirror(q);
+      }
 #pragma unroll 1
-    for (int t = 1; t < KT; ++t) step(F{});
+      for (int t = KT >= 8 ? 8 : 4; t < KT; ++t) step(F{}, I<-1>{});
+    } else {
+      step(T{}, I<-1>{});
+#pragma unroll 1
+      for (int t = 1; t < KT; ++t) step(F{}, I<-1>{});
+    }
 
-    // Everything requested so far (the next tile's first D K tiles) lands before the first store
-    // is issued (store_tile waits): the next tile's waits then never depend on how loads and
-    // stores complete relative to each other.
     float alpha = g.alpha;
     if (g.bscale) {
       const float sc = g.bscale[tc.b];
       alpha *= (g.bscale_pow == 2) ? sc * sc : sc;
     }
-    unsigned char* const stage = smem + (p == 0 ? RING - BUF : p - BUF) + wave * 1024;
 #define MLC_STORE(C, M, T, DG, U) \
-  store_tile<TI, TJ, C, M, T, DG, U>(g, acc, tc, alpha, wbase_m, wbase_n, lane, stage)
+  store_tile<TI, TJ, C, M, T, DG, U>(g, acc, tc, alpha, wbase_m, wbase_n, lane, pend)
     // Symmetric products (Gram, polynomial) are those with a K-contiguous B, the apply products
     // those with a K-strided one: each kernel holds only the forms its products have.
     if constexpr (!BKS) {
@@ -598,9 +710,28 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
       MLC_STORE(false, false, false, false, false);
     }
 #undef MLC_STORE
+    stored = true;
+    mirrored = tc.mirror;
+    if constexpr (DEFER) {
+      pend_rd = __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, 0xffffffff, 0x00020000);
+      int l = lane;
+      asm volatile("" : "+v"(l));
+      const int row0 = tc.m0 + wbase_m + TI * (l & 15), col0 = tc.n0 + wbase_n + 8 * (l >> 4);
+      pend_ld = (unsigned int)(g.ldd * 2);
+      pend_m = (unsigned int)(((long)(col0 + 64) * g.ldd + row0) * 2);
+      const int o = l & 1;
+      pend_n = BKS && g.transposed ? pend_m : (unsigned int)(((long)(row0 - TI * o) * g.ldd + col0 + 64 + 32 * o) * 2);
+    }
     if (!more) break;
     logical = next;
     tc = tn;
+  }
+  if constexpr (DEFER) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) drain(i);
+    if (!BKS && mirrored)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) drain_mirror(q);
   }
   // nothing may land in the ring after this workgroup has left it
   __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -788,7 +919,7 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
   double us = estimate_us(128, form, tiles[1], kt, cus);
   const double e64 = estimate_us(64, form, tiles[2], kt, cus);
   if (kt >= 4 && e64 < 0.95 * us) { small = 64; us = e64; }
-  if (!divides) return small;
+  if (!divides || kt < 4) return small;        // the large tile leaves stores for its first four K tiles
   return us < (bytes > 64e6 ? 0.85 : 0.95) * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
 }
 

@@ -196,6 +196,42 @@ def test_every_tile_gives_the_same_bits(m, n, counts):
         first = out
 
 
+# more 256 x 256 tiles than compute units, whose stores a workgroup has left over go out during the next
+# tile's K tiles: products of 4 and 6 K tiles (fewer than the stores take), 8 and 10 (exactly as many,
+# and more), and many; tall ones store transposed
+LEFT_OVER = [
+    (600, 256, 256, (256, 128, 256)), (900, 256, 384, (256, 128, 128)), (300, 512, 512, (256, 256, 256)),
+    (300, 512, 640, (256, 256, 128)), (700, 256, 512, (256, 128, 256)), (700, 512, 256, (256, 128, 256)),
+    (100, 1024, 768, (256, 256, 256)),
+]
+
+
+@pytest.mark.parametrize("cnt,m,n,tiles", LEFT_OVER)
+def test_stores_left_for_the_next_tile(cnt, m, n, tiles):
+    """Every matrix has the bits that it gets alone or nearly so (in smaller tiles, where nothing is left
+    over), also where the last product updates bf16 weights."""
+    assert ns_tiles([(cnt, m, n)]) == [tiles]
+    some = S.normal((6, m, n), S.GRAD_STD, seed=21, stream=m + n, dtype=torch.bfloat16).to(DEV)
+    few = torch.stack([o for x in some for o in _run(x[None])])
+    x = some.repeat((cnt + 5) // 6, 1, 1)[:cnt]
+    out = _run(x)
+    for i in range(cnt):
+        assert torch.equal(out[i].view(torch.int16), few[i % 6].view(torch.int16)), i
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-3, beta=0.9)
+
+    def step(grad):
+        W = torch.full_like(grad, 0.02)
+        g = mlc.InnerGroup(W, grad.contiguous(), torch.zeros(grad.shape, device=DEV), 0.7)
+        ws = torch.empty(mlc.muloco_inner_workspace_bytes([g]), dtype=torch.uint8, device=DEV)
+        mlc.muloco_inner_step([g], hp, ws)
+        torch.cuda.synchronize()
+        return W.cpu().view(torch.int16)
+    few = [step(v[None])[0] for v in some]
+    W = step(x)
+    for i in range(cnt):
+        assert torch.equal(W[i], few[i % 6]), i
+
+
 @pytest.mark.parametrize("cnt,m,n", [(1, 384, 256), (2, 1000, 333), (6, 1536, 512), (48, 1024, 256), (12, 2048, 1024)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_tall_is_the_wide_result_transposed(cnt, m, n, dtype):
