@@ -449,6 +449,15 @@ size_t muloco_inner_workspace_min_bytes(const mlc_inner_group* groups, int n_gro
   return need;
 }
 
+// Do two of these parameter arrays share memory?  (They are then updated one launch after the other.)
+static bool updates_overlap(const UpdateDesc* d, int n) {
+  auto end = [](const UpdateDesc& x) { return (uintptr_t)x.W + (size_t)x.count * x.m * x.n * elem_size(x.dtype); };
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < i; ++j)
+      if ((uintptr_t)d[i].W < end(d[j]) && (uintptr_t)d[j].W < end(d[i])) return true;
+  return false;
+}
+
 int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muon_hparams* hp,
                       void* workspace, size_t workspace_bytes, void* stream_) {
   if (!hp) return MLC_ERR_NULL;
@@ -488,13 +497,18 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
     if (rc != MLC_OK) return rc;
     rc = run_ns_jobs(jobs, n_groups, hp->ns_iters, hp->ns_a, hp->ns_b, hp->ns_c, hp->ns_eps, stream);
     if (rc != MLC_OK) return rc;
+    UpdateDesc upd[MAX_NS_JOBS];
+    int n_upd = 0;
     for (int gi = 0; gi < n_groups; ++gi) {
       const mlc_inner_group& g = groups[gi];
       const NsJob& j = jobs[gi];
       if (j.result_buf < 0) continue;      // the last product wrote W
-      rc = launch_param_update(g.param, g.param_dtype, j.w.X[j.result_buf],
-                               hp->ns_iters == 0 ? j.w.scale : nullptr, g.count, g.m, g.n, j.p.mp, j.p.ldx,
-                               decay_factor, hp->eta * g.lr_scale, stream);
+      upd[n_upd++] = UpdateDesc{g.param, g.param_dtype, j.w.X[j.result_buf], hp->ns_iters == 0 ? j.w.scale : nullptr,
+                                g.count, g.m, g.n, j.p.mp, j.p.ldx, hp->eta * g.lr_scale};
+    }
+    if (!updates_overlap(upd, n_upd)) return launch_param_update(upd, n_upd, decay_factor, stream);
+    for (int i = 0; i < n_upd; ++i) {
+      rc = launch_param_update(&upd[i], 1, decay_factor, stream);
       if (rc != MLC_OK) return rc;
     }
     return MLC_OK;
@@ -520,8 +534,9 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
                         fuse ? (bf16_t*)param : nullptr, decay_factor, hp->eta * g.lr_scale);
       if (rc != MLC_OK) return rc;
       if (res < 0) continue;               // the last product wrote W
-      rc = launch_param_update(param, g.param_dtype, w.X[res], hp->ns_iters == 0 ? w.scale : nullptr,
-                               cc, g.m, g.n, p.mp, p.ldx, decay_factor, hp->eta * g.lr_scale, stream);
+      const UpdateDesc ud{param, g.param_dtype, w.X[res], hp->ns_iters == 0 ? w.scale : nullptr,
+                          cc, g.m, g.n, p.mp, p.ldx, hp->eta * g.lr_scale};
+      rc = launch_param_update(&ud, 1, decay_factor, stream);
       if (rc != MLC_OK) return rc;
     }
   }

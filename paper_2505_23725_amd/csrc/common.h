@@ -241,9 +241,12 @@ int launch_ns_load(const void* in, int dtype, bf16_t* U, float* partials, int nb
                    bool transposed, hipStream_t stream);
 int launch_norm_finalize(const float* partials, int nblk, float* scale, int64_t count,
                          float eps, hipStream_t stream);
-int launch_param_update(void* W, int dtype, const bf16_t* O, const float* oscale,
-                        int64_t count, int64_t m, int64_t n, int64_t mp, int64_t ldx,
-                        float decay_factor, float step, hipStream_t stream);
+struct UpdateDesc {
+  void* W; int dtype; const bf16_t* O; const float* oscale;
+  int64_t count, m, n, mp, ldx; float step;
+};
+// No two of the n parameter arrays may share memory.
+int launch_param_update(const UpdateDesc* d, int n, float decay_factor, hipStream_t stream);
 int launch_ns_store(const bf16_t* X, const float* oscale, void* out, int dtype, int64_t count,
                     int64_t m, int64_t n, int64_t mp, int64_t ldx, hipStream_t stream);
 

@@ -309,3 +309,34 @@ def test_more_groups_than_one_momentum_launch_holds():
     for i, (a, b) in enumerate(zip(one, many)):
         assert torch.equal(a.momentum, b.momentum), f"group {i}"
         assert torch.equal(a.param, b.param), f"group {i}"
+
+
+@pytest.mark.parametrize("shapes", [[(5, 128, 128)] * 5 + [(1, 77, 333), (2, 333, 77)],       # more than share a launch; ragged apart
+                                    [(1, 300, 200), (3, 200, 300)]])
+@pytest.mark.parametrize("shared", [False, True])
+def test_updates_that_share_a_launch(shapes, shared):
+    """fp32 weights of several groups: the bits of one call per group, also where two groups name the
+    same weights (which are then updated twice, in order)."""
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-3, beta=0.9)
+    if shared:
+        shapes = shapes + shapes[:1]
+
+    def groups():
+        out = []
+        for i, s in enumerate(shapes):
+            W = S.normal(s, S.PARAM_STD, 31, i).to(DEV)
+            if shared and i == len(shapes) - 1:
+                W = out[0].param
+            out.append(mlc.InnerGroup(W, S.normal(s, S.GRAD_STD, 32, i).to(DEV), S.normal(s, S.GRAD_STD, 33, i).to(DEV), 0.5 + i))
+        return out
+
+    def run(gs):
+        ws = torch.empty(mlc.muloco_inner_workspace_bytes(gs), dtype=torch.uint8, device=DEV)
+        mlc.muloco_inner_step(gs, hp, ws)
+        torch.cuda.synchronize()
+    together, apart = groups(), groups()
+    run(together)
+    for g in apart:
+        run([g])
+    for a, b in zip(together, apart):
+        assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
