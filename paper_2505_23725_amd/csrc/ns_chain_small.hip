@@ -9,7 +9,7 @@
 // from the first iteration to the last; HBM is touched once to read X and once to write it.
 // The arithmetic and its rounding points are those of the batched path: A, B' and X are
 // rounded to bf16 where that path stores them, products accumulate in fp32 on
-// v_mfma_f32_32x32x16_bf16, the normalisation s = 1/(|U| + eps) enters as a factor s^2 of the
+// v_mfma_f32_16x16x32_bf16, the normalisation s = 1/(|U| + eps) enters as a factor s^2 of the
 // first Gram matrix and s of the first product with X.  The kernel forms s itself from the
 // partial sums of squares that the pass which wrote U left per matrix.
 //
@@ -17,18 +17,16 @@
 // always 128 x L with L >= 128: the iteration commutes with transposition.
 //
 // LDS layout: X is [128][LP] bf16 (LP = 128, 256 or 512), A is [128][128] bf16 behind it;
-// with LP = 512 that is all 160 KiB of a CU.  The 16-byte chunk c of row r sits at position
-// c ^ (r % 16) of its aligned group of 16 chunks, so that the 32 rows an MFMA operand
-// fragment touches (same k chunk) spread over all banks.
+// with LP = 512 that is all 160 KiB of a CU.  The 16-byte chunks of a row are swizzled within
+// aligned groups of 16 (row_swizzle).
 #include <atomic>
+#include <type_traits>
 
 #include "common.h"
 
 namespace mlc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 namespace {
 
 constexpr int S = 128;                 // padded short side
@@ -56,17 +54,93 @@ __device__ __forceinline__ unsigned int halves_hi(unsigned int x, unsigned int y
   return __builtin_amdgcn_perm(y, x, 0x07060302u);
 }
 
-// byte offset of element (r, c) in a swizzled matrix of `pitch` bytes per row
-__device__ __forceinline__ int swz_pos(int r, int c, int pitch) {
-  return r * pitch + ((((c >> 3) ^ (r & 15))) << 4) + ((c & 7) << 1);
+// Byte offset of 16-byte chunk `chunk` of row r in a matrix of `pitch` bytes (a multiple of 256) per
+// row.  The LDS serves a 128-bit read 16 lanes at a time over 256 bytes, so the 16 rows of a
+// fragment's k chunk must meet 16 different positions: rows 16 i + idx, and rows 32 J + 8 (idx / 4) + 4 p
+// + idx % 4.  A transposing read takes 4 chunks of each of 4 consecutive rows: the row's lowest two
+// bits therefore choose among groups of four chunks.  The function is linear in the bits of r, so a
+// lane's part of an address is computed once and the rest is an exclusive or with a constant.
+__device__ __forceinline__ int row_swizzle(int r) {
+  return ((r & 3) << 2) ^ ((((r >> 2) ^ (r >> 4)) & 1) << 1) ^ (3 * ((r >> 3) & 1));
+}
+__device__ __forceinline__ int chunk_pos(int r, int chunk, int pitch) { return r * pitch + ((chunk ^ row_swizzle(r)) << 4); }
+constexpr int SWZ_ROW4 = 32;      // what bit 2 (or 4) of the row does to a position
+
+// acc = b a (+ acc).  Inline assembly keeps the accumulators where they are (left to choose, the
+// compiler copies them between slices, with wait states around every copy); it then does not know of
+// the MFMAs' latency, so `settle` stands between the last of them and the first acc_read.
+template <bool ZERO>
+__device__ __forceinline__ void mfma(f32x4& acc, const u32x4& b, const u32x4& a) {
+  if constexpr (ZERO) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
+template <int M, int N>
+__device__ __forceinline__ void settle(f32x4 (&acc)[M][N]) {
+  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+  // nothing may read an accumulator's value from before the wait
+#pragma unroll
+  for (int n = 0; n < M * N; ++n) asm volatile("" : "+a"(acc[n / N][n % N]));
+}
+__device__ __forceinline__ f32x4 acc_read(f32x4 a) {
+  asm volatile("" : "+v"(a));
+  return a;
 }
 
-__device__ __forceinline__ f32x16 mfma(const u32x4& a, const u32x4& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+// Fragments and results.  Operand order is swapped, so a lane (idx = lane % 16, lg = lane / 16) holds, in
+// accumulator tiles 2 J and 2 J + 1 of a row, columns 32 J + 8 lg .. + 7 (tile j's fragment has column
+// 32 (j / 2) + 8 (idx / 4) + 4 (j % 2) + idx % 4 in lane idx): results leave as 16-byte LDS writes.  Rows
+// go the same way in the products of a matrix with its own transpose, so that a wavefront on the
+// diagonal reads its fragments once for both operands; B' X has row 16 i + idx in tile i.
+// Lane parts of the addresses: `row` + (chunk byte ^ `x`) is the position of k chunk lg of row idx (or
+// of tile 0's column); tile i is 16 i rows further, and the chunk byte of k chunk 4 c is 64 c.
+struct LanePos { int row, x; };
+__device__ __forceinline__ LanePos lane_rows(int pitch, int row0, int idx, int lg) {
+  return LanePos{(row0 + idx) * pitch, (row_swizzle(idx) ^ lg) << 4};
+}
+__device__ __forceinline__ LanePos lane_cols(int pitch, int row0, int idx, int lg) {
+  const int r = 8 * (idx >> 2) + (idx & 3);
+  return LanePos{(row0 + r) * pitch, (row_swizzle(r) ^ lg) << 4};
+}
+__device__ __forceinline__ u32x4 frag_row(const unsigned char* m, int pitch, const LanePos& p, int i, int at) {
+  return *reinterpret_cast<const u32x4*>(m + p.row + (p.x ^ at ^ ((i & 1) * SWZ_ROW4)) + 16 * i * pitch);
+}
+__device__ __forceinline__ u32x4 frag_col(const unsigned char* m, int pitch, const LanePos& p, int j, int at) {
+  return *reinterpret_cast<const u32x4*>(m + p.row + (p.x ^ at ^ ((j & 1) * SWZ_ROW4)) + (32 * (j >> 1) + 4 * (j & 1)) * pitch);
+}
+// K-strided fragment of rows 32 sl + 8 lg .. + 7, two transposing reads of 4; `at`: byte of column block 0
+__device__ __forceinline__ LanePos lane_strided(int pitch, int idx, int lg, int at) {
+  const int k = 8 * lg + (idx >> 2);
+  return LanePos{k * pitch, ((row_swizzle(k) ^ (idx & 3)) << 4) ^ at};
+}
+__device__ __forceinline__ u32x4 frag_tr(const unsigned char* m, int pitch, const LanePos& p, int j, int sl) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  u32x4 v;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int pos = p.row + (p.x ^ (64 * (j >> 1)) ^ (h * SWZ_ROW4)) + (32 * sl + 4 * h) * pitch + 8 * (j & 1);
+    const u32x2 w = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)((lds_byte*)m + pos)));
+    v[2 * h] = w.x;
+    v[2 * h + 1] = w.y;
+  }
+  return v;
+}
+__device__ __forceinline__ u32x4 pack8(const f32x4& x, const f32x4& y) {
+  u32x4 w;
+  w.x = pack_bf16x2(x[0], x[1]); w.y = pack_bf16x2(x[2], x[3]);
+  w.z = pack_bf16x2(y[0], y[1]); w.w = pack_bf16x2(y[2], y[3]);
+  return w;
 }
 
 // The whole chain of matrix `mat` of a batch, by one workgroup.
+//
+// Bound by what cannot overlap in one wavefront per SIMD: a phase's conversions and its barriers, and
+// in the Gram product the LDS, which takes as long to read 64 x 64 blocks as their MFMAs to run.  Cycles of
+// an iteration on 128 x 512: Gram 5200 (MFMAs 4100), its result 900, square 1750, polynomial 2400, product
+// with X 4900 (4100), its result 3000.  An iteration took 8.8 us and takes 7.7 (128 x 128: 5.2 and 4.1), the
+// launch around five of them 18 and 12 us, since fragments are read ahead of their use, K-strided ones
+// with the transposing read, and all loads of X are in flight at once.
 template <int TT>
 __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   constexpr int LP = 128 * TT;
@@ -78,238 +152,211 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   unsigned char* as = smem + X_BYTES;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lg = lane >> 5;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int idx = lane & 15, lg = lane >> 4;
   const bf16_t* in = g.in + mat * g.stride;
   bf16_t* out = g.out + mat * g.stride;
   const int L = g.L;
+
   // 1 / (|U| + eps) from the partial sums the pass that wrote U left behind (every wavefront
   // adds them up for itself, in the same order)
-  float tot = 0.f;
-  for (int i = lane; i < g.nblk; i += 64) tot += g.partials[mat * g.nblk + i];
-  const float sumsq = wave_sum(tot);
-  const float s = sumsq > 0.f ? 1.0f / (sqrtf(sumsq) + g.eps) : 0.f;   // all-zero matrix: 0, also when eps = 0
+  const float* partials = g.partials + mat * g.nblk;
+  float tot = lane < g.nblk ? partials[lane] : 0.f;
 
-  // ---- X from memory into LDS (columns L .. LP-1 are zero) -----------------------------
+  // ---- X from memory into LDS (columns L .. LP-1 are zero).  All of a thread's loads go out before the
+  // first is awaited: one workgroup has a round trip to memory to itself.
   if (!g.tall) {
-#pragma unroll 4
-    for (int q = tid; q < S * CPR; q += 256) {
-      const int r = q / CPR, ch = q % CPR;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (ch * 8 < L) v = *reinterpret_cast<const u32x4*>(in + (long)r * g.ld + ch * 8);
-      *reinterpret_cast<u32x4*>(xs + r * X_PITCH + ((ch ^ (r & 15)) << 4)) = v;
+    u32x4 v[8 * TT];
+#pragma unroll
+    for (int t = 0; t < 8 * TT; ++t) {
+      const int r = (t * 256 + tid) / CPR, ch = (t * 256 + tid) % CPR;
+      v[t] = *reinterpret_cast<const u32x4*>(in + (long)r * g.ld + (ch * 8 < L ? ch * 8 : 0));
+    }
+#pragma unroll
+    for (int t = 0; t < 8 * TT; ++t) {
+      const int r = (t * 256 + tid) / CPR, ch = (t * 256 + tid) % CPR;
+      if (ch * 8 >= L) v[t] = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(xs + chunk_pos(r, ch, X_PITCH)) = v[t];
     }
   } else {
-    // memory row rg = resident column; consecutive lanes take consecutive rg, so that the
-    // 2-byte LDS stores of a wavefront fall side by side
-#pragma unroll 2
-    for (int q = tid; q < LP * (S / 8); q += 256) {
-      const int cg = q / LP, rg = q % LP;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (rg < L) v = *reinterpret_cast<const u32x4*>(in + (long)rg * g.ld + cg * 8);
-      const unsigned int w[4] = {v.x, v.y, v.z, v.w};
+    // a thread turns 8 columns of 4 rows of memory over
+    const int cg = tid & 15;
+    u32x4 v[2 * TT][4];
+#pragma unroll
+    for (int t = 0; t < 2 * TT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int rg = (t * 16 + (tid >> 4)) * 4 + e;
+        v[t][e] = *reinterpret_cast<const u32x4*>(in + (long)(rg < L ? rg : 0) * g.ld + cg * 8);
+      }
+#pragma unroll
+    for (int t = 0; t < 2 * TT; ++t) {
+      const int rg = (t * 16 + (tid >> 4)) * 4;
+      if (rg >= L)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[t][e] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const unsigned short h = (unsigned short)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
-        *reinterpret_cast<unsigned short*>(xs + swz_pos(cg * 8 + e, rg, X_PITCH)) = h;
+        u32x2 w;
+        w.x = (e & 1) ? halves_hi(v[t][0][e / 2], v[t][1][e / 2]) : halves_lo(v[t][0][e / 2], v[t][1][e / 2]);
+        w.y = (e & 1) ? halves_hi(v[t][2][e / 2], v[t][3][e / 2]) : halves_lo(v[t][2][e / 2], v[t][3][e / 2]);
+        *reinterpret_cast<u32x2*>(xs + chunk_pos(cg * 8 + e, rg >> 3, X_PITCH) + (rg & 4) * 2) = w;
       }
     }
   }
+  for (int i = lane + 64; i < g.nblk; i += 64) tot += partials[i];
+  const float sumsq = wave_sum(tot);
+  const float s = sumsq > 0.f ? 1.0f / (sqrtf(sumsq) + g.eps) : 0.f;   // all-zero matrix: 0, also when eps = 0
   __syncthreads();
 
-  const int wm = wave >> 1, wn = wave & 1;     // 2 x 2 wavefronts over the 128 x 128 products
-  const int ra = wm * 64 + l32, rb = wn * 64 + l32;
-  const int swz = l32 & 15;                    // (row % 16) of every row this lane reads as an operand
-  const int cb = wave * 32 * TT;               // first column of the wavefront's block of X
+  const int rm = (wave >> 1) * 64, rn = (wave & 1) * 64;     // 2 x 2 wavefronts over the 128 x 128 products
+  constexpr int NT = 2 * TT;                                 // column tiles of the wavefront's block of X
+  const int cb = wave * 32 * TT;                             // and its first column
+
+  // What follows from the lane is computed at the start of each phase: kept across the phases the
+  // addresses would take the registers that the accumulators need.
+  int ix = idx, gx = lg;
+  auto fresh = [&] { asm volatile("" : "+v"(ix), "+v"(gx)); };
+
+  // A 64 x 64 block of m m^T over `bytes` of a row, 32-deep slices.  A slice's 16 MFMAs take about as long as
+  // an LDS read, so fragments are read two slices ahead, into the set of four that the last slice but
+  // one has left.  DIAG: both operands are the same rows, read once.
+  u32x4 fa[4][4], fb[4][4];
+  LanePos pr, pc;
+  auto read64 = [&](auto diag, const unsigned char* m, int pitch, int set, int r, int at) {
+    if (r < 4) fb[set][r] = frag_col(m, pitch, pc, r, at);
+    else if (!decltype(diag)::value) fa[set][r - 4] = frag_col(m, pitch, pr, r - 4, at);
+  };
+  auto group64 = [&](auto diag, auto first, f32x4 (&acc)[4][4], const unsigned char* m, int pitch, int c, int last) {
+    constexpr bool DIAG = decltype(diag)::value;
+#pragma unroll
+    for (int sl = 0; sl < 4; ++sl) {
+      const int next = sl < 2 ? c + 64 * (sl + 2) : last + 64 * (sl - 2);
+#pragma unroll
+      for (int n = 0; n < 16; ++n) {
+        const u32x4& a = DIAG ? fb[sl][n / 4] : fa[sl][n / 4];
+        if (decltype(first)::value && sl == 0) mfma<true>(acc[n / 4][n % 4], fb[sl][n % 4], a);
+        else mfma<false>(acc[n / 4][n % 4], fb[sl][n % 4], a);
+        if (n % 2 == 0) read64(diag, m, pitch, (sl + 2) & 3, n / 2, next);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  auto product64 = [&](auto diag, f32x4 (&acc)[4][4], const unsigned char* m, int pitch, int bytes) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) read64(diag, m, pitch, r / 8, r % 8, 64 * (r / 8));
+    // (after the last group the reads ahead are of the first slices again, and not used)
+    group64(diag, std::true_type{}, acc, m, pitch, 0, bytes > 256 ? 256 : 0);
+#pragma unroll 1
+    for (int c = 256; c < bytes; c += 256) group64(diag, std::false_type{}, acc, m, pitch, c, c + 256 < bytes ? c + 256 : 0);
+  };
+  auto square64 = [&](f32x4 (&acc)[4][4], const unsigned char* m, int pitch, int bytes) {
+    fresh();
+    pr = lane_cols(pitch, rm, ix, gx);
+    pc = lane_cols(pitch, rn, ix, gx);
+    if (rm == rn) product64(std::true_type{}, acc, m, pitch, bytes);
+    else product64(std::false_type{}, acc, m, pitch, bytes);
+    settle(acc);
+    fresh();
+  };
+  // this lane's 16 bytes of a 64 x 64 block of A: tile row i, columns 32 J + 8 lg .. + 7
+  auto a_at = [&](int i, int J) -> u32x4* {
+    const LanePos p = lane_cols(A_PITCH, rm, ix, gx);
+    return reinterpret_cast<u32x4*>(as + p.row + (p.x ^ (2 * rn) ^ (64 * J) ^ ((i & 1) * SWZ_ROW4)) +
+                                    (32 * (i >> 1) + 4 * (i & 1)) * A_PITCH);
+  };
 
   for (int it = 0; it < g.iters; ++it) {
     const float alpha_a = it == 0 ? s * s : 1.f;
-    const float alpha_x = it == 0 ? s : 1.f;
 
     // ---- A = alpha_a X X^T : each wavefront one 64 x 64 block -------------------------
     {
-      f32x16 acc[2][2];
+      f32x4 acc[4][4];
+      square64(acc, xs, X_PITCH, 2 * L);                       // L is a multiple of 128
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      // four 16-deep steps per trip, so that the LDS reads of one step overlap the MFMAs of
-      // another (L is a multiple of 128)
-      for (int k64 = 0; k64 < L / 64; ++k64) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int chunk = (((k64 * 4 + u) * 2 + lg) ^ swz) << 4;
-          u32x4 fa[2], fb[2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            fa[i] = *reinterpret_cast<const u32x4*>(xs + (ra + 32 * i) * X_PITCH + chunk);
-            fb[i] = *reinterpret_cast<const u32x4*>(xs + (rb + 32 * i) * X_PITCH + chunk);
-          }
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma(fa[i], fb[j], acc[i][j]);
-        }
-      }
-      // The lane holds, for a fixed column, groups of 4 consecutive rows.  A is symmetric bit
-      // for bit (the same products are summed in the same order for (i, j) and (j, i)), so
-      // element (row, col) is stored at [col][row]: four adjacent values, one 8-byte store.
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int row0 = wm * 64 + i * 32 + q4 * 8 + lg * 4;
-            const int col = wn * 64 + j * 32 + l32;
-            u32x2 w;
-            w.x = pack_bf16x2(alpha_a * acc[i][j][4 * q4], alpha_a * acc[i][j][4 * q4 + 1]);
-            w.y = pack_bf16x2(alpha_a * acc[i][j][4 * q4 + 2], alpha_a * acc[i][j][4 * q4 + 3]);
-            *reinterpret_cast<u32x2*>(as + swz_pos(col, row0, A_PITCH)) = w;
-          }
+        for (int J = 0; J < 2; ++J) *a_at(i, J) = pack8(alpha_a * acc_read(acc[i][2 * J]), alpha_a * acc_read(acc[i][2 * J + 1]));
     }
     __syncthreads();
 
-    // ---- B' = c A A + b A + a I, in place over A ---------------------------------------
+    // ---- B' = c A A + b A + a I, in place over A (a column of A is its row) -------------
     {
-      f32x16 acc[2][2];
+      f32x4 acc[4][4];
+      square64(acc, as, A_PITCH, A_PITCH);
+      u32x4 res[4][2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int J = 0; J < 2; ++J) {
+          const u32x4 av = *a_at(i, J);
+          f32x4 v[2] = {acc_read(acc[i][2 * J]), acc_read(acc[i][2 * J + 1])};
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll 4
-      for (int k16 = 0; k16 < S / 16; ++k16) {
-        const int chunk = ((k16 * 2 + lg) ^ swz) << 4;
-        u32x4 fa[2], fb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          fa[i] = *reinterpret_cast<const u32x4*>(as + (ra + 32 * i) * A_PITCH + chunk);
-          fb[i] = *reinterpret_cast<const u32x4*>(as + (rb + 32 * i) * A_PITCH + chunk);   // column of A = its row
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = mfma(fa[i], fb[j], acc[i][j]);
-      }
-      u32x2 res[2][2][4];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int row0 = wm * 64 + i * 32 + q4 * 8 + lg * 4;
-            const int col = wn * 64 + j * 32 + l32;
-            const u32x2 av = *reinterpret_cast<const u32x2*>(as + swz_pos(col, row0, A_PITCH));
-            float v[4];
-            v[0] = g.c * acc[i][j][4 * q4] + g.b * bf16lo(av.x);
-            v[1] = g.c * acc[i][j][4 * q4 + 1] + g.b * bf16hi(av.x);
-            v[2] = g.c * acc[i][j][4 * q4 + 2] + g.b * bf16lo(av.y);
-            v[3] = g.c * acc[i][j][4 * q4 + 3] + g.b * bf16hi(av.y);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (row0 + e == col) v[e] += g.a;
-            res[i][j][q4].x = pack_bf16x2(v[0], v[1]);
-            res[i][j][q4].y = pack_bf16x2(v[2], v[3]);
+          for (int e = 0; e < 8; ++e) {
+            const float ae = (e & 1) ? bf16hi(av[e / 2]) : bf16lo(av[e / 2]);
+            v[e / 4][e % 4] = g.c * v[e / 4][e % 4] + g.b * ae;
           }
+          if (J == i / 2 && rm == rn) {                        // the diagonal crosses this tile
+            const int d = 8 * (ix >> 2) + 4 * (i & 1) + (ix & 3) - 8 * gx;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (e == d) v[e / 4][e % 4] += g.a;
+          }
+          res[i][J] = pack8(v[0], v[1]);
+        }
       __syncthreads();            // every wavefront is done reading A
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int row0 = wm * 64 + i * 32 + q4 * 8 + lg * 4;
-            const int col = wn * 64 + j * 32 + l32;
-            *reinterpret_cast<u32x2*>(as + swz_pos(col, row0, A_PITCH)) = res[i][j][q4];
-          }
+        for (int J = 0; J < 2; ++J) *a_at(i, J) = res[i][J];
     }
     __syncthreads();
 
-    // ---- X <- alpha_x B' X, in place: each wavefront all 128 rows of 32 TT columns --------
-    // Lane l of column tile t owns column cb + TT l + t: the TT values it needs from a row
-    // of X are adjacent, and so are the TT results it stores.
+    // ---- X <- B' X (s B' X at first), in place: each wavefront all 128 rows of 32 TT columns --------
     {
-      f32x16 acc[4][TT];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int t = 0; t < TT; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
-      const int c0 = cb + TT * l32;
-      auto step = [&](int k16) {
-        const int chunk = ((k16 * 2 + lg) ^ swz) << 4;
-        u32x4 fa[4], fb[TT];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          fa[i] = *reinterpret_cast<const u32x4*>(as + (32 * i + l32) * A_PITCH + chunk);
-        const int k0 = k16 * 16 + lg * 8;
-        if constexpr (TT == 1) {
-          unsigned int raw[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            raw[e] = *reinterpret_cast<const unsigned short*>(xs + swz_pos(k0 + e, c0, X_PITCH));
-#pragma unroll
-          for (int q = 0; q < 4; ++q) fb[0][q] = raw[2 * q] | (raw[2 * q + 1] << 16);
-        } else if constexpr (TT == 2) {
-          unsigned int raw[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            raw[e] = *reinterpret_cast<const unsigned int*>(xs + swz_pos(k0 + e, c0, X_PITCH));
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            fb[0][q] = halves_lo(raw[2 * q], raw[2 * q + 1]);
-            fb[1][q] = halves_hi(raw[2 * q], raw[2 * q + 1]);
-          }
-        } else {
-          static_assert(TT == 1 || TT == 2 || TT == 4, "L pads to 128, 256 or 512");
-          u32x2 raw[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            raw[e] = *reinterpret_cast<const u32x2*>(xs + swz_pos(k0 + e, c0, X_PITCH));
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            fb[0][q] = halves_lo(raw[2 * q].x, raw[2 * q + 1].x);
-            fb[1][q] = halves_hi(raw[2 * q].x, raw[2 * q + 1].x);
-            fb[2 % TT][q] = halves_lo(raw[2 * q].y, raw[2 * q + 1].y);
-            fb[3 % TT][q] = halves_hi(raw[2 * q].y, raw[2 * q + 1].y);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int t = 0; t < TT; ++t) acc[i][t] = mfma(fa[i], fb[t], acc[i][t]);
+      fresh();
+      f32x4 acc[8][NT];
+      // fragments of the next slice in the other set, or, where slices are short, of the next but one
+      constexpr int SETS = TT == 4 ? 2 : 4, AHEAD = SETS / 2;
+      u32x4 ga[SETS][8], gb[SETS][NT];
+      pr = lane_rows(A_PITCH, 0, ix, gx);
+      pc = lane_strided(X_PITCH, ix, gx, 2 * cb);
+      auto read = [&](int r, int sl) {
+        if (r == 0 || r > NT) ga[sl % SETS][r == 0 ? 0 : r - NT] = frag_row(as, A_PITCH, pr, r == 0 ? 0 : r - NT, 64 * sl);
+        else gb[sl % SETS][r - 1] = frag_tr(xs, X_PITCH, pc, r - 1, sl);
       };
-      if constexpr (TT == 4) {    // 256 accumulators: a second set of fragments in flight would spill
-        for (int k16 = 0; k16 < S / 16; ++k16) step(k16);
-      } else {
-#pragma unroll 2
-        for (int k16 = 0; k16 < S / 16; ++k16) step(k16);
-      }
-      __syncthreads();            // every wavefront is done reading X and B'
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int r = 0; r < AHEAD * (8 + NT); ++r) read(r % (8 + NT), r / (8 + NT));
+      constexpr int NM = 8 * NT;                              // MFMAs of a slice
+      constexpr int STEP = NM / (8 + NT) > 2 ? 2 : 1;         // MFMAs per read
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = 32 * i + (r >> 2) * 8 + lg * 4 + (r & 3);
-          unsigned char* p = xs + swz_pos(row, c0, X_PITCH);
-          if constexpr (TT == 1) {
-            *reinterpret_cast<unsigned short*>(p) =
-                (unsigned short)(pack_bf16x2(alpha_x * acc[i][0][r], 0.f) & 0xffffu);
-          } else if constexpr (TT == 2) {
-            *reinterpret_cast<unsigned int*>(p) = pack_bf16x2(alpha_x * acc[i][0][r], alpha_x * acc[i][1][r]);
-          } else {
-            u32x2 w;
-            w.x = pack_bf16x2(alpha_x * acc[i][0][r], alpha_x * acc[i][1 % TT][r]);
-            w.y = pack_bf16x2(alpha_x * acc[i][2 % TT][r], alpha_x * acc[i][3 % TT][r]);
-            *reinterpret_cast<u32x2*>(p) = w;
-          }
+      for (int sl = 0; sl < 4; ++sl) {
+#pragma unroll
+        for (int n = 0; n < NM; ++n) {
+          const int i = n / NT, j = n % NT;
+          if (sl == 0) mfma<true>(acc[i][j], gb[sl % SETS][j], ga[sl % SETS][i]);
+          else mfma<false>(acc[i][j], gb[sl % SETS][j], ga[sl % SETS][i]);
+          if (sl + AHEAD < 4 && n % STEP == 0 && n / STEP < 8 + NT) read(n / STEP, sl + AHEAD);
+          __builtin_amdgcn_sched_barrier(0);
         }
+      }
+      settle(acc);
+      __syncthreads();            // every wavefront is done reading X and B'
+      fresh();
+      auto put = [&](auto&& value) {
+        const LanePos p = lane_rows(X_PITCH, 0, ix, gx);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int J = 0; J < TT; ++J) {
+            // keep the scheduler from pulling all accumulator reads up here
+            __builtin_amdgcn_sched_barrier(0);
+            *reinterpret_cast<u32x4*>(xs + p.row + (p.x ^ (2 * cb) ^ (64 * J) ^ ((i & 1) * SWZ_ROW4)) + 16 * i * X_PITCH) =
+                pack8(value(acc_read(acc[i][2 * J])), value(acc_read(acc[i][2 * J + 1])));
+          }
+      };
+      if (it == 0) put([&](const f32x4& v) { return s * v; });
+      else put([](const f32x4& v) { return v; });
     }
     __syncthreads();
   }
@@ -321,21 +368,18 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
       const int r = q / CPR, ch = q % CPR;
       if (ch * 8 < L)
         *reinterpret_cast<u32x4*>(out + (long)r * g.ld + ch * 8) =
-            *reinterpret_cast<const u32x4*>(xs + r * X_PITCH + ((ch ^ (r & 15)) << 4));
+            *reinterpret_cast<const u32x4*>(xs + chunk_pos(r, ch, X_PITCH));
     }
   } else {
-#pragma unroll 2
-    for (int q = tid; q < LP * (S / 8); q += 256) {
-      const int cg = q / LP, rg = q % LP;
-      if (rg < L) {
-        unsigned int h[8];
+    // a K-strided fragment is 8 adjacent values of a row of memory
+    pc = lane_strided(X_PITCH, idx, lg, 2 * cb);
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          h[e] = *reinterpret_cast<const unsigned short*>(xs + swz_pos(cg * 8 + e, rg, X_PITCH));
-        u32x4 v;
-        v.x = h[0] | (h[1] << 16); v.y = h[2] | (h[3] << 16);
-        v.z = h[4] | (h[5] << 16); v.w = h[6] | (h[7] << 16);
-        *reinterpret_cast<u32x4*>(out + (long)rg * g.ld + cg * 8) = v;
+    for (int j = 0; j < NT; ++j) {
+      const int rg = cb + 32 * (j >> 1) + 8 * (idx >> 2) + 4 * (j & 1) + (idx & 3);
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl) {
+        const u32x4 v = frag_tr(xs, X_PITCH, pc, j, sl);
+        if (cb + 32 * (j >> 1) < L) *reinterpret_cast<u32x4*>(out + (long)rg * g.ld + (4 * sl + lg) * 8) = v;
       }
     }
   }
@@ -346,10 +390,10 @@ __global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
   ns_chain_body<TT>(g, (long)blockIdx.x);
 }
 
-// Batches of several shapes in one launch.  A chain is a serial walk of one workgroup (32 us for
-// 128 x 128, 60 us for 128 x 512) that leaves the other compute units idle, so batches that fit
+// Batches of several shapes in one launch.  A chain is a serial walk of one workgroup (25 us for
+// 128 x 128, 45 us for 128 x 512) that leaves the other compute units idle, so batches that fit
 // the chip together go side by side: 8 / 2 / 2 matrices of 128 x 128, 128 x 512 and 512 x 128 take
-// 60 us instead of 150 one after the other.
+// 48 us instead of 115 one after the other.
 struct ChainTable { ChainArgs s[MAX_CHAINS]; unsigned int blk0[MAX_CHAINS]; int n; };
 __global__ __launch_bounds__(256) void ns_chain_multi_kernel(ChainTable tab) {
   int si = 0;
