@@ -137,11 +137,18 @@ int64_t chunk_for(const NsPlan& p, size_t ws_bytes, int64_t count) {
 struct NsJob {
   NsPlan p; NsBuffers w; int64_t chunk; int result_buf;
   bf16_t* fuse_W = nullptr; float fuse_decay = 0.f, fuse_step = 0.f;
+  // With direct_out set the last product (or the one-launch chain) stores O there, [chunk][m][n] without
+  // padding, instead of in the work space; result_buf is -1 then, too.
+  bf16_t* direct_out = nullptr;
 };
 // The update can ride on the last product when W is bf16 and has the shape the products work
 // on (no padding), and the matrices are not small enough for the one-launch chain.
 static bool can_fuse_update(const NsPlan& p, int param_dtype, int iters) {
   return iters >= 1 && param_dtype == MLC_BF16 && p.m == p.mp && p.n == p.np && !ns_chain_small_fits(p.mp, p.np);
+}
+// A bf16 result without padding needs no pass that stores it (one 1024 x 1024 matrix: 129 -> 125 us).
+static bool can_store_direct(const NsPlan& p, int io_dtype, int iters) {
+  return iters >= 1 && io_dtype == MLC_BF16 && p.m == p.mp && p.n == p.np;
 }
 constexpr int MAX_NS_JOBS = 16;
 
@@ -207,6 +214,7 @@ static GemmDesc apply_desc(const NsJob& j, const bf16_t* X, bf16_t* Xn, bool fir
   if (last) {          // back to the caller's orientation
     g.ldd = p.ldx; g.strideD = p.mp * p.ldx;
     g.transposed = p.mp > p.np;
+    if (j.direct_out) { g.D = j.direct_out; g.ldd = p.n; g.strideD = p.m * p.n; }
   }
   g.C = nullptr; g.batch = (int)j.chunk;
   g.alpha = 1.f; g.beta = 0.f; g.gamma = 0.f;
@@ -236,9 +244,10 @@ int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float 
     NsJob& j = jobs[i];
     if (iters >= 1 && ns_chain_small_fits(j.p.mp, j.p.np)) {
       // small matrices: norm and all iterations in one launch, X and A resident in LDS
-      j.result_buf = 1;
-      chain[nchain++] = ChainDesc{j.w.X[0], j.w.X[1], j.p.ldx, j.p.mp * j.p.ldx, j.p.mp, j.p.np,
-                                  j.w.partials, j.p.nblk, j.chunk};
+      j.result_buf = j.direct_out ? -1 : 1;
+      chain[nchain++] = ChainDesc{j.w.X[0], j.direct_out ? j.direct_out : j.w.X[1], j.p.ldx, j.p.mp * j.p.ldx,
+                                  j.direct_out ? j.p.n : j.p.ldx, j.p.mp * (j.direct_out ? j.p.n : j.p.ldx),
+                                  j.p.mp, j.p.np, j.w.partials, j.p.nblk, j.chunk};
       continue;
     }
     const int rc = launch_norm_finalize(j.w.partials, j.p.nblk, j.w.scale, j.chunk, eps, stream);
@@ -267,14 +276,15 @@ int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float 
     if (rc != MLC_OK) return rc;
     cur ^= 1;
   }
-  for (int i = 0; i < nbig; ++i) big[i]->result_buf = (iters >= 1 && big[i]->fuse_W) ? -1 : cur;
+  for (int i = 0; i < nbig; ++i) big[i]->result_buf = (iters >= 1 && (big[i]->fuse_W || big[i]->direct_out)) ? -1 : cur;
   return MLC_OK;
 }
 
 int run_ns_chunk(const NsPlan& p, const NsBuffers& w, int64_t chunk, int iters, float a, float b,
-                 float c, float eps, hipStream_t stream, int* result_buf, bf16_t* fuse_W = nullptr,
+                 float c, float eps, hipStream_t stream, int* result_buf, bf16_t* direct_out, bf16_t* fuse_W = nullptr,
                  float fuse_decay = 0.f, float fuse_step = 0.f) {
   NsJob j{p, w, chunk, 0};
+  j.direct_out = direct_out;
   j.fuse_W = fuse_W; j.fuse_decay = fuse_decay; j.fuse_step = fuse_step;
   const int rc = run_ns_jobs(&j, 1, iters, a, b, c, eps, stream);
   *result_buf = j.result_buf;
@@ -345,8 +355,10 @@ static int newton_schulz_in(const void* in, void* out, int io_dtype, int64_t cou
                         store_transposed(p, iters), stream);
     if (rc != MLC_OK) return rc;
     int res = 0;
-    rc = run_ns_chunk(p, w, cc, iters, a, b, c, eps, stream, &res);
+    rc = run_ns_chunk(p, w, cc, iters, a, b, c, eps, stream, &res,
+                      can_store_direct(p, io_dtype, iters) ? (bf16_t*)dst : nullptr);
     if (rc != MLC_OK) return rc;
+    if (res < 0) continue;                 // the result is there
     rc = launch_ns_store(w.X[res], iters == 0 ? w.scale : nullptr, dst, io_dtype, cc, m, n, p.mp,
                          p.ldx, stream);
     if (rc != MLC_OK) return rc;
@@ -530,7 +542,7 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
       if (rc != MLC_OK) return rc;
       int res = 0;
       const bool fuse = can_fuse_update(p, g.param_dtype, hp->ns_iters);
-      rc = run_ns_chunk(p, w, cc, hp->ns_iters, hp->ns_a, hp->ns_b, hp->ns_c, hp->ns_eps, stream, &res,
+      rc = run_ns_chunk(p, w, cc, hp->ns_iters, hp->ns_a, hp->ns_b, hp->ns_c, hp->ns_eps, stream, &res, nullptr,
                         fuse ? (bf16_t*)param : nullptr, decay_factor, hp->eta * g.lr_scale);
       if (rc != MLC_OK) return rc;
       if (res < 0) continue;               // the last product wrote W

@@ -214,12 +214,12 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream);
 // ---- whole Newton-Schulz chain of a small matrix in one workgroup (ns_chain_small.hip) ----
 // Fits when the padded short side is 128 and the padded long side at most 512.
 bool ns_chain_small_fits(int64_t mp, int64_t np);
-// in/out: [count] padded mp x np bf16 matrices, row pitch ld, batch stride `stride`
+// in/out: [count] padded mp x np bf16 matrices, row pitch ld (ldo), batch stride `stride` (`strideo`)
 // (elements); partials: per matrix nblk partial sums of squares of the input, from which the
 // kernel forms 1 / (norm + eps); iters >= 1.  in == out is allowed.
 struct ChainDesc {
   const bf16_t* in; bf16_t* out;
-  int64_t ld, stride, mp, np;
+  int64_t ld, stride, ldo, strideo, mp, np;
   const float* partials; int nblk;
   int64_t count;
 };

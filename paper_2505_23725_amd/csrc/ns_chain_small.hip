@@ -35,8 +35,8 @@ constexpr int A_PITCH = S * 2;         // bytes per row of A
 constexpr int64_t CHAIN_SHARE_MAX = 256;     // compute units of the chip
 struct ChainArgs {
   const bf16_t* in;        // [batch] matrices, row pitch ld, batch stride `stride` (elements)
-  bf16_t* out;             // same layout
-  long ld, stride;
+  bf16_t* out;             // row pitch ldo, batch stride strideo
+  long ld, stride, ldo, strideo;
   int tall;                // 0: matrix is 128 x L in memory ; 1: L x 128
   int L;                   // padded long side, a multiple of 128, <= LP
   const float* partials;   // per matrix nblk partial sums of squares of the input
@@ -155,7 +155,7 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int idx = lane & 15, lg = lane >> 4;
   const bf16_t* in = g.in + mat * g.stride;
-  bf16_t* out = g.out + mat * g.stride;
+  bf16_t* out = g.out + mat * g.strideo;
   const int L = g.L;
 
   // 1 / (|U| + eps) from the partial sums the pass that wrote U left behind (every wavefront
@@ -367,7 +367,7 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
     for (int q = tid; q < S * CPR; q += 256) {
       const int r = q / CPR, ch = q % CPR;
       if (ch * 8 < L)
-        *reinterpret_cast<u32x4*>(out + (long)r * g.ld + ch * 8) =
+        *reinterpret_cast<u32x4*>(out + (long)r * g.ldo + ch * 8) =
             *reinterpret_cast<const u32x4*>(xs + chunk_pos(r, ch, X_PITCH));
     }
   } else {
@@ -379,7 +379,7 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
 #pragma unroll
       for (int sl = 0; sl < 4; ++sl) {
         const u32x4 v = frag_tr(xs, X_PITCH, pc, j, sl);
-        if (cb + 32 * (j >> 1) < L) *reinterpret_cast<u32x4*>(out + (long)rg * g.ld + (4 * sl + lg) * 8) = v;
+        if (cb + 32 * (j >> 1) < L) *reinterpret_cast<u32x4*>(out + (long)rg * g.ldo + (4 * sl + lg) * 8) = v;
       }
     }
   }
@@ -463,9 +463,11 @@ int launch_ns_chain_small(const ChainDesc* d, int n, float eps, int iters, float
     if (c_.count < 1 || c_.count > 0x7fffffff || c_.nblk < 1) return MLC_ERR_ARG;
     // every 16-byte access stays inside a row of the padded matrix
     if (c_.ld % 8 || c_.stride % 8 || c_.ld < c_.np || c_.stride < c_.mp * c_.ld) return MLC_ERR_SHAPE;
+    if (c_.ldo % 8 || c_.strideo % 8 || c_.ldo < c_.np || c_.strideo < c_.mp * c_.ldo) return MLC_ERR_SHAPE;
     const bool tall = c_.mp > c_.np;
     ChainArgs& g = tab.s[i];
     g.in = c_.in; g.out = c_.out; g.ld = c_.ld; g.stride = c_.stride;
+    g.ldo = c_.ldo; g.strideo = c_.strideo;
     g.tall = tall ? 1 : 0;
     g.L = (int)(tall ? c_.mp : c_.np);
     g.partials = c_.partials; g.nblk = c_.nblk; g.eps = eps;

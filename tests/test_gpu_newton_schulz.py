@@ -289,3 +289,18 @@ def test_work_space_too_small_is_an_error():
     with pytest.raises(mlc.MulocoError) as e:
         mlc.newton_schulz(x, x, ws)
     assert e.value.code == -4
+
+
+@pytest.mark.parametrize("cnt,m,n", [(3, 128, 128), (2, 128, 384), (2, 512, 128), (3, 256, 640), (3, 640, 256), (5, 768, 512), (70, 512, 512)])
+@pytest.mark.parametrize("how", ["apart", "in place", "chunks"])
+def test_bf16_results_without_padding_need_no_last_pass(cnt, m, n, how):
+    """They have the values of fp32 results of the same input, which go through the work space."""
+    x = S.normal((cnt, m, n), S.GRAD_STD, seed=23, stream=m + n, dtype=torch.bfloat16)
+    ws = 2 * mlc.newton_schulz_workspace_bytes(1, m, n) if how == "chunks" else None
+    mlc.muloco_timing_enable(True)
+    mlc.muloco_timing_read()
+    out = _run(x, ws_bytes=ws, inplace=how == "in place")
+    passes = mlc.muloco_timing_read()["convert"]["launches"]
+    mlc.muloco_timing_enable(False)
+    assert passes == (1 if ws is None else -(-cnt // 2))          # the input's alone
+    assert torch.equal(out.float(), _run(S.normal((cnt, m, n), S.GRAD_STD, seed=23, stream=m + n, dtype=torch.bfloat16).float()))
