@@ -207,7 +207,7 @@ struct GemmDesc {
                          // tiles and store each off-diagonal tile twice
   int transposed;        // D and C are N x M in memory: element (i,j) at ptr[j*ld + i]
 };
-// n independent products (n <= 64).  Those of equal depth K, tile and layout share launches, up
+// n independent products (n <= 64).  Those of one layout share launches where they run one tile, up
 // to three at a time.
 int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream);
 

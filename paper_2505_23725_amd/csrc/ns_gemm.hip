@@ -39,6 +39,7 @@
 // of 7 us that also waited for all its stores, staged through the LDS) the same work took 1.04 (2048
 // wide) to 1.06 (768 wide) times as long.  Cycles are not time here: the part runs at its power limit,
 // 1.7 GHz in these launches, and 16 % fewer cycles at 768 gave 5 %.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -66,7 +67,7 @@ struct GemmArgs {
   bf16_t* D; long ldd, strideD;
   const bf16_t* C; long ldc, strideC;
   int K, batch;
-  int tiles_m, tiles_n, tiles_per_mat, total_tiles, tiles_per_xcd, wg_per_xcd;
+  int tiles_m, tiles_n, tiles_per_mat, total_tiles, tiles_per_xcd;
   int group_m;                    // tile rows per group of the tile order
   int symmetric, transposed;
   float alpha, beta, gamma;
@@ -359,14 +360,18 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   }
 }
 
+// A workgroup's share of a product's tiles (see run_tiles).
+struct Deal { int at, end, step, at2, end2, step2; };
+
 // Persistent kernel: one workgroup per CU slot walks over its share of the output tiles.
 // Workgroups are dealt round-robin to the 8 XCDs, so XCD x owns the contiguous range of
 // tiles [x * tiles_per_xcd, (x + 1) * tiles_per_xcd) and its workgroups take them in
 // order: tiles that share operand panels run at the same time behind the same L2.
-// The tiles logical, logical + g.wg_per_xcd, ... below range_end of one product, by one workgroup.
+// The tiles at, at + step, ... below end of one product and then at2, at2 + step2, ... below end2, by one
+// workgroup.
 // BKS: operand B is K-strided.  NB: buffers of the ring; K >= 64 * (NB - 1) / 2.
 template <int BM, int BN, bool BKS, int NB>
-__device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const int range_end) {
+__device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
   static_assert(BM == BN && NB % 2 == 1, "one buffer size, an odd ring");
   constexpr int TI = BM / 32, TJ = BN / 32;          // accumulator tiles per wavefront
   constexpr int NM = TI * TJ;                        // MFMAs per slice
@@ -377,7 +382,9 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   typedef __attribute__((address_space(3))) unsigned char lds_byte;
   const unsigned int lds0 = (unsigned int)(unsigned long)(lds_byte*)smem;
-  if (logical >= range_end) return;
+  auto second = [&] { deal.at = deal.at2; deal.end = deal.end2; deal.step = deal.step2; deal.at2 = deal.end2; };
+  if (deal.at >= deal.end) second();
+  if (deal.at >= deal.end) return;
 
   auto decode = [&](int t) {
     TileCoord tc;
@@ -596,7 +603,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   };
   auto wrap = [](unsigned int p) { return p >= RING ? p - RING : p; };
 
-  TileCoord tc = decode(logical);
+  TileCoord tc = decode(deal.at);
   aim(tc);
 #pragma unroll
   for (int t = 0; t < D; ++t) {
@@ -629,9 +636,10 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
     for (int r = 0; r < NR; ++r) read_one(0, r);
     // The next output tile of this workgroup; after the last one the same requests go to this
     // tile's own first K tiles again (in bounds, never read).
-    const int next = logical + g.wg_per_xcd;
-    const bool more = next < range_end;
-    const TileCoord tn = more ? decode(next) : tc;
+    deal.at += deal.step;
+    if (deal.at >= deal.end) second();
+    const bool more = deal.at < deal.end;
+    const TileCoord tn = more ? decode(deal.at) : tc;
     auto step = [&](auto first_tag, auto drain_tag) {
       if (left == 0) aim(tn);
       runA = soA;
@@ -723,7 +731,6 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
       pend_n = BKS && g.transposed ? pend_m : (unsigned int)(((long)(row0 - TI * o) * g.ldd + col0 + 64 + 32 * o) * 2);
     }
     if (!more) break;
-    logical = next;
     tc = tn;
   }
   if constexpr (DEFER) {
@@ -738,13 +745,16 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, int logical, const 
   block_sync();
 }
 
-// Up to MAX_MULTI products of equal depth K in one launch (the same product of a Newton-Schulz
-// iteration for several shape groups).  A launch whose tile count is not a multiple of the
-// number of compute units pays for a partly empty last round; sharing a launch leaves one
-// such round instead of one per group.  XCD x still owns a contiguous range of every
-// product's tile order; inside it the workgroups take the products one after the other, each
-// starting with the workgroup after the one that took the previous product's last tile, so
-// that no workgroup ends up with more than one tile over the average.
+// Up to MAX_MULTI products in one launch (the same product of a Newton-Schulz iteration for several
+// shape groups), the deepest first.  A launch whose tile count is not a multiple of the number of
+// compute units pays for a partly empty last round; sharing a launch leaves one such round instead
+// of one per group.  XCD x still owns a contiguous range of every product's tile order; inside it the
+// workgroups take the products one after the other, each starting with the workgroup after the one
+// that took the previous product's last tile, so that no workgroup ends up with more than one tile
+// over the average.  Where the next product is shallower, the workgroups that are a tile short take as
+// many of its tiles ahead of the others as run in that time.  (Gram products of 16 x 1024 x 2816, 0.6
+// rounds, and 32 x 1024 x 1024, 1.25: 135 us in two launches, 100 in one; of a 15B-scale layer 1350
+// and 1240.)
 constexpr int MAX_MULTI = 3;
 struct MultiArgs { GemmArgs seg[MAX_MULTI]; int nseg; };
 
@@ -752,16 +762,29 @@ template <int BM, int BN, bool BKS, int NB>
 __global__ __launch_bounds__(NTHREADS, 1) void ns_gemm_bf16_kernel(MultiArgs m) {
   const int xcd = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD;
   const int W = (int)(gridDim.x / NUM_XCD);
-  int off = 0;         // workgroups of this XCD that already received a tile more than the others
+  int first = 0;       // the workgroup whose turn it is
+  int late = 0;        // how many before it have a tile of the last product more than the others
+  int last_k = 0;
 #pragma unroll 1
   for (int j = 0; j < m.nseg; ++j) {
     const GemmArgs g = m.seg[j];
     const int lo = min(xcd * g.tiles_per_xcd, g.total_tiles);
     const int hi = min((xcd + 1) * g.tiles_per_xcd, g.total_tiles);
-    int pos = slot - off;
+    int pos = slot - first;
     if (pos < 0) pos += W;
-    if (lo + pos < hi) run_tiles<BM, BN, BKS, NB>(g, lo + pos, hi);
-    off = (off + (hi - lo)) % W;
+    int ahead = 0;                     // tiles that the W - late others take first
+    const int early = W - late;
+    if (late && g.K < last_k) {
+      // an epilogue is about three K tiles
+      const int kt = g.K / BK + 3, kt_last = last_k / BK + 3;
+      ahead = min(hi - lo, (2 * kt_last + kt) / (2 * kt) * early);
+    }
+    run_tiles<BM, BN, BKS, NB>(g, Deal{pos < early ? lo + pos : hi, lo + ahead, early, lo + ahead + pos, hi, W});
+    if (!ahead || ahead < hi - lo) {   // (else the late ones are still the late ones)
+      first = (first + (hi - lo - ahead)) % W;
+      late = ((ahead ? 0 : late) + (hi - lo - ahead)) % W;
+    }
+    last_k = g.K;
     // the next product's first transfers overwrite the ring: every wavefront must have left it
     __syncthreads();
   }
@@ -784,7 +807,7 @@ int cus_per_xcd(int slot) {
 
 // Kernel arguments of one product with BM x BN tiles.
 template <int BM, int BN>
-int make_args(const GemmDesc& d, int wg_per_xcd, GemmArgs& g) {
+int make_args(const GemmDesc& d, GemmArgs& g) {
   g.A = d.A; g.lda = d.lda; g.strideA = d.strideA;
   g.B = d.B; g.ldb = d.ldb; g.strideB = d.strideB;
   g.D = d.D; g.ldd = d.ldd; g.strideD = d.strideD;
@@ -806,7 +829,6 @@ int make_args(const GemmDesc& d, int wg_per_xcd, GemmArgs& g) {
   if (total <= 0 || total > (1L << 30)) return MLC_ERR_SHAPE;
   g.total_tiles = (int)total;
   g.tiles_per_xcd = (int)((total + NUM_XCD - 1) / NUM_XCD);
-  g.wg_per_xcd = wg_per_xcd;
   g.alpha = d.alpha; g.beta = d.beta; g.gamma = d.gamma;
   g.bscale = d.bscale; g.bscale_pow = d.bscale_pow;
   return MLC_OK;
@@ -832,7 +854,7 @@ bool valid_desc(const GemmDesc& d) {
   return true;
 }
 
-// n (1 .. MAX_MULTI) products of one depth K and one layout in one launch.
+// n (1 .. MAX_MULTI) products of one layout in one launch, in descending order of depth.
 template <int BM, int BN, bool BKS, int NB>
 int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   MultiArgs m;
@@ -849,16 +871,13 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   int most = 0;
   for (int j = 0; j < MAX_MULTI; ++j) {
     const GemmDesc& dj = *d[j < n ? j : 0];
-    const int rc = make_args<BM, BN>(dj, W, m.seg[j]);
+    const int rc = make_args<BM, BN>(dj, m.seg[j]);
     if (rc != MLC_OK) return rc;
     if (j >= n) continue;
     flops += 2.0 * BM * BN * (double)dj.K * (double)m.seg[j].total_tiles;   // executed, not nominal
     most += m.seg[j].tiles_per_xcd;
   }
-  if (most < W) {            // fewer tiles than compute units
-    W = most;
-    for (GemmArgs& g : m.seg) g.wg_per_xcd = W;
-  }
+  if (most < W) W = most;    // fewer tiles than compute units
   static_assert((size_t)NB * BM * BK * 2 <= CU_LDS, "the ring fits a CU");
   auto kern = ns_gemm_bf16_kernel<BM, BN, BKS, NB>;
   static std::atomic<bool> attr_set[MAX_DEVICES];
@@ -923,12 +942,14 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
   return us < (bytes > 64e6 ? 0.85 : 0.95) * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
 }
 
-template <bool BKS>
-int launch_tiles(const GemmDesc* const* d, int n, hipStream_t stream) {
+// Products of one depth and layout, and the kernel that they run in.
+struct GemmSet { const GemmDesc* d[MAX_MULTI]; int n, tile, ring; };
+
+void choose_kernel(GemmSet& s) {
   const int cus = cus_per_xcd(device_slot()) * NUM_XCD;
-  const int tile = pick_tile(d, n, cus);
-  if (tile == 256) return launch_cfg<256, 256, BKS, 5>(d, n, stream);
-  if (tile == 64) return launch_cfg<64, 64, BKS, 9>(d, n, stream);
+  s.tile = pick_tile(s.d, s.n, cus);
+  s.ring = s.tile == 64 ? 9 : 5;
+  if (s.tile != 128) return;
   // The small tiles leave room for a ring of nine buffers, four K tiles ahead.  Up to ten K tiles
   // two are better while a launch is short: a wavefront has requested all that its ring holds ahead
   // before its first MFMA, and a CU takes 64 bytes a cycle (15 products of 32 / 64 matrices of
@@ -937,10 +958,17 @@ int launch_tiles(const GemmDesc* const* d, int n, hipStream_t stream) {
   // (400 matrices of 384 x 384: 1273 us, with the short one 1320; 96 of 640 x 640 977, 1022), and with
   // four from about eight tiles on (400 of 256 x 256 491, short 481; 101 of 2088 x 178 623, short 638).
   long tiles = 0;
-  for (int j = 0; j < n; ++j) tiles += tiles_of(*d[j], 128);
-  const int64_t K = d[0]->K;
-  if (K < 256 || tiles <= (K == 256 ? 8 : K <= 640 ? 2 : 0) * cus) return launch_cfg<128, 128, BKS, 5>(d, n, stream);
-  return launch_cfg<128, 128, BKS, 9>(d, n, stream);
+  for (int j = 0; j < s.n; ++j) tiles += tiles_of(*s.d[j], 128);
+  const int64_t K = s.d[0]->K;
+  if (!(K < 256 || tiles <= (K == 256 ? 8 : K <= 640 ? 2 : 0) * cus)) s.ring = 9;
+}
+
+template <bool BKS>
+int launch_set(const GemmSet& s, hipStream_t stream) {
+  if (s.tile == 256) return launch_cfg<256, 256, BKS, 5>(s.d, s.n, stream);
+  if (s.tile == 64) return launch_cfg<64, 64, BKS, 9>(s.d, s.n, stream);
+  if (s.ring == 5) return launch_cfg<128, 128, BKS, 5>(s.d, s.n, stream);
+  return launch_cfg<128, 128, BKS, 9>(s.d, s.n, stream);
 }
 
 }  // namespace
@@ -951,23 +979,37 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   for (int i = 0; i < n; ++i)
     if (!valid_desc(d[i])) return MLC_ERR_SHAPE;
   auto divides = [](const GemmDesc& g) { return g.M % 256 == 0 && g.N % 256 == 0; };
+  GemmSet sets[64];
+  int n_sets = 0;
   for (int i = 0; i < n; ++i) {
     if (done[i]) continue;
     // products that can share a launch with product i: same depth (a tile then takes the same
     // time in each, so dealing tiles out evenly balances the time), same tile, same layout
-    const GemmDesc* pick[MAX_MULTI] = {&d[i], nullptr, nullptr};
-    int idx[MAX_MULTI] = {i, -1, -1};
-    int np = 1;
-    for (int j = i + 1; j < n && np < MAX_MULTI; ++j) {
+    GemmSet& s = sets[n_sets++];
+    s.n = 0;
+    for (int j = i; j < n && s.n < MAX_MULTI; ++j) {
       if (done[j] || d[j].K != d[i].K || divides(d[j]) != divides(d[i]) ||
           (d[j].b_kstrided != 0) != (d[i].b_kstrided != 0))
         continue;
-      pick[np] = &d[j];
-      idx[np++] = j;
+      s.d[s.n++] = &d[j];
+      done[j] = true;
     }
-    const int rc = d[i].b_kstrided ? launch_tiles<true>(pick, np, stream) : launch_tiles<false>(pick, np, stream);
+    choose_kernel(s);
+  }
+  // Sets of large tiles share launches as well, the deeper ones first.  (A tile that is small because
+  // there are few of them stays alone: its launch is shorter than a large tile.)
+  std::stable_sort(sets, sets + n_sets, [](const GemmSet& a, const GemmSet& b) { return a.d[0]->K > b.d[0]->K; });
+  for (int i = 0; i < n_sets; ++i) {
+    GemmSet& s = sets[i];
+    if (s.n == 0) continue;            // went out with an earlier one
+    for (int j = i + 1; j < n_sets && s.tile == 256; ++j) {
+      GemmSet& t = sets[j];
+      if (t.n == 0 || t.tile != 256 || s.n + t.n > MAX_MULTI || (t.d[0]->b_kstrided != 0) != (s.d[0]->b_kstrided != 0)) continue;
+      for (int k = 0; k < t.n; ++k) s.d[s.n++] = t.d[k];
+      t.n = 0;
+    }
+    const int rc = s.d[0]->b_kstrided ? launch_set<true>(s, stream) : launch_set<false>(s, stream);
     if (rc != MLC_OK) return rc;
-    for (int k = 0; k < np; ++k) done[idx[k]] = true;
   }
   return MLC_OK;
 }

@@ -340,3 +340,41 @@ def test_updates_that_share_a_launch(shapes, shared):
         run([g])
     for a, b in zip(together, apart):
         assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
+
+
+# Gram products of two depths, both in 256 x 256 tiles: workgroups that are a tile short in the deeper one
+# take several of the shallower one's; few and many tiles of either, and more products than share a launch
+DEPTHS = [([(16, 1024, 2816), (32, 1024, 1024)], 15), ([(30, 512, 3072), (30, 3072, 512), (140, 512, 512)], 15),
+          ([(27, 768, 3072), (60, 768, 768)], 15), ([(40, 768, 3072), (60, 768, 768)], 15),
+          ([(16, 1024, 2816), (9, 2816, 1024), (16, 2048, 1024), (32, 1024, 1024)], None)]
+
+
+@pytest.mark.parametrize("shapes,launches", DEPTHS)
+def test_products_of_two_depths_side_by_side(shapes, launches):
+    """The bits of one group after the other (a work space with no room for all)."""
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-3, beta=0.9)
+    gen = torch.Generator(device=DEV).manual_seed(7)
+
+    def groups():
+        gen.manual_seed(7)
+        out = []
+        for s in shapes:
+            few = torch.randn((3, *s[1:]), generator=gen, device=DEV) * S.GRAD_STD
+            grad = few.repeat(-(-s[0] // 3), 1, 1)[:s[0]].bfloat16()
+            out.append(mlc.InnerGroup(torch.zeros(s, dtype=torch.bfloat16, device=DEV), grad, torch.zeros(s, device=DEV), 1.0))
+        return out
+    a, b = groups(), groups()
+    room = mlc.muloco_inner_workspace_bytes(a)
+    ws = torch.empty(room, dtype=torch.uint8, device=DEV)
+    mlc.muloco_timing_enable(True)
+    mlc.muloco_timing_read()
+    mlc.muloco_inner_step(a, hp, ws)
+    n = mlc.muloco_timing_read()["ns_gemm"]["launches"]
+    mlc.muloco_timing_enable(False)
+    assert launches in (None, n)
+    for g in b:
+        mlc.muloco_inner_step([g], hp, ws)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):
+        assert torch.equal(x.param.view(torch.int16), y.param.view(torch.int16))
+        assert all(torch.equal(x.param[i], x.param[i % 3]) for i in range(x.param.shape[0]))
