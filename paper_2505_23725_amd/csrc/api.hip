@@ -233,7 +233,7 @@ static GemmDesc apply_update_desc(const NsJob& j, const bf16_t* X, bool first) {
 // The `iters` Newton-Schulz iterations on n independent jobs.  On return result_buf of a job
 // is the index of the buffer that holds its result; with iters == 0 the result is X[0] still
 // unscaled, and its factor 1/(norm+eps) sits in `scale`.  The same product of several jobs
-// goes out as one set, so that products of equal depth can share launches.
+// goes out as one set, so that products can share launches.
 int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float eps, hipStream_t stream) {
   if (n < 1 || n > MAX_NS_JOBS) return MLC_ERR_ARG;
   NsJob* big[MAX_NS_JOBS];
@@ -461,13 +461,25 @@ size_t muloco_inner_workspace_min_bytes(const mlc_inner_group* groups, int n_gro
   return need;
 }
 
-// Do two of these parameter arrays share memory?  (They are then updated one launch after the other.)
-static bool updates_overlap(const UpdateDesc* d, int n) {
-  auto end = [](const UpdateDesc& x) { return (uintptr_t)x.W + (size_t)x.count * x.m * x.n * elem_size(x.dtype); };
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < i; ++j)
-      if ((uintptr_t)d[i].W < end(d[j]) && (uintptr_t)d[j].W < end(d[i])) return true;
+// Do any two of these memory ranges overlap?  (Sorts them.)
+struct Span { uintptr_t lo, hi; };
+static Span span(const void* p, size_t bytes) { return Span{(uintptr_t)p, (uintptr_t)p + bytes}; }
+static bool any_overlap(Span* s, int n) {
+  std::sort(s, s + n, [](const Span& a, const Span& b) { return a.lo < b.lo; });
+  for (int i = 1; i < n; ++i)
+    if (s[i].lo < s[i - 1].hi) return true;
   return false;
+}
+
+// Do any two of what the groups write (weights, momenta) share memory?
+static bool inner_overlap(const mlc_inner_group* g, int n) {
+  Span s[2 * MAX_NS_JOBS];
+  for (int i = 0; i < n; ++i) {
+    const size_t elems = (size_t)g[i].count * g[i].m * g[i].n;
+    s[2 * i] = span(g[i].param, elems * elem_size(g[i].param_dtype));
+    s[2 * i + 1] = span(g[i].momentum, elems * 4);
+  }
+  return any_overlap(s, 2 * n);
 }
 
 int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muon_hparams* hp,
@@ -482,10 +494,11 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
   hipStream_t stream = (hipStream_t)stream_;
   const float decay_factor = 1.0f - hp->eta * hp->weight_decay;
   // With room for every group at once the groups go through Newton-Schulz side by side, so that
-  // their products of equal depth share launches; otherwise one group after the other, in
-  // chunks that fit.  Both give the same bits.
+  // their products share launches; otherwise one group after the other, in chunks that fit.  Both give
+  // the same bits.  Groups that write the same memory also go one after the other: side by side their
+  // momentum passes, last products (which write bf16 weights) or updates would be in one launch.
   const size_t all = (n_groups >= 2 && n_groups <= MAX_NS_JOBS) ? inner_workspace_all(groups, n_groups) : 0;
-  if (all && workspace_bytes >= all) {
+  if (all && workspace_bytes >= all && !inner_overlap(groups, n_groups)) {
     NsJob jobs[MAX_NS_JOBS];
     MomentumDesc mom[MAX_NS_JOBS];
     unsigned char* base = (unsigned char*)workspace;
@@ -518,12 +531,7 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
       upd[n_upd++] = UpdateDesc{g.param, g.param_dtype, j.w.X[j.result_buf], hp->ns_iters == 0 ? j.w.scale : nullptr,
                                 g.count, g.m, g.n, j.p.mp, j.p.ldx, hp->eta * g.lr_scale};
     }
-    if (!updates_overlap(upd, n_upd)) return launch_param_update(upd, n_upd, decay_factor, stream);
-    for (int i = 0; i < n_upd; ++i) {
-      rc = launch_param_update(&upd[i], 1, decay_factor, stream);
-      if (rc != MLC_OK) return rc;
-    }
-    return MLC_OK;
+    return launch_param_update(upd, n_upd, decay_factor, stream);
   }
   for (int gi = 0; gi < n_groups; ++gi) {
     const mlc_inner_group& g = groups[gi];
@@ -792,19 +800,13 @@ int muloco_topk_outer_step(const mlc_outer_group* groups, int n_groups, const ml
 // Do any two of the memory ranges that these tensors name overlap?  (Such tensors are updated one
 // launch after the other.)
 static bool adamw_overlap(const mlc_adamw_group* g, int n) {
-  struct Span { uintptr_t lo, hi; } s[4 * ADAMW_MAX_SEG];
+  Span s[4 * ADAMW_MAX_SEG];
   for (int i = 0; i < n; ++i) {
     const void* p[4] = {g[i].param, g[i].grad, g[i].exp_avg, g[i].exp_avg_sq};
     const size_t es[4] = {elem_size(g[i].param_dtype), elem_size(g[i].grad_dtype), 4, 4};
-    for (int x = 0; x < 4; ++x) {
-      const uintptr_t lo = (uintptr_t)p[x];
-      s[4 * i + x] = Span{lo, lo + (size_t)g[i].count * es[x]};
-    }
+    for (int x = 0; x < 4; ++x) s[4 * i + x] = span(p[x], (size_t)g[i].count * es[x]);
   }
-  std::sort(s, s + 4 * n, [](const Span& a, const Span& b) { return a.lo < b.lo; });
-  for (int i = 1; i < 4 * n; ++i)
-    if (s[i].lo < s[i - 1].hi) return true;
-  return false;
+  return any_overlap(s, 4 * n);
 }
 
 int muloco_adamw_step(const mlc_adamw_group* groups, int n_groups, const mlc_adamw_hparams* hp,

@@ -342,6 +342,44 @@ def test_updates_that_share_a_launch(shapes, shared):
         assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
 
 
+# Groups whose bf16 weights the last product updates, two of which name the same memory: in tiles of 64; in
+# tiles of 256, where a launch would hold products of one depth, and of two
+@pytest.mark.parametrize("shapes,tile", [([(2, 256, 384), (1, 384, 256), (2, 256, 384)], 64),
+                                         ([(40, 768, 768), (40, 768, 768)], 256),
+                                         ([(64, 512, 1024), (32, 1024, 1024)], 256)])
+@pytest.mark.parametrize("what", ["param", "momentum"])
+def test_groups_that_write_the_same_memory_go_one_after_the_other(shapes, tile, what):
+    """The bits and the launches of one call per group."""
+    assert all(ns_tiles([s])[0][2] == tile for s in shapes)          # the last product's
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-3, beta=0.9)
+
+    def groups():
+        out = []
+        for i, s in enumerate(shapes):
+            g = mlc.InnerGroup(S.normal(s, S.PARAM_STD, 34, i, dtype=torch.bfloat16).to(DEV),
+                               S.normal(s, S.GRAD_STD, 35, i, dtype=torch.bfloat16).to(DEV),
+                               S.normal(s, S.GRAD_STD, 36, i).to(DEV), 0.5 + i)
+            if i == len(shapes) - 1:
+                setattr(g, what, getattr(out[0], what).view(s))
+            out.append(g)
+        return out
+
+    def run(gs):
+        ws = torch.empty(mlc.muloco_inner_workspace_bytes(gs), dtype=torch.uint8, device=DEV)
+        mlc.muloco_timing_enable(True)
+        mlc.muloco_timing_read()
+        mlc.muloco_inner_step(gs, hp, ws)
+        torch.cuda.synchronize()
+        n = mlc.muloco_timing_read()["ns_gemm"]["launches"]
+        mlc.muloco_timing_enable(False)
+        return n
+    together, apart = groups(), groups()
+    launches = run(together)
+    assert launches == sum(run([g]) for g in apart)
+    for a, b in zip(together, apart):
+        assert torch.equal(a.param.view(torch.int16), b.param.view(torch.int16)) and torch.equal(a.momentum, b.momentum)
+
+
 # Gram products of two depths, both in 256 x 256 tiles: workgroups that are a tile short in the deeper one
 # take several of the shallower one's; few and many tiles of either, and more products than share a launch
 DEPTHS = [([(16, 1024, 2816), (32, 1024, 1024)], 15), ([(30, 512, 3072), (30, 3072, 512), (140, 512, 512)], 15),
