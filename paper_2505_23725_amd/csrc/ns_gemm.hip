@@ -148,22 +148,15 @@ __device__ __forceinline__ f32x4 acc_read(f32x4 a) {
   asm volatile("" : "+v"(a));
   return a;
 }
-// The wait states between the last MFMA and the first acc_read of its result (the compiler
-// does not see into either statement); the operands tie the statements to every accumulator.
+// The wait states between the last MFMA written out above and the first acc_read of its result, which the
+// compiler does not know of.  Every accumulator passes through a statement behind the wait, so that
+// nothing can read one's value from before it.
 template <int TI, int TJ>
-__device__ __forceinline__ void acc_settle(const f32x4 (&acc)[TI][TJ]) {
+__device__ __forceinline__ void acc_settle(f32x4 (&acc)[TI][TJ]) {
   __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    if constexpr (TJ == 8)
-      asm volatile("" :: "a"(acc[i][0]), "a"(acc[i][1]), "a"(acc[i][2]), "a"(acc[i][3]),
-                         "a"(acc[i][4]), "a"(acc[i][5]), "a"(acc[i][6]), "a"(acc[i][7]));
-    else if constexpr (TJ == 2)
-      asm volatile("" :: "a"(acc[i][0]), "a"(acc[i][1]));
-    else
-      asm volatile("" :: "a"(acc[i][0]), "a"(acc[i][1]), "a"(acc[i][2]), "a"(acc[i][3]));
-  }
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < TI * TJ; ++n) asm volatile("" : "+a"(acc[n / TJ][n % TJ]));
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -261,7 +254,6 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
           d.y = v.y;
         }
       }
-    acc_settle(acc);
 #pragma unroll
     for (int x4 = 0; x4 < NX; x4 += 4)
 #pragma unroll
@@ -303,7 +295,6 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
     const unsigned int voff_n =
         (unsigned int)(((long)(row0 - (NH == 2 && odd ? TI : 0)) * g.ldd + col0 + (NH == 2 && odd ? 32 : 0)) * 2);
     const int diag = col0 - row0;         // i - (32 J + e) of the lane's elements on the diagonal
-    acc_settle(acc);
     u32x4 first[TI][NH];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -688,6 +679,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
       for (int t = 1; t < KT; ++t) step(F{}, I<-1>{});
     }
 
+    if constexpr (DEFER) acc_settle(acc);
     float alpha = g.alpha;
     if (g.bscale) {
       const float sc = g.bscale[tc.b];
