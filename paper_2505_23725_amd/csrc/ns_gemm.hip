@@ -44,6 +44,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "tile_deal.h"
 
 namespace mlc {
 
@@ -351,15 +352,10 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   }
 }
 
-// A workgroup's share of a product's tiles (see run_tiles).
-struct Deal { int at, end, step, at2, end2, step2; };
-
 // Persistent kernel: one workgroup per CU slot walks over its share of the output tiles.
 // Workgroups are dealt round-robin to the 8 XCDs, so XCD x owns the contiguous range of
 // tiles [x * tiles_per_xcd, (x + 1) * tiles_per_xcd) and its workgroups take them in
 // order: tiles that share operand panels run at the same time behind the same L2.
-// The tiles at, at + step, ... below end of one product and then at2, at2 + step2, ... below end2, by one
-// workgroup.
 // BKS: operand B is K-strided.  NB: buffers of the ring; K >= 64 * (NB - 1) / 2.
 template <int BM, int BN, bool BKS, int NB>
 __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
@@ -740,43 +736,35 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
 // Up to MAX_MULTI products in one launch (the same product of a Newton-Schulz iteration for several
 // shape groups), the deepest first.  A launch whose tile count is not a multiple of the number of
 // compute units pays for a partly empty last round; sharing a launch leaves one such round instead
-// of one per group.  XCD x still owns a contiguous range of every product's tile order; inside it the
-// workgroups take the products one after the other, each starting with the workgroup after the one
-// that took the previous product's last tile, so that no workgroup ends up with more than one tile
-// over the average.  Where the next product is shallower, the workgroups that are a tile short take as
-// many of its tiles ahead of the others as run in that time.  (Gram products of 16 x 1024 x 2816, 0.6
+// of one per group.  XCD x still owns a contiguous range of every product's tile order; inside it
+// each product of one depth starts with the workgroup after the one that took the previous product's last
+// tile, and deal_tiles evens out the time of different depths.  (Gram products of 16 x 1024 x 2816, 0.6
 // rounds, and 32 x 1024 x 1024, 1.25: 135 us in two launches, 100 in one; of a 15B-scale layer 1350
 // and 1240.)
 constexpr int MAX_MULTI = 3;
-struct MultiArgs { GemmArgs seg[MAX_MULTI]; int nseg; };
+struct MultiArgs { GemmArgs seg[MAX_MULTI]; int nseg, mixed; };
 
 template <int BM, int BN, bool BKS, int NB>
 __global__ __launch_bounds__(NTHREADS, 1) void ns_gemm_bf16_kernel(MultiArgs m) {
   const int xcd = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD;
   const int W = (int)(gridDim.x / NUM_XCD);
-  int first = 0;       // the workgroup whose turn it is
-  int late = 0;        // how many before it have a tile of the last product more than the others
-  int last_k = 0;
+  int first = 0;                       // of equal depth: the workgroup whose turn it is
+  Dealer dealer{W, slot, 0, 0};        // of different depth, which only the large tile's launches mix
 #pragma unroll 1
   for (int j = 0; j < m.nseg; ++j) {
     const GemmArgs g = m.seg[j];
     const int lo = min(xcd * g.tiles_per_xcd, g.total_tiles);
     const int hi = min((xcd + 1) * g.tiles_per_xcd, g.total_tiles);
-    int pos = slot - first;
-    if (pos < 0) pos += W;
-    int ahead = 0;                     // tiles that the W - late others take first
-    const int early = W - late;
-    if (late && g.K < last_k) {
-      // an epilogue is about three K tiles
-      const int kt = g.K / BK + 3, kt_last = last_k / BK + 3;
-      ahead = min(hi - lo, (2 * kt_last + kt) / (2 * kt) * early);
+    const bool more = j + 1 < m.nseg;
+    Deal deal;
+    if (BM == 256 && m.mixed) {
+      deal = deal_tiles(dealer, lo, hi - lo, g.K / BK + 3, more);
+    } else {
+      const int pos = slot - first;
+      deal = Deal{lo + (pos < 0 ? pos + W : pos), hi, W, hi, hi, W};
+      if (more) first = (int)((unsigned)(first + hi - lo) % (unsigned)W);
     }
-    run_tiles<BM, BN, BKS, NB>(g, Deal{pos < early ? lo + pos : hi, lo + ahead, early, lo + ahead + pos, hi, W});
-    if (!ahead || ahead < hi - lo) {   // (else the late ones are still the late ones)
-      first = (first + (hi - lo - ahead)) % W;
-      late = ((ahead ? 0 : late) + (hi - lo - ahead)) % W;
-    }
-    last_k = g.K;
+    run_tiles<BM, BN, BKS, NB>(g, deal);
     // the next product's first transfers overwrite the ring: every wavefront must have left it
     __syncthreads();
   }
@@ -851,6 +839,7 @@ template <int BM, int BN, bool BKS, int NB>
 int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   MultiArgs m;
   m.nseg = n;
+  m.mixed = d[0]->K != d[n - 1]->K;
   // Every launch asks for the whole LDS of a CU, however small its ring, so that its workgroups
   // share a CU with no other workgroup that holds LDS, neither of this kernel nor of one that runs on
   // another stream: an earlier 128 x 128 kernel gave wrong tiles when two of its workgroups were on
