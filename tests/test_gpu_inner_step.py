@@ -384,7 +384,9 @@ def test_groups_that_write_the_same_memory_go_one_after_the_other(shapes, tile, 
 # take several of the shallower one's; few and many tiles of either, and more products than share a launch
 DEPTHS = [([(16, 1024, 2816), (32, 1024, 1024)], 15), ([(30, 512, 3072), (30, 3072, 512), (140, 512, 512)], 15),
           ([(27, 768, 3072), (60, 768, 768)], 15), ([(40, 768, 3072), (60, 768, 768)], 15),
-          ([(16, 1024, 2816), (9, 2816, 1024), (16, 2048, 1024), (32, 1024, 1024)], None)]
+          ([(16, 1024, 2816), (9, 2816, 1024), (16, 2048, 1024), (32, 1024, 1024)], 30),     # three and one
+          # last products of three depths: the workgroups that are a tile short take the middle one whole
+          ([(2, 2560, 2048), (24, 2560, 256), (4, 1280, 2048)], 30), ([(17, 256, 2816), (2, 2048, 2816), (3, 768, 4096)], 30)]
 
 
 @pytest.mark.parametrize("shapes,launches", DEPTHS)
@@ -409,7 +411,7 @@ def test_products_of_two_depths_side_by_side(shapes, launches):
     mlc.muloco_inner_step(a, hp, ws)
     n = mlc.muloco_timing_read()["ns_gemm"]["launches"]
     mlc.muloco_timing_enable(False)
-    assert launches in (None, n)
+    assert launches == n
     for g in b:
         mlc.muloco_inner_step([g], hp, ws)
     torch.cuda.synchronize()
