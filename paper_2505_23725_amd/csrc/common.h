@@ -216,7 +216,7 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream);
 bool ns_chain_small_fits(int64_t mp, int64_t np);
 // in/out: [count] padded mp x np bf16 matrices, row pitch ld (ldo), batch stride `stride` (`strideo`)
 // (elements); partials: per matrix nblk partial sums of squares of the input, from which the
-// kernel forms 1 / (norm + eps); iters >= 1.  in == out is allowed.
+// kernel forms 1 / (norm + eps); iters >= 1.  in and out must not overlap.
 struct ChainDesc {
   const bf16_t* in; bf16_t* out;
   int64_t ld, stride, ldo, strideo, mp, np;

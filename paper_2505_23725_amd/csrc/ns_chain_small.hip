@@ -138,9 +138,9 @@ __device__ __forceinline__ u32x4 pack8(const f32x4& x, const f32x4& y) {
 // Bound by what cannot overlap in one wavefront per SIMD: a phase's conversions and its barriers, and
 // in the Gram product the LDS, which takes as long to read 64 x 64 blocks as their MFMAs to run.  Cycles of
 // an iteration on 128 x 512: Gram 5200 (MFMAs 4100), its result 900, square 1750, polynomial 2400, product
-// with X 4900 (4100), its result 3000.  An iteration took 8.8 us and takes 7.7 (128 x 128: 5.2 and 4.1), the
-// launch around five of them 18 and 12 us, since fragments are read ahead of their use, K-strided ones
-// with the transposing read, and all loads of X are in flight at once.
+// with X 4900 (4100), its result 3000.  Kernel times: an iteration took 8.6 us and takes 7.4 (128 x 128: 5.1
+// and 3.9), the launch around five of them 13.7 and 7.1 us (6.9 and 4.6), since fragments are read ahead of their
+// use, K-strided ones with the transposing read, and all loads of X are in flight at once.
 template <int TT>
 __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   constexpr int LP = 128 * TT;
@@ -390,10 +390,10 @@ __global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
   ns_chain_body<TT>(g, (long)blockIdx.x);
 }
 
-// Batches of several shapes in one launch.  A chain is a serial walk of one workgroup (25 us for
-// 128 x 128, 45 us for 128 x 512) that leaves the other compute units idle, so batches that fit
-// the chip together go side by side: 8 / 2 / 2 matrices of 128 x 128, 128 x 512 and 512 x 128 take
-// 48 us instead of 115 one after the other.
+// Batches of several shapes in one launch.  A chain is a serial walk of one workgroup (24 us for
+// 128 x 128, 44 for 128 x 512, 47 for 512 x 128) that leaves the other compute units idle, so batches
+// that fit the chip together go side by side: 8 / 2 / 2 matrices of these shapes take 47 us instead of
+// 115 one after the other.
 struct ChainTable { ChainArgs s[MAX_CHAINS]; unsigned int blk0[MAX_CHAINS]; int n; };
 __global__ __launch_bounds__(256) void ns_chain_multi_kernel(ChainTable tab) {
   int si = 0;

@@ -740,7 +740,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
 // each product of one depth starts with the workgroup after the one that took the previous product's last
 // tile, and deal_tiles evens out the time of different depths.  (Gram products of 16 x 1024 x 2816, 0.6
 // rounds, and 32 x 1024 x 1024, 1.25: 135 us in two launches, 100 in one; of a 15B-scale layer 1350
-// and 1240.)
+// and 1240.  Launches apart cost about 7 us each beside what their rounds cost.)
 constexpr int MAX_MULTI = 3;
 struct MultiArgs { GemmArgs seg[MAX_MULTI]; int nseg, mixed; };
 
@@ -874,13 +874,13 @@ long tiles_of(const GemmDesc& d, int tile) {
   return (d.symmetric ? tm * (tm + 1) / 2 : tm * tn) * d.batch;
 }
 
-// Microseconds that a launch of `tiles` output tiles of kt K tiles takes, from kernel traces of 142
-// batches (1 to 200 matrices of 128 to 2048, K to 4096): a first round of one tile per compute unit,
-// and further ones that overlap its ends.  Nine in ten launches lie between 0.85 and 1.12 of it, the
-// others being sets of matrices that fit no cache.  The 256 x 256 tile runs faster in a round that
+// Microseconds that a launch of `tiles` output tiles of kt K tiles takes: a first round of one tile per
+// compute unit, and further ones that overlap its ends.  The 256 x 256 tile runs faster in a round that
 // leaves compute units idle (the chip is power-limited).  Symmetric results pay for the transposed
-// copy, the polynomial for its C operand too.  The large tile was traced when nothing of its epilogue
-// overlapped the next tile; full rounds of it now take 4 to 6 % less than this says.
+// copy, the polynomial for its C operand too.  Fitted to kernel traces of earlier forms of all three tiles,
+// whose epilogues were longer: over 194 batches (1 to 200 matrices of 128 to 2048, K to 4096) in each tile
+// that fits, nine in ten launches now take 0.83 to 1.09 of this, the median 0.91 with 64 x 64 tiles and 0.95
+// with the others.
 enum { FORM_GRAM, FORM_POLY, FORM_APPLY };
 double estimate_us(int tile, int form, long tiles, int kt, int cus) {
   const long full = tiles / cus, rest = tiles - full * cus;
@@ -897,14 +897,16 @@ double estimate_us(int tile, int form, long tiles, int kt, int cus) {
 }
 
 // The tile for a launch of these products.  One large tile moves half the operand bytes per FLOP
-// of a 128 x 128 one (1.25 against 0.9 PFLOP/s where both fill the chip), but products with few
-// tiles leave most of the chip idle: one 1024 x 1024 matrix takes 27 us a product in 16 tiles of
-// 256, 12 in 64 of 128, 9 in 256 of 64; 200 of 256 x 256 take 17 / 23 / 20 in tiles of 256 and
-// 16 / 18 / 21 in tiles of 128.  A smaller tile has to be ahead by 5 %, and by 15 % over operands of
+// of a 128 x 128 one (20 of 2048 x 2048: 1.2 to 1.3 against 0.84 to 0.89 PFLOP/s), but products with few
+// tiles leave most of the chip idle: one 1024 x 1024 matrix takes 26 us a product in 16 tiles of
+// 256, 12 in 64 of 128, 8 in 256 of 64; 200 of 256 x 256 take 15 / 18 / 18 in tiles of 256 and
+// 14 / 16 / 17 in tiles of 128.  A smaller tile has to be ahead by 5 %, and by 15 % over operands of
 // more than 64 MB, of which X, its next iterate, A and B' fill the 256 MB memory-side cache: the operand
-// bytes then decide (Gram products of 32 x 1024 x 1024 beside 16 of 1024 x 2816: 62 us in tiles of
-// 256, 68 in tiles of 128; alone 59 and 54).  Over the traced batches this takes 1.004 of the time
-// of the best tile for each.  The 64 x 64 tile's ring needs four K tiles.
+// bytes then decide (Gram products of 32 x 1024 x 1024, alone 56 us in tiles of 256 and 52 in tiles of
+// 128, took 62 and 68 beside 16 of 1024 x 2816, with earlier epilogues).  Over those 194 batches the choice takes
+// 1.006 of the time of the best tile for each; one launch in ten is over 1.03, the worst (apply product of 72 x 256 x
+// 1024) 1.30.  The tile is chosen before it is known whether sets of different depth will share a launch.  The 64 x 64
+// tile's ring needs four K tiles.
 int pick_tile(const GemmDesc* const* d, int n, int cus) {
   long tiles[3] = {0, 0, 0};
   bool divides = true;
@@ -924,7 +926,7 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
   return us < (bytes > 64e6 ? 0.85 : 0.95) * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
 }
 
-// Products of one depth and layout, and the kernel that they run in.
+// Products of one layout, at first of one depth, and the kernel that they run in.
 struct GemmSet { const GemmDesc* d[MAX_MULTI]; int n, tile, ring; };
 
 void choose_kernel(GemmSet& s) {
@@ -965,8 +967,8 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   int n_sets = 0;
   for (int i = 0; i < n; ++i) {
     if (done[i]) continue;
-    // products that can share a launch with product i: same depth (a tile then takes the same
-    // time in each, so dealing tiles out evenly balances the time), same tile, same layout
+    // products that share a launch with product i whatever their tile: same depth (a tile then takes the
+    // same time in each, so dealing tiles out evenly balances the time), same divisors, same layout
     GemmSet& s = sets[n_sets++];
     s.n = 0;
     for (int j = i; j < n && s.n < MAX_MULTI; ++j) {
