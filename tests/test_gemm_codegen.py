@@ -220,10 +220,10 @@ def assembled(lines):
 
 
 @pytest.mark.parametrize("lines", GOOD)
-def test_checker_accepts(lines):
+def test_sound_listings_are_accepted(lines):
     assert not faults(assembled(lines), True)
 
 
 @pytest.mark.parametrize("lines", BAD)
-def test_checker_refuses(lines):
+def test_faulty_listings_are_refused(lines):
     assert faults(assembled(lines), True)

@@ -177,7 +177,7 @@ SIDE_BY_SIDE = [
 
 @pytest.mark.parametrize("shapes,tiles", SIDE_BY_SIDE)
 def test_groups_side_by_side_give_the_bits_of_one_group_after_the_other(shapes, tiles):
-    """With a work space that holds all groups at once, products of equal depth share launches;
+    """With a work space that holds all groups at once, products of several groups share launches;
     with the smaller one each group runs alone.  Both must give the same bits, and one group
     of each call is checked against the oracle."""
     assert ns_tiles(shapes) == tiles
