@@ -296,7 +296,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
                                 hipStream_t stream);
 // Radix-select state of one (worker, matrix) pair of the top-k sparsifier.
 constexpr int TOPK_BINS = 2048;     // widest digit of the radix select: 11 bits
-struct TopkState { unsigned int hist[TOPK_BINS]; unsigned int prefix, mask, rank, pad; };
+struct TopkState { unsigned int hist[TOPK_BINS]; unsigned int lo, width, rank, ctl; };
 size_t topk_workspace_bytes(int64_t count, int K);
 // thresholds: per worker [count] floats (may be null): the k-th largest magnitude found.
 int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype, float* u,

@@ -670,15 +670,271 @@ __global__ __launch_bounds__(OT_THREADS) void dequant_outer_kernel(
 
 // ---- top-k sparsification (Sec. 2 "Compressed Communication") --------------------------
 // Of each matrix of each worker the k entries of largest magnitude are kept (all entries
-// that tie with the k-th one included).  The k-th largest magnitude is found exactly by a
-// radix select over the bit pattern of |v| (ordered like an unsigned for non-negative
-// floats; bit 31 is always clear): three passes with digits of 11, 10 and 10 bits, each a
-// histogram of the entries that match the digits found so far, then the digit in which the
-// k-th entry falls.
+// that tie with the k-th one, tau, included).  Magnitudes are compared as the bit patterns of |v|
+// (ordered like unsigned numbers; bit 31 is always clear).  The state of a (worker, matrix) pair is
+// an interval of 2^width such keys from `lo` on that holds tau's, and tau's rank in it; a pass over
+// the values counts those of the interval in up to 2048 bins, and the workgroup that ends last
+// narrows the interval to the bin that holds tau.  Three passes lead from all 2^31 keys to one.
+//
+// Large matrices start from an interval that a sample of 16384 values suggests, which the pass that
+// computes v counts in bins of its own.  Where the bin that holds tau has at most TOPK_LIST values for every
+// worker, the update of the matrix follows at once: values above the interval are sent, those
+// below are not, and the few inside are listed and left as they are, for topk_settle to select
+// tau among them exactly and to update their elements.  The values are then read twice in all.  What
+// this does not settle (a sample that misled, many equal magnitudes) goes through the three passes.
+// All of this is bound by memory: with error feedback 14 bytes an element in the first pass and 26 in the
+// update (bf16 replicas, fp32 global copy), where three counting passes and the update took 48: six layers of
+// 2048 / 8192, one worker, 5 %: 2873 -> 2520 us, without error feedback 24 matrices of 2048 x 2048 703 -> 528.
+// Matrices whose magnitudes all tie take the same 790 us (24 of 2048 x 2048) as normally distributed ones, 906 before.
+constexpr int TOPK_LIST = (TOPK_BINS - 2) / 2;     // primaries of two words and the two counts fit the histogram
+constexpr int TOPK_WINDOW = TOPK_BINS - 1;         // bins of the first pass; the last word counts what is above
+constexpr unsigned int TOPK_EARLY = 1u << 31;      // in ctl: the pass over the window left few enough values
+constexpr int TOPK_WINDOW_THREADS = 1024;
+constexpr int TOPK_SAMPLE_THREADS = 1024;
+constexpr int TOPK_SAMPLE_PER = 2;                 // runs of 8 values that a thread of the sample reads
+
+__device__ __forceinline__ unsigned int magnitude_key(float v) { return __float_as_uint(fabsf(v)); }
+
 __global__ void topk_init_kernel(TopkState* st, unsigned int kcount) {
   TopkState& s = st[blockIdx.x];
   for (int i = threadIdx.x; i < TOPK_BINS; i += blockDim.x) s.hist[i] = 0u;
-  if (threadIdx.x == 0) { s.prefix = 0u; s.mask = 0u; s.rank = kcount; s.pad = 0u; }
+  if (threadIdx.x == 0) { s.lo = 0u; s.width = 31u; s.rank = kcount; s.ctl = 0u; }
+}
+
+// The 8 values v of worker k from element i on (`left` of them before the end of the matrix).
+template <typename WT, typename GT, bool VEC>
+__device__ __forceinline__ void topk_values(const GT* tg, const WT* tk, const float* res, long i, int left,
+                                            float ef_beta, float (&vals)[8]) {
+  float a[8], c[8];
+  load8<GT, !VEC>(tg + i, left, a); load8<WT, !VEC>(tk + i, left, c);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) vals[j] = a[j] - c[j];
+  if (res) {
+    float e[8];
+    load8<float, !VEC>(res + i, left, e);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) vals[j] = ef_input(vals[j], e[j], ef_beta);
+  }
+}
+
+// Bin of a sampled key: 32 to an octave over the 64 octaves below 2^5; what is smaller or larger
+// falls into the first or the last bin.
+constexpr unsigned int TOPK_SAMPLE_BASE = (127u - 59u) << 23;
+__device__ __forceinline__ unsigned int sample_bin(unsigned int key) {
+  return key < TOPK_SAMPLE_BASE ? 0u : min((key - TOPK_SAMPLE_BASE) >> 18, (unsigned int)TOPK_BINS - 1u);
+}
+
+// First interval of each state, one workgroup each, from a histogram of 2048 runs of 8 values, one from each
+// of 2048 equal stretches of the matrix at a place that a hash picks (a fixed stride would meet the same
+// columns again and again): the keys from five standard deviations of a sample's rank below
+// the rank sought to as many above, at the resolution of the bins.  Where so many magnitudes tie that they fill all of
+// that (replicas that did not move), the interval is one key and the pass over the window settles it.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(TOPK_SAMPLE_THREADS) void topk_sample_kernel(
+    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count,
+    unsigned int kcount, float ef_beta) {
+  constexpr int WAVES = TOPK_SAMPLE_THREADS / 64, RUNS = TOPK_SAMPLE_THREADS * TOPK_SAMPLE_PER;
+  static_assert(TOPK_BINS == 2 * TOPK_SAMPLE_THREADS, "a thread owns two bins");
+  __shared__ unsigned int hist[TOPK_BINS];
+  __shared__ unsigned int part[WAVES], first, last, least, most;
+  const long b = blockIdx.x;
+  const int k = blockIdx.y, t = threadIdx.x;
+  TopkState& s = st[(long)k * count + b];
+  const GT* tg = theta_g + b * elems;
+  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
+  const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
+  const unsigned int stretch = (unsigned int)(elems / 8 / RUNS);           // >= 1, below 2^18
+  hist[t] = 0u; hist[t + TOPK_SAMPLE_THREADS] = 0u;
+  s.hist[t] = 0u; s.hist[t + TOPK_SAMPLE_THREADS] = 0u;
+  if (t == 0) { first = 0u; last = TOPK_BINS - 1; least = ~0u; most = 0u; }
+  float v[TOPK_SAMPLE_PER][8];
+#pragma unroll
+  for (int c = 0; c < TOPK_SAMPLE_PER; ++c) {
+    const unsigned int r = (unsigned int)(c * TOPK_SAMPLE_THREADS + t);
+    unsigned int h = r * 2654435761u;
+    h = (h ^ (h >> 15)) * 2246822519u;
+    const long at = (long)r * stretch + __umulhi(h, stretch);
+    topk_values<WT, GT, VEC>(tg, tk, res, at * 8, 8, ef_beta, v[c]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < TOPK_SAMPLE_PER; ++c)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) atomicAdd(&hist[sample_bin(magnitude_key(v[c][j]))], 1u);
+  __syncthreads();
+  const unsigned int h0 = hist[2 * t], h1 = hist[2 * t + 1];
+  unsigned int from = h0 + h1;                   // entries of this lane and the lanes above it
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned int add = __shfl_down(from, off, 64);
+    if ((t & 63) + off < 64) from += add;
+  }
+  if ((t & 63) == 0) part[t >> 6] = from;
+  __syncthreads();
+  for (int wv = (t >> 6) + 1; wv < WAVES; ++wv) from += part[wv];
+  const float share = (float)kcount / (float)elems;
+  const float mean = share * (RUNS * 8);
+  const float margin = 5.f * sqrtf(mean * (1.f - share)) + 12.f;
+  const unsigned int few = (unsigned int)fmaxf(mean - margin, 0.f), many = (unsigned int)(mean + margin);
+  // the lowest bin that `many` entries reach, and the highest that more than `few` do
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const unsigned int upto = i ? h1 + from - h0 - h1 : from, beyond = i ? from - h0 - h1 : from - h0;
+    if (beyond < many && upto >= many) first = (unsigned int)(2 * t + i);
+    if (beyond <= few && upto > few) last = (unsigned int)(2 * t + i);
+  }
+  __syncthreads();
+  // the lowest key sampled in the first of these bins and the highest in the last: one key, where many tie
+  const unsigned int low = first, high = last;
+  unsigned int min_key = ~0u, max_key = 0u;
+#pragma unroll
+  for (int c = 0; c < TOPK_SAMPLE_PER; ++c)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const unsigned int key = magnitude_key(v[c][j]), at = sample_bin(key);
+      if (at == low) min_key = min(min_key, key);
+      if (at == high) max_key = max(max_key, key);
+    }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    min_key = min(min_key, (unsigned int)__shfl_xor((int)min_key, off, 64));
+    max_key = max(max_key, (unsigned int)__shfl_xor((int)max_key, off, 64));
+  }
+  if ((t & 63) == 0) { atomicMin(&least, min_key); atomicMax(&most, max_key); }
+  __syncthreads();
+  if (t == 0) {
+    // a rank outside the sample: from 0 on, or to four times the largest
+    const unsigned int lo = many > RUNS * 8 ? 0u : least;
+    const unsigned int keys = most + (few ? 1u : 1u << 24) - lo;
+    unsigned int shift = 0u;
+    while (shift < 20u && (keys + (1u << shift) - 1u) >> shift > (unsigned int)TOPK_WINDOW) ++shift;
+    s.lo = lo; s.width = shift; s.rank = kcount; s.ctl = 0u;
+  }
+}
+
+// True in every thread of the workgroup of `n` (gridDim.x) that comes last to this state.  What the
+// workgroups hand over are atomic sums at device scope: each thread's have been performed when its wait returns,
+// so they precede the workgroup's ticket.  (A release fence would also write back
+// the L2 cache, which holds the values that the pass has just stored.)
+__device__ __forceinline__ bool last_of_state(TopkState& s, unsigned int& early) {
+  __shared__ unsigned int ticket;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) ticket = __hip_atomic_fetch_add(&s.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  early = ticket & TOPK_EARLY;
+  return (ticket & 0xffffu) == gridDim.x - 1;
+}
+
+// The last workgroup narrows the interval: bins of 2^shift keys from s.lo on have been counted; the one that
+// holds the rank-th largest entry is the new interval.  Thread t owns 8 adjacent bins.  WINDOW: the
+// last word holds the number of entries above all bins; where tau is not in any bin, the interval
+// becomes all keys.
+template <bool WINDOW>
+__device__ __forceinline__ void topk_narrow(TopkState& s, int shift, unsigned int early) {
+  __shared__ unsigned int part[OT_THREADS / 64];  // entries in the bins of a wavefront
+  constexpr int PER = TOPK_BINS / OT_THREADS;
+  const int t = threadIdx.x;
+  const bool owns = t < OT_THREADS;
+  unsigned int h[PER] = {};
+  unsigned int mine = 0u, beyond = 0u;
+  if (owns) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      h[i] = __hip_atomic_load(&s.hist[t * PER + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (WINDOW && i == PER - 1 && t == OT_THREADS - 1) h[i] = 0u;
+      mine += h[i];
+    }
+  }
+  if (WINDOW) beyond = __hip_atomic_load(&s.hist[TOPK_WINDOW], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned int rank = s.rank, lo = s.lo;
+  unsigned int upto = mine;                                   // entries in the bins of this lane and those above it
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned int add = __shfl_down(upto, off, 64);
+    if ((t & 63) + off < 64) upto += add;
+  }
+  if (owns && (t & 63) == 0) part[t >> 6] = upto;
+  __syncthreads();                                            // and everyone has read the state
+  unsigned int total = 0u, above = beyond + upto - mine;      // entries above the bins of thread t
+#pragma unroll
+  for (int wv = 0; wv < OT_THREADS / 64; ++wv) {
+    total += part[wv];
+    if (wv > t >> 6) above += part[wv];
+  }
+  if (!owns) return;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) s.hist[t * PER + i] = 0u;     // for the next pass, or the counts of the list
+  if (WINDOW && (beyond >= rank || beyond + total < rank)) {
+    if (t == 0) { s.lo = 0u; s.width = 31u; s.ctl = 0u; }
+  } else if (above < rank && above + mine >= rank) {
+    unsigned int ab = above, held = h[0];
+    int pick = 0;
+    bool found = false;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      if (!found) {
+        if (ab + h[i] >= rank) { pick = i; held = h[i]; found = true; }
+        else ab += h[i];
+      }
+    }
+    s.lo = lo + ((unsigned int)(t * PER + pick) << shift);
+    s.width = (unsigned int)shift;
+    s.rank = rank - ab;
+    s.ctl = !WINDOW ? early : held <= (unsigned int)TOPK_LIST || shift == 0 ? TOPK_EARLY : 0u;
+  }
+}
+
+// The pass that computes v = beta E + (theta_g - theta_k) of every matrix and counts it in the window.
+// With error feedback it leaves v in E, where it ends up anyway unless it is sent: the update then reads
+// 4 bytes an element instead of 6 and needs no worker parameters.  A few per cent of the values fall
+// into the window, so one histogram a workgroup takes them; 16 wavefronts share it, since its
+// bins leave as one atomic each at the end (4 wavefronts: 0 to 3 % slower).  14 bytes an element at 4.8 TB/s.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(TOPK_WINDOW_THREADS) void topk_window_kernel(
+    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, float ef_beta) {
+  __shared__ unsigned int lh[TOPK_BINS];
+  const long b = blockIdx.y;
+  const int k = blockIdx.z;
+  TopkState& s = st[(long)k * count + b];
+  const unsigned int lo = s.lo, shift = s.width;
+  for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_WINDOW_THREADS) lh[i] = 0u;
+  __syncthreads();
+  const GT* tg = theta_g + b * elems;
+  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
+  float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
+  unsigned int above = 0u;
+  for (long i = ((long)blockIdx.x * TOPK_WINDOW_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)gridDim.x * TOPK_WINDOW_THREADS * 8) {
+    float vals[8];
+    const int left = (int)min(elems - i, 8L);
+    topk_values<WT, GT, VEC>(tg, tk, res, i, left, ef_beta, vals);
+    if (res) store8<float, !VEC>(res + i, vals, left);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (!VEC && j >= left) break;
+      const unsigned int key = magnitude_key(vals[j]);
+      const unsigned int at = (key - lo) >> shift;        // a key below lo wraps round to 2^31 and more
+      const bool in = at < (unsigned int)TOPK_WINDOW;
+      above += !in && key >= lo ? 1u : 0u;
+      const unsigned long lanes = __ballot(in);
+      if (__popcll(lanes) < 16) {
+        if (in) atomicAdd(&lh[at], 1u);
+      } else {                                            // many equal magnitudes: those of one bin at once
+        const int head = __builtin_ctzl(lanes);
+        const unsigned int bin = (unsigned int)__builtin_amdgcn_readlane((int)at, head);
+        const unsigned long same = __ballot(in && at == bin);
+        if ((int)(threadIdx.x & 63) == head) atomicAdd(&lh[bin], (unsigned int)__popcll(same));
+        if (in && at != bin) atomicAdd(&lh[at], 1u);
+      }
+    }
+  }
+  if (above) atomicAdd(&lh[TOPK_WINDOW], above);
+  __syncthreads();
+  for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_WINDOW_THREADS)
+    if (lh[i]) __hip_atomic_fetch_add(&s.hist[i], lh[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  unsigned int early;
+  if (last_of_state(s, early)) topk_narrow<true>(s, (int)shift, early);
 }
 
 // The first digits (bits from `shift` up) of a lane's first cnt of 8 values.  They mostly change
@@ -692,7 +948,7 @@ __device__ __forceinline__ void count_first_digit(unsigned int* hist, const floa
                                                   unsigned int& zeros) {
   unsigned int key[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) key[j] = __float_as_uint(fabsf(vals[j]));
+  for (int j = 0; j < 8; ++j) key[j] = magnitude_key(vals[j]);
   const unsigned int mine = key[0] >> shift;
   const unsigned int d0 = (unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
   if (__popcll(__ballot(mine == d0)) < 16) {
@@ -722,20 +978,30 @@ __device__ __forceinline__ void count_first_digit(unsigned int* hist, const floa
   }
 }
 
-// FIRST: the pass that computes v = beta E + (theta_g - theta_k).  With error feedback it leaves v
-// in E, where it ends up anyway unless it is sent: the later passes then read 4 bytes an element
-// instead of 10, and the update needs no worker parameters (six layers of 2048 / 8192, K = 1:
-// 3300 -> 2880 us).
+// Did the pass over the window leave few enough values of this matrix for every worker?  (The bit is not touched by
+// later passes.)
+__device__ __forceinline__ bool topk_early(const TopkState* st, long b, int count, int K) {
+  bool early = true;
+  for (int k = 0; k < K; ++k)
+    early = early && (__hip_atomic_load(&st[(long)k * count + b].ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+                      TOPK_EARLY) != 0u;
+  return early;
+}
+
+// One pass of the radix select over the matrices that the window did not settle.  FIRST: the pass over all keys that
+// computes v, where no window was tried (with error feedback it leaves v in E).
 template <typename WT, typename GT, bool VEC, bool FIRST>
 __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
     WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count,
-    int shift, int nbins, float ef_beta) {
+    float ef_beta, int window) {
   __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];     // one histogram per wavefront
   const long b = blockIdx.y;
   const int k = blockIdx.z;
   TopkState& s = st[(long)k * count + b];
-  const unsigned int prefix = s.prefix, mask = s.mask;
-  const unsigned int digit_mask = (unsigned int)nbins - 1u;
+  if (!FIRST && window && (s.width == 0u || topk_early(st, b, count, (int)gridDim.z))) return;
+  const unsigned int lo = FIRST ? 0u : s.lo, width = FIRST ? 31u : s.width;
+  const int shift = width > 20u ? 20 : width > 10u ? 10 : 0;   // digits of 11, 10 and 10 bits
+  const int nbins = 1 << (width - shift);
   for (int wv = 0; wv < OT_THREADS / 64; ++wv)
     for (int i = threadIdx.x; i < nbins; i += OT_THREADS) lh[wv][i] = 0u;
   __syncthreads();
@@ -751,17 +1017,8 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
     if (!FIRST && res) {
       load8<float, !VEC>(res + i, left, vals);
     } else {
-      float a[8], c[8];
-      load8<GT, !VEC>(tg + i, left, a); load8<WT, !VEC>(tk + i, left, c);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) vals[j] = a[j] - c[j];
-      if (res) {
-        float e[8];
-        load8<float, !VEC>(res + i, left, e);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) vals[j] = ef_input(vals[j], e[j], ef_beta);
-        store8<float, !VEC>(res + i, vals, left);
-      }
+      topk_values<WT, GT, VEC>(tg, tk, res, i, left, ef_beta, vals);
+      if (res) store8<float, !VEC>(res + i, vals, left);
     }
     if constexpr (FIRST) {
       count_first_digit(mine, vals, VEC ? 8 : left, shift, run);
@@ -770,9 +1027,9 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (!VEC && j >= left) break;
-      const unsigned int key = __float_as_uint(fabsf(vals[j]));
-      if ((key & mask) == prefix) {
-        const unsigned int bin = (key >> shift) & digit_mask;
+      const unsigned int at = magnitude_key(vals[j]) - lo;
+      if (at >> width == 0u) {
+        const unsigned int bin = at >> shift;
         if (bin == cur) {
           ++run;
         } else {
@@ -788,73 +1045,42 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
     unsigned int tot = 0u;
 #pragma unroll
     for (int wv = 0; wv < OT_THREADS / 64; ++wv) tot += lh[wv][i];
-    if (tot) atomicAdd(&s.hist[i], tot);
+    if (tot) __hip_atomic_fetch_add(&s.hist[i], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  unsigned int early;
+  if (last_of_state(s, early)) topk_narrow<false>(s, shift, early);
+}
+
+// Element `at` of a matrix waits for the exact threshold of this state's worker: as a primary entry with the sum
+// over the workers before it, or, where an earlier worker's list has it, as one that only counts.  A settled
+// state's interval holds at most TOPK_LIST values; the bounds are for residuals that share memory.
+__device__ __forceinline__ void topk_wait(TopkState& s, unsigned int at, bool primary, float sum) {
+  if (primary) {
+    const unsigned int n = atomicAdd(&s.hist[TOPK_BINS - 2], 1u);
+    if (n >= (unsigned int)TOPK_LIST) return;
+    s.hist[2 * n] = at;
+    s.hist[2 * n + 1] = __float_as_uint(sum);
+  } else {
+    const unsigned int n = atomicAdd(&s.hist[TOPK_BINS - 1], 1u);
+    if (n < (unsigned int)TOPK_LIST) s.hist[TOPK_BINS - 3 - n] = at;
   }
 }
 
-// The digit that holds the k-th largest entry: the highest bin b for which the bins b and
-// above hold at least `rank` entries (bin 0 if none does).  Thread t owns the PER = nbins / 256
-// adjacent bins [PER t, PER (t + 1)); a suffix scan over the per-thread sums finds the owner.
-__global__ __launch_bounds__(256) void topk_pick_kernel(TopkState* st, int shift, int nbins) {
-  TopkState& s = st[blockIdx.x];
-  __shared__ unsigned int suffix[256];       // entries in the bins of threads t .. 255
-  const int t = threadIdx.x;
-  const int per = nbins / 256;               // 8 or 4
-  constexpr int MAX_PER = TOPK_BINS / 256;
-  unsigned int h[MAX_PER];
-  unsigned int mine = 0u;
-#pragma unroll
-  for (int i = 0; i < MAX_PER; ++i) {
-    h[i] = i < per ? s.hist[t * per + i] : 0u;
-    mine += h[i];
-  }
-  suffix[t] = mine;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const unsigned int add = t + off < 256 ? suffix[t + off] : 0u;
-    __syncthreads();
-    suffix[t] += add;
-    __syncthreads();
-  }
-  const unsigned int rank = s.rank;
-  const unsigned int above = suffix[t] - mine;          // entries in the bins of threads t+1 .. 255
-  const unsigned int total = suffix[0];
-  __syncthreads();                                       // everyone has read the old rank
-#pragma unroll
-  for (int i = 0; i < MAX_PER; ++i)
-    if (i < per) s.hist[t * per + i] = 0u;               // ready for the next pass
-  const bool owner = (above < rank && above + mine >= rank) || (t == 0 && total < rank);
-  if (owner) {
-    // from the thread's top bin down (bins at and beyond `per` are empty); with
-    // total < rank (more entries asked for than matched) this ends in bin 0 of thread 0
-    unsigned int ab = above;
-    int pick = 0;
-    bool found = false;
-#pragma unroll
-    for (int i = MAX_PER - 1; i > 0; --i) {
-      if (!found) {
-        if (ab + h[i] >= rank) { pick = i; found = true; }
-        else ab += h[i];
-      }
-    }
-    const unsigned int bin = (unsigned int)(t * per + pick);
-    s.prefix |= bin << shift;
-    s.mask |= ((unsigned int)nbins - 1u) << shift;
-    s.rank = rank - ab;
-  }
-}
-
-template <typename WT, typename GT, bool VEC>
-__global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
-    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
-    const TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov,
-    int write_back) {
-  __shared__ unsigned int tau[MLC_MAX_WORKERS];
+// The update, of the matrices that the pass over the window settled for all workers (EARLY; values inside a worker's
+// interval make their element wait), or of the others, whose intervals are single keys by now.
+template <typename WT, typename GT, bool VEC, bool EARLY>
+__device__ __forceinline__ void topk_update(
+    const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef,
+    const ScalePtrs& thresholds, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k,
+    int nesterov, int write_back) {
+  __shared__ unsigned int from[MLC_MAX_WORKERS], held[MLC_MAX_WORKERS];
   const long b = blockIdx.y;
   if (threadIdx.x < K) {
-    tau[threadIdx.x] = st[(long)threadIdx.x * count + b].prefix;
-    if (blockIdx.x == 0 && thresholds.p[threadIdx.x])
-      thresholds.p[threadIdx.x][b] = __uint_as_float(tau[threadIdx.x]);
+    const TopkState& s = st[(long)threadIdx.x * count + b];
+    from[threadIdx.x] = s.lo;
+    held[threadIdx.x] = EARLY && s.width ? 1u << s.width : 0u;          // one key: nothing has to wait
+    if (!EARLY && blockIdx.x == 0 && thresholds.p[threadIdx.x])
+      thresholds.p[threadIdx.x][b] = __uint_as_float(s.lo);
   }
   __syncthreads();
   GT* tg = theta_g + b * elems;
@@ -866,6 +1092,7 @@ __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
     load8<GT, !VEC>(tg + i, left, a); load8<float, !VEC>(ub + i, left, uv);
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    unsigned int wait = 0u;                // elements of which some worker's value is inside its interval
     for (int k = 0; k < K; ++k) {
       float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
       float v[8];
@@ -876,9 +1103,23 @@ __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = a[j] - v[j];
       }
+      const unsigned int lo = from[k], range = held[k];
+      if constexpr (EARLY) {
+        unsigned int inside = 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if ((VEC || j < left) && magnitude_key(v[j]) - lo < range) inside |= 1u << j;
+        if (inside) {
+          TopkState& s = st[(long)k * count + b];
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (inside >> j & 1u) topk_wait(s, (unsigned int)(i + j), !(wait >> j & 1u), acc[j]);
+          wait |= inside;
+        }
+      }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const bool keep = __float_as_uint(fabsf(v[j])) >= tau[k];
+        const bool keep = magnitude_key(v[j]) >= lo + range && !(wait >> j & 1u);
         acc[j] += keep ? v[j] : 0.f;
         v[j] = keep ? 0.f : v[j];           // what was not sent
       }
@@ -886,11 +1127,116 @@ __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) outer_update<GT>(a[j], uv[j], __fmul_rn(acc[j], inv_k), eta, mu, nesterov);
-    store8<GT, !VEC>(tg + i, a, left);
-    store8<float, !VEC>(ub + i, uv, left);
-    if (write_back)
-      for (int k = 0; k < K; ++k) store8<WT, !VEC>(reinterpret_cast<WT*>(w.p[k]) + b * elems + i, a, left);
+    if (wait == 0u) {
+      store8<GT, !VEC>(tg + i, a, left);
+      store8<float, !VEC>(ub + i, uv, left);
+      if (write_back)
+        for (int k = 0; k < K; ++k) store8<WT, !VEC>(reinterpret_cast<WT*>(w.p[k]) + b * elems + i, a, left);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if (j >= left || (wait >> j & 1u)) continue;
+        Vec8<GT>::store1(tg + i + j, a[j]);
+        ub[i + j] = uv[j];
+        if (write_back)
+          for (int k = 0; k < K; ++k) Vec8<WT>::store1(reinterpret_cast<WT*>(w.p[k]) + b * elems + i + j, a[j]);
+      }
+    }
   }
+}
+
+// The thresholds of a matrix that topk_update<EARLY> went over, by one workgroup: a wavefront takes a worker's list and finds the
+// rank-th largest of its keys, built bit by bit from counts that ballots give; then the elements that waited, from
+// the first worker that made them wait on.  Bound by the latency of a few dependent loads.
+template <typename WT, typename GT>
+__device__ __forceinline__ void topk_settle(
+    const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef,
+    const ScalePtrs& thresholds, const TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k,
+    int nesterov, int write_back) {
+  __shared__ unsigned int tau[MLC_MAX_WORKERS], primaries[MLC_MAX_WORKERS];
+  const long b = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  GT* tg = theta_g + b * elems;
+  float* ub = u + b * elems;
+  auto value = [&](int k, long at) {
+    at = min(at, elems - 1);
+    return ef.p[k] ? ef.p[k][b * elems + at]
+                   : Vec8<GT>::load1(tg + at) - Vec8<WT>::load1(reinterpret_cast<const WT*>(w.p[k]) + b * elems + at);
+  };
+  for (int k = wave; k < K; k += OT_THREADS / 64) {
+    const TopkState& s = st[(long)k * count + b];
+    const unsigned int lo = s.lo, rank = s.rank;
+    const int width = (int)s.width;
+    const int first = width ? (int)min(s.hist[TOPK_BINS - 2], (unsigned int)TOPK_LIST) : 0;
+    const int n = width ? (int)min(first + s.hist[TOPK_BINS - 1], (unsigned int)TOPK_LIST) : 0;
+    constexpr int PER = (TOPK_LIST + 63) / 64;
+    unsigned int at[PER];                 // distance from lo, plus one: 0 is no entry
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = i * 64 + lane;
+      at[i] = e < n ? magnitude_key(value(k, s.hist[e < first ? 2 * e : TOPK_BINS - 3 - (e - first)])) - lo + 1u : 0u;
+    }
+    unsigned int best = 0u;
+    for (int bit = width - 1; bit >= 0; --bit) {
+      const unsigned int next = best | 1u << bit;
+      unsigned int reach = 0u;
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (i * 64 < n) reach += (unsigned int)__popcll(__ballot(at[i] > next));
+      if (reach >= rank) best = next;
+    }
+    if (lane == 0) {
+      tau[k] = lo + best;
+      primaries[k] = (unsigned int)first;
+      if (thresholds.p[k]) thresholds.p[k][b] = __uint_as_float(lo + best);
+    }
+  }
+  __syncthreads();
+  int k0 = 0;
+  unsigned int before = 0u;                 // primary entries of the workers before k0
+  for (unsigned int e = threadIdx.x;; e += OT_THREADS) {
+    while (k0 < K && e - before >= primaries[k0]) before += primaries[k0++];
+    if (k0 == K) break;
+    const TopkState& s = st[(long)k0 * count + b];
+    const long at = s.hist[2 * (e - before)];
+    if (at >= elems) continue;
+    float acc = __uint_as_float(s.hist[2 * (e - before) + 1]);
+    for (int k = k0; k < K; ++k) {
+      const float v = value(k, at);
+      const bool keep = magnitude_key(v) >= tau[k];
+      acc += keep ? v : 0.f;
+      if (ef.p[k] && keep) ef.p[k][b * elems + at] = 0.f;
+    }
+    float a = Vec8<GT>::load1(tg + at), uv = ub[at];
+    outer_update<GT>(a, uv, __fmul_rn(acc, inv_k), eta, mu, nesterov);
+    Vec8<GT>::store1(tg + at, a);
+    ub[at] = uv;
+    if (write_back)
+      for (int k = 0; k < K; ++k) Vec8<WT>::store1(reinterpret_cast<WT*>(w.p[k]) + b * elems + at, a);
+  }
+}
+
+// The update behind the pass over the window.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(OT_THREADS) void topk_early_kernel(
+    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
+    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+  if (topk_early(st, blockIdx.y, count, K))
+    topk_update<WT, GT, VEC, true>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+                                   write_back);
+}
+
+// The update of the matrices that went through the three passes, and what is left of the others.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
+    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
+    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
+    int window) {
+  if (!window || !topk_early(st, blockIdx.y, count, K))
+    topk_update<WT, GT, VEC, false>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+                                    write_back);
+  else if (blockIdx.x == 0)
+    topk_settle<WT, GT>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov, write_back);
 }
 
 int check_launch() { return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH; }
@@ -1221,6 +1567,14 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
 
 size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * sizeof(TopkState); }
 
+// Do these states start from a sample?  The two passes over the values that it saves have to make up for
+// the sample, the listed values and the launches that find nothing left to do, some 45 us a group: groups of
+// 2.4 M values (768 x 3072, one worker) are as fast either way.  A sample
+// takes 16384 values, which a matrix has to have several times over.
+static bool topk_window(long elems, int n_states) {
+  return elems >= 65536 && (double)elems * n_states >= (double)(1 << 22);
+}
+
 int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype, float* u,
                       const ResidualPtrs& ef, const ScalePtrs& thresholds, int64_t count, int64_t m,
                       int64_t n, int K, unsigned int kcount, float ef_beta, float eta_out, float mu,
@@ -1229,48 +1583,69 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
   TopkState* st = (TopkState*)workspace;
   const long elems = m * n;
   const bool vec = elems % 8 == 0;
-  const int nblk = cap_blocks(((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, 256);
+  const long full = ((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS;      // a workgroup meets each element once
+  const int full_grid = cap_blocks(full, 256);
+  const int window_grid = cap_blocks((full * OT_THREADS + TOPK_WINDOW_THREADS - 1) / TOPK_WINDOW_THREADS, 256);
   const int n_states = (int)(count * K);
   const bool fb = has_residuals(ef);
   const double inputs = K * (esize(worker_dtype) + esize(global_dtype));
-  // three passes over the values (with error feedback: the inputs once, then the residuals), the update
-  const double passes = fb ? inputs + 8.0 * K + 2 * 4.0 * K : 3 * inputs;
+  const bool window = topk_window(elems, n_states);
+  // the values once (or, small matrices, three times: with error feedback the inputs, then the residuals), the update
+  const double passes = window ? inputs + (fb ? 8.0 * K : 0.0) : fb ? inputs + 8.0 * K + 2 * 4.0 * K : 3 * inputs;
   const double last = (fb ? 8.0 * K : K * esize(worker_dtype)) + (write_back ? K * esize(worker_dtype) : 0.0) +
                       2 * esize(global_dtype) + 8;
   LaunchScope scope(MLC_KERNEL_TOPK, stream, 0.0, (double)count * elems * (passes + last));
-  hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
-  // digits of 11, 10 and 10 bits cover bits 30 .. 0 of |v|
-  const int shifts[3] = {20, 10, 0}, bins[3] = {2048, 1024, 1024};
-  for (int pass = 0; pass < 3; ++pass) {
-    const int shift = shifts[pass], nbins = bins[pass];
-#define MLC_HIST(WT, GT, V, F)                                                                    \
-  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(nblk, (unsigned)count, K),             \
-                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, \
-                     shift, nbins, ef_beta)
+  const float inv_k = 1.0f / (float)K;
+#define MLC_UPDATE(KERNEL, WT, GT, V, NBLK, ...)                                                    \
+  hipLaunchKernelGGL((KERNEL<WT, GT, V>), dim3(NBLK, (unsigned)count), dim3(OT_THREADS), 0, stream, w, \
+                     (GT*)theta_g, u, ef, thresholds, st, elems, (int)count, K, eta_out, mu, inv_k,  \
+                     nesterov, write_back, ##__VA_ARGS__)
+  if (window) {
+#define MLC_SAMPLE(WT, GT, V)                                                                     \
+  hipLaunchKernelGGL((topk_sample_kernel<WT, GT, V>), dim3((unsigned)count, K), dim3(TOPK_SAMPLE_THREADS), 0, \
+                     stream, w, (const GT*)theta_g, ef, st, elems, (int)count, kcount, ef_beta)
+#define MLC_WINDOW(WT, GT, V)                                                                     \
+  hipLaunchKernelGGL((topk_window_kernel<WT, GT, V>), dim3(window_grid, (unsigned)count, K),                  \
+                     dim3(TOPK_WINDOW_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta)
+#define MLC_CALL(WT, GT) do { if (vec) MLC_SAMPLE(WT, GT, true); else MLC_SAMPLE(WT, GT, false); } while (0)
+    MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
+#undef MLC_CALL
 #define MLC_CALL(WT, GT)                                                                          \
   do {                                                                                            \
-    if (vec) { if (pass == 0) MLC_HIST(WT, GT, true, true); else MLC_HIST(WT, GT, true, false); } \
-    else { if (pass == 0) MLC_HIST(WT, GT, false, true); else MLC_HIST(WT, GT, false, false); }   \
+    if (vec) { MLC_WINDOW(WT, GT, true); MLC_UPDATE(topk_early_kernel, WT, GT, true, full_grid); }              \
+    else { MLC_WINDOW(WT, GT, false); MLC_UPDATE(topk_early_kernel, WT, GT, false, full_grid); }                \
+  } while (0)
+    MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
+#undef MLC_CALL
+#undef MLC_WINDOW
+#undef MLC_SAMPLE
+  } else {
+    hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
+  }
+  // Behind a window these passes mostly find nothing to do: no more workgroups than fill the chip.
+  const int late_grid = window ? cap_blocks(full, (1024 + n_states - 1) / n_states) : full_grid;
+  for (int pass = 0; pass < 3; ++pass) {
+#define MLC_HIST(WT, GT, V, F)                                                                    \
+  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(late_grid, (unsigned)count, K),             \
+                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta, (int)window)
+#define MLC_CALL(WT, GT)                                                                          \
+  do {                                                                                            \
+    const bool first = pass == 0 && !window;                                                      \
+    if (vec) { if (first) MLC_HIST(WT, GT, true, true); else MLC_HIST(WT, GT, true, false); }     \
+    else { if (first) MLC_HIST(WT, GT, false, true); else MLC_HIST(WT, GT, false, false); }       \
   } while (0)
     MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
 #undef MLC_HIST
-    hipLaunchKernelGGL(topk_pick_kernel, dim3(n_states), dim3(256), 0, stream, st, shift, nbins);
   }
-  const float inv_k = 1.0f / (float)K;
 #define MLC_CALL(WT, GT)                                                                          \
   do {                                                                                            \
-    if (vec)                                                                                      \
-      hipLaunchKernelGGL((topk_outer_kernel<WT, GT, true>), dim3(nblk, (unsigned)count),           \
-                         dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, ef, thresholds, st, elems, \
-                         (int)count, K, eta_out, mu, inv_k, nesterov, write_back);       \
-    else                                                                                          \
-      hipLaunchKernelGGL((topk_outer_kernel<WT, GT, false>), dim3(nblk, (unsigned)count),          \
-                         dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, ef, thresholds, st, elems, \
-                         (int)count, K, eta_out, mu, inv_k, nesterov, write_back);       \
+    if (vec) MLC_UPDATE(topk_outer_kernel, WT, GT, true, late_grid, (int)window);                              \
+    else MLC_UPDATE(topk_outer_kernel, WT, GT, false, late_grid, (int)window);                                 \
   } while (0)
   MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
+#undef MLC_UPDATE
   return check_launch();
 }
 

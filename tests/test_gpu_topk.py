@@ -120,3 +120,56 @@ def test_topk_few_distinct_magnitudes(cnt, m, n, ef, steps):
     if ef:
         assert np.array_equal(res.cpu().numpy().reshape(-1, n).view(np.uint32), ref["residuals"][0].view(np.uint32))
     assert_fp32_close(u.cpu().reshape(-1, n), ref["u"], "outer momentum")
+
+
+# The smallest groups that start from a sample (4 M values, matrices of 65536), one value below either, off
+# the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
+# kept into one row, `grid` takes a few distinct magnitudes, `one` a single one.
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,kind", [
+    (1, 2048, 2048, 1, torch.bfloat16, torch.float32, 0.05, True, "normal"),
+    (32, 256, 256, 2, torch.bfloat16, torch.float32, 0.005, True, "normal"),
+    (70, 255, 257, 1, torch.float32, torch.float32, 0.1, False, "normal"),
+    (5, 1001, 901, 1, torch.bfloat16, torch.float32, 0.2, True, "normal"),
+    (1, 723, 727, 8, torch.bfloat16, torch.bfloat16, 0.02, False, "normal"),
+    (1, 1449, 1451, 2, torch.float32, torch.bfloat16, 1.0, True, "normal"),
+    (1, 1449, 1451, 2, torch.bfloat16, torch.float32, 1e-9, True, "normal"),
+    (4, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.0009, True, "rare"),
+    (2, 1024, 1024, 2, torch.bfloat16, torch.float32, 0.05, True, "grid"),
+    (2, 1024, 1024, 2, torch.bfloat16, torch.float32, 0.05, False, "one"),
+])
+def test_topk_from_a_sample(cnt, m, n, K, wd, gd, frac, ef, kind):
+    gen = torch.Generator().manual_seed(m + n + K)
+    deltas = [S.DELTA_STD * torch.randn(cnt, m, n, generator=gen) for _ in range(K)]
+    tg0 = torch.zeros(cnt, m, n, dtype=gd)
+    for d in deltas:
+        if kind == "rare":
+            d[:, 700] *= 1e3
+        if kind in ("grid", "one"):
+            d.copy_(d.sign() * torch.exp2(torch.randint(-9, -7 if kind == "grid" else -8, d.shape, generator=gen)))
+    if kind == "normal":
+        tg0 = (S.PARAM_STD * torch.randn(cnt, m, n, generator=gen)).to(gd)
+    ws0 = [(tg0.float() - d).to(wd) for d in deltas]
+    u0 = 1e-3 * torch.randn(cnt, m, n, generator=gen)
+    scale = 0.0 if kind in ("grid", "one") else 2e-3
+    res0 = [scale * torch.randn(cnt, m, n, generator=gen) for _ in range(K)] if ef else None
+    tg, u, ws = tg0.to(DEV), u0.to(DEV), [w.to(DEV) for w in ws0]
+    res = [r.to(DEV) for r in res0] if ef else None
+    taus = [torch.full((cnt,), -1.0, device=DEV) for _ in range(K)]
+    grp = mlc.OuterGroup(ws, tg, u, None, taus, res)
+    hp = mlc.OuterHParams(K=K, eta_out=0.9, mu=0.8, error_feedback=ef, ef_beta=0.9)
+    wsp = torch.full((mlc.muloco_topk_workspace_bytes([grp], K),), 0xCD, dtype=torch.uint8, device=DEV)
+    mlc.muloco_topk_outer_step([grp], hp, frac, wsp)
+    torch.cuda.synchronize()
+    ref = diloco.outer_step(to_f64(tg0).reshape(-1, n), to_f64(u0).reshape(-1, n),
+                            [to_f64(w).reshape(-1, n) for w in ws0], eta_out=0.9, mu=0.8,
+                            residuals=[r.numpy().reshape(-1, n) for r in res0] if ef else None, ef_beta=0.9,
+                            topk_fraction=frac, rows_per_matrix=m)
+    for k in range(K):
+        assert np.array_equal(taus[k].cpu().numpy().view(np.uint32), ref["thresholds"][k].view(np.uint32))
+        if ef:
+            assert np.array_equal(res[k].cpu().numpy().reshape(-1, n).view(np.uint32),
+                                  ref["residuals"][k].view(np.uint32))
+    assert_fp32_close(u.cpu().reshape(-1, n), ref["u"], "outer momentum")
+    assert_stored_close(tg.cpu().reshape(-1, n), ref["theta"], "global parameters")
+    for k in range(K):
+        assert torch.equal(ws[k].cpu(), tg.cpu().to(wd))
