@@ -176,7 +176,7 @@ __device__ __forceinline__ void pair_rows(const u32x4& x, const u32x4& y, bool o
 }
 
 // Position of an output tile.
-struct TileCoord { int b, m0, n0, mirror; };
+struct TileCoord { int b, m0, n0, mirror, diag; };
 
 // TI adjacent bf16 values of a row <-> TI / 2 words.
 template <int TI>
@@ -352,6 +352,189 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   }
 }
 
+// Word k of lane p of every four lanes becomes word p of lane k.
+__device__ __forceinline__ u32x4 transpose_quad(u32x4 w, int p) {
+  const bool p1 = p & 1, p2 = p & 2;
+#pragma unroll
+  for (int x = 0; x < 4; x += 2) {
+    const unsigned int got = (unsigned int)__builtin_amdgcn_mov_dpp((int)(p1 ? w[x] : w[x + 1]), 0xb1, 0xf, 0xf, true);
+    w[x + 1] = p1 ? w[x + 1] : got;
+    w[x] = p1 ? got : w[x];
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const unsigned int got = (unsigned int)__builtin_amdgcn_mov_dpp((int)(p2 ? w[x] : w[x + 2]), 0x4e, 0xf, 0xf, true);
+    w[x + 2] = p2 ? w[x + 2] : got;
+    w[x] = p2 ? got : w[x];
+  }
+  return w;
+}
+
+// Epilogue of a tile on the diagonal of a symmetric product, in which a lane holds rows 32 (i / 2) + 8 (idx / 4) + 4 (i % 2)
+// + idx % 4 in accumulator tile i, and columns as everywhere.  DG: a quarter on the diagonal, of which the
+// blocks (I, J) of 32 x 32 with J <= I have been computed; its diagonal is the matrix's.  Otherwise 128 x 64 of the
+// lower left quarter.  Every block off the diagonal is stored a second time, transposed: four lanes hold a column's
+// 8 adjacent rows between them, and turn them over.  Stores cover whole lines except where a row of blocks
+// ends in the middle of one.
+constexpr int TRIANGLE_STORES = 32;
+// Deepest product whose triangles leave operand A's transfers out.  A triangle then takes 0.7 to 0.8 of a whole
+// tile's time (0.9 with the transfers), and the workgroups behind one L2 no longer read the same K tiles at the same time:
+// deeper operands do not fit there, and come from memory again.  Gram and polynomial products of 150M-scale, eight
+// replicas (K = 768 and 3072): 590 and 414 us with whole tiles, 556 and 387 with the transfers, 530 and 357 by this rule; the
+// Gram products of 1.76B-scale (K = 2048 and 8192) 1940, 1860, and without the transfers at any depth 2280.
+constexpr int TRIANGLE_ONE_OPERAND = 2560;
+template <bool DG>
+__device__ __forceinline__ void triangle_settle(f32x4 (&acc)[8][8]) {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < (DG ? 8 : 4); ++j)
+      if (!DG || j / 2 <= i / 2) asm volatile("" : "+a"(acc[i][j]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <bool DG>
+__device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&acc)[8][8], int b, int row0, int col0,
+                                               float alpha, int lane) {
+  asm volatile("" : "+v"(lane));
+  const int idx = lane & 15, lg = lane >> 4, q = idx >> 2, p = idx & 3, odd = idx & 1;
+  const __amdgpu_buffer_rsrc_t rd =
+      __builtin_amdgcn_make_buffer_rsrc(g.D + (long)b * g.strideD, 0, 0xffffffff, 0x00020000);
+  // (opaque: its multiples would otherwise be kept in scalar registers all through the K loop)
+  unsigned int ldd2 = (unsigned int)(g.ldd * 2);
+  asm volatile("" : "+s"(ldd2));
+  const int row = row0 + 8 * q + p, col = col0 + 8 * lg;
+  constexpr int NJ = DG ? 4 : 2;
+  auto has = [](int i, int J) { return !DG || J <= i / 2; };
+  auto up = [](int i) { return (unsigned int)(32 * (i / 2) + 4 * (i & 1)); };       // rows of tile i above `row`
+  // C of the upper half is awaited before the first store, and that of the lower half requested before it (see
+  // store_tile: a wait for a load is one for the stores before it)
+  u32x4 c[8][NJ];
+  auto load_c = [&](int half) {
+    if (!g.C) {
+      if constexpr (!DG)
+#pragma unroll
+        for (int i = 4 * half; i < 4 * half + 4; ++i)
+#pragma unroll
+          for (int J = 0; J < NJ; ++J) c[i][J] = u32x4{0u, 0u, 0u, 0u};
+      return;
+    }
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(g.C) + (long)b * g.strideC, 0, 0xffffffff, 0x00020000);
+    unsigned int ldc2 = (unsigned int)(g.ldc * 2);
+    asm volatile("" : "+s"(ldc2));
+    const unsigned int voff_c = (unsigned int)(((long)row * g.ldc + col) * 2);
+#pragma unroll
+    for (int i = 4 * half; i < 4 * half + 4; ++i)
+#pragma unroll
+      for (int J = 0; J < NJ; ++J)
+        if (has(i, J)) c[i][J] = __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c + 64u * J, up(i) * ldc2, 0);
+  };
+  const int diag = col - row;              // 32 (i / 2) + 4 (i % 2) - (32 J + e) on the diagonal
+  u32x4 v[8][NJ];
+  auto round_half = [&](int half, auto c_tag, auto unit_tag) {
+    constexpr bool HAS_C = decltype(c_tag)::value, UNIT = decltype(unit_tag)::value;
+#pragma unroll
+    for (int i = 4 * half; i < 4 * half + 4; ++i)
+#pragma unroll
+      for (int J = 0; J < NJ; ++J) {
+        if (!has(i, J)) continue;
+        __builtin_amdgcn_sched_barrier(0);
+        const f32x4 lo = acc_read(acc[i][2 * J]), hi = acc_read(acc[i][2 * J + 1]);
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          float v0 = e < 4 ? lo[e % 4] : hi[e % 4], v1 = e < 4 ? lo[e % 4 + 1] : hi[e % 4 + 1];
+          if constexpr (!UNIT) { v0 *= alpha; v1 *= alpha; }
+          if constexpr (HAS_C) {
+            v0 += g.beta * bf16lo(c[i][J][e / 2]);
+            v1 += g.beta * bf16hi(c[i][J][e / 2]);
+          }
+          if (DG && J == i / 2) {
+            if (4 * (i & 1) - e == diag) v0 += g.gamma;
+            if (4 * (i & 1) - (e + 1) == diag) v1 += g.gamma;
+          }
+          v[i][J][e / 2] = pack_bf16x2(v0, v1);
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const unsigned int at = (unsigned int)(((long)row * g.ldd + col) * 2);
+  const unsigned int at2 = (unsigned int)(((long)(row - odd) * g.ldd + col + 32 * odd) * 2);     // two blocks' lines
+  auto store_row = [&](int i) {
+#pragma unroll
+    for (int J = 0; J < NJ; J += 2) {
+      if (!has(i, J)) continue;
+      const unsigned int soff = up(i) * ldd2;
+      if (has(i, J + 1)) {
+        u32x4 x, y;
+        pair_rows(v[i][J], v[i][J + 1], odd, x, y);
+        __builtin_amdgcn_raw_buffer_store_b128(x, rd, at2 + 64u * J, soff, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(y, rd, at2 + 64u * J, soff + ldd2, 0);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b128(v[i][J], rd, at + 64u * J, soff, 0);
+      }
+    }
+  };
+  // columns 32 J + 8 lg + 2 p and + 1 of block (I, J), rows 8 q .. + 7
+  auto turn = [&](int I, int J, u32x4& even, u32x4& next) {
+    const u32x4 r0 = transpose_quad(v[2 * I][J], p), r1 = transpose_quad(v[2 * I + 1][J], p);
+    even = u32x4{pair_lo(r0[0], r0[1]), pair_lo(r0[2], r0[3]), pair_lo(r1[0], r1[1]), pair_lo(r1[2], r1[3])};
+    next = u32x4{pair_hi(r0[0], r0[1]), pair_hi(r0[2], r0[3]), pair_hi(r1[0], r1[1]), pair_hi(r1[2], r1[3])};
+  };
+  const int trow = col0 + 8 * lg + 2 * p, tcol = row0 + 8 * q;
+  const unsigned int mt = (unsigned int)(((long)trow * g.ldd + tcol) * 2);
+  const unsigned int mt2 = (unsigned int)(((long)(trow - 2 * odd) * g.ldd + tcol + 32 * odd) * 2);
+  auto store_turned = [&](int I, int J) {            // one block
+    u32x4 x, y;
+    turn(I, J, x, y);
+    const unsigned int soff = 32u * J * ldd2;
+    __builtin_amdgcn_raw_buffer_store_b128(x, rd, mt + 64u * I, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(y, rd, mt + 64u * I, soff + ldd2, 0);
+  };
+  auto store_turned2 = [&](int I, int J) {           // blocks (I, J) and (I + 1, J)
+    u32x4 x[2], y[2];
+    turn(I, J, x[0], y[0]);
+    turn(I + 1, J, x[1], y[1]);
+    const unsigned int soff = 32u * J * ldd2;
+    u32x4 s, t;
+    pair_rows(x[0], x[1], odd, s, t);
+    __builtin_amdgcn_raw_buffer_store_b128(s, rd, mt2 + 64u * I, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(t, rd, mt2 + 64u * I, soff + 2 * ldd2, 0);
+    pair_rows(y[0], y[1], odd, s, t);
+    __builtin_amdgcn_raw_buffer_store_b128(s, rd, mt2 + 64u * I, soff + ldd2, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(t, rd, mt2 + 64u * I, soff + 3 * ldd2, 0);
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+  const bool unit = alpha == 1.f;
+  load_c(0);
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int I = 2 * half;
+    if constexpr (!DG) round_half(half, T{}, F{});           // (C is zero where there is none)
+    else if (g.C && unit) round_half(half, T{}, T{});
+    else if (g.C) round_half(half, T{}, F{});
+    else if (unit) round_half(half, F{}, T{});
+    else round_half(half, F{}, F{});
+    if (half == 0) load_c(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 2 * I; i < 2 * I + 4; ++i) {
+      store_row(i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (DG) {
+      store_turned(I + 1, I);
+      if (half) { store_turned2(2, 0); store_turned2(2, 1); }
+    } else {
+      store_turned2(I, 0);
+      store_turned2(I, 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // Persistent kernel: one workgroup per CU slot walks over its share of the output tiles.
 // Workgroups are dealt round-robin to the 8 XCDs, so XCD x owns the contiguous range of
 // tiles [x * tiles_per_xcd, (x + 1) * tiles_per_xcd) and its workgroups take them in
@@ -373,6 +556,11 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
   if (deal.at >= deal.end) second();
   if (deal.at >= deal.end) return;
 
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // A tile on the diagonal of a symmetric product is symmetric itself, and only its lower triangle of 32 x 32 blocks is
+  // computed (store_triangle).
+  constexpr bool TRI = BM == 256 && !BKS;
   auto decode = [&](int t) {
     TileCoord tc;
     tc.b = t / g.tiles_per_mat;
@@ -398,11 +586,10 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
     tc.n0 = __builtin_amdgcn_readfirstlane(tn * BN);
     tc.b = __builtin_amdgcn_readfirstlane(tc.b);
     tc.mirror = g.symmetric && tm != tn ? 1 : 0;
+    tc.diag = TRI && tm == tn ? 1 : 0;
     return tc;
   };
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int idx = lane & 15, lg = lane >> 4;
   const int wbase_m = (wave >> 1) * (BM / 2), wbase_n = (wave & 1) * (BN / 2);
 
@@ -529,7 +716,8 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
   // half of that: 2600 cycles more a K tile.)
   constexpr bool DEFER = TI == 8;
   u32x4 pend[DEFER ? 16 : 1];
-  bool stored = false, mirrored = false;      // this workgroup's last tile: is there one, has it a transposed copy
+  // this workgroup's last tile: has it left half of it in `pend`, has that a transposed copy, was it a triangle
+  bool stored = false, mirrored = false, triangle = false;
   __amdgpu_buffer_rsrc_t pend_rd;
   unsigned int pend_n = 0, pend_m = 0, pend_ld = 0;      // lane offsets, plain and transposed; row pitch
   auto drain = [&](int i) {          // row i of a lane's eight (transposed: columns 2 i and 2 i + 1 of its 16)
@@ -617,16 +805,157 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
   // Transfers that may be in flight at a K tile's barrier, which publishes the next K tile: all
   // requested after it.
   constexpr int STEADY = (NB - 4) * NCH;
+  // ---- a tile on the diagonal.  Rows and columns are the same, so operand B's buffer serves for both, and tile i of
+  // rows holds what tile j = i of columns does.  Wavefronts 0 and 3 take the quarters on the diagonal (DG: ten of
+  // their sixteen 32 x 32 blocks, from one set of fragments), 1 and 2 half of the lower left quarter each (128
+  // rows, 64 columns): 40 and 32 MFMAs a slice instead of 64.  Leaving out the upper right quarter alone, with its
+  // wavefront idle, gave 0.5 % of an inner step, this 1 to 4 %.
+  // B's transfers go first: its buffer of two K tiles ahead is the one that A's of this K tile would fill.  A's, where
+  // they go out (always towards a whole tile that follows), come in the second slice.  Either way a wait leaves
+  // as many transfers in flight as in a whole tile, all of them behind what it awaits.
+  // The last tile's left-over stores leave in four K tiles, and the K loop is unrolled by two: the
+  // whole kernel stays within the reach of a branch.
+  auto run_triangle = [&](auto tri_tag, const TileCoord& tn) {
+    constexpr bool DG = decltype(tri_tag)::value;
+    constexpr int MF = DG ? 40 : 32, NF = DG ? 8 : 12;        // MFMAs and fragments of a slice
+    u32x4 ta[2][8], tb[2][8];
+    bool rows_a = g.K > TRIANGLE_ONE_OPERAND;       // do operand A's transfers go out
+    const unsigned int base = fragB[0] - (unsigned int)wbase_n * 128;
+    auto point = [&](unsigned int bufB, int kk) {
+      const unsigned int at = (base ^ (kk ? 64u : 0u)) + bufB;
+      rb[0] = at + (DG ? (unsigned int)wbase_n * 128 : wave == 1 ? 4u * 2048 : 0u);
+      ra = at + 128u * 128;
+    };
+    // in the order of their use
+    auto read = [&](int set, int r) {
+      if constexpr (DG) tb[set][r] = *reinterpret_cast<const u32x4*>(smem + rb[0] + r * 2048);
+      else if (r == 0 || r > 4) ta[set][r == 0 ? 0 : r - 4] = *reinterpret_cast<const u32x4*>(smem + ra + (r == 0 ? 0 : r - 4) * 2048);
+      else tb[set][r - 1] = *reinterpret_cast<const u32x4*>(smem + rb[0] + (r - 1) * 2048);
+    };
+    auto tri_slice = [&](auto set_tag, auto zero_tag, auto drain_tag, auto rows_tag, auto b_tag, unsigned int dst) {
+      constexpr int DR = decltype(drain_tag)::value, ROWS = decltype(rows_tag)::value;       // rows that leave
+      constexpr bool OPB = decltype(b_tag)::value;
+      constexpr int S = decltype(set_tag)::value;
+      constexpr bool ZERO = decltype(zero_tag)::value;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int m = i / 2, cols = DG ? 2 * m + 2 : 4;
+        const int n0 = DG ? 2 * m * (m + 1) + (i & 1) * (2 * m + 2) : 4 * i;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          if (x >= cols) break;
+          const int n = n0 + x, j = (i & 1) ? cols - 1 - x : x;
+          const u32x4& a = DG ? tb[S][i] : ta[S][i];
+          if (OPB && n % (MF / NCH) == 1) {
+            dma_n(n / (MF / NCH), [&](auto it) {
+              mfma_dma<ZERO, decltype(it)::value * 4096>(acc[i][j], tb[S][j], a, rsB, voffB, runB, dst);
+            });
+          } else {
+            mfma<ZERO>(acc[i][j], tb[S][j], a);
+            if (OPB && n % (MF / NCH) == 2) next_b(n / (MF / NCH));
+            if (!OPB && n == 8 && rows_a)
+#pragma unroll 1
+              for (int it = 0; it < NCH; ++it) {
+                dma16<0>(rsA, voffA, runA, dst + (unsigned int)it * 4096);
+                next_a(it);
+              }
+          }
+          if (n % 2 == 0 && n / 2 < NF) read(1 - S, n / 2);
+          if constexpr (ROWS > 0) {
+            if (n == 8 && stored) drain(DR);
+            if (n == 18 && mirrored) drain_mirror(2 * DR);
+            if (n == 21 && mirrored) drain_mirror(2 * DR + 1);
+          }
+          if constexpr (ROWS > 1) {
+            if (n == 14 && stored) drain(DR + 1);
+            if (n == 24 && mirrored) drain_mirror(2 * DR + 2);
+            if (n == 27 && mirrored) drain_mirror(2 * DR + 3);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    point(wrap(p + BUF), 0);
+#pragma unroll
+    for (int r = 0; r < NF; ++r) read(0, r);
+    auto tri_step = [&](auto first_tag, auto drain_tag, auto rows_tag) {
+      if (left == 0) {
+        aim(tn);
+        rows_a = !tn.diag;
+      }
+      runA = soA;
+      runB = soB;
+      const unsigned int pb = wrap(p + BUF), pa1 = wrap(p + 2 * BUF), pb1 = wrap(p + 3 * BUF);
+      const unsigned int free0 = lds_wave + (p == 0 ? RING - BUF : p - BUF), free1 = lds_wave + p;
+      point(pb, 1);
+      tri_slice(I<0>{}, first_tag, drain_tag, rows_tag, T{}, free1);
+      constexpr int DR = 2 * decltype(rows_tag)::value;
+      constexpr bool FIRST = decltype(first_tag)::value;
+      if (FIRST && triangle) wait_vmcnt<STEADY + TRIANGLE_STORES>();
+      else if (DR + FIRST == 0 || !stored) wait_vmcnt<STEADY>();
+      else if (mirrored) wait_vmcnt<STEADY + 2 * DR + (FIRST ? epilogue_stores(TI, true) : 0)>();
+      else wait_vmcnt<STEADY + DR + (FIRST ? epilogue_stores(TI, false) : 0)>();
+      block_sync();
+      point(pb1, 0);
+      tri_slice(I<1>{}, F{}, I<0>{}, I<0>{}, F{}, free0);
+      soA += advA;
+      soB += advB;
+      --left;
+      p = pa1;
+    };
+    // (two rows a K tile; the number of K tiles is even)
+    tri_step(T{}, I<0>{}, I<2>{});
+    tri_step(F{}, I<2>{}, I<2>{});
+    tri_step(F{}, I<4>{}, I<2>{});
+    tri_step(F{}, I<6>{}, I<2>{});
+    int t = 4;
+    if (DG && KT > 4) {
+      tri_step(F{}, I<0>{}, I<0>{});
+      tri_step(F{}, I<0>{}, I<0>{});
+      t = 6;
+    }
+#pragma unroll 1
+    for (; t < KT; t += 2) {
+      tri_step(F{}, I<0>{}, I<0>{});
+      tri_step(F{}, I<0>{}, I<0>{});
+    }
+    triangle_settle<DG>(acc);
+    float alpha = g.alpha;
+    if (g.bscale) {
+      const float sc = g.bscale[tc.b];
+      alpha *= (g.bscale_pow == 2) ? sc * sc : sc;
+    }
+    const int row0 = tc.m0 + (DG ? wbase_n : 128), col0 = tc.n0 + (DG ? wbase_n : wave == 1 ? 64 : 0);
+    store_triangle<DG>(g, acc, tc.b, row0, col0, alpha, lane);
+  };
+
   while (true) {
+    // The next output tile of this workgroup; after the last one the same requests go to this
+    // tile's own first K tiles again (in bounds, never read).
+    bool more;
+    TileCoord tn;
+    auto advance = [&] {
+      deal.at += deal.step;
+      if (deal.at >= deal.end) second();
+      more = deal.at < deal.end;
+      tn = more ? decode(deal.at) : tc;
+    };
+    if constexpr (TRI) {
+      if (tc.diag) {
+        advance();
+        if (wave == 1 || wave == 2) run_triangle(F{}, tn);
+        else run_triangle(T{}, tn);
+        stored = mirrored = false;
+        triangle = true;
+        if (!more) break;
+        tc = tn;
+        continue;
+      }
+    }
     point_at(p, wrap(p + BUF), 0);
 #pragma unroll
     for (int r = 0; r < NR; ++r) read_one(0, r);
-    // The next output tile of this workgroup; after the last one the same requests go to this
-    // tile's own first K tiles again (in bounds, never read).
-    deal.at += deal.step;
-    if (deal.at >= deal.end) second();
-    const bool more = deal.at < deal.end;
-    const TileCoord tn = more ? decode(deal.at) : tc;
+    advance();
     auto step = [&](auto first_tag, auto drain_tag) {
       if (left == 0) aim(tn);
       runA = soA;
@@ -639,7 +968,8 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
       // K tile, the last epilogue's stores
       constexpr int DR = decltype(drain_tag)::value >= 0 ? 2 : 0;
       constexpr bool FIRST = decltype(first_tag)::value;
-      if (DR + FIRST == 0 || !stored) wait_vmcnt<STEADY>();
+      if (TRI && FIRST && triangle) wait_vmcnt<STEADY + TRIANGLE_STORES>();
+      else if (DR + FIRST == 0 || !stored) wait_vmcnt<STEADY>();
       else if (!BKS && mirrored) wait_vmcnt<STEADY + 2 * DR + (FIRST ? epilogue_stores(TI, true) : 0)>();
       else wait_vmcnt<STEADY + DR + (FIRST ? epilogue_stores(TI, false) : 0)>();
       block_sync();
@@ -686,14 +1016,15 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
     // Symmetric products (Gram, polynomial) are those with a K-contiguous B, the apply products
     // those with a K-strided one: each kernel holds only the forms its products have.
     if constexpr (!BKS) {
-      if (g.C) {
-        if (tc.mirror) MLC_STORE(true, true, false, false, false);
-        else MLC_STORE(true, false, false, true, false);
-      } else if (tc.mirror) {
-        if (alpha == 1.f) MLC_STORE(false, true, false, false, true);
-        else MLC_STORE(false, true, false, false, false);
+      if (!TRI && !tc.mirror) {
+        if (g.C) MLC_STORE(true, false, false, true, false);
+        else MLC_STORE(false, false, false, true, false);
+      } else if (g.C) {
+        MLC_STORE(true, true, false, false, false);
+      } else if (alpha == 1.f) {
+        MLC_STORE(false, true, false, false, true);
       } else {
-        MLC_STORE(false, false, false, true, false);
+        MLC_STORE(false, true, false, false, false);
       }
     } else if (g.transposed) {
       if (g.C) MLC_STORE(true, false, true, false, false);
@@ -707,6 +1038,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
     }
 #undef MLC_STORE
     stored = true;
+    triangle = false;
     mirrored = tc.mirror;
     if constexpr (DEFER) {
       pend_rd = __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, 0xffffffff, 0x00020000);
@@ -722,8 +1054,9 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
     tc = tn;
   }
   if constexpr (DEFER) {
+    if (stored)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) drain(i);
+      for (int i = 0; i < 8; ++i) drain(i);
     if (!BKS && mirrored)
 #pragma unroll
       for (int q = 0; q < 16; ++q) drain_mirror(q);
@@ -855,7 +1188,8 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
     const int rc = make_args<BM, BN>(dj, m.seg[j]);
     if (rc != MLC_OK) return rc;
     if (j >= n) continue;
-    flops += 2.0 * BM * BN * (double)dj.K * (double)m.seg[j].total_tiles;   // executed, not nominal
+    // of whole output tiles (9 / 16 of a 256 x 256 tile on the diagonal are executed)
+    flops += 2.0 * BM * BN * (double)dj.K * (double)m.seg[j].total_tiles;
     most += m.seg[j].tiles_per_xcd;
   }
   if (most < W) W = most;    // fewer tiles than compute units

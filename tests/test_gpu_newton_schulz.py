@@ -232,6 +232,22 @@ def test_stores_left_for_the_next_tile(cnt, m, n, tiles):
         assert torch.equal(W[i], few[i % 6]), i
 
 
+# 256 x 256 tiles on the diagonal, of which a triangle is computed: as many K tiles as go without operand A's
+# transfers, and more; whole tiles before and behind them; deep and shallow products in one launch
+@pytest.mark.parametrize("cnt,m,n,tiles", [
+    (40, 768, 2560, (256, 256, 256)), (40, 768, 3328, (256, 256, 256)), (40, 3328, 768, (256, 256, 256)),
+    (20, 1280, 1280, (256, 128, 256)), (300, 512, 512, (256, 256, 256)),
+])
+def test_triangles_give_the_bits_of_whole_tiles(cnt, m, n, tiles):
+    assert ns_tiles([(cnt, m, n)]) == [tiles]
+    some = S.normal((3, m, n), S.GRAD_STD, seed=22, stream=m + n, dtype=torch.bfloat16).to(DEV)
+    few = torch.stack([o for x in some for o in _run(x[None])])         # in smaller tiles, without triangles
+    assert all(256 not in t for t in ns_tiles([(1, m, n)]))
+    out = _run(some.repeat((cnt + 2) // 3, 1, 1)[:cnt])
+    for i in range(cnt):
+        assert torch.equal(out[i].view(torch.int16), few[i % 3].view(torch.int16)), i
+
+
 @pytest.mark.parametrize("cnt,m,n", [(1, 384, 256), (2, 1000, 333), (6, 1536, 512), (48, 1024, 256), (12, 2048, 1024)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_tall_is_the_wide_result_transposed(cnt, m, n, dtype):
