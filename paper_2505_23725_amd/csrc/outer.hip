@@ -349,25 +349,35 @@ __global__ __launch_bounds__(OT_THREADS) void quantize_rows_kernel(
 // for all K workers and every theta_k exactly once.  Same arithmetic as above.  With
 // OUTER the dequantised values go straight into the mean and eq. 3 without re-reading
 // theta_g or the codes; codes, scales and offsets are written either way.
+// G0 = 0: the workgroup is as large as one row needs (quant_whole_row), G0 > 0: the group's threads.
 // `blk` is the index of the workgroup among those that share these arguments; the pointer sets
 // may be the 32-wide ones of a single-group launch or the narrow ones of a launch that covers
 // several groups.
 // RAG: rows of any length, so neither the rows nor their codes are aligned and the last vector of
 // a row may be a part of one (24 / 6 / 6 matrices of 1001 x 1001, 1001 x 2730 and 2730 x 1001, two
 // workers, 8 bits with error feedback: 1500 us element by element in two passes, 516 like this).
-template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG, typename PW, typename PC, typename PS,
+template <typename WT, typename GT, int NV, int G0, bool OUTER, bool RAG, typename PW, typename PC, typename PS,
           typename PO, typename PE>
 __device__ __forceinline__ void quantize_rows_reg_body(
     const PW& w, GT* __restrict__ theta_g, float* __restrict__ u, const PC& codes, const PS& scales,
     const PO& offsets, const PE& ef, long rows, int n, int K, const QuantForm& form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
     float* mean_offsets, long blk) {
-  constexpr int ROWS_PER_BLOCK = OT_THREADS / G;
-  constexpr int NW = OT_THREADS / 64;
+  constexpr bool WHOLE = G0 == 0;
+  const int G = WHOLE ? (int)blockDim.x : G0;
+  constexpr int NW = WHOLE ? 16 : OT_THREADS / 64;
+  const int waves = WHOLE ? (int)blockDim.x / 64 : NW;
   __shared__ float red[2][2][NW];          // [parity of k][min, max][wavefront]
   __shared__ float red2[2][NW];
-  const int t = threadIdx.x % G;
-  const long row = blk * ROWS_PER_BLOCK + threadIdx.x / G;
+  const int t = WHOLE ? threadIdx.x : threadIdx.x % G;
+  const long row = WHOLE ? blk : blk * (OT_THREADS / G) + threadIdx.x / G;
+  auto across = [&](const float (&r)[2][NW], float& mn, float& mx) {
+    mn = r[0][0];
+    mx = r[1][0];
+#pragma unroll
+    for (int wv = 1; wv < NW; ++wv)
+      if (wv < waves) { mn = fminf(mn, r[0][wv]); mx = fmaxf(mx, r[1][wv]); }
+  };
   const bool live = row < rows;            // whole groups are live or not; no early return
   const long rbase = live ? row * n : 0;   // (the workgroup-wide barrier below needs everyone)
   const int bits = form.bits;
@@ -436,11 +446,10 @@ __device__ __forceinline__ void quantize_rows_reg_body(
       rg = stored_range(scales, offsets, k, grp, form);
     } else {
       mn = wave_min(mn); mx = wave_max(mx);
-      if constexpr (G > 64) {
+      if constexpr (WHOLE || G0 > 64) {
         if ((threadIdx.x & 63) == 0) { red[k & 1][0][threadIdx.x >> 6] = mn; red[k & 1][1][threadIdx.x >> 6] = mx; }
         __syncthreads();
-        mn = fminf(fminf(red[k & 1][0][0], red[k & 1][0][1]), fminf(red[k & 1][0][2], red[k & 1][0][3]));
-        mx = fmaxf(fmaxf(red[k & 1][1][0], red[k & 1][1][1]), fmaxf(red[k & 1][1][2], red[k & 1][1][3]));
+        across(red[k & 1], mn, mx);
       }
       rg = make_range(mn, mx, form);
       if (live && t == 0) {
@@ -485,11 +494,10 @@ __device__ __forceinline__ void quantize_rows_reg_body(
           for (int j = 0; j < 8; ++j) { mn = fminf(mn, acc[i][j]); mx = fmaxf(mx, acc[i][j]); }
       }
       mn = wave_min(mn); mx = wave_max(mx);
-      if constexpr (G > 64) {
+      if constexpr (WHOLE || G0 > 64) {
         if ((threadIdx.x & 63) == 0) { red2[0][threadIdx.x >> 6] = mn; red2[1][threadIdx.x >> 6] = mx; }
         __syncthreads();
-        mn = fminf(fminf(red2[0][0], red2[0][1]), fminf(red2[0][2], red2[0][3]));
-        mx = fmaxf(fmaxf(red2[1][0], red2[1][1]), fmaxf(red2[1][2], red2[1][3]));
+        across(red2, mn, mx);
       }
       const Range rg = make_range(mn, mx, form);
       if (live && t == 0) {
@@ -527,6 +535,27 @@ __device__ __forceinline__ void quantize_rows_reg_body(
   }
 }
 
+// Vectors per thread of the quantised update where a workgroup has just the wavefronts that a row of n
+// needs (G = 0), or 0: groups of 256 threads, of which a row may leave most idle in their last vector.
+// With two vectors a CU holds 16 wavefronts: rows of up to 5120 (5 to a workgroup) and over 6144 (7 and 8)
+// nearly fill it, those between (6) three quarters; over 8192 only one workgroup fits, which up to 12288 is
+// worse than 256 threads with six vectors.  Beyond, where a thread of 256 held eight or twelve vectors,
+// it is better by far.  26 M elements * 4 / (K + 3), K = 1 / 4 / 8 replicas at 4 bits and K = 2 at 8 bits with
+// error feedback, us with groups of 256 threads and with such workgroups:
+//    2560   90 / 115 / 122, 176    91 / 104 / 115, 178   (taken from three replicas on, up to 4096)
+//    4104  120 / 123 / 134, 196    96 / 119 / 124, 184
+//    6144  104 / 106 / 114, 187    89 / 114 / 127, 179   (taken up to two replicas, from 5121 on)
+//    8192  112 / 105 / 118, 189    88 / 103 / 116, 177
+//   10240   95 / 110 / 119, 187    99 / 138 / 160, 190   (not taken)
+//   16384  116 / 156 / 196, 225    96 / 128 / 161, 190
+//   24576  121 / 168 / 196, 258   109 / 131 / 158, 209   (three vectors)
+// One vector a thread and twice the wavefronts: rows of 2560 to 8192 5 to 45 % slower from four replicas on.
+static int quant_whole_row(int64_t n, int K) {
+  if (n <= 2048 || (n <= 4096 && K <= 2)) return 0;
+  if (n > 12288) return n <= 16384 ? 2 : 3;
+  return n <= 5120 || (n <= 8192 && (n > 6144 || K <= 2)) ? 2 : 0;
+}
+
 // Wavefronts per SIMD the register allocation is held to: one more than the compiler reaches on
 // its own where that is a few registers away (these kernels wait on memory with little else to
 // do, so a resident wavefront more is worth more than the registers).
@@ -535,7 +564,7 @@ constexpr int quant_min_waves(int nv, bool outer) {
 }
 
 template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG>
-__global__ __launch_bounds__(OT_THREADS, quant_min_waves(NV, OUTER)) void quantize_rows_reg_kernel(
+__global__ __launch_bounds__(G ? OT_THREADS : 1024, quant_min_waves(NV, OUTER)) void quantize_rows_reg_kernel(
     WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, CodePtrs codes, ScalePtrs scales,
     OffsetPtrs offsets, ResidualPtrs ef, long rows, int n, int K, QuantForm form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
@@ -1427,7 +1456,9 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
   // Vectors per thread.  The row, its running mean and the current worker's delta all live in
   // registers (24 floats per vector), so the steps are fine where it buys occupancy: 6 instead
   // of 8 vectors lets two workgroups share a CU (10240 columns: 3.3 -> 4.x TB/s with K = 4).
-  const int nv = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 6 ? 6 : need <= 8 ? 8 : 12;
+  const int nv = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 6;
+  const int whole = quant_whole_row(n, K);
+  const int threads = whole ? (int)((n + whole * 512 - 1) / (whole * 512)) * 64 : OT_THREADS;
   const long rpb = OT_THREADS / g;
   const long nblk = (rows + rpb - 1) / rpb;
   if (nblk > 0x7fffffffL) return MLC_ERR_SHAPE;
@@ -1440,18 +1471,18 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
   const float inv_k = 1.0f / (float)K;
 #define MLC_QO_R(WT, GT, NV, G, RAG)                                                              \
   hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, true, RAG>), dim3((unsigned)nblk),   \
-                     dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, codes, scales, offsets, ef,  \
+                     dim3(threads), 0, stream, w, (GT*)theta_g, u, codes, scales, offsets, ef,  \
                      (long)rows, (int)n, K, form, eta_out, mu, inv_k, nesterov, write_back, requant, \
                      mean_codes, mean_scales, mean_offsets)
 #define MLC_QO(WT, GT, NV, G)                                                                     \
   do { if (quant_ragged(n)) MLC_QO_R(WT, GT, NV, G, true); else MLC_QO_R(WT, GT, NV, G, false); } while (0)
 #define MLC_QO_NV(WT, GT)                                                                         \
   do {                                                                                            \
-    if (g == 64) { if (nv == 1) MLC_QO(WT, GT, 1, 64); else if (nv == 2) MLC_QO(WT, GT, 2, 64);   \
+    if (whole == 2) MLC_QO(WT, GT, 2, 0); else if (whole == 3) MLC_QO(WT, GT, 3, 0);              \
+    else if (g == 64) { if (nv == 1) MLC_QO(WT, GT, 1, 64); else if (nv == 2) MLC_QO(WT, GT, 2, 64);   \
                    else MLC_QO(WT, GT, 4, 64); }                                                  \
     else { if (nv <= 2) MLC_QO(WT, GT, 2, 256); else if (nv == 4) MLC_QO(WT, GT, 4, 256);         \
-           else if (nv == 6) MLC_QO(WT, GT, 6, 256);                                              \
-           else if (nv == 8) MLC_QO(WT, GT, 8, 256); else MLC_QO(WT, GT, 12, 256); }              \
+           else MLC_QO(WT, GT, 6, 256); }                                                         \
   } while (0)
   if (worker_dtype == MLC_BF16 && global_dtype == MLC_F32) MLC_QO_NV(bf16_t, float);
   else if (worker_dtype == MLC_BF16) MLC_QO_NV(bf16_t, bf16_t);

@@ -331,3 +331,12 @@ def test_ragged_and_aligned_groups_in_one_call_equal_one_call_per_group():
         for x, y in zip([a.global_param, a.outer_momentum, *a.worker_params, *a.codes, *a.scales, *a.residuals, *a.offsets],
                         [b.global_param, b.outer_momentum, *b.worker_params, *b.codes, *b.scales, *b.residuals, *b.offsets]):
             assert torch.equal(x, y)
+
+
+# rows on either side of the lines at which a workgroup takes the size of its row: one wavefront's vector more or
+# less, the last vector partly or hardly used, the most wavefronts, two and three vectors a thread
+@pytest.mark.parametrize("n", [2056, 3072, 3080, 5120, 5128, 6144, 6152, 8192, 8200, 12288, 12296, 16384, 16392, 24576])
+@pytest.mark.parametrize("K", [2, 3])
+def test_workgroups_of_one_row(n, K):
+    bits = 4 if n % 16 else 8
+    test_quantiser_forms_bit_exact(1, 5, n, K, torch.bfloat16, torch.float32, bits, K == 3, False, K == 2, K == 2)
