@@ -841,18 +841,18 @@ __global__ __launch_bounds__(TOPK_SAMPLE_THREADS) void topk_sample_kernel(
   }
 }
 
-// True in every thread of the workgroup of `n` (gridDim.x) that comes last to this state.  What the
+// True in every thread of the workgroup of `n` that comes last to this state.  What the
 // workgroups hand over are atomic sums at device scope: each thread's have been performed when its wait returns,
 // so they precede the workgroup's ticket.  (A release fence would also write back
 // the L2 cache, which holds the values that the pass has just stored.)
-__device__ __forceinline__ bool last_of_state(TopkState& s, unsigned int& early) {
+__device__ __forceinline__ bool last_of_state(TopkState& s, unsigned int n, unsigned int& early) {
   __shared__ unsigned int ticket;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) ticket = __hip_atomic_fetch_add(&s.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   early = ticket & TOPK_EARLY;
-  return (ticket & 0xffffu) == gridDim.x - 1;
+  return (ticket & 0xffffu) == n - 1;
 }
 
 // The last workgroup narrows the interval: bins of 2^shift keys from s.lo on have been counted; the one that
@@ -963,7 +963,7 @@ __global__ __launch_bounds__(TOPK_WINDOW_THREADS) void topk_window_kernel(
   for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_WINDOW_THREADS)
     if (lh[i]) __hip_atomic_fetch_add(&s.hist[i], lh[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   unsigned int early;
-  if (last_of_state(s, early)) topk_narrow<true>(s, (int)shift, early);
+  if (last_of_state(s, gridDim.x, early)) topk_narrow<true>(s, (int)shift, early);
 }
 
 // The first digits (bits from `shift` up) of a lane's first cnt of 8 values.  They mostly change
@@ -1007,27 +1007,80 @@ __device__ __forceinline__ void count_first_digit(unsigned int* hist, const floa
   }
 }
 
-// Did the pass over the window leave few enough values of this matrix for every worker?  (The bit is not touched by
-// later passes.)
-__device__ __forceinline__ bool topk_early(const TopkState* st, long b, int count, int K) {
-  bool early = true;
-  for (int k = 0; k < K; ++k)
-    early = early && (__hip_atomic_load(&st[(long)k * count + b].ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
-                      TOPK_EARLY) != 0u;
-  return early;
+// Did the pass over the window leave few enough values of this matrix for this worker?  (Later passes do not touch the
+// bit.)
+__device__ __forceinline__ bool state_early(const TopkState& s) {
+  return (__hip_atomic_load(&s.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & TOPK_EARLY) != 0u;
 }
 
-// One pass of the radix select over the matrices that the window did not settle.  FIRST: the pass over all keys that
+// And of matrix b for every worker?  A whole workgroup asks, and the workers' bits are read at the same time.
+__device__ __forceinline__ bool topk_early(const TopkState* st, long b, int count, int K) {
+  return __syncthreads_and((int)threadIdx.x >= K || state_early(st[(long)threadIdx.x * count + b])) != 0;
+}
+
+// And of all matrices of the group?
+__device__ __forceinline__ bool topk_all_early(const TopkState* st, int n_states) {
+  bool early = true;
+  for (int i = threadIdx.x; i < n_states; i += OT_THREADS) early &= state_early(st[i]);
+  return __syncthreads_and(early) != 0;
+}
+
+// The launches behind a window have one grid for the whole group, whose workgroups share what is left between them:
+// mostly nothing, one matrix of many, or all of them.  The matrices that the window left open are listed
+// 256 at a time, the same in every workgroup, and each of their `parts` is split over as many workgroups as there
+// are for it, `most` at the most.  work(matrix, part, workgroup, workgroups) is called by whole workgroups.
+// (With an equal share of 1024 workgroups for every state, open or not: 6 matrices of 2048 x 2048, eight bf16 workers and
+// a bf16 global copy, whose ties the window does not settle, 1125 us, now 579; 4096 x 16384, eight workers, 20 % without
+// error feedback, 2627, now 1435; one open matrix of 64 of 768 x 768, eight workers, 2688, now 1717.)
+constexpr int TOPK_LATE_GRID = 1024, TOPK_FINISH_GRID = 2048;
+template <typename Work>
+__device__ __forceinline__ void topk_each_open(const TopkState* st, int count, int K, int parts, int most,
+                                               Work&& work) {
+  __shared__ unsigned int open[OT_THREADS], waves[OT_THREADS / 64];
+  const int t = threadIdx.x;
+  unsigned int dealt = 0u;                  // items of the matrices listed before
+  for (int b0 = 0; b0 < count; b0 += OT_THREADS) {
+    const int nb = min(count - b0, OT_THREADS);
+    open[t] = 0u;
+    __syncthreads();
+    for (int i = t; i < nb * K; i += OT_THREADS) {
+      const int k = i / nb, b = i - k * nb;
+      if (!state_early(st[(long)k * count + b0 + b])) open[b] = 1u;
+    }
+    __syncthreads();
+    const bool is_open = open[t] != 0u;
+    const unsigned long lanes = __ballot(is_open);
+    if ((t & 63) == 0) waves[t >> 6] = (unsigned int)__popcll(lanes);
+    __syncthreads();
+    int at = __popcll(lanes & ((1ul << (t & 63)) - 1ul)), n = 0;
+#pragma unroll
+    for (int wv = 0; wv < OT_THREADS / 64; ++wv) {
+      if (wv < t >> 6) at += (int)waves[wv];
+      n += (int)waves[wv];
+    }
+    if (is_open) open[at] = (unsigned int)(b0 + t);
+    __syncthreads();
+    const unsigned int states = (unsigned int)(n * parts), grid = gridDim.x;
+    const unsigned int share = states ? min(max(grid / states, 1u), (unsigned int)most) : 1u;
+    // item i of the group goes to workgroup i % grid
+    const unsigned int behind = dealt % grid;
+    for (unsigned int i = blockIdx.x >= behind ? blockIdx.x - behind : blockIdx.x + grid - behind; i < states * share;
+         i += grid) {
+      const unsigned int state = i / share, m = state / (unsigned int)parts;
+      work((long)open[m], (int)(state - m * parts), (int)(i - state * share), (int)share);
+      __syncthreads();                      // its shared memory may be written again
+    }
+    dealt += states * share;
+    __syncthreads();
+  }
+}
+
+// One pass of the radix select over a state's interval, by workgroup blk of nblk.  FIRST: the pass over all keys that
 // computes v, where no window was tried (with error feedback it leaves v in E).
 template <typename WT, typename GT, bool VEC, bool FIRST>
-__global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count,
-    float ef_beta, int window) {
-  __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];     // one histogram per wavefront
-  const long b = blockIdx.y;
-  const int k = blockIdx.z;
-  TopkState& s = st[(long)k * count + b];
-  if (!FIRST && window && (s.width == 0u || topk_early(st, b, count, (int)gridDim.z))) return;
+__device__ __forceinline__ void topk_count(const WorkerPtrs& w, const GT* __restrict__ theta_g, const ResidualPtrs& ef,
+                                           TopkState& s, unsigned int (&lh)[OT_THREADS / 64][TOPK_BINS], long elems,
+                                           long b, int k, float ef_beta, int blk, int nblk) {
   const unsigned int lo = FIRST ? 0u : s.lo, width = FIRST ? 31u : s.width;
   const int shift = width > 20u ? 20 : width > 10u ? 10 : 0;   // digits of 11, 10 and 10 bits
   const int nbins = 1 << (width - shift);
@@ -1039,8 +1092,8 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
   const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
   float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
   unsigned int cur = FIRST ? 0u : 0xffffffffu, run = 0u;       // run-length of the current digit
-  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * 8; i < elems;
-       i += (long)gridDim.x * OT_THREADS * 8) {
+  for (long i = ((long)blk * OT_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)nblk * OT_THREADS * 8) {
     float vals[8];
     const int left = (int)min(elems - i, 8L);
     if (!FIRST && res) {
@@ -1077,7 +1130,30 @@ __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
     if (tot) __hip_atomic_fetch_add(&s.hist[i], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   unsigned int early;
-  if (last_of_state(s, early)) topk_narrow<false>(s, shift, early);
+  if (last_of_state(s, (unsigned int)nblk, early)) topk_narrow<false>(s, shift, early);
+}
+
+template <typename WT, typename GT, bool VEC, bool FIRST>
+__global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
+    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, float ef_beta) {
+  __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];     // one histogram per wavefront
+  const long b = blockIdx.y;
+  const int k = blockIdx.z;
+  topk_count<WT, GT, VEC, FIRST>(w, theta_g, ef, st[(long)k * count + b], lh, elems, b, k, ef_beta, blockIdx.x,
+                                 gridDim.x);
+}
+
+// A pass over the matrices that the window left open, except for workers whose interval is one key already.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
+    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, int K,
+    float ef_beta, int most) {
+  __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];
+  if (topk_all_early(st, count * K)) return;
+  topk_each_open(st, count, K, K, most, [&](long b, int k, int blk, int nblk) {
+    TopkState& s = st[(long)k * count + b];
+    if (s.width) topk_count<WT, GT, VEC, false>(w, theta_g, ef, s, lh, elems, b, k, ef_beta, blk, nblk);
+  });
 }
 
 // Element `at` of a matrix waits for the exact threshold of this state's worker: as a primary entry with the sum
@@ -1101,21 +1177,20 @@ template <typename WT, typename GT, bool VEC, bool EARLY>
 __device__ __forceinline__ void topk_update(
     const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef,
     const ScalePtrs& thresholds, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k,
-    int nesterov, int write_back) {
+    int nesterov, int write_back, long b, int blk, int nblk) {
   __shared__ unsigned int from[MLC_MAX_WORKERS], held[MLC_MAX_WORKERS];
-  const long b = blockIdx.y;
   if (threadIdx.x < K) {
     const TopkState& s = st[(long)threadIdx.x * count + b];
     from[threadIdx.x] = s.lo;
     held[threadIdx.x] = EARLY && s.width ? 1u << s.width : 0u;          // one key: nothing has to wait
-    if (!EARLY && blockIdx.x == 0 && thresholds.p[threadIdx.x])
+    if (!EARLY && blk == 0 && thresholds.p[threadIdx.x])
       thresholds.p[threadIdx.x][b] = __uint_as_float(s.lo);
   }
   __syncthreads();
   GT* tg = theta_g + b * elems;
   float* ub = u + b * elems;
-  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * 8; i < elems;
-       i += (long)gridDim.x * OT_THREADS * 8) {
+  for (long i = ((long)blk * OT_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)nblk * OT_THREADS * 8) {
     float a[8], uv[8], acc[8];
     const int left = (int)min(elems - i, 8L);
     load8<GT, !VEC>(tg + i, left, a); load8<float, !VEC>(ub + i, left, uv);
@@ -1181,9 +1256,8 @@ template <typename WT, typename GT>
 __device__ __forceinline__ void topk_settle(
     const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef,
     const ScalePtrs& thresholds, const TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k,
-    int nesterov, int write_back) {
+    int nesterov, int write_back, long b) {
   __shared__ unsigned int tau[MLC_MAX_WORKERS], primaries[MLC_MAX_WORKERS];
-  const long b = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   GT* tg = theta_g + b * elems;
   float* ub = u + b * elems;
@@ -1252,20 +1326,35 @@ __global__ __launch_bounds__(OT_THREADS) void topk_early_kernel(
     TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
   if (topk_early(st, blockIdx.y, count, K))
     topk_update<WT, GT, VEC, true>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
-                                   write_back);
+                                   write_back, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
-// The update of the matrices that went through the three passes, and what is left of the others.
+// What is left of the matrices that the window settled, and the update of those that it left open.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(OT_THREADS) void topk_finish_kernel(
+    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
+    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
+    int most) {
+  const bool none_open = topk_all_early(st, count * K);
+  for (long b = blockIdx.x; b < count; b += gridDim.x) {
+    if (none_open || topk_early(st, b, count, K))
+      topk_settle<WT, GT>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov, write_back, b);
+    __syncthreads();                        // its shared memory may be written again
+  }
+  if (none_open) return;
+  topk_each_open(st, count, K, 1, most, [&](long b, int, int blk, int nblk) {
+    topk_update<WT, GT, VEC, false>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+                                    write_back, b, blk, nblk);
+  });
+}
+
+// The update of groups that went through the three passes from the start.
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
     WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
-    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
-    int window) {
-  if (!window || !topk_early(st, blockIdx.y, count, K))
-    topk_update<WT, GT, VEC, false>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
-                                    write_back);
-  else if (blockIdx.x == 0)
-    topk_settle<WT, GT>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov, write_back);
+    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+  topk_update<WT, GT, VEC, false>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+                                  write_back, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
 int check_launch() { return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH; }
@@ -1627,10 +1716,10 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
                       2 * esize(global_dtype) + 8;
   LaunchScope scope(MLC_KERNEL_TOPK, stream, 0.0, (double)count * elems * (passes + last));
   const float inv_k = 1.0f / (float)K;
-#define MLC_UPDATE(KERNEL, WT, GT, V, NBLK, ...)                                                    \
-  hipLaunchKernelGGL((KERNEL<WT, GT, V>), dim3(NBLK, (unsigned)count), dim3(OT_THREADS), 0, stream, w, \
-                     (GT*)theta_g, u, ef, thresholds, st, elems, (int)count, K, eta_out, mu, inv_k,  \
-                     nesterov, write_back, ##__VA_ARGS__)
+#define MLC_UPDATE(KERNEL, WT, GT, V, GRID, ...)                                                    \
+  hipLaunchKernelGGL((KERNEL<WT, GT, V>), GRID, dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, ef, \
+                     thresholds, st, elems, (int)count, K, eta_out, mu, inv_k, nesterov, write_back, ##__VA_ARGS__)
+  const dim3 all(full_grid, (unsigned)count);
   if (window) {
 #define MLC_SAMPLE(WT, GT, V)                                                                     \
   hipLaunchKernelGGL((topk_sample_kernel<WT, GT, V>), dim3((unsigned)count, K), dim3(TOPK_SAMPLE_THREADS), 0, \
@@ -1638,44 +1727,43 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
 #define MLC_WINDOW(WT, GT, V)                                                                     \
   hipLaunchKernelGGL((topk_window_kernel<WT, GT, V>), dim3(window_grid, (unsigned)count, K),                  \
                      dim3(TOPK_WINDOW_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta)
-#define MLC_CALL(WT, GT) do { if (vec) MLC_SAMPLE(WT, GT, true); else MLC_SAMPLE(WT, GT, false); } while (0)
-    MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
-#undef MLC_CALL
-#define MLC_CALL(WT, GT)                                                                          \
+#define MLC_LATE(WT, GT, V)                                                                       \
+  hipLaunchKernelGGL((topk_late_kernel<WT, GT, V>), dim3(TOPK_LATE_GRID), dim3(OT_THREADS), 0, stream, w,     \
+                     (const GT*)theta_g, ef, st, elems, (int)count, K, ef_beta, late_most)
+#define MLC_WINDOWED(WT, GT, V)                                                                   \
   do {                                                                                            \
-    if (vec) { MLC_WINDOW(WT, GT, true); MLC_UPDATE(topk_early_kernel, WT, GT, true, full_grid); }              \
-    else { MLC_WINDOW(WT, GT, false); MLC_UPDATE(topk_early_kernel, WT, GT, false, full_grid); }                \
+    MLC_SAMPLE(WT, GT, V);                                                                        \
+    MLC_WINDOW(WT, GT, V);                                                                        \
+    MLC_UPDATE(topk_early_kernel, WT, GT, V, all);                                                \
+    for (int pass = 0; pass < 3; ++pass) MLC_LATE(WT, GT, V);                                     \
+    MLC_UPDATE(topk_finish_kernel, WT, GT, V, dim3(TOPK_FINISH_GRID), finish_most);               \
   } while (0)
+#define MLC_CALL(WT, GT) do { if (vec) MLC_WINDOWED(WT, GT, true); else MLC_WINDOWED(WT, GT, false); } while (0)
+    const int late_most = cap_blocks(full, 512), finish_most = cap_blocks(full, TOPK_FINISH_GRID);
     MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
+#undef MLC_WINDOWED
+#undef MLC_LATE
 #undef MLC_WINDOW
 #undef MLC_SAMPLE
   } else {
     hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
-  }
-  // Behind a window these passes mostly find nothing to do: no more workgroups than fill the chip.
-  const int late_grid = window ? cap_blocks(full, (1024 + n_states - 1) / n_states) : full_grid;
-  for (int pass = 0; pass < 3; ++pass) {
 #define MLC_HIST(WT, GT, V, F)                                                                    \
-  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(late_grid, (unsigned)count, K),             \
-                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta, (int)window)
-#define MLC_CALL(WT, GT)                                                                          \
+  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(full_grid, (unsigned)count, K),        \
+                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta)
+#define MLC_PASSES(WT, GT, V)                                                                     \
   do {                                                                                            \
-    const bool first = pass == 0 && !window;                                                      \
-    if (vec) { if (first) MLC_HIST(WT, GT, true, true); else MLC_HIST(WT, GT, true, false); }     \
-    else { if (first) MLC_HIST(WT, GT, false, true); else MLC_HIST(WT, GT, false, false); }       \
+    MLC_HIST(WT, GT, V, true);                                                                    \
+    MLC_HIST(WT, GT, V, false);                                                                   \
+    MLC_HIST(WT, GT, V, false);                                                                   \
+    MLC_UPDATE(topk_outer_kernel, WT, GT, V, all);                                                \
   } while (0)
+#define MLC_CALL(WT, GT) do { if (vec) MLC_PASSES(WT, GT, true); else MLC_PASSES(WT, GT, false); } while (0)
     MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
+#undef MLC_PASSES
 #undef MLC_HIST
   }
-#define MLC_CALL(WT, GT)                                                                          \
-  do {                                                                                            \
-    if (vec) MLC_UPDATE(topk_outer_kernel, WT, GT, true, late_grid, (int)window);                              \
-    else MLC_UPDATE(topk_outer_kernel, WT, GT, false, late_grid, (int)window);                                 \
-  } while (0)
-  MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
-#undef MLC_CALL
 #undef MLC_UPDATE
   return check_launch();
 }
