@@ -1689,10 +1689,11 @@ size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * s
 
 // Do these states start from a sample?  The two passes over the values that it saves have to make up for
 // the sample, the listed values and the launches that find nothing left to do, some 45 us a group: groups of
-// 2.4 M values (768 x 3072, one worker) are as fast either way.  A sample
-// takes 16384 values, which a matrix has to have several times over.
-static bool topk_window(long elems, int n_states) {
-  return elems >= 65536 && (double)elems * n_states >= (double)(1 << 22);
+// 2.4 M values (768 x 3072, one worker) are as fast either way.  A sample reads 16384 values, with error feedback 10 bytes
+// each to save 8 an element: 1023 matrices of 256 x 256 take 659 us by passes and 692 by the window, 655 of 320 x 320 643
+// and 635; without it 534 and 481, 531 and 433.
+static bool topk_window(long elems, int n_states, bool feedback) {
+  return elems >= (feedback ? 98304 : 65536) && (double)elems * n_states >= (double)(1 << 22);
 }
 
 int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype, float* u,
@@ -1709,7 +1710,7 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
   const int n_states = (int)(count * K);
   const bool fb = has_residuals(ef);
   const double inputs = K * (esize(worker_dtype) + esize(global_dtype));
-  const bool window = topk_window(elems, n_states);
+  const bool window = topk_window(elems, n_states, fb);
   // the values once (or, small matrices, three times: with error feedback the inputs, then the residuals), the update
   const double passes = window ? inputs + (fb ? 8.0 * K : 0.0) : fb ? inputs + 8.0 * K + 2 * 4.0 * K : 3 * inputs;
   const double last = (fb ? 8.0 * K : K * esize(worker_dtype)) + (write_back ? K * esize(worker_dtype) : 0.0) +

@@ -122,8 +122,8 @@ def test_topk_few_distinct_magnitudes(cnt, m, n, ef, steps):
     assert_fp32_close(u.cpu().reshape(-1, n), ref["u"], "outer momentum")
 
 
-# The smallest groups that start from a sample (4 M values, matrices of 65536), one value below either, off
-# the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
+# The smallest groups that start from a sample (4 M values, matrices of 65536, of 98304 with error feedback), one value
+# below either, off the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
 # kept into one row, `grid` takes a few distinct magnitudes, `one` a single one.
 @pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,kind", [
     (1, 2048, 2048, 1, torch.bfloat16, torch.float32, 0.05, True, "normal"),
@@ -259,3 +259,27 @@ def test_topk_open_matrices_have_the_whole_chip():
             times.append(a.elapsed_time(b))
         us[name] = sorted(times)[2]
     assert us["open"] < 1.5 * us["settled"], us
+
+
+# The bytes recorded tell the route: with error feedback (K = 1, bf16 replicas) the window's pass and the update move 40
+# an element and three passes 48, without it 26 and 38.  Matrices of few values, of which the sample is a large part, take the passes.
+@pytest.mark.parametrize("cnt,m,n,ef,per_element", [
+    (64, 256, 256, True, 48), (64, 256, 256, False, 26), (65, 255, 256, False, 38), (43, 256, 384, True, 40),
+    (43, 313, 314, True, 48), (4, 1024, 1024, True, 40), (3, 1024, 1024, True, 48),
+])
+def test_topk_route_by_size(cnt, m, n, ef, per_element):
+    grp = _misled(cnt, m, n, 1, torch.bfloat16, torch.float32, ef, lambda k, i: False)
+    alone = [_clone(grp, slice(i, i + 1)) for i in range(0, cnt, 9)]
+    mlc.muloco_timing_enable(True)
+    try:
+        mlc.muloco_timing_read()
+        _topk([grp], 1, 0.05, ef)
+        torch.cuda.synchronize()
+        moved = mlc.muloco_timing_read()["topk"]["bytes"]
+    finally:
+        mlc.muloco_timing_enable(False)
+    assert moved == cnt * m * n * per_element
+    _topk(alone, 1, 0.05, ef)
+    for i, a in enumerate(alone):
+        assert torch.equal(grp.scales[0][9 * i], a.scales[0][0]), i
+        assert torch.equal(grp.global_param[9 * i], a.global_param[0]), i
