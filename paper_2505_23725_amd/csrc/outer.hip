@@ -8,6 +8,7 @@
 // The K worker replicas live on this GPU, so the average is a loop over K pointers
 // in a fixed order: ((d_1 + d_2) + ...) * (1/K).
 #include "common.h"
+#include "quant_rule.h"
 
 namespace mlc {
 namespace {
@@ -533,27 +534,6 @@ __device__ __forceinline__ void quantize_rows_reg_body(
       }
     }
   }
-}
-
-// Vectors per thread of the quantised update where a workgroup has just the wavefronts that a row of n
-// needs (G = 0), or 0: groups of 256 threads, of which a row may leave most idle in their last vector.
-// With two vectors a CU holds 16 wavefronts: rows of up to 5120 (5 to a workgroup) and over 6144 (7 and 8)
-// nearly fill it, those between (6) three quarters; over 8192 only one workgroup fits, which up to 12288 is
-// worse than 256 threads with six vectors.  Beyond, where a thread of 256 held eight or twelve vectors,
-// it is better by far.  26 M elements * 4 / (K + 3), K = 1 / 4 / 8 replicas at 4 bits and K = 2 at 8 bits with
-// error feedback, us with groups of 256 threads and with such workgroups:
-//    2560   90 / 115 / 122, 176    91 / 104 / 115, 178   (taken from three replicas on, up to 4096)
-//    4104  120 / 123 / 134, 196    96 / 119 / 124, 184
-//    6144  104 / 106 / 114, 187    89 / 114 / 127, 179   (taken up to two replicas, from 5121 on)
-//    8192  112 / 105 / 118, 189    88 / 103 / 116, 177
-//   10240   95 / 110 / 119, 187    99 / 138 / 160, 190   (not taken)
-//   16384  116 / 156 / 196, 225    96 / 128 / 161, 190
-//   24576  121 / 168 / 196, 258   109 / 131 / 158, 209   (three vectors)
-// One vector a thread and twice the wavefronts: rows of 2560 to 8192 5 to 45 % slower from four replicas on.
-static int quant_whole_row(int64_t n, int K) {
-  if (n <= 2048 || (n <= 4096 && K <= 2)) return 0;
-  if (n > 12288) return n <= 16384 ? 2 : 3;
-  return n <= 5120 || (n <= 8192 && (n > 6144 || K <= 2)) ? 2 : 0;
 }
 
 // Wavefronts per SIMD the register allocation is held to: one more than the compiler reaches on
@@ -1546,7 +1526,8 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
   // registers (24 floats per vector), so the steps are fine where it buys occupancy: 6 instead
   // of 8 vectors lets two workgroups share a CU (10240 columns: 3.3 -> 4.x TB/s with K = 4).
   const int nv = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 6;
-  const int whole = quant_whole_row(n, K);
+  const int whole = quant_whole_row(QuantRow{(long)n, K, form.bits, worker_dtype == MLC_F32,
+                                             global_dtype == MLC_BF16, has_residuals(ef), requant != 0});
   const int threads = whole ? (int)((n + whole * 512 - 1) / (whole * 512)) * 64 : OT_THREADS;
   const long rpb = OT_THREADS / g;
   const long nblk = (rows + rpb - 1) / rpb;
