@@ -29,15 +29,6 @@ PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 matrix-core peak
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E peak
 
 
-def executed_ns_flops(job, recorded: float, steps: int) -> float:
-    """The recorder counts whole output tiles; where all are 256 x 256, those on the diagonal of symmetric products run a
-    triangle only."""
-    tiles = job.ns_tile_flops()
-    if tiles is None or abs(recorded / (steps * tiles[0]) - 1) > 1e-9:
-        return recorded
-    return recorded - steps * tiles[1]
-
-
 def cpu_baseline(workload, budget_s: float):
     """Time the fp64 oracle (NumPy) on a bounded sample of the workload's matrices."""
     import numpy as np
@@ -163,7 +154,6 @@ def main() -> int:
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     timing = mlc.muloco_timing_read()
-    timing["ns_gemm"]["flops"] = executed_ns_flops(job, timing["ns_gemm"]["flops"], args.steps)
     step_ms = sorted(marks[i].elapsed_time(marks[i + 1]) for i in range(args.steps))
 
     # Spread over steps (outside the timed region): the recorder is read after every step, which
@@ -173,7 +163,7 @@ def main() -> int:
         step()
         t1 = mlc.muloco_timing_read()["ns_gemm"]
         if t1["total_ms"] > 0:
-            per_step_tf.append(executed_ns_flops(job, t1["flops"], 1) / (t1["total_ms"] * 1e-3) * 1e-12)
+            per_step_tf.append(t1["flops"] / (t1["total_ms"] * 1e-3) * 1e-12)
     per_step_tf.sort()
     mlc.muloco_timing_enable(False)
 
@@ -394,8 +384,7 @@ def main() -> int:
         for _ in range(reps):
             j2.inner_step()
             t2 = mlc.muloco_timing_read()
-            g2 = dict(t2["ns_gemm"])
-            g2["flops"] = executed_ns_flops(j2, g2["flops"], 1)
+            g2 = t2["ns_gemm"]
             per.append(g2["flops"] / (g2["total_ms"] * 1e-3) * 1e-12 if g2["total_ms"] > 0 else 0.0)
             tot["ms"] += g2["total_ms"]; tot["flops"] += g2["flops"]; tot["launches"] += g2["launches"]
             tot["all_ms"] += sum(t2[k]["total_ms"] for k in ("ns_gemm", "momentum", "norm", "update"))

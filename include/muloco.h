@@ -319,7 +319,7 @@ enum {
 typedef struct {
   int64_t launches;      /* launches recorded since the last read                      */
   double total_ms;       /* sum of their durations                                     */
-  double flops;          /* matrix-core FLOP of their output tiles (0 if n/a)          */
+  double flops;          /* matrix-core FLOP executed by those launches (0 if n/a)     */
   double bytes;          /* algorithmic HBM bytes of those launches (0 if n/a)         */
 } mlc_kernel_timing;
 

@@ -1188,8 +1188,9 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
     const int rc = make_args<BM, BN>(dj, m.seg[j]);
     if (rc != MLC_OK) return rc;
     if (j >= n) continue;
-    // of whole output tiles (9 / 16 of a 256 x 256 tile on the diagonal are executed)
-    flops += 2.0 * BM * BN * (double)dj.K * (double)m.seg[j].total_tiles;
+    // executed, not nominal: whole output tiles, and 144 of 256 MFMAs of a 256 x 256 tile on the diagonal
+    const double diagonal = BM == 256 && !BKS ? (double)m.seg[j].tiles_m * m.seg[j].batch : 0.0;
+    flops += 2.0 * BM * BN * (double)dj.K * ((double)m.seg[j].total_tiles - diagonal * 112 / 256);
     most += m.seg[j].tiles_per_xcd;
   }
   if (most < W) W = most;    // fewer tiles than compute units

@@ -278,17 +278,3 @@ class MulocoJob:
             s, l = min(mp, np_), max(mp, np_)
             tot += c * iters * (4.0 * s * s * l + 2.0 * s ** 3)
         return tot
-
-    def ns_tile_flops(self, iters: int = 5):
-        """(FLOP of whole 256 x 256 output tiles, what the triangles on the diagonal leave out of them) of one inner
-        step over all replicas, or None where a shape does not divide into such tiles.  Of a tile on the
-        diagonal of a symmetric product 144 of 256 MFMAs are executed."""
-        whole = left_out = 0.0
-        for (c, m, n) in self.shapes:
-            s, l = min(m, n), max(m, n)
-            if s % 256 or l % 256:
-                return None
-            t = s // 256
-            whole += self.K * c * iters * 2.0 * (t * (t + 1) // 2 * 65536.0 * (l + s) + float(s) * l * s)
-            left_out += self.K * c * iters * 2.0 * t * 65536.0 * (l + s) * 112 / 256
-        return whole, left_out

@@ -206,7 +206,7 @@ def ns_executed_flops(groups, iters=5):
         mp, np_ = -(-m // 128) * 128, -(-n // 128) * 128
         s, l = min(mp, np_), max(mp, np_)
 
-        def sym(t):
-            return (s // t) * (s // t + 1) // 2 * t * t
+        def sym(t):          # of a 256 x 256 tile on the diagonal 144 of 256 MFMAs are executed
+            return ((s // t) * (s // t + 1) / 2 - (s // t * 112 / 256 if t == 256 else 0)) * t * t
         total += iters * c * 2.0 * (sym(gram) * l + sym(poly) * s + s * l * s)
     return total

@@ -248,6 +248,20 @@ def test_triangles_give_the_bits_of_whole_tiles(cnt, m, n, tiles):
         assert torch.equal(out[i].view(torch.int16), few[i % 3].view(torch.int16)), i
 
 
+# The recorder counts executed FLOP: of a triangle its 144 of 256 MFMAs, also where the shape is padded and where
+# only one of the two symmetric products takes large tiles.
+@pytest.mark.parametrize("cnt,m,n,tiles", [
+    (100, 1001, 1001, (256, 256, 256)), (20, 1280, 1280, (256, 128, 256)), (40, 3328, 768, (256, 256, 256)),
+])
+def test_recorder_counts_executed_flop(cnt, m, n, tiles):
+    assert ns_tiles([(cnt, m, n)]) == [tiles]
+    _run_recorded(S.normal((cnt, m, n), S.GRAD_STD, seed=23, stream=n, dtype=torch.bfloat16), (cnt, m, n))
+    s, l = sorted(-(-x // 256) * 256 for x in (m, n))
+    t = s // 256                              # tiles a side
+    gram, poly = ((t * (t + 1) / 2 - t * 7 / 16) / t ** 2 if w == 256 else (2 * t + 1) / (4 * t) for w in tiles[:2])
+    assert abs(ns_executed_flops([(cnt, m, n)]) / (5 * cnt * 2.0 * s * s * (gram * l + poly * s + l)) - 1) < 1e-12
+
+
 @pytest.mark.parametrize("cnt,m,n", [(1, 384, 256), (2, 1000, 333), (6, 1536, 512), (48, 1024, 256), (12, 2048, 1024)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_tall_is_the_wide_result_transposed(cnt, m, n, dtype):
