@@ -418,3 +418,34 @@ def test_products_of_two_depths_side_by_side(shapes, launches):
     for x, y in zip(a, b):
         assert torch.equal(x.param.view(torch.int16), y.param.view(torch.int16))
         assert all(torch.equal(x.param[i], x.param[i % 3]) for i in range(x.param.shape[0]))
+
+
+# Triangles in a launch that mixes depths: products with and without operand A's transfers one behind the other in a
+# workgroup, and shares that end in a triangle
+@pytest.mark.parametrize("shapes", [
+    [(30, 768, 3328), (40, 2560, 768), (60, 768, 768)], [(16, 1024, 2816), (32, 1024, 1024)],
+    [(20, 1280, 2816), (30, 1280, 1280), (10, 2560, 1280)],
+])
+def test_triangles_of_several_depths_in_one_launch(shapes):
+    """The bits of the matrices one by one, in smaller tiles."""
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-3, beta=0.9)
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    few = [(torch.randn((3, *s[1:]), generator=gen, device=DEV) * S.GRAD_STD).bfloat16() for s in shapes]
+    zeros = lambda c, s, dt: torch.zeros((c, *s[1:]), dtype=dt, device=DEV)  # noqa: E731
+    together = [mlc.InnerGroup(zeros(s[0], s, torch.bfloat16), f.repeat(-(-s[0] // 3), 1, 1)[:s[0]].contiguous(),
+                               zeros(s[0], s, torch.float32), 1.0) for s, f in zip(shapes, few)]
+    assert all(t[0] == 256 for t in ns_tiles(shapes))
+    ws = torch.empty(mlc.muloco_inner_workspace_bytes(together), dtype=torch.uint8, device=DEV)
+    mlc.muloco_timing_enable(True)
+    mlc.muloco_timing_read()
+    mlc.muloco_inner_step(together, hp, ws)
+    launches = mlc.muloco_timing_read()["ns_gemm"]["launches"]
+    mlc.muloco_timing_enable(False)
+    assert launches == 15                    # the Gram products of all groups share one
+    for g, s, f in zip(together, shapes, few):
+        for i in range(3):
+            assert 256 not in ns_tiles([(1, *s[1:])])[0]
+            one = mlc.InnerGroup(zeros(1, s, torch.bfloat16), f[i:i + 1].clone(), zeros(1, s, torch.float32), 1.0)
+            mlc.muloco_inner_step([one], hp, ws)
+            for j in range(i, s[0], 3):
+                assert torch.equal(g.param[j].view(torch.int16), one.param[0].view(torch.int16)), (s, j)

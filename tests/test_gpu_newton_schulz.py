@@ -233,7 +233,7 @@ def test_stores_left_for_the_next_tile(cnt, m, n, tiles):
 
 
 # 256 x 256 tiles on the diagonal, of which a triangle is computed: as many K tiles as go without operand A's
-# transfers, and more; whole tiles before and behind them; deep and shallow products in one launch
+# transfers, and more; whole tiles before and behind them (several depths in a launch: test_gpu_inner_step.py)
 @pytest.mark.parametrize("cnt,m,n,tiles", [
     (40, 768, 2560, (256, 256, 256)), (40, 768, 3328, (256, 256, 256)), (40, 3328, 768, (256, 256, 256)),
     (20, 1280, 1280, (256, 128, 256)), (300, 512, 512, (256, 256, 256)),

@@ -283,3 +283,54 @@ def test_topk_route_by_size(cnt, m, n, ef, per_element):
     for i, a in enumerate(alone):
         assert torch.equal(grp.scales[0][9 * i], a.scales[0][0]), i
         assert torch.equal(grp.global_param[9 * i], a.global_param[0]), i
+
+
+# Not-a-numbers and infinities compare by their bit patterns, above every number: in groups that start from a sample as in
+# those that take the passes.
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,every", [
+    (4, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.05, True, (100003, 70001)),    # few: all of them are sent
+    (5, 1000, 1001, 2, torch.float32, torch.float32, 0.01, False, (64, 31)),            # more than are sent: the threshold is one
+    (3, 1024, 2048, 1, torch.bfloat16, torch.bfloat16, 0.3, True, (0, 3)),              # infinities tie
+])
+def test_topk_not_a_number_from_a_sample(cnt, m, n, K, wd, gd, frac, ef, every):
+    grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: False)
+    for w in grp.worker_params:
+        if every[0]:
+            w.view(-1)[::every[0]] = float("nan")
+        w.view(-1)[5::every[1]] = float("inf")
+        w.view(-1)[6::2 * every[1]] = -float("inf")
+    alone = [_clone(grp, slice(i, i + 1)) for i in range(cnt)]
+    assert m * n * K < 1 << 22 <= cnt * m * n * K
+    _topk([grp], K, frac, ef)
+    _topk(alone, K, frac, ef)
+    torch.cuda.synchronize()
+    bits = lambda t: t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)  # noqa: E731
+    for k in range(K):
+        assert torch.equal(bits(grp.scales[k]), bits(torch.cat([a.scales[k] for a in alone]))), k
+        if ef:
+            assert torch.equal(bits(grp.residuals[k]), bits(torch.cat([a.residuals[k] for a in alone]))), k
+    for got, ref in [(grp.global_param, [a.global_param for a in alone]), (grp.outer_momentum, [a.outer_momentum for a in alone])]:
+        ref = torch.cat(ref)
+        assert torch.equal(torch.isnan(got), torch.isnan(ref))
+        assert torch.equal(bits(torch.nan_to_num(got)), bits(torch.nan_to_num(ref)))
+
+
+# Matrices too large for the window's bins (67 M values, 20 %: some 2000 in the bin of the threshold), against the oracle's rule
+# on the device: the k-th largest magnitude, and everything from it on sent.
+def test_topk_matrix_too_large_to_settle():
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    m, n, frac = 4096, 16384, 0.2
+    tg0 = S.PARAM_STD * torch.randn(1, m, n, generator=gen, device=DEV)
+    w0 = (tg0 - S.DELTA_STD * torch.randn(1, m, n, generator=gen, device=DEV)).bfloat16()
+    e0 = 2e-3 * torch.randn(1, m, n, generator=gen, device=DEV)
+    u0 = 1e-3 * torch.randn(1, m, n, generator=gen, device=DEV)
+    grp = mlc.OuterGroup([w0.clone()], tg0.clone(), u0.clone(), None, [torch.zeros(1, device=DEV)], [e0.clone()])
+    _topk([grp], 1, frac, True)
+    v = 0.9 * e0 + (tg0 - w0.float())        # rounded after the product and after each sum, as in the kernel
+    k = -(-m * n * 2 // 10)
+    tau = v.abs().view(-1).kthvalue(m * n - k + 1).values
+    assert torch.equal(grp.scales[0], tau.view(1))
+    sent = v.abs() >= tau
+    assert torch.equal(grp.residuals[0], torch.where(sent, torch.zeros_like(v), v))
+    u1 = 0.8 * u0.double() + 0.9 * torch.where(sent, v, torch.zeros_like(v)).double()
+    assert ((grp.outer_momentum.double() - u1).norm() / u1.norm()).item() < 1e-5
