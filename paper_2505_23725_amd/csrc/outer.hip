@@ -836,22 +836,27 @@ __device__ __forceinline__ bool last_of_state(TopkState& s, unsigned int n) {
   return (ticket & TOPK_TICKETS) == n - 1;
 }
 
-// The last workgroup narrows the interval: bins of 2^shift keys from s.lo on have been counted; the one that
-// holds the rank-th largest entry is the new interval.  Thread t owns 8 adjacent bins.  WINDOW: the
-// last word holds the number of entries above all bins; where tau is not in any bin, the interval
-// becomes all keys.  st: the group's states.
-template <bool WINDOW>
-__device__ __forceinline__ void topk_narrow(TopkState& s, int shift, TopkState* st) {
+// The interval is narrowed: `nbins` bins of 2^shift keys from s.lo on have been counted; the one that
+// holds the rank-th largest entry is the new interval.  Thread t owns 8 adjacent bins, or 4 of 1024.
+// By the workgroup that ends the pass over the window (the last word holds the number of entries above all bins; where tau
+// is not in any bin, the interval becomes all keys; st: the group's states) or another pass last, or in a
+// launch of its own, which needs no atomics.
+enum Narrow { WINDOW_LAST, PASS_LAST, OWN_LAUNCH };
+template <Narrow BY>
+__device__ __forceinline__ void topk_narrow(TopkState& s, int nbins, int shift, TopkState* st) {
+  constexpr bool WINDOW = BY == WINDOW_LAST;
   __shared__ unsigned int part[OT_THREADS / 64];  // entries in the bins of a wavefront
   constexpr int PER = TOPK_BINS / OT_THREADS;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, per = WINDOW || nbins > TOPK_BINS / 2 ? PER : PER / 2;
   const bool owns = t < OT_THREADS;
   unsigned int h[PER] = {};
   unsigned int mine = 0u, beyond = 0u;
   if (owns) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      h[i] = __hip_atomic_load(&s.hist[t * PER + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (i >= per) break;
+      h[i] = BY == OWN_LAUNCH ? s.hist[t * per + i]
+                              : __hip_atomic_load(&s.hist[t * per + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (WINDOW && i == PER - 1 && t == OT_THREADS - 1) h[i] = 0u;
       mine += h[i];
     }
@@ -874,9 +879,11 @@ __device__ __forceinline__ void topk_narrow(TopkState& s, int shift, TopkState* 
   }
   if (!owns) return;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) s.hist[t * PER + i] = 0u;     // for the next pass, or the counts of the list
+  for (int i = 0; i < PER; ++i)
+    if (i < per) s.hist[t * per + i] = 0u;                    // for the next pass, or the counts of the list
   // (other states' workgroups may be setting TOPK_OPEN in the first of these words)
-  if (t == 0) __hip_atomic_fetch_and(&s.ctl, ~TOPK_TICKETS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (BY != OWN_LAUNCH && t == 0)
+    __hip_atomic_fetch_and(&s.ctl, ~TOPK_TICKETS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   auto left_open = [&] { __hip_atomic_fetch_or(&st->ctl, TOPK_OPEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   if (WINDOW && (beyond >= rank || beyond + total < rank)) {
     if (t == 0) { s.lo = 0u; s.width = 31u; left_open(); }
@@ -891,7 +898,7 @@ __device__ __forceinline__ void topk_narrow(TopkState& s, int shift, TopkState* 
         else ab += h[i];
       }
     }
-    s.lo = lo + ((unsigned int)(t * PER + pick) << shift);
+    s.lo = lo + ((unsigned int)(t * per + pick) << shift);
     s.width = (unsigned int)shift;
     s.rank = rank - ab;
     if constexpr (WINDOW) {
@@ -951,7 +958,7 @@ __global__ __launch_bounds__(TOPK_WINDOW_THREADS) void topk_window_kernel(
   __syncthreads();
   for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_WINDOW_THREADS)
     if (lh[i]) __hip_atomic_fetch_add(&s.hist[i], lh[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (last_of_state(s, gridDim.x)) topk_narrow<true>(s, (int)shift, st);
+  if (last_of_state(s, gridDim.x)) topk_narrow<WINDOW_LAST>(s, TOPK_BINS, (int)shift, st);
 }
 
 // The first digits (bits from `shift` up) of a lane's first cnt of 8 values.  They mostly change
@@ -1062,14 +1069,18 @@ __device__ __forceinline__ void topk_each_open(const TopkState* st, int count, i
   }
 }
 
+// Digits of 11, 10 and 10 bits, by the width of the interval.
+__device__ __forceinline__ int topk_shift(unsigned int width) { return width > 20u ? 20 : width > 10u ? 10 : 0; }
+
 // One pass of the radix select over a state's interval, by workgroup blk of nblk.  FIRST: the pass over all keys that
-// computes v, where no window was tried (with error feedback it leaves v in E).
+// computes v, where no window was tried (with error feedback it leaves v in E).  `pick`: the workgroup that ends last narrows
+// the interval; otherwise topk_pick_kernel does.
 template <typename WT, typename GT, bool VEC, bool FIRST>
 __device__ __forceinline__ void topk_count(const WorkerPtrs& w, const GT* __restrict__ theta_g, const ResidualPtrs& ef,
                                            TopkState& s, unsigned int (&lh)[OT_THREADS / 64][TOPK_BINS], long elems,
-                                           long b, int k, float ef_beta, int blk, int nblk) {
+                                           long b, int k, float ef_beta, int blk, int nblk, bool pick) {
   const unsigned int lo = FIRST ? 0u : s.lo, width = FIRST ? 31u : s.width;
-  const int shift = width > 20u ? 20 : width > 10u ? 10 : 0;   // digits of 11, 10 and 10 bits
+  const int shift = topk_shift(width);
   const int nbins = 1 << (width - shift);
   for (int wv = 0; wv < OT_THREADS / 64; ++wv)
     for (int i = threadIdx.x; i < nbins; i += OT_THREADS) lh[wv][i] = 0u;
@@ -1116,17 +1127,24 @@ __device__ __forceinline__ void topk_count(const WorkerPtrs& w, const GT* __rest
     for (int wv = 0; wv < OT_THREADS / 64; ++wv) tot += lh[wv][i];
     if (tot) __hip_atomic_fetch_add(&s.hist[i], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (last_of_state(s, (unsigned int)nblk)) topk_narrow<false>(s, shift, nullptr);
+  if (pick && last_of_state(s, (unsigned int)nblk)) topk_narrow<PASS_LAST>(s, nbins, shift, nullptr);
 }
 
 template <typename WT, typename GT, bool VEC, bool FIRST>
 __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, float ef_beta) {
+    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, float ef_beta,
+    int pick) {
   __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];     // one histogram per wavefront
   const long b = blockIdx.y;
   const int k = blockIdx.z;
   topk_count<WT, GT, VEC, FIRST>(w, theta_g, ef, st[(long)k * count + b], lh, elems, b, k, ef_beta, blockIdx.x,
-                                 gridDim.x);
+                                 gridDim.x, pick != 0);
+}
+
+__global__ __launch_bounds__(OT_THREADS) void topk_pick_kernel(TopkState* st) {
+  TopkState& s = st[blockIdx.x];
+  const int shift = topk_shift(s.width);
+  topk_narrow<OWN_LAUNCH>(s, 1 << (s.width - shift), shift, nullptr);
 }
 
 // A pass over the matrices that the window left open, except for workers whose interval is one key already.
@@ -1138,7 +1156,7 @@ __global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
   if (topk_all_early(st)) return;
   topk_each_open(st, count, K, K, most, [&](long b, int k, int blk, int nblk) {
     TopkState& s = st[(long)k * count + b];
-    if (s.width) topk_count<WT, GT, VEC, false>(w, theta_g, ef, s, lh, elems, b, k, ef_beta, blk, nblk);
+    if (s.width) topk_count<WT, GT, VEC, false>(w, theta_g, ef, s, lh, elems, b, k, ef_beta, blk, nblk, true);
   });
 }
 
@@ -1674,6 +1692,9 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
 
 size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * sizeof(TopkState); }
 
+// Workgroups of a counting pass up to which the one that ends last picks the digit.
+constexpr long TOPK_LAST_PICKS = 512;
+
 // Do these states start from a sample?  The two passes over the values that it saves have to make up for
 // the sample, the listed values and the launches that find nothing left to do, some 45 us a group: groups of
 // 2.4 M values (768 x 3072, one worker) are as fast either way.  A sample reads 16384 values, with error feedback 10 bytes
@@ -1736,9 +1757,11 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
 #undef MLC_SAMPLE
   } else {
     hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
+    const bool last_picks = (long)full_grid * n_states <= TOPK_LAST_PICKS;
 #define MLC_HIST(WT, GT, V, F)                                                                    \
   hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(full_grid, (unsigned)count, K),        \
-                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta)
+                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta, (int)last_picks);   \
+  if (!last_picks) hipLaunchKernelGGL(topk_pick_kernel, dim3(n_states), dim3(OT_THREADS), 0, stream, st)
 #define MLC_PASSES(WT, GT, V)                                                                     \
   do {                                                                                            \
     MLC_HIST(WT, GT, V, true);                                                                    \

@@ -334,3 +334,35 @@ def test_topk_matrix_too_large_to_settle():
     assert torch.equal(grp.residuals[0], torch.where(sent, torch.zeros_like(v), v))
     u1 = 0.8 * u0.double() + 0.9 * torch.where(sent, v, torch.zeros_like(v)).double()
     assert ((grp.outer_momentum.double() - u1).norm() / u1.norm()).item() < 1e-5
+
+
+def _terabytes_per_second(first, K, frac, ef):
+    """Recorded bytes of a call over its median time."""
+    rates = []
+    mlc.muloco_timing_enable(True)
+    try:
+        for _ in range(7):
+            grp = _clone(first)
+            torch.cuda.synchronize()
+            mlc.muloco_timing_read()
+            _topk([grp], K, frac, ef)
+            torch.cuda.synchronize()
+            t = mlc.muloco_timing_read()["topk"]
+            rates.append(t["bytes"] / t["total_ms"] * 1e-9)
+    finally:
+        mlc.muloco_timing_enable(False)
+    return sorted(rates)[3]
+
+
+def test_topk_many_small_matrices_run_at_memory_speed():
+    """4000 matrices of 128 x 128, four workers: 4.2 of the 5 TB/s that a stream reaches.  (Where the last workgroup
+    of every state picked the digit, all 128000 took a ticket and waited for it: 2.3.)"""
+    grp = _misled(4000, 128, 128, 4, torch.bfloat16, torch.float32, True, lambda k, i: False)
+    assert _terabytes_per_second(grp, 4, 0.05, True) > 3.0
+
+
+# as many workgroups a pass as the last picks among, and more
+@pytest.mark.parametrize("cnt,m,n,K", [(64, 128, 128, 1), (65, 128, 128, 1), (2, 1024, 512, 1), (1, 1024, 512, 3), (513, 8, 16, 1)])
+@pytest.mark.parametrize("ef", [False, True])
+def test_topk_digits_picked_last_and_in_launches(cnt, m, n, K, ef):
+    test_topk_outer_step_matches_oracle(cnt, m, n, K, torch.bfloat16, torch.float32, 0.03, ef)
