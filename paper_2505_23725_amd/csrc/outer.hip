@@ -881,12 +881,19 @@ __device__ __forceinline__ void topk_narrow(TopkState& s, int nbins, int shift, 
 #pragma unroll
   for (int i = 0; i < PER; ++i)
     if (i < per) s.hist[t * per + i] = 0u;                    // for the next pass, or the counts of the list
-  // (other states' workgroups may be setting TOPK_OPEN in the first of these words)
-  if (BY != OWN_LAUNCH && t == 0)
+  if (BY == PASS_LAST && t == 0)
     __hip_atomic_fetch_and(&s.ctl, ~TOPK_TICKETS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  auto left_open = [&] { __hip_atomic_fetch_or(&st->ctl, TOPK_OPEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto set_early = [&](bool early) {
+    if (&s != st) {
+      s.ctl = early ? TOPK_EARLY : 0u;
+    } else {                       // other states' workgroups may be setting TOPK_OPEN in this word
+      __hip_atomic_fetch_and(&s.ctl, ~TOPK_TICKETS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (early) __hip_atomic_fetch_or(&s.ctl, TOPK_EARLY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!early) __hip_atomic_fetch_or(&st->ctl, TOPK_OPEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   if (WINDOW && (beyond >= rank || beyond + total < rank)) {
-    if (t == 0) { s.lo = 0u; s.width = 31u; left_open(); }
+    if (t == 0) { s.lo = 0u; s.width = 31u; set_early(false); }
   } else if (above < rank && above + mine >= rank) {
     unsigned int ab = above, held = h[0];
     int pick = 0;
@@ -901,12 +908,7 @@ __device__ __forceinline__ void topk_narrow(TopkState& s, int nbins, int shift, 
     s.lo = lo + ((unsigned int)(t * per + pick) << shift);
     s.width = (unsigned int)shift;
     s.rank = rank - ab;
-    if constexpr (WINDOW) {
-      if (held <= (unsigned int)TOPK_LIST || shift == 0)
-        __hip_atomic_fetch_or(&s.ctl, TOPK_EARLY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else
-        left_open();
-    }
+    if (WINDOW) set_early(held <= (unsigned int)TOPK_LIST || shift == 0);
   }
 }
 
@@ -1027,6 +1029,9 @@ __device__ __forceinline__ bool topk_all_early(const TopkState* st) {
 // a bf16 global copy, whose ties the window does not settle, 1125 us, now 579; 4096 x 16384, eight workers, 20 % without
 // error feedback, 2627, now 1435; one open matrix of 64 of 768 x 768, eight workers, 2688, now 1717.)
 constexpr int TOPK_LATE_GRID = 1024, TOPK_FINISH_GRID = 2048;
+// Workgroups for the elements that wait, at least one a matrix.  (Those that find none are not free: 24 matrices of 2048 x
+// 2048, eight workers, 18 us with four a matrix, 27 with 16, 63 with 64.)
+constexpr int TOPK_SETTLE_GRID = 128, TOPK_SETTLE_MOST = 64;
 template <typename Work>
 __device__ __forceinline__ void topk_each_open(const TopkState* st, int count, int K, int parts, int most,
                                                Work&& work) {
@@ -1147,19 +1152,6 @@ __global__ __launch_bounds__(OT_THREADS) void topk_pick_kernel(TopkState* st) {
   topk_narrow<OWN_LAUNCH>(s, 1 << (s.width - shift), shift, nullptr);
 }
 
-// A pass over the matrices that the window left open, except for workers whose interval is one key already.
-template <typename WT, typename GT, bool VEC>
-__global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, int K,
-    float ef_beta, int most) {
-  __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];
-  if (topk_all_early(st)) return;
-  topk_each_open(st, count, K, K, most, [&](long b, int k, int blk, int nblk) {
-    TopkState& s = st[(long)k * count + b];
-    if (s.width) topk_count<WT, GT, VEC, false>(w, theta_g, ef, s, lh, elems, b, k, ef_beta, blk, nblk, true);
-  });
-}
-
 // Element `at` of a matrix waits for the exact threshold of this state's worker: as a primary entry with the sum
 // over the workers before it, or, where an earlier worker's list has it, as one that only counts.  A settled
 // state's interval holds at most TOPK_LIST values; the bounds are for residuals that share memory.
@@ -1253,74 +1245,137 @@ __device__ __forceinline__ void topk_update(
   }
 }
 
-// The thresholds of a matrix that topk_update<EARLY> went over, by one workgroup: a wavefront takes a worker's list and finds the
-// rank-th largest of its keys, built bit by bit from counts that ballots give; then the elements that waited, from
-// the first worker that made them wait on.  Bound by the latency of a few dependent loads.
+// The threshold of a state whose matrix topk_update<EARLY> went over, by one wavefront: the rank-th largest of the keys
+// listed, built bit by bit from counts that ballots give.  The interval becomes that key.  Bound by latency: a lane
+// requests four entries and their values at a time.
 template <typename WT, typename GT>
-__device__ __forceinline__ void topk_settle(
-    const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef,
-    const ScalePtrs& thresholds, const TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k,
-    int nesterov, int write_back, long b) {
-  __shared__ unsigned int tau[MLC_MAX_WORKERS], primaries[MLC_MAX_WORKERS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  GT* tg = theta_g + b * elems;
-  float* ub = u + b * elems;
-  auto value = [&](int k, long at) {
-    at = min(at, elems - 1);
-    return ef.p[k] ? ef.p[k][b * elems + at]
-                   : Vec8<GT>::load1(tg + at) - Vec8<WT>::load1(reinterpret_cast<const WT*>(w.p[k]) + b * elems + at);
-  };
-  for (int k = wave; k < K; k += OT_THREADS / 64) {
-    const TopkState& s = st[(long)k * count + b];
-    const unsigned int lo = s.lo, rank = s.rank;
-    const int width = (int)s.width;
-    const int first = width ? (int)min(s.hist[TOPK_BINS - 2], (unsigned int)TOPK_LIST) : 0;
-    const int n = width ? (int)min(first + s.hist[TOPK_BINS - 1], (unsigned int)TOPK_LIST) : 0;
-    constexpr int PER = (TOPK_LIST + 63) / 64;
-    unsigned int at[PER];                 // distance from lo, plus one: 0 is no entry
+__device__ __forceinline__ void topk_threshold(const WorkerPtrs& w, const GT* __restrict__ theta_g,
+                                               const ResidualPtrs& ef, const ScalePtrs& thresholds, TopkState& s,
+                                               long elems, long b, int k) {
+  constexpr int PER = (TOPK_LIST + 63) / 64, SIDE = 4;
+  static_assert(PER % SIDE == 0, "whole batches");
+  const int lane = threadIdx.x & 63;
+  const unsigned int lo = s.lo, rank = s.rank;
+  const int width = (int)s.width;
+  const int first = width ? (int)min(s.hist[TOPK_BINS - 2], (unsigned int)TOPK_LIST) : 0;
+  const int n = width ? (int)min(first + s.hist[TOPK_BINS - 1], (unsigned int)TOPK_LIST) : 0;
+  const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
+  const GT* tg = theta_g + b * elems;
+  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
+  unsigned int key[PER];                  // distance from lo, plus one: 0 is no entry
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = i * 64 + lane;
-      at[i] = e < n ? magnitude_key(value(k, s.hist[e < first ? 2 * e : TOPK_BINS - 3 - (e - first)])) - lo + 1u : 0u;
-    }
-    unsigned int best = 0u;
-    for (int bit = width - 1; bit >= 0; --bit) {
-      const unsigned int next = best | 1u << bit;
-      unsigned int reach = 0u;
+  for (int i = 0; i < PER; i += SIDE) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (i * 64 < n) reach += (unsigned int)__popcll(__ballot(at[i] > next));
-      if (reach >= rank) best = next;
-    }
-    if (lane == 0) {
-      tau[k] = lo + best;
-      primaries[k] = (unsigned int)first;
-      if (thresholds.p[k]) thresholds.p[k][b] = __uint_as_float(lo + best);
+    for (int j = 0; j < SIDE; ++j) key[i + j] = 0u;
+    if (i * 64 < n) {
+      long at[SIDE];
+      float v[SIDE];
+#pragma unroll
+      for (int j = 0; j < SIDE; ++j) {
+        const int e = min((i + j) * 64 + lane, n - 1);
+        at[j] = min((long)s.hist[e < first ? 2 * e : TOPK_BINS - 3 - (e - first)], elems - 1);
+      }
+      if (res) {
+#pragma unroll
+        for (int j = 0; j < SIDE; ++j) v[j] = res[at[j]];
+      } else {
+#pragma unroll
+        for (int j = 0; j < SIDE; ++j) v[j] = Vec8<GT>::load1(tg + at[j]) - Vec8<WT>::load1(tk + at[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < SIDE; ++j) if ((i + j) * 64 + lane < n) key[i + j] = magnitude_key(v[j]) - lo + 1u;
     }
   }
+  unsigned int best = 0u;
+  for (int bit = width - 1; bit >= 0; --bit) {
+    const unsigned int next = best | 1u << bit;
+    unsigned int reach = 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (i * 64 < n) reach += (unsigned int)__popcll(__ballot(key[i] > next));
+    if (reach >= rank) best = next;
+  }
+  if (lane == 0) {
+    s.lo = lo + best;
+    s.width = 0u;
+    if (thresholds.p[k]) thresholds.p[k][b] = __uint_as_float(lo + best);
+  }
+}
+
+// The elements of matrix b that topk_update<EARLY> left waiting, from the first worker that made them wait on, by workgroup blk of
+// nblk, once the thresholds are there.  A lane requests four workers' values at a time.  (By one workgroup a matrix, thresholds
+// included and value by value: 177 us for 1024 x 1024, eight workers with lists of 700; a call on 768 x 3072, sixteen bf16 workers of a
+// bf16 global copy, took 445 us, 167 like this, and on 24 of 2048 x 2048, eight workers with lists of 60, 43 us of it and 17.)
+template <typename WT, typename GT>
+__device__ __forceinline__ void topk_settle(
+    const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef, const TopkState* st,
+    long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back, long b, int blk,
+    int nblk) {
+  __shared__ unsigned int tau[MLC_MAX_WORKERS], primaries[MLC_MAX_WORKERS];
+  constexpr int SIDE = 4;
+  if ((int)threadIdx.x < K) {
+    const TopkState& s = st[(long)threadIdx.x * count + b];
+    tau[threadIdx.x] = s.lo;
+    primaries[threadIdx.x] = min(s.hist[TOPK_BINS - 2], (unsigned int)TOPK_LIST);
+  }
   __syncthreads();
+  GT* tg = theta_g + b * elems;
+  float* ub = u + b * elems;
   int k0 = 0;
   unsigned int before = 0u;                 // primary entries of the workers before k0
-  for (unsigned int e = threadIdx.x;; e += OT_THREADS) {
+  for (unsigned int e = blk * OT_THREADS + threadIdx.x;; e += nblk * OT_THREADS) {
     while (k0 < K && e - before >= primaries[k0]) before += primaries[k0++];
     if (k0 == K) break;
     const TopkState& s = st[(long)k0 * count + b];
     const long at = s.hist[2 * (e - before)];
-    if (at >= elems) continue;
     float acc = __uint_as_float(s.hist[2 * (e - before) + 1]);
-    for (int k = k0; k < K; ++k) {
-      const float v = value(k, at);
-      const bool keep = magnitude_key(v) >= tau[k];
-      acc += keep ? v : 0.f;
-      if (ef.p[k] && keep) ef.p[k][b * elems + at] = 0.f;
-    }
+    if (at >= elems) continue;
     float a = Vec8<GT>::load1(tg + at), uv = ub[at];
+    // (from the first lane's worker, which no lane precedes: a wavefront reads one worker's values at a time)
+    for (int kk = __builtin_amdgcn_readfirstlane(k0); kk < K; kk += SIDE) {
+      float v[SIDE];
+#pragma unroll
+      for (int i = 0; i < SIDE; ++i) {
+        const int k = min(kk + i, K - 1);
+        v[i] = ef.p[k] ? ef.p[k][b * elems + at] : a - Vec8<WT>::load1(reinterpret_cast<const WT*>(w.p[k]) + b * elems + at);
+      }
+#pragma unroll
+      for (int i = 0; i < SIDE; ++i) {
+        if (kk + i >= K) break;
+        const bool keep = kk + i >= k0 && magnitude_key(v[i]) >= tau[kk + i];
+        acc += keep ? v[i] : 0.f;
+        if (ef.p[kk + i] && keep) ef.p[kk + i][b * elems + at] = 0.f;
+      }
+    }
     outer_update<GT>(a, uv, __fmul_rn(acc, inv_k), eta, mu, nesterov);
     Vec8<GT>::store1(tg + at, a);
     ub[at] = uv;
     if (write_back)
       for (int k = 0; k < K; ++k) Vec8<WT>::store1(reinterpret_cast<WT*>(w.p[k]) + b * elems + at, a);
   }
+}
+
+// What the window left: a pass over the matrices left open, except for workers whose interval is one key already, and, in the
+// first of these launches, the thresholds of the others.
+template <typename WT, typename GT, bool VEC>
+__global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
+    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, ScalePtrs thresholds, TopkState* st, long elems,
+    int count, int K, float ef_beta, int most, int first) {
+  __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];
+  const bool none_open = topk_all_early(st);
+  if (first)
+    for (long i = (long)blockIdx.x * (OT_THREADS / 64) + (threadIdx.x >> 6); i < (long)count * K;
+         i += (long)gridDim.x * (OT_THREADS / 64)) {
+      const int k = (int)(i / count), lane = threadIdx.x & 63;
+      const long b = i - (long)k * count;
+      if (none_open || __all(lane >= K || state_early(st[(long)min(lane, K - 1) * count + b])))
+        topk_threshold<WT, GT>(w, theta_g, ef, thresholds, st[i], elems, b, k);
+    }
+  if (none_open) return;
+  topk_each_open(st, count, K, K, most, [&](long b, int k, int blk, int nblk) {
+    TopkState& s = st[(long)k * count + b];
+    if (s.width) topk_count<WT, GT, VEC, false>(w, theta_g, ef, s, lh, elems, b, k, ef_beta, blk, nblk, true);
+  });
 }
 
 // The update behind the pass over the window.
@@ -1340,9 +1395,12 @@ __global__ __launch_bounds__(OT_THREADS) void topk_finish_kernel(
     TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
     int most) {
   const bool none_open = topk_all_early(st);
-  for (long b = blockIdx.x; b < count; b += gridDim.x) {
+  const int parts = max(min(TOPK_SETTLE_GRID / count, TOPK_SETTLE_MOST), 1);
+  for (int i = blockIdx.x; i < count * parts; i += gridDim.x) {
+    const long b = i / parts;
     if (none_open || topk_early(st, b, count, K))
-      topk_settle<WT, GT>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov, write_back, b);
+      topk_settle<WT, GT>(w, theta_g, u, ef, st, elems, count, K, eta, mu, inv_k, nesterov, write_back, b,
+                          i - (int)b * parts, parts);
     __syncthreads();                        // its shared memory may be written again
   }
   if (none_open) return;
@@ -1738,7 +1796,7 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
                      dim3(TOPK_WINDOW_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta)
 #define MLC_LATE(WT, GT, V)                                                                       \
   hipLaunchKernelGGL((topk_late_kernel<WT, GT, V>), dim3(TOPK_LATE_GRID), dim3(OT_THREADS), 0, stream, w,     \
-                     (const GT*)theta_g, ef, st, elems, (int)count, K, ef_beta, late_most)
+                     (const GT*)theta_g, ef, thresholds, st, elems, (int)count, K, ef_beta, late_most, (int)(pass == 0))
 #define MLC_WINDOWED(WT, GT, V)                                                                   \
   do {                                                                                            \
     MLC_SAMPLE(WT, GT, V);                                                                        \

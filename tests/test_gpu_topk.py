@@ -366,3 +366,47 @@ def test_topk_many_small_matrices_run_at_memory_speed():
 @pytest.mark.parametrize("ef", [False, True])
 def test_topk_digits_picked_last_and_in_launches(cnt, m, n, K, ef):
     test_topk_outer_step_matches_oracle(cnt, m, n, K, torch.bfloat16, torch.float32, 0.03, ef)
+
+
+def _crowded(cnt, m, n, K, wd, gd, ef, seed=5):
+    """Values of which a tenth lies close about one magnitude, the threshold's at 5 %: long lists."""
+    grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: False, seed)
+    gen = torch.Generator(device=DEV).manual_seed(seed + 1)
+    for k in range(K):
+        d = 1e-3 * torch.randn(cnt, m, n, generator=gen, device=DEV)
+        at = torch.rand(cnt, m, n, generator=gen, device=DEV) < 0.1
+        d[at] = (0.02 + 2e-4 * torch.randn(int(at.sum()), generator=gen, device=DEV)) * torch.sign(d[at])
+        if ef:
+            grp.residuals[k].zero_()
+        grp.worker_params[k].copy_(grp.global_param.float() - d)
+    return grp
+
+
+# Lists of many entries and of many workers, elements that several workers' lists hold, more matrices than
+# workgroups for them: the same bits as matrix by matrix, where groups of less than 4 M values take the passes.
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,ef", [
+    (17, 1024, 1024, 3, torch.float32, torch.float32, False), (9, 768, 768, 6, torch.float32, torch.float32, True),
+    (150, 300, 300, 3, torch.float32, torch.bfloat16, True), (7, 500, 1001, 8, torch.bfloat16, torch.float32, True),
+    (40, 257, 1023, 7, torch.bfloat16, torch.bfloat16, False),
+])
+def test_topk_long_lists(cnt, m, n, K, wd, gd, ef):
+    grp = _crowded(cnt, m, n, K, wd, gd, ef)
+    alone = [_clone(grp, slice(i, i + 1)) for i in range(cnt)]
+    assert m * n * K < 1 << 22 <= cnt * m * n * K
+    _topk([grp], K, 0.05, ef)
+    _topk(alone, K, 0.05, ef)
+    torch.cuda.synchronize()
+    for k in range(K):
+        assert torch.equal(grp.scales[k], torch.cat([a.scales[k] for a in alone])), k
+        assert torch.equal(grp.worker_params[k], torch.cat([a.worker_params[k] for a in alone])), k
+        if ef:
+            assert torch.equal(grp.residuals[k], torch.cat([a.residuals[k] for a in alone])), k
+    assert torch.equal(grp.global_param, torch.cat([a.global_param for a in alone]))
+    assert torch.equal(grp.outer_momentum, torch.cat([a.outer_momentum for a in alone]))
+
+
+def test_topk_long_lists_do_not_hold_a_call_up():
+    """768 x 3072, sixteen bf16 workers of a bf16 global copy, whose ties make lists of hundreds: 2 TB/s of the recorded bytes
+    (0.7 when one workgroup settled all of them)."""
+    grp = _misled(1, 768, 3072, 16, torch.bfloat16, torch.bfloat16, False, lambda k, i: False)
+    assert _terabytes_per_second(grp, 16, 0.05, False) > 1.3
