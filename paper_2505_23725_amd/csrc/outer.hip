@@ -1753,13 +1753,21 @@ size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * s
 // Workgroups of a counting pass up to which the one that ends last picks the digit.
 constexpr long TOPK_LAST_PICKS = 512;
 
-// Do these states start from a sample?  The two passes over the values that it saves have to make up for
-// the sample, the listed values and the launches that find nothing left to do, some 45 us a group: groups of
-// 2.4 M values (768 x 3072, one worker) are as fast either way.  A sample reads 16384 values, with error feedback 10 bytes
-// each to save 8 an element: 1023 matrices of 256 x 256 take 659 us by passes and 692 by the window, 655 of 320 x 320 643
-// and 635; without it 534 and 481, 531 and 433.
-static bool topk_window(long elems, int n_states, bool feedback) {
-  return elems >= (feedback ? 98304 : 65536) && (double)elems * n_states >= (double)(1 << 22);
+// Do these states start from a sample?  Microseconds that the window saves over the passes and that it costs, fitted to 1720
+// groups of 3 to 70 M values (matrices of 256 x 256 to 2048 x 8192, 1 to 16 workers, calls one behind the other) that
+// were timed both ways.  The workgroups of two passes, each of which adds its histogram to its state's, cost
+// more than the bytes; the window, the sample of 16384 values a state, three launches that find little to do, and the lists, which
+// are longer where values tie.  A single large matrix is read by 256 workgroups in every pass, and gains from 6 M values on.  By passes
+// and by the window, us: 16 of 512 x 512 67 and 61, 4 of 1024 x 1024 62 and 60, 8 of them 100 and 84; without error feedback 1024 x 1024
+// with four workers 46 and 49, two of 1536 x 1536 with two 63 and 68, 16 of 512 x 512 with two 73 and 59.  Over all groups the choice takes
+// 1.004 of the faster way's time and 0.84 of that by passes, and in eight of them 1.02 to 1.07 of it.
+static bool topk_window(long elems, int64_t count, int K, int blocks, bool feedback, bool ties) {
+  const double states = (double)count * K, values = elems * states * 1e-6, workgroups = blocks * states;
+  if (elems < 65536 || elems * states < (double)(1 << 22)) return false;
+  if (elems >= 6 << 20) return true;
+  if (feedback) return 0.37 * values + 0.0071 * workgroups > 10.5 + 0.25 * K + 0.5 * K / count + 0.13 * states;
+  if (ties) return 0.1 * values + 0.0056 * workgroups > 10.0 + 0.8 * K + 0.065 * states;
+  return 0.77 * values + 0.0048 * workgroups > 10.0 + 0.7 * K + 0.35 * K / count + 0.11 * states;
 }
 
 int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype, float* u,
@@ -1776,7 +1784,8 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
   const int n_states = (int)(count * K);
   const bool fb = has_residuals(ef);
   const double inputs = K * (esize(worker_dtype) + esize(global_dtype));
-  const bool window = topk_window(elems, n_states, fb);
+  const bool window = topk_window(elems, count, K, full_grid, fb,
+                                  worker_dtype == MLC_BF16 && global_dtype == MLC_BF16);
   // the values once (or, small matrices, three times: with error feedback the inputs, then the residuals), the update
   const double passes = window ? inputs + (fb ? 8.0 * K : 0.0) : fb ? inputs + 8.0 * K + 2 * 4.0 * K : 3 * inputs;
   const double last = (fb ? 8.0 * K : K * esize(worker_dtype)) + (write_back ? K * esize(worker_dtype) : 0.0) +

@@ -122,8 +122,7 @@ def test_topk_few_distinct_magnitudes(cnt, m, n, ef, steps):
     assert_fp32_close(u.cpu().reshape(-1, n), ref["u"], "outer momentum")
 
 
-# The smallest groups that start from a sample (4 M values, matrices of 65536, of 98304 with error feedback), one value
-# below either, off the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
+# Groups of about 4 M values (by the passes; test_topk_from_a_sample_of_larger_groups has those that start from a sample) off the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
 # kept into one row, `grid` takes a few distinct magnitudes, `one` a single one.
 @pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,kind", [
     (1, 2048, 2048, 1, torch.bfloat16, torch.float32, 0.05, True, "normal"),
@@ -214,25 +213,49 @@ def _topk(groups, K, frac, ef):
     mlc.muloco_topk_outer_step(groups, hp, frac, wsp)
 
 
-# Groups of which the window leaves some matrices open (one of them, some of more than are listed at a time, those of
-# one worker, all), or a matrix too large for its bins: the same bits as matrix by matrix, where
-# groups of less than 4 M values take three passes from the start.
+def _bytes(grp, K, ef, window):
+    """What the recorder counts for a group, by its route."""
+    w, g = (2 if t.dtype == torch.bfloat16 else 4 for t in (grp.worker_params[0], grp.global_param))
+    values = K * (w + g)
+    values = (values + 8 * K if ef else values) if window else (values + 16 * K if ef else 3 * values)
+    return grp.global_param.numel() * (values + (8 * K if ef else K * w) + K * w + 2 * g + 8)
+
+
+def _recorded(groups, K, frac, ef):
+    mlc.muloco_timing_enable(True)
+    try:
+        mlc.muloco_timing_read()
+        _topk(groups, K, frac, ef)
+        torch.cuda.synchronize()
+        return mlc.muloco_timing_read()["topk"]["bytes"]
+    finally:
+        mlc.muloco_timing_enable(False)
+
+
+def _together_and_alone(grp, K, frac, ef):
+    """The matrices of a group that starts from a sample, also one by one, which take the passes."""
+    alone = [_clone(grp, slice(i, i + 1)) for i in range(grp.global_param.shape[0])]
+    assert _recorded([grp], K, frac, ef) == _bytes(grp, K, ef, True)
+    assert _recorded(alone, K, frac, ef) == sum(_bytes(a, K, ef, False) for a in alone)
+    return alone
+
+
+# Groups of which the window leaves some matrices open (one of them, the first, the last, some of more than are listed at a time,
+# those of one worker, all), or whose ties do: the same bits as matrix by matrix.
 @pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,which", [
-    (5, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.05, True, "one"),
+    (8, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.05, True, "one"),
     (300, 512, 512, 1, torch.bfloat16, torch.float32, 0.05, True, "some"),
+    (300, 300, 301, 2, torch.bfloat16, torch.float32, 0.05, False, "first"),
+    (260, 256, 256, 3, torch.bfloat16, torch.float32, 0.05, True, "last"),
     (12, 513, 517, 3, torch.float32, torch.float32, 0.1, False, "worker"),
-    (6, 768, 768, 2, torch.bfloat16, torch.bfloat16, 0.02, False, "all"),
+    (9, 768, 768, 2, torch.bfloat16, torch.bfloat16, 0.02, False, "all"),
     (4, 1000, 1001, 3, torch.bfloat16, torch.float32, 0.3, True, "all"),
-    (3, 1024, 2048, 1, torch.bfloat16, torch.bfloat16, 0.05, False, "ties"),
+    (12, 1024, 2048, 1, torch.bfloat16, torch.bfloat16, 0.05, False, "ties"),
 ])
 def test_topk_matrices_that_the_window_leaves_open(cnt, m, n, K, wd, gd, frac, ef, which):
-    grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: {"one": i == cnt // 2, "some": i % 7 == 3, "all": True,
+    grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: {"one": i == cnt // 2, "first": i == 0, "last": i == cnt - 1, "some": i % 7 == 3, "all": True,
                                                           "worker": k == 1, "ties": False}[which])
-    alone = [_clone(grp, slice(i, i + 1)) for i in range(cnt)]
-    assert m * n * K < 1 << 22 <= cnt * m * n * K
-    _topk([grp], K, frac, ef)
-    _topk(alone, K, frac, ef)
-    torch.cuda.synchronize()
+    alone = _together_and_alone(grp, K, frac, ef)
     for k in range(K):
         assert torch.equal(grp.scales[k], torch.cat([a.scales[k] for a in alone])), k
         assert torch.equal(grp.worker_params[k], torch.cat([a.worker_params[k] for a in alone])), k
@@ -261,36 +284,52 @@ def test_topk_open_matrices_have_the_whole_chip():
     assert us["open"] < 1.5 * us["settled"], us
 
 
-# The bytes recorded tell the route: with error feedback (K = 1, bf16 replicas) the window's pass and the update move 40
-# an element and three passes 48, without it 26 and 38.  Matrices of few values, of which the sample is a large part, take the passes.
-@pytest.mark.parametrize("cnt,m,n,ef,per_element", [
-    (64, 256, 256, True, 48), (64, 256, 256, False, 26), (65, 255, 256, False, 38), (43, 256, 384, True, 40),
-    (43, 313, 314, True, 48), (4, 1024, 1024, True, 40), (3, 1024, 1024, True, 48),
+# On either side of the lines of the rule for the window: matrices of few values, few matrices, many workers, ties, one large matrix.
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,ef,window", [
+    (400, 256, 256, 1, torch.bfloat16, torch.float32, True, True), (400, 255, 256, 1, torch.bfloat16, torch.float32, True, False),
+    (16, 512, 512, 1, torch.bfloat16, torch.float32, True, True), (15, 512, 512, 1, torch.bfloat16, torch.float32, True, False),
+    (4, 1024, 1024, 1, torch.bfloat16, torch.float32, True, False), (8, 1024, 1024, 1, torch.bfloat16, torch.float32, True, True),
+    (1, 1024, 1024, 8, torch.bfloat16, torch.float32, True, True), (1, 1024, 1024, 8, torch.bfloat16, torch.float32, False, False),
+    (2, 1024, 1024, 8, torch.bfloat16, torch.float32, False, True), (2, 1536, 1536, 2, torch.bfloat16, torch.float32, False, False),
+    (8, 1024, 1024, 1, torch.bfloat16, torch.bfloat16, False, True), (6, 1024, 1024, 1, torch.bfloat16, torch.bfloat16, False, False),
+    (1, 2560, 2560, 1, torch.bfloat16, torch.float32, True, True), (1, 2048, 2560, 1, torch.float32, torch.float32, True, False),
 ])
-def test_topk_route_by_size(cnt, m, n, ef, per_element):
-    grp = _misled(cnt, m, n, 1, torch.bfloat16, torch.float32, ef, lambda k, i: False)
-    alone = [_clone(grp, slice(i, i + 1)) for i in range(0, cnt, 9)]
-    mlc.muloco_timing_enable(True)
-    try:
-        mlc.muloco_timing_read()
-        _topk([grp], 1, 0.05, ef)
-        torch.cuda.synchronize()
-        moved = mlc.muloco_timing_read()["topk"]["bytes"]
-    finally:
-        mlc.muloco_timing_enable(False)
-    assert moved == cnt * m * n * per_element
-    _topk(alone, 1, 0.05, ef)
-    for i, a in enumerate(alone):
-        assert torch.equal(grp.scales[0][9 * i], a.scales[0][0]), i
-        assert torch.equal(grp.global_param[9 * i], a.global_param[0]), i
+def test_topk_route_by_size(cnt, m, n, K, wd, gd, ef, window):
+    grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: False)
+    some = slice(0, cnt, max(1, cnt // 5))
+    alone = [_clone(grp, slice(i, i + 1)) for i in range(cnt)[some]]
+    assert _recorded([grp], K, 0.05, ef) == _bytes(grp, K, ef, window)
+    _topk(alone, K, 0.05, ef)
+    for k in range(K):
+        assert torch.equal(grp.scales[k][some], torch.cat([a.scales[k] for a in alone])), k
+    assert torch.equal(grp.global_param[some], torch.cat([a.global_param for a in alone]))
+
+
+# The cases of test_topk_from_a_sample in groups that do start from one
+@pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,kind", [
+    (1, 2560, 2560, 1, torch.bfloat16, torch.float32, 0.05, True, "normal"),
+    (64, 300, 300, 2, torch.bfloat16, torch.float32, 0.005, True, "normal"),
+    (90, 313, 315, 1, torch.float32, torch.float32, 0.1, False, "normal"),
+    (9, 1001, 901, 1, torch.bfloat16, torch.float32, 0.2, True, "normal"),
+    (3, 723, 727, 8, torch.bfloat16, torch.bfloat16, 0.02, False, "normal"),
+    (2, 1449, 1451, 4, torch.float32, torch.bfloat16, 1.0, True, "normal"),
+    (2, 1449, 1451, 4, torch.bfloat16, torch.float32, 1e-9, True, "normal"),
+    (9, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.0009, True, "rare"),
+    (4, 1024, 1024, 3, torch.bfloat16, torch.float32, 0.05, True, "grid"),
+    (6, 1024, 1024, 2, torch.bfloat16, torch.float32, 0.05, False, "one"),
+])
+def test_topk_from_a_sample_of_larger_groups(cnt, m, n, K, wd, gd, frac, ef, kind):
+    grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: False)
+    assert _recorded([grp], K, frac, ef) == _bytes(grp, K, ef, True)
+    test_topk_from_a_sample(cnt, m, n, K, wd, gd, frac, ef, kind)
 
 
 # Not-a-numbers and infinities compare by their bit patterns, above every number: in groups that start from a sample as in
 # those that take the passes.
 @pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,every", [
-    (4, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.05, True, (100003, 70001)),    # few: all of them are sent
-    (5, 1000, 1001, 2, torch.float32, torch.float32, 0.01, False, (64, 31)),            # more than are sent: the threshold is one
-    (3, 1024, 2048, 1, torch.bfloat16, torch.bfloat16, 0.3, True, (0, 3)),              # infinities tie
+    (9, 1024, 1024, 1, torch.bfloat16, torch.float32, 0.05, True, (100003, 70001)),    # few: all of them are sent
+    (6, 1000, 1001, 2, torch.float32, torch.float32, 0.01, False, (64, 31)),            # more than are sent: the threshold is one
+    (12, 1024, 2048, 1, torch.bfloat16, torch.bfloat16, 0.3, True, (0, 3)),              # infinities tie
 ])
 def test_topk_not_a_number_from_a_sample(cnt, m, n, K, wd, gd, frac, ef, every):
     grp = _misled(cnt, m, n, K, wd, gd, ef, lambda k, i: False)
@@ -299,11 +338,7 @@ def test_topk_not_a_number_from_a_sample(cnt, m, n, K, wd, gd, frac, ef, every):
             w.view(-1)[::every[0]] = float("nan")
         w.view(-1)[5::every[1]] = float("inf")
         w.view(-1)[6::2 * every[1]] = -float("inf")
-    alone = [_clone(grp, slice(i, i + 1)) for i in range(cnt)]
-    assert m * n * K < 1 << 22 <= cnt * m * n * K
-    _topk([grp], K, frac, ef)
-    _topk(alone, K, frac, ef)
-    torch.cuda.synchronize()
+    alone = _together_and_alone(grp, K, frac, ef)
     bits = lambda t: t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)  # noqa: E731
     for k in range(K):
         assert torch.equal(bits(grp.scales[k]), bits(torch.cat([a.scales[k] for a in alone]))), k
@@ -383,7 +418,7 @@ def _crowded(cnt, m, n, K, wd, gd, ef, seed=5):
 
 
 # Lists of many entries and of many workers, elements that several workers' lists hold, more matrices than
-# workgroups for them: the same bits as matrix by matrix, where groups of less than 4 M values take the passes.
+# workgroups for them: the same bits as matrix by matrix.
 @pytest.mark.parametrize("cnt,m,n,K,wd,gd,ef", [
     (17, 1024, 1024, 3, torch.float32, torch.float32, False), (9, 768, 768, 6, torch.float32, torch.float32, True),
     (150, 300, 300, 3, torch.float32, torch.bfloat16, True), (7, 500, 1001, 8, torch.bfloat16, torch.float32, True),
@@ -391,11 +426,7 @@ def _crowded(cnt, m, n, K, wd, gd, ef, seed=5):
 ])
 def test_topk_long_lists(cnt, m, n, K, wd, gd, ef):
     grp = _crowded(cnt, m, n, K, wd, gd, ef)
-    alone = [_clone(grp, slice(i, i + 1)) for i in range(cnt)]
-    assert m * n * K < 1 << 22 <= cnt * m * n * K
-    _topk([grp], K, 0.05, ef)
-    _topk(alone, K, 0.05, ef)
-    torch.cuda.synchronize()
+    alone = _together_and_alone(grp, K, 0.05, ef)
     for k in range(K):
         assert torch.equal(grp.scales[k], torch.cat([a.scales[k] for a in alone])), k
         assert torch.equal(grp.worker_params[k], torch.cat([a.worker_params[k] for a in alone])), k
