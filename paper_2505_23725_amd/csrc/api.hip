@@ -672,8 +672,7 @@ int muloco_quantize_delta(const mlc_outer_group* groups, int n_groups, const mlc
 static bool multi_launch_covers(const mlc_outer_group& g, const mlc_outer_hparams& hp) {
   if (hp.K > OUTER_MAX_SEG_K || hp.second_quantisation || hp.quant_per_matrix) return false;
   if (hp.quant_bits == 0) return true;
-  const int cfg = quant_reg_cfg(g.n);
-  return cfg >= 0 && cfg <= QUANT_MULTI_MAX_CFG && !quant_two_pass(g.count * g.m, g.n, hp.quant_bits) &&
+  return quant_reg_cfg(g.n) >= 0 && !quant_two_pass(g.count * g.m, g.n, hp.quant_bits) &&
          !(g.worker_dtype == MLC_F32 && g.global_dtype == MLC_BF16);
 }
 

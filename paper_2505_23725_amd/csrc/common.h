@@ -273,9 +273,8 @@ struct OuterGroupArgs {
   WorkerPtrs w; CodePtrs codes; ScalePtrs scales; ScalePtrs offsets; ResidualPtrs ef;
   void* theta_g; float* u; int64_t rows, n;
 };
-// >= 0 when the one-pass quantiser covers rows of length n; rows up to 8192 columns
-// (configurations 0 .. QUANT_MULTI_MAX_CFG) can share a launch with other groups, longer ones
-// need so many registers per thread that they would halve the occupancy of the whole launch.
+// >= 0 when groups with rows of length n can share a launch of the one-pass quantiser (up to 8192 columns; longer rows
+// would need so many registers of its 256 threads that they would halve the occupancy of the whole launch).
 int quant_reg_cfg(int64_t n);
 // Rows whose length is a multiple of 8 start on 16 bytes (8 for codes) whatever their index.
 static inline bool quant_ragged(int64_t n) { return n % 8 != 0; }
@@ -287,7 +286,6 @@ static inline bool quant_ragged(int64_t n) { return n % 8 != 0; }
 static inline bool quant_two_pass(int64_t rows, int64_t n, int bits) {
   return bits == 8 && n < 64 && quant_ragged(n) && rows >= 8192;
 }
-constexpr int QUANT_MULTI_MAX_CFG = 4;
 struct QuantForm;
 int launch_outer_fused_multi(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K,
                              float eta_out, float mu, int nesterov, int write_back, hipStream_t stream);

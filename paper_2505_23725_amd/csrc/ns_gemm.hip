@@ -379,7 +379,9 @@ __device__ __forceinline__ u32x4 transpose_quad(u32x4 w, int p) {
 constexpr int TRIANGLE_STORES = 32;
 // Deepest product whose triangles leave operand A's transfers out.  A triangle then takes 0.7 to 0.8 of a whole
 // tile's time (0.9 with the transfers), and the workgroups behind one L2 no longer read the same K tiles at the same time:
-// deeper operands do not fit there, and come from memory again.  Gram and polynomial products of 150M-scale, eight
+// deeper operands do not fit there, and come from memory again.  Without the transfers against with them, newton_schulz over
+// 3e8 elements, 512 to 5120 wide: 0.97 to 1.00 up to K = 1536, 0.99 to 1.01 at 2048 and 2560, 0.99 to 1.02 at 2304, 0.99 to 1.03 from
+// 2816 to 3584, 0.97 to 1.01 beyond.  Gram and polynomial products of 150M-scale, eight
 // replicas (K = 768 and 3072): 590 and 414 us with whole tiles, 556 and 387 with the transfers, 530 and 357 by this rule; the
 // Gram products of 1.76B-scale (K = 2048 and 8192) 1940, 1860, and without the transfers at any depth 2280.
 constexpr int TRIANGLE_ONE_OPERAND = 2560;
@@ -1302,8 +1304,9 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   int n_sets = 0;
   for (int i = 0; i < n; ++i) {
     if (done[i]) continue;
-    // products that share a launch with product i whatever their tile: same depth (a tile then takes the
-    // same time in each, so dealing tiles out evenly balances the time), same divisors, same layout
+    // products that share a launch with product i whatever their tile: same depth (a whole tile then takes the
+    // same time in each, so dealing tiles out evenly balances the time but for triangles, which take 0.7 to 0.9 of
+    // it), same divisors, same layout
     GemmSet& s = sets[n_sets++];
     s.n = 0;
     for (int j = i; j < n && s.n < MAX_MULTI; ++j) {

@@ -573,12 +573,12 @@ struct QuantSeg {
 };
 struct QuantSegTable { QuantSeg s[OUTER_MAX_SEG]; int nseg; };
 
-// (NV, G) of a row length, as launch_quantize_outer_fused picks them; -1: not covered
+// Vectors per thread and threads per row in a launch that several groups share (its workgroups have 256 threads, so
+// none is of its row's size)
 struct RegCfg { int nv, g; };
 __host__ __device__ constexpr RegCfg reg_cfg(int idx) {
   return idx == 0 ? RegCfg{1, 64} : idx == 1 ? RegCfg{2, 64} : idx == 2 ? RegCfg{4, 64}
-       : idx == 3 ? RegCfg{2, 256} : idx == 4 ? RegCfg{4, 256} : idx == 5 ? RegCfg{6, 256}
-       : idx == 6 ? RegCfg{8, 256} : RegCfg{12, 256};
+       : idx == 3 ? RegCfg{2, 256} : RegCfg{4, 256};
 }
 
 template <typename WT, typename GT, bool RAG>
@@ -599,8 +599,8 @@ __global__ __launch_bounds__(OT_THREADS, 3) void quantize_outer_multi_kernel(
     case 1: MLC_SEG_BODY(1); break;
     case 2: MLC_SEG_BODY(2); break;
     case 3: MLC_SEG_BODY(3); break;
-    default: MLC_SEG_BODY(4); break;      // rows that need more vectors per thread (and with
-  }                                        // them more registers) are not taken: see the launcher
+    default: MLC_SEG_BODY(4); break;
+  }
 #undef MLC_SEG_BODY
 }
 
@@ -682,19 +682,25 @@ __global__ __launch_bounds__(OT_THREADS) void dequant_outer_kernel(
 // that tie with the k-th one, tau, included).  Magnitudes are compared as the bit patterns of |v|
 // (ordered like unsigned numbers; bit 31 is always clear).  The state of a (worker, matrix) pair is
 // an interval of 2^width such keys from `lo` on that holds tau's, and tau's rank in it; a pass over
-// the values counts those of the interval in up to 2048 bins, and the workgroup that ends last
+// the values counts those of the interval in up to 2048 bins, and the workgroup that ends last, or a launch of its own,
 // narrows the interval to the bin that holds tau.  Three passes lead from all 2^31 keys to one.
 //
-// Large matrices start from an interval that a sample of 16384 values suggests, which the pass that
+// Large matrices and groups (topk_window) start from an interval that a sample of 16384 values suggests, which the pass that
 // computes v counts in bins of its own.  Where the bin that holds tau has at most TOPK_LIST values for every
 // worker, the update of the matrix follows at once: values above the interval are sent, those
-// below are not, and the few inside are listed and left as they are, for topk_settle to select
-// tau among them exactly and to update their elements.  The values are then read twice in all.  What
-// this does not settle (a sample that misled, many equal magnitudes) goes through the three passes.
-// All of this is bound by memory: with error feedback 14 bytes an element in the first pass and 26 in the
-// update (bf16 replicas, fp32 global copy), where three counting passes and the update took 48: six layers of
-// 2048 / 8192, one worker, 5 %: 2873 -> 2520 us, without error feedback 24 matrices of 2048 x 2048 703 -> 528.
-// Matrices whose magnitudes all tie take the same 790 us (24 of 2048 x 2048) as normally distributed ones, 906 before.
+// below are not, and the few inside are listed and left as they are, for topk_threshold to select
+// tau among them exactly and topk_settle to update their elements.  The values are then read twice in all.
+//
+// What this leaves open goes through up to three further passes, one where the bin was merely too full: equal
+// magnitudes (bf16 replicas of a bf16 global copy), and matrices too large for bins that a fixed sample spreads.  Normally
+// distributed values settle up to 67 M at 2 % and less, 50 M at 5 %, 33 M at 10 % and 25 M at 20 %; of 110 M (5120 x
+// 20480) at 5 % and of 67 M (4096 x 16384) at 20 % none do.  A sample misleads seldom: in none of 2900 draws of matrices with normal, heavy-tailed
+// or row- or column-scaled values, in 2 of 100 where each 8 adjacent magnitudes are alike.
+//
+// All of this is bound by memory, per element with error feedback (bf16 replicas, fp32 global copy): 14 bytes in the
+// window's pass and 26 in the update, and 4 a further pass; by passes from the start 48.  Against those: six layers of
+// 2048 / 8192, one worker, 5 %, 2873 -> 2520 us; 4096 x 16384 at 20 % and left open 745 -> 588; 24 matrices of 2048 x 2048
+// 921 -> 808, whose magnitudes all tie 906 -> 790, and 925 -> 1046 if all are misled about.
 constexpr int TOPK_LIST = (TOPK_BINS - 2) / 2;     // primaries of two words and the two counts fit the histogram
 constexpr int TOPK_WINDOW = TOPK_BINS - 1;         // bins of the first pass; the last word counts what is above
 constexpr unsigned int TOPK_EARLY = 1u << 31;      // in ctl: the pass over the window left few enough values;
@@ -1684,14 +1690,8 @@ int launch_outer_fused_multi(const OuterGroupArgs* gs, int ng, int worker_dtype,
   return check_launch();
 }
 
-// Index of the (vectors per thread, threads per row) pair of the one-pass kernel for rows of
-// length n, or -1 when the one-pass kernel does not cover them.
 int quant_reg_cfg(int64_t n) {
-  if (n > 24576) return -1;
-  const int g = n <= 2048 ? 64 : OT_THREADS;
-  const int need = (int)((n + g * 8 - 1) / (g * 8));
-  if (g == 64) return need <= 1 ? 0 : need <= 2 ? 1 : 2;
-  return need <= 2 ? 3 : need <= 4 ? 4 : need <= 6 ? 5 : need <= 8 ? 6 : 7;
+  return n <= 512 ? 0 : n <= 1024 ? 1 : n <= 2048 ? 2 : n <= 4096 ? 3 : n <= 8192 ? 4 : -1;
 }
 
 // One launch for the quantised outer step (quantise + dequantise + mean + eq. 3 + write-back)
@@ -1710,7 +1710,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     QuantSeg& sg = tab.s[i];
     if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
     const int cfg = quant_reg_cfg(gs[i].n);
-    if (cfg < 0 || cfg > QUANT_MULTI_MAX_CFG || quant_two_pass(gs[i].rows, gs[i].n, form.bits) ||
+    if (cfg < 0 || quant_two_pass(gs[i].rows, gs[i].n, form.bits) ||
         quant_ragged(gs[i].n) != quant_ragged(gs[0].n))
       return MLC_ERR_UNSUPPORTED;
     for (int k = 0; k < OUTER_MAX_SEG_K; ++k) {
@@ -1750,7 +1750,8 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
 
 size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * sizeof(TopkState); }
 
-// Workgroups of a counting pass up to which the one that ends last picks the digit.
+// Workgroups of a counting pass up to which the one that ends last picks the digit.  Against a launch of its own after every
+// pass, 0.75 of a call's time with up to 250 of them, 0.78 to 0.99 with 512, 0.9 to 1.15 with 1024, 0.95 to 1.7 with 4096.
 constexpr long TOPK_LAST_PICKS = 512;
 
 // Do these states start from a sample?  Microseconds that the window saves over the passes and that it costs, fitted to 1720
