@@ -17,6 +17,8 @@ namespace mlc {
 //    2056  bf16         1.00  1.00   .93   .91   .90   .93   .92   .93   .89    (256 threads up to two replicas)
 //          bf16, ef     1.01  1.00  1.01  1.00  1.02  1.01  1.01  1.03  1.04
 //          f32          1.00  1.00  1.04  1.04  1.03  1.04  1.03  1.10  1.10
+//    2523  bf16, ragged  1.00  1.00   .95   .95   .94   .95   .96   .94   .91
+//    3001  bf16, ragged, ef 1.00 1.00 1.00  1.00  1.00  1.04   .96  1.04  1.06
 //    3073  bf16, ragged  1.00 1.01  1.04  1.05  1.06  1.06  1.08  1.10  1.12
 //    4104  bf16          .80   .91   .85   .93   .95   .92   .99  1.05  1.07
 //    5001  bf16, ragged  .90   .96  1.04  1.06  1.04  1.03  1.05  1.02  1.03
@@ -39,7 +41,7 @@ inline int quant_whole_row(const QuantRow& q) {
   if (q.n <= 2048 || q.n > 8192) return 0;
   int most;                                  // replicas
   if (q.n % 8 != 0) {
-    if (q.n <= 4096) return 0;
+    if (q.n <= 4096) return q.n <= 3072 && !q.worker_f32 && q.K >= 3 && q.K <= 5 ? 2 : 0;
     const bool spills = q.worker_f32 || q.global_bf16;
     most = q.n <= 5120 ? (spills ? 32 : 2) : q.n <= 6144 ? 2 : spills ? 32 : 8;
   } else if (q.n <= 4096) {

@@ -25,6 +25,8 @@ MEASURED = [
     (2056, 4, 4, 0, 0, 0, 0, 0.91), (2056, 8, 8, 0, 1, 0, 0, 0.87), (2560, 16, 8, 0, 0, 0, 0, 0.90),
     (2056, 4, 8, 1, 0, 0, 0, 1.04), (2056, 16, 8, 1, 0, 0, 0, 1.10), (2056, 32, 8, 0, 0, 1, 0, 1.05),
     (2808, 5, 4, 0, 0, 1, 0, 1.05), (3072, 32, 8, 0, 1, 0, 0, 1.03), (3001, 16, 8, 0, 0, 0, 0, 1.11),
+    (2402, 4, 8, 0, 1, 0, 0, 0.95), (2523, 3, 8, 0, 0, 1, 0, 0.96), (2601, 12, 8, 0, 0, 0, 0, 1.06),
+    (2901, 6, 8, 0, 0, 1, 0, 1.03), (2901, 5, 8, 0, 0, 0, 0, 0.96), (2049, 16, 8, 1, 0, 0, 0, 1.07),
     (3073, 4, 8, 0, 0, 0, 0, 1.05), (3073, 32, 8, 0, 0, 0, 0, 1.12), (4096, 16, 4, 0, 0, 1, 0, 1.06),
     (4104, 1, 4, 0, 0, 0, 0, 0.80), (4104, 4, 8, 0, 1, 0, 0, 0.83), (4104, 16, 8, 0, 1, 0, 0, 1.13),
     (4601, 8, 8, 1, 0, 0, 0, 0.64), (4601, 4, 8, 0, 1, 0, 0, 0.72), (5001, 1, 8, 0, 0, 0, 0, 0.90),
