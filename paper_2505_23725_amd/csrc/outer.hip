@@ -1750,9 +1750,10 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
 
 size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * sizeof(TopkState); }
 
-// Workgroups of a counting pass up to which the one that ends last picks the digit.  Against a launch of its own after every
-// pass, 0.75 of a call's time with up to 250 of them, 0.78 to 0.99 with 512, 0.9 to 1.15 with 1024, 0.95 to 1.7 with 4096.
-constexpr long TOPK_LAST_PICKS = 512;
+// Does the workgroup that ends a counting pass last pick the digit?  Against a launch of its own after every pass, 0.75 of a
+// call's time with up to 250 workgroups, 0.78 to 0.99 with 512, 0.83 to 0.96 with 700; with 1024 0.97 to 1.04 where a matrix has 32 of them
+// and more, 1.06 to 1.15 with 2 to 20, and with 4096 1.1 to 1.7.
+static bool topk_last_picks(int blocks, int n_states) { return (long)blocks * n_states <= (blocks >= 32 ? 1024 : 704); }
 
 // Do these states start from a sample?  Microseconds that the window saves over the passes and that it costs, fitted to 1720
 // groups of 3 to 70 M values (matrices of 256 x 256 to 2048 x 8192, 1 to 16 workers, calls one behind the other) that
@@ -1825,7 +1826,7 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
 #undef MLC_SAMPLE
   } else {
     hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
-    const bool last_picks = (long)full_grid * n_states <= TOPK_LAST_PICKS;
+    const bool last_picks = topk_last_picks(full_grid, n_states);
 #define MLC_HIST(WT, GT, V, F)                                                                    \
   hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(full_grid, (unsigned)count, K),        \
                      dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta, (int)last_picks);   \

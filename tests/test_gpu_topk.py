@@ -397,7 +397,7 @@ def test_topk_many_small_matrices_run_at_memory_speed():
 
 
 # as many workgroups a pass as the last picks among, and more
-@pytest.mark.parametrize("cnt,m,n,K", [(64, 128, 128, 1), (65, 128, 128, 1), (2, 1024, 512, 1), (1, 1024, 512, 3), (513, 8, 16, 1)])
+@pytest.mark.parametrize("cnt,m,n,K", [(88, 128, 128, 1), (89, 128, 128, 1), (4, 1024, 512, 1), (2, 1024, 513, 2), (5, 1024, 512, 1), (705, 8, 16, 1)])
 @pytest.mark.parametrize("ef", [False, True])
 def test_topk_digits_picked_last_and_in_launches(cnt, m, n, K, ef):
     test_topk_outer_step_matches_oracle(cnt, m, n, K, torch.bfloat16, torch.float32, 0.03, ef)
