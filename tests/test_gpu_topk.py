@@ -122,7 +122,8 @@ def test_topk_few_distinct_magnitudes(cnt, m, n, ef, steps):
     assert_fp32_close(u.cpu().reshape(-1, n), ref["u"], "outer momentum")
 
 
-# Groups of about 4 M values (by the passes; test_topk_from_a_sample_of_larger_groups has those that start from a sample) off the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
+# Groups of about 4 M values (by the passes; test_topk_from_a_sample_of_larger_groups has those that start from a
+# sample) off the vector, many workers, and values that a sample misjudges: `rare` puts the entries that are
 # kept into one row, `grid` takes a few distinct magnitudes, `one` a single one.
 @pytest.mark.parametrize("cnt,m,n,K,wd,gd,frac,ef,kind", [
     (1, 2048, 2048, 1, torch.bfloat16, torch.float32, 0.05, True, "normal"),
