@@ -69,6 +69,7 @@ struct GemmArgs {
   const bf16_t* C; long ldc, strideC;
   int K, batch;
   int tiles_m, tiles_n, tiles_per_mat, total_tiles, tiles_per_xcd;
+  int last_m, last_n;             // first row and column of the last tile row and column
   int group_m;                    // tile rows per group of the tile order
   int symmetric, transposed;
   float alpha, beta, gamma;
@@ -175,8 +176,12 @@ __device__ __forceinline__ void pair_rows(const u32x4& x, const u32x4& y, bool o
   }
 }
 
+// End of the buffers that a tile is stored through: no matrix reaches it (with its row padding one has at most 2^32 bytes), and
+// a store at this offset is dropped, whatever its scalar offset.
+constexpr unsigned int BUFFER_END = 0xfffffff0u;
+
 // Position of an output tile.
-struct TileCoord { int b, m0, n0, mirror, diag; };
+struct TileCoord { int b, m0, n0, mirror, diag, edge; };
 
 // TI adjacent bf16 values of a row <-> TI / 2 words.
 template <int TI>
@@ -213,7 +218,7 @@ constexpr int epilogue_stores(int ti, bool mirror) {      // what store_tile lea
 template <int TI, int TJ, bool HAS_C, bool MIRROR, bool TOUT, bool DIAG, bool UNIT>
 __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)[TI][TJ],
                                            const TileCoord& tc, float alpha, int wbase_m, int wbase_n,
-                                           int lane, u32x4 (&pend)[TI == 8 ? 16 : 1]) {
+                                           int lane, bool drop, u32x4 (&pend)[TI == 8 ? 16 : 1]) {
   // what follows from the lane is computed here, not kept in registers through the K loop
   asm volatile("" : "+v"(lane));
   // lane's first row and column; its element (i, J, e) is row row0 + i, column col0 + 32 J + e.
@@ -227,13 +232,13 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   constexpr int NP = NJ / NH;             // the second of two such groups is the one left in `pend`
   static_assert(NP == (TI == 8 ? 2 : 1), "which columns are stored when");
   const __amdgpu_buffer_rsrc_t rd =
-      __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, 0xffffffff, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, BUFFER_END, 0x00020000);
   __amdgpu_buffer_rsrc_t rc = rd;
   if constexpr (HAS_C)
     rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.C) + (long)tc.b * g.strideC, 0,
-                                           0xffffffff, 0x00020000);
+                                           BUFFER_END, 0x00020000);
   const unsigned int ldd2 = (unsigned int)(g.ldd * 2), ldc2 = (unsigned int)(g.ldc * 2);
-  const unsigned int voff_m = (unsigned int)(((long)col0 * g.ldd + row0) * 2);   // transposed
+  const unsigned int voff_m = drop ? BUFFER_END : (unsigned int)(((long)col0 * g.ldd + row0) * 2);   // transposed
   const unsigned int voff_c =
       HAS_C ? (unsigned int)(((TOUT ? (long)col0 * g.ldc + row0 : (long)row0 * g.ldc + col0)) * 2) : 0u;
   auto value = [&](float v) { return UNIT ? v : alpha * v; };
@@ -293,7 +298,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
         c[x / TI / NH][x / TI % NH][x % TI] =
             __builtin_amdgcn_raw_buffer_load_b128(rc, voff_c + 64u * (x / TI), (unsigned int)(x % TI) * ldc2, 0);
     const bool odd = idx & 1;
-    const unsigned int voff_n =
+    const unsigned int voff_n = drop ? BUFFER_END :
         (unsigned int)(((long)(row0 - (NH == 2 && odd ? TI : 0)) * g.ldd + col0 + (NH == 2 && odd ? 32 : 0)) * 2);
     const int diag = col0 - row0;         // i - (32 J + e) of the lane's elements on the diagonal
     u32x4 first[TI][NH];
@@ -398,11 +403,11 @@ __device__ __forceinline__ void triangle_settle(f32x4 (&acc)[8][8]) {
 }
 template <bool DG>
 __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&acc)[8][8], int b, int row0, int col0,
-                                               float alpha, int lane) {
+                                               float alpha, bool drop, int lane) {
   asm volatile("" : "+v"(lane));
   const int idx = lane & 15, lg = lane >> 4, q = idx >> 2, p = idx & 3, odd = idx & 1;
   const __amdgpu_buffer_rsrc_t rd =
-      __builtin_amdgcn_make_buffer_rsrc(g.D + (long)b * g.strideD, 0, 0xffffffff, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(g.D + (long)b * g.strideD, 0, BUFFER_END, 0x00020000);
   // (opaque: its multiples would otherwise be kept in scalar registers all through the K loop)
   unsigned int ldd2 = (unsigned int)(g.ldd * 2);
   asm volatile("" : "+s"(ldd2));
@@ -423,7 +428,7 @@ __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&
       return;
     }
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(g.C) + (long)b * g.strideC, 0, 0xffffffff, 0x00020000);
+        const_cast<bf16_t*>(g.C) + (long)b * g.strideC, 0, BUFFER_END, 0x00020000);
     unsigned int ldc2 = (unsigned int)(g.ldc * 2);
     asm volatile("" : "+s"(ldc2));
     const unsigned int voff_c = (unsigned int)(((long)row * g.ldc + col) * 2);
@@ -461,8 +466,8 @@ __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&
       }
     __builtin_amdgcn_sched_barrier(0);
   };
-  const unsigned int at = (unsigned int)(((long)row * g.ldd + col) * 2);
-  const unsigned int at2 = (unsigned int)(((long)(row - odd) * g.ldd + col + 32 * odd) * 2);     // two blocks' lines
+  const unsigned int at = drop ? BUFFER_END : (unsigned int)(((long)row * g.ldd + col) * 2);
+  const unsigned int at2 = drop ? BUFFER_END : (unsigned int)(((long)(row - odd) * g.ldd + col + 32 * odd) * 2);     // two blocks' lines
   auto store_row = [&](int i) {
 #pragma unroll
     for (int J = 0; J < NJ; J += 2) {
@@ -471,10 +476,10 @@ __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&
       if (has(i, J + 1)) {
         u32x4 x, y;
         pair_rows(v[i][J], v[i][J + 1], odd, x, y);
-        __builtin_amdgcn_raw_buffer_store_b128(x, rd, at2 + 64u * J, soff, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(y, rd, at2 + 64u * J, soff + ldd2, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(x, rd, at2, soff + 64u * J, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(y, rd, at2, soff + ldd2 + 64u * J, 0);
       } else {
-        __builtin_amdgcn_raw_buffer_store_b128(v[i][J], rd, at + 64u * J, soff, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(v[i][J], rd, at, soff + 64u * J, 0);
       }
     }
   };
@@ -485,14 +490,14 @@ __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&
     next = u32x4{pair_hi(r0[0], r0[1]), pair_hi(r0[2], r0[3]), pair_hi(r1[0], r1[1]), pair_hi(r1[2], r1[3])};
   };
   const int trow = col0 + 8 * lg + 2 * p, tcol = row0 + 8 * q;
-  const unsigned int mt = (unsigned int)(((long)trow * g.ldd + tcol) * 2);
-  const unsigned int mt2 = (unsigned int)(((long)(trow - 2 * odd) * g.ldd + tcol + 32 * odd) * 2);
+  const unsigned int mt = drop ? BUFFER_END : (unsigned int)(((long)trow * g.ldd + tcol) * 2);
+  const unsigned int mt2 = drop ? BUFFER_END : (unsigned int)(((long)(trow - 2 * odd) * g.ldd + tcol + 32 * odd) * 2);
   auto store_turned = [&](int I, int J) {            // one block
     u32x4 x, y;
     turn(I, J, x, y);
     const unsigned int soff = 32u * J * ldd2;
-    __builtin_amdgcn_raw_buffer_store_b128(x, rd, mt + 64u * I, soff, 0);
-    __builtin_amdgcn_raw_buffer_store_b128(y, rd, mt + 64u * I, soff + ldd2, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(x, rd, mt, soff + 64u * I, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(y, rd, mt, soff + ldd2 + 64u * I, 0);
   };
   auto store_turned2 = [&](int I, int J) {           // blocks (I, J) and (I + 1, J)
     u32x4 x[2], y[2];
@@ -501,11 +506,11 @@ __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&
     const unsigned int soff = 32u * J * ldd2;
     u32x4 s, t;
     pair_rows(x[0], x[1], odd, s, t);
-    __builtin_amdgcn_raw_buffer_store_b128(s, rd, mt2 + 64u * I, soff, 0);
-    __builtin_amdgcn_raw_buffer_store_b128(t, rd, mt2 + 64u * I, soff + 2 * ldd2, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(s, rd, mt2, soff + 64u * I, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(t, rd, mt2, soff + 2 * ldd2 + 64u * I, 0);
     pair_rows(y[0], y[1], odd, s, t);
-    __builtin_amdgcn_raw_buffer_store_b128(s, rd, mt2 + 64u * I, soff + ldd2, 0);
-    __builtin_amdgcn_raw_buffer_store_b128(t, rd, mt2 + 64u * I, soff + 3 * ldd2, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(s, rd, mt2, soff + ldd2 + 64u * I, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(t, rd, mt2, soff + 3 * ldd2 + 64u * I, 0);
   };
   using T = std::true_type;
   using F = std::false_type;
@@ -584,8 +589,10 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
       tn = r / rows;
       tm = first_m + (r - tn * rows);
     }
-    tc.m0 = __builtin_amdgcn_readfirstlane(tm * BM);
-    tc.n0 = __builtin_amdgcn_readfirstlane(tn * BN);
+    // the last tile row (column) of a matrix that is no multiple of the tile begins half a tile early
+    tc.m0 = __builtin_amdgcn_readfirstlane(min(tm * BM, g.last_m));
+    tc.n0 = __builtin_amdgcn_readfirstlane(min(tn * BN, g.last_n));
+    tc.edge = BM == 256 ? (tc.m0 % BM ? 1 : 0) + (tc.n0 % BN ? 2 : 0) : 0;
     tc.b = __builtin_amdgcn_readfirstlane(tc.b);
     tc.mirror = g.symmetric && tm != tn ? 1 : 0;
     tc.diag = TRI && tm == tn ? 1 : 0;
@@ -928,7 +935,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
       alpha *= (g.bscale_pow == 2) ? sc * sc : sc;
     }
     const int row0 = tc.m0 + (DG ? wbase_n : 128), col0 = tc.n0 + (DG ? wbase_n : wave == 1 ? 64 : 0);
-    store_triangle<DG>(g, acc, tc.b, row0, col0, alpha, lane);
+    store_triangle<DG>(g, acc, tc.b, row0, col0, alpha, tc.edge && wave != 3, lane);
   };
 
   while (true) {
@@ -1008,13 +1015,15 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
     }
 
     if constexpr (DEFER) acc_settle(acc);
+    // what a neighbouring tile computes too is left to it: beyond the reach of a buffer stores are dropped
+    const bool drop = ((tc.edge & 1) && wbase_m == 0) || ((tc.edge & 2) && wbase_n == 0);
     float alpha = g.alpha;
     if (g.bscale) {
       const float sc = g.bscale[tc.b];
       alpha *= (g.bscale_pow == 2) ? sc * sc : sc;
     }
 #define MLC_STORE(C, M, T, DG, U) \
-  store_tile<TI, TJ, C, M, T, DG, U>(g, acc, tc, alpha, wbase_m, wbase_n, lane, pend)
+  store_tile<TI, TJ, C, M, T, DG, U>(g, acc, tc, alpha, wbase_m, wbase_n, lane, drop, pend)
     // Symmetric products (Gram, polynomial) are those with a K-contiguous B, the apply products
     // those with a K-strided one: each kernel holds only the forms its products have.
     if constexpr (!BKS) {
@@ -1043,14 +1052,15 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
     triangle = false;
     mirrored = tc.mirror;
     if constexpr (DEFER) {
-      pend_rd = __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, 0xffffffff, 0x00020000);
+      pend_rd = __builtin_amdgcn_make_buffer_rsrc(g.D + (long)tc.b * g.strideD, 0, BUFFER_END, 0x00020000);
       int l = lane;
       asm volatile("" : "+v"(l));
       const int row0 = tc.m0 + wbase_m + TI * (l & 15), col0 = tc.n0 + wbase_n + 8 * (l >> 4);
       pend_ld = (unsigned int)(g.ldd * 2);
       pend_m = (unsigned int)(((long)(col0 + 64) * g.ldd + row0) * 2);
       const int o = l & 1;
-      pend_n = BKS && g.transposed ? pend_m : (unsigned int)(((long)(row0 - TI * o) * g.ldd + col0 + 64 + 32 * o) * 2);
+      if (drop) pend_m = BUFFER_END;
+      pend_n = drop || (BKS && g.transposed) ? pend_m : (unsigned int)(((long)(row0 - TI * o) * g.ldd + col0 + 64 + 32 * o) * 2);
     }
     if (!more) break;
     tc = tn;
@@ -1120,7 +1130,8 @@ int cus_per_xcd(int slot) {
   return cus / NUM_XCD;
 }
 
-// Kernel arguments of one product with BM x BN tiles.
+// Kernel arguments of one product with BM x BN tiles.  Tiles cover M x N; the last row and column of 256 x 256 tiles may
+// begin half a tile before the end of those before them.
 template <int BM, int BN>
 int make_args(const GemmDesc& d, GemmArgs& g) {
   g.A = d.A; g.lda = d.lda; g.strideA = d.strideA;
@@ -1128,7 +1139,9 @@ int make_args(const GemmDesc& d, GemmArgs& g) {
   g.D = d.D; g.ldd = d.ldd; g.strideD = d.strideD;
   g.C = d.C; g.ldc = d.ldc; g.strideC = d.strideC;
   g.K = d.K; g.batch = d.batch;
-  g.tiles_m = d.M / BM; g.tiles_n = d.N / BN;
+  g.tiles_m = (d.M + BM - 1) / BM; g.tiles_n = (d.N + BN - 1) / BN;
+  g.last_m = d.M - BM; g.last_n = d.N - BN;
+  if (g.last_m < 0 || g.last_n < 0) return MLC_ERR_SHAPE;
   g.symmetric = d.symmetric ? 1 : 0;
   g.transposed = d.transposed ? 1 : 0;
   {   // equal groups of at most GROUP_M tile rows (10 rows -> 5 + 5, not 8 + 2)
@@ -1206,8 +1219,16 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   return hipGetLastError() == hipSuccess ? MLC_OK : MLC_ERR_LAUNCH;
 }
 
+// Can the 256 x 256 tile serve this product?  A side that it does not divide ends with half a tile that two tile rows
+// (columns) compute; below 896 that is more than a seventh of the work.  All products in that tile against all in the smaller
+// ones, newton_schulz: 192 of 896 x 896 4440 -> 3606 us, 63 of 1664 x 1664 7353 -> 5721, 18 of 3200 x 3200 13650 -> 9900;
+// but 63 of 640 x 640 520 -> 700, 70 of 384 x 1536 440 -> 565, 341 of 640 x 640 3266 -> 2955.
+bool large_fits(const GemmDesc& d) {
+  return d.M >= 256 && d.N >= 256 && (d.M % 256 == 0 || d.M >= 896) && (d.N % 256 == 0 || d.N >= 896);
+}
+
 long tiles_of(const GemmDesc& d, int tile) {
-  const long tm = d.M / tile, tn = d.N / tile;
+  const long tm = (d.M + tile - 1) / tile, tn = (d.N + tile - 1) / tile;
   return (d.symmetric ? tm * (tm + 1) / 2 : tm * tn) * d.batch;
 }
 
@@ -1246,11 +1267,11 @@ double estimate_us(int tile, int form, long tiles, int kt, int cus) {
 // tile's ring needs four K tiles.
 int pick_tile(const GemmDesc* const* d, int n, int cus) {
   long tiles[3] = {0, 0, 0};
-  bool divides = true;
+  bool large = true;
   double bytes = 0.0;
   for (int j = 0; j < n; ++j) {
     bytes += 2.0 * d[j]->batch * d[j]->K * (d[j]->M + (d[j]->symmetric ? 0.0 : (double)d[j]->N));
-    divides = divides && d[j]->M % 256 == 0 && d[j]->N % 256 == 0;
+    large = large && large_fits(*d[j]);
     for (int t = 0; t < 3; ++t) tiles[t] += tiles_of(*d[j], 256 >> t);
   }
   const int kt = d[0]->K / BK;
@@ -1259,7 +1280,7 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
   double us = estimate_us(128, form, tiles[1], kt, cus);
   const double e64 = estimate_us(64, form, tiles[2], kt, cus);
   if (kt >= 4 && e64 < 0.95 * us) { small = 64; us = e64; }
-  if (!divides || kt < 4) return small;        // the large tile leaves stores for its first four K tiles
+  if (!large || kt < 4) return small;        // the large tile leaves stores for its first four K tiles
   return us < (bytes > 64e6 ? 0.85 : 0.95) * estimate_us(256, form, tiles[0], kt, cus) ? small : 256;
 }
 
@@ -1299,7 +1320,6 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   bool done[64] = {};
   for (int i = 0; i < n; ++i)
     if (!valid_desc(d[i])) return MLC_ERR_SHAPE;
-  auto divides = [](const GemmDesc& g) { return g.M % 256 == 0 && g.N % 256 == 0; };
   GemmSet sets[64];
   int n_sets = 0;
   for (int i = 0; i < n; ++i) {
@@ -1310,7 +1330,7 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
     GemmSet& s = sets[n_sets++];
     s.n = 0;
     for (int j = i; j < n && s.n < MAX_MULTI; ++j) {
-      if (done[j] || d[j].K != d[i].K || divides(d[j]) != divides(d[i]) ||
+      if (done[j] || d[j].K != d[i].K || large_fits(d[j]) != large_fits(d[i]) ||
           (d[j].b_kstrided != 0) != (d[i].b_kstrided != 0))
         continue;
       s.d[s.n++] = &d[j];

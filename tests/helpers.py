@@ -169,14 +169,16 @@ def ns_tiles(groups, cus=256):
                 _, c, s, l = j
                 return c, s, (l if form == 2 else s), (l if form == 0 else s)       # batch, M, N, K
             first = shape(todo[0])
-            divides = first[1] % 256 == 0 and first[2] % 256 == 0
-            some = [j for j in todo if shape(j)[3] == first[3] and
-                    (shape(j)[1] % 256 == 0 and shape(j)[2] % 256 == 0) == divides][:3]
+
+            def large(M, N):     # sides that the 256 x 256 tile divides, or long enough for half a tile twice
+                return all(d >= 256 and (d % 256 == 0 or d >= 896) for d in (M, N))
+            fits = large(*first[1:3])
+            some = [j for j in todo if shape(j)[3] == first[3] and large(*shape(j)[1:3]) == fits][:3]
             todo = [j for j in todo if j not in some]
             kt = first[3] // 64
             tiles, nbytes = {}, 0
             for t in (64, 128, 256):
-                tiles[t] = sum(c * ((M // t) * (M // t + 1) // 2 if form < 2 else (M // t) * (N // t))
+                tiles[t] = sum(c * (-(-M // t) * (-(-M // t) + 1) // 2 if form < 2 else -(-M // t) * -(-N // t))
                                for c, M, N, K in map(shape, some))
             for c, M, N, K in map(shape, some):
                 nbytes += 2 * c * K * (M + (N if form == 2 else 0))
@@ -192,7 +194,7 @@ def ns_tiles(groups, cus=256):
             tile, us = 128, estimate(128)
             if kt >= 4 and estimate(64) < 0.95 * us:
                 tile, us = 64, estimate(64)
-            if divides and not us < (0.85 if nbytes > 64e6 else 0.95) * estimate(256):
+            if fits and not us < (0.85 if nbytes > 64e6 else 0.95) * estimate(256):
                 tile = 256
             for j in some:
                 out[j[0]][form] = tile
@@ -202,11 +204,11 @@ def ns_tiles(groups, cus=256):
 def ns_executed_flops(groups, iters=5):
     """Matrix-core FLOP that the library's recorder counts for groups off the one-workgroup chain."""
     total = 0.0
-    for (c, m, n), (gram, poly, _) in zip(groups, ns_tiles(groups)):
+    for (c, m, n), (gram, poly, apply) in zip(groups, ns_tiles(groups)):
         mp, np_ = -(-m // 128) * 128, -(-n // 128) * 128
         s, l = min(mp, np_), max(mp, np_)
 
         def sym(t):          # of a 256 x 256 tile on the diagonal 144 of 256 MFMAs are executed
-            return ((s // t) * (s // t + 1) / 2 - (s // t * 112 / 256 if t == 256 else 0)) * t * t
-        total += iters * c * 2.0 * (sym(gram) * l + sym(poly) * s + s * l * s)
+            return (-(-s // t) * (-(-s // t) + 1) / 2 - (-(-s // t) * 112 / 256 if t == 256 else 0)) * t * t
+        total += iters * c * 2.0 * (sym(gram) * l + sym(poly) * s + -(-s // apply) * -(-l // apply) * apply ** 2 * s)
     return total

@@ -449,3 +449,39 @@ def test_triangles_of_several_depths_in_one_launch(shapes):
             mlc.muloco_inner_step([one], hp, ws)
             for j in range(i, s[0], 3):
                 assert torch.equal(g.param[j].view(torch.int16), one.param[0].view(torch.int16)), (s, j)
+
+
+# Sides that the 256 x 256 tile does not divide: its last tile row (column) begins half a tile early, and what the
+# neighbours compute too must not be stored twice (the last product updates the weights in place).  Rows, columns and both;
+# tall and wide; a padded result and one without
+@pytest.mark.parametrize("shapes,tiles", [
+    ([(24, 1408, 1408)], [(256, 256, 256)]), ([(24, 1024, 1152)], [(256, 256, 256)]), ([(24, 1152, 1024)], [(256, 256, 256)]),
+    ([(20, 896, 1664), (20, 1664, 896)], [(256, 128, 256)] * 2), ([(40, 1150, 901)], [(256, 256, 256)]),
+])
+def test_half_tiles_at_the_edge(shapes, tiles):
+    """The bits of the matrices one by one, in tiles that divide every side; nothing beside the weights is written."""
+    assert ns_tiles(shapes) == tiles
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-2, beta=0.9)
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    few = [[(torch.randn((3, *s[1:]), generator=gen, device=DEV) * d).bfloat16() for d in (S.GRAD_STD, S.PARAM_STD)] for s in shapes]
+    guard, groups, held = 4096, [], []
+    for s, (g, w) in zip(shapes, few):
+        many = lambda t: t.repeat(-(-s[0] // 3), 1, 1)[:s[0]].contiguous()  # noqa: E731
+        flat = torch.full((w[0].numel() * s[0] + 2 * guard,), 7.0, dtype=torch.bfloat16, device=DEV)
+        held.append(flat)
+        param = flat[guard:-guard].view(s)
+        param.copy_(many(w))
+        groups.append(mlc.InnerGroup(param, many(g), torch.zeros(s, device=DEV), 0.7))
+    ws = torch.empty(mlc.muloco_inner_workspace_bytes(groups), dtype=torch.uint8, device=DEV)
+    mlc.muloco_inner_step(groups, hp, ws)
+    for s, (g, w), grp, flat in zip(shapes, few, groups, held):
+        assert bool((flat[:guard] == 7).all()) and bool((flat[-guard:] == 7).all())
+        assert 256 not in ns_tiles([(1, *s[1:])])[0]
+        for i in range(3):
+            one = mlc.InnerGroup(w[i:i + 1].clone(), g[i:i + 1].clone(), torch.zeros((1, *s[1:]), device=DEV), 0.7)
+            mlc.muloco_inner_step([one], hp, ws)
+            for j in range(i, s[0], 3):
+                assert torch.equal(grp.param[j].view(torch.int16), one.param[0].view(torch.int16)), (s, j)
+    (g, w), s = few[0], shapes[0]
+    _check_group(w[:1].cpu(), g[:1].cpu(), torch.zeros((1, *s[1:])), groups[0].param[:1].cpu(), groups[0].momentum[:1].cpu(), hp,
+                 0.7, f"{s}")
