@@ -237,6 +237,7 @@ static GemmDesc apply_update_desc(const NsJob& j, const bf16_t* X, bool first) {
 int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float eps, hipStream_t stream) {
   if (n < 1 || n > MAX_NS_JOBS) return MLC_ERR_ARG;
   NsJob* big[MAX_NS_JOBS];
+  NormDesc norm[MAX_NS_JOBS];
   ChainDesc chain[MAX_CHAINS];
   static_assert(MAX_CHAINS >= MAX_NS_JOBS, "every job may be a chain");
   int nbig = 0, nchain = 0;
@@ -250,10 +251,13 @@ int run_ns_jobs(NsJob* jobs, int n, int iters, float a, float b, float c, float 
                                   j.p.mp, j.p.np, j.w.partials, j.p.nblk, j.chunk};
       continue;
     }
-    const int rc = launch_norm_finalize(j.w.partials, j.p.nblk, j.w.scale, j.chunk, eps, stream);
-    if (rc != MLC_OK) return rc;
     j.result_buf = 0;
+    norm[nbig] = NormDesc{j.w.partials, j.p.nblk, j.w.scale, j.chunk};
     big[nbig++] = &j;
+  }
+  if (nbig) {
+    const int rc = launch_norm_finalize(norm, nbig, eps, stream);
+    if (rc != MLC_OK) return rc;
   }
   if (nchain) {
     const int rc = launch_ns_chain_small(chain, nchain, eps, iters, a, b, c, stream);

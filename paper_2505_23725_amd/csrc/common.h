@@ -239,8 +239,8 @@ int launch_momentum(const MomentumDesc* d, int n, float beta, int nesterov, hipS
 int launch_ns_load(const void* in, int dtype, bf16_t* U, float* partials, int nblk,
                    int64_t count, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t ldx,
                    bool transposed, hipStream_t stream);
-int launch_norm_finalize(const float* partials, int nblk, float* scale, int64_t count,
-                         float eps, hipStream_t stream);
+struct NormDesc { const float* partials; int nblk; float* scale; int64_t count; };
+int launch_norm_finalize(const NormDesc* d, int n, float eps, hipStream_t stream);
 struct UpdateDesc {
   void* W; int dtype; const bf16_t* O; const float* oscale;
   int64_t count, m, n, mp, ldx; float step;

@@ -33,6 +33,7 @@ __device__ __forceinline__ float block_sum(float v) {
 struct MomentumSeg {
   const void* grad; float* mom; bf16_t* U; float* partials;
   int m, n, mp, np, ldx, nblk;
+  int kind;                          // MOM_*
   unsigned int blk0;                 // first workgroup of this group
 };
 struct MomentumTable { MomentumSeg s[INNER_MAX_SEG]; };
@@ -48,8 +49,7 @@ __device__ __forceinline__ int find_seg(const Table& tab) {
 // m <- beta m + g ; U = g + beta m (or m) -> padded bf16 ; per-workgroup sum of U^2.
 // WITH_MOM = false: U = in (stand-alone Newton-Schulz entry).
 template <typename GT, bool WITH_MOM, bool VEC>
-__global__ __launch_bounds__(EW_THREADS) void muon_momentum_kernel(MomentumTable tab, float beta, int nesterov) {
-  const MomentumSeg& sg = tab.s[find_seg(tab)];
+__device__ __forceinline__ void momentum_rows(const MomentumSeg& sg, float beta, int nesterov) {
   const int rel = (int)(blockIdx.x - sg.blk0), b = rel / sg.nblk, bx = rel - b * sg.nblk;
   const int m = sg.m, n = sg.n, mp = sg.mp, np = sg.np, ldx = sg.ldx;
   const long mat = (long)b * m * n;
@@ -106,9 +106,7 @@ __global__ __launch_bounds__(EW_THREADS) void muon_momentum_kernel(MomentumTable
 // which spreads a wavefront's 2-byte stores over the banks.
 constexpr int TR_M = 128, TR_N = 64;
 template <typename GT, bool WITH_MOM, bool VEC>
-__global__ __launch_bounds__(EW_THREADS) void muon_momentum_t_kernel(MomentumTable tab, float beta, int nesterov) {
-  __shared__ __attribute__((aligned(16))) bf16_t tile[TR_N * TR_M];
-  const MomentumSeg& sg = tab.s[find_seg(tab)];
+__device__ __forceinline__ void momentum_transposed(const MomentumSeg& sg, bf16_t* tile, float beta, int nesterov) {
   const int rel = (int)(blockIdx.x - sg.blk0), b = rel / sg.nblk, bx = rel - b * sg.nblk;
   const int m = sg.m, n = sg.n, mp = sg.mp, np = sg.np, ldx = sg.ldx;
   const long mat = (long)b * m * n;
@@ -173,15 +171,29 @@ __global__ __launch_bounds__(EW_THREADS) void muon_momentum_t_kernel(MomentumTab
   if (threadIdx.x == 0) sg.partials[(long)b * sg.nblk + bx] = tot;
 }
 
+// KINDS: those of the groups of a launch, a bit each.
+enum { MOM_VEC = 1, MOM_TRANSPOSED = 2 };
+template <typename GT, bool WITH_MOM, int KINDS>
+__global__ __launch_bounds__(EW_THREADS) void muon_momentum_kernel(MomentumTable tab, float beta, int nesterov) {
+  __shared__ __attribute__((aligned(16))) bf16_t tile[KINDS >> MOM_TRANSPOSED ? TR_N * TR_M : 8];
+  const MomentumSeg& sg = tab.s[find_seg(tab)];
+  auto is = [&](int kind) { return KINDS == 1 << kind || (KINDS >> kind & 1 && sg.kind == kind); };
+  if (is(0)) momentum_rows<GT, WITH_MOM, false>(sg, beta, nesterov);
+  else if (is(MOM_VEC)) momentum_rows<GT, WITH_MOM, true>(sg, beta, nesterov);
+  else if (is(MOM_TRANSPOSED)) momentum_transposed<GT, WITH_MOM, false>(sg, tile, beta, nesterov);
+  else if (is(MOM_TRANSPOSED | MOM_VEC)) momentum_transposed<GT, WITH_MOM, true>(sg, tile, beta, nesterov);
+}
+
 // scale[b] = 1 / (sqrt(sum_b) + eps); an all-zero matrix gets 0, also when eps = 0
-__global__ __launch_bounds__(EW_THREADS) void muon_norm_kernel(const float* __restrict__ partials,
-                                                               int nblk, float* __restrict__ scale,
-                                                               float eps) {
-  const int b = blockIdx.x;
+struct NormSeg { const float* partials; float* scale; int nblk; unsigned int blk0; };
+struct NormTable { NormSeg s[INNER_MAX_SEG]; };
+__global__ __launch_bounds__(EW_THREADS) void muon_norm_kernel(NormTable tab, float eps) {
+  const NormSeg& sg = tab.s[find_seg(tab)];
+  const int b = (int)(blockIdx.x - sg.blk0), nblk = sg.nblk;
   float s = 0.f;
-  for (int i = threadIdx.x; i < nblk; i += EW_THREADS) s += partials[(long)b * nblk + i];
+  for (int i = threadIdx.x; i < nblk; i += EW_THREADS) s += sg.partials[(long)b * nblk + i];
   const float tot = block_sum(s);
-  if (threadIdx.x == 0) scale[b] = tot > 0.f ? 1.0f / (sqrtf(tot) + eps) : 0.f;
+  if (threadIdx.x == 0) sg.scale[b] = tot > 0.f ? 1.0f / (sqrtf(tot) + eps) : 0.f;
 }
 
 // W <- decay_factor * W - step * oscale_b * O     (decay_factor = 1 - eta*lambda,
@@ -193,12 +205,12 @@ struct UpdateSeg {
   int m, n, mp, ldx;
   float step;
   int nblk;                          // workgroups per matrix
+  int vec;                           // rows are a multiple of 8
   unsigned int blk0;                 // first workgroup of this group
 };
 struct UpdateTable { UpdateSeg s[INNER_MAX_SEG]; };
 template <typename WT, bool VEC>
-__global__ __launch_bounds__(EW_THREADS) void muon_update_kernel(UpdateTable tab, float decay_factor) {
-  const UpdateSeg& sg = tab.s[find_seg(tab)];
+__device__ __forceinline__ void update_rows(const UpdateSeg& sg, float decay_factor) {
   const unsigned int rel = blockIdx.x - sg.blk0, b = rel / (unsigned int)sg.nblk, bx = rel - b * (unsigned int)sg.nblk;
   const int m = sg.m, n = sg.n, ldx = sg.ldx;
   WT* w = (WT*)sg.W + (long)b * m * n;
@@ -227,6 +239,14 @@ __global__ __launch_bounds__(EW_THREADS) void muon_update_kernel(UpdateTable tab
       Vec8U<WT>::store(w + off, wv, n - col);
     }
   }
+}
+
+// KINDS: 1 for rows that are not a multiple of 8, 2 for others, 3 for groups of both.
+template <typename WT, int KINDS>
+__global__ __launch_bounds__(EW_THREADS) void muon_update_kernel(UpdateTable tab, float decay_factor) {
+  const UpdateSeg& sg = tab.s[find_seg(tab)];
+  if (KINDS == 2 || (KINDS == 3 && sg.vec)) update_rows<WT, true>(sg, decay_factor);
+  else update_rows<WT, false>(sg, decay_factor);
 }
 
 // out = oscale_b * X (padded bf16 -> caller's layout and dtype)
@@ -324,16 +344,19 @@ int grid_blocks(long items, int cap) {
   return (int)blocks;
 }
 
-// n (1 .. INNER_MAX_SEG) groups of one kind in one launch.
+// n (1 .. INNER_MAX_SEG) groups in one launch.
 template <typename GT, bool WITH_MOM>
 int launch_momentum_set(const MomentumDesc* const* d, int n, float beta, int nesterov, hipStream_t stream) {
   MomentumTable tab;
   unsigned long blk = 0;
   double bytes = 0.0;
+  int kinds = 0;
   for (int i = 0; i < INNER_MAX_SEG; ++i) {
     const MomentumDesc& x = *d[i < n ? i : 0];
+    const int kind = (x.n % 8 == 0 ? MOM_VEC : 0) | (x.transposed ? MOM_TRANSPOSED : 0);
+    kinds |= 1 << kind;
     tab.s[i] = MomentumSeg{x.grad, x.mom, x.U, x.partials, (int)x.m, (int)x.n, (int)x.mp, (int)x.np, (int)x.ldx,
-                           x.nblk, i < n ? (unsigned int)blk : 0xffffffffu};
+                           x.nblk, kind, i < n ? (unsigned int)blk : 0xffffffffu};
     if (i >= n) continue;
     blk += (unsigned long)x.nblk * (unsigned long)x.count;
     if (blk > 0x7fffffffUL) return MLC_ERR_SHAPE;
@@ -341,11 +364,16 @@ int launch_momentum_set(const MomentumDesc* const* d, int n, float beta, int nes
   }
   const dim3 grid((unsigned)blk), block(EW_THREADS);
   LaunchScope scope(WITH_MOM ? MLC_KERNEL_MOMENTUM : MLC_KERNEL_CONVERT, stream, 0.0, bytes);
-#define MLC_MOM(KERNEL, V) \
-  hipLaunchKernelGGL((KERNEL<GT, WITH_MOM, V>), grid, block, 0, stream, tab, beta, nesterov)
-  const bool vec = d[0]->n % 8 == 0;
-  if (d[0]->transposed) { if (vec) MLC_MOM(muon_momentum_t_kernel, true); else MLC_MOM(muon_momentum_t_kernel, false); }
-  else { if (vec) MLC_MOM(muon_momentum_kernel, true); else MLC_MOM(muon_momentum_kernel, false); }
+#define MLC_MOM(KINDS) \
+  hipLaunchKernelGGL((muon_momentum_kernel<GT, WITH_MOM, KINDS>), grid, block, 0, stream, tab, beta, nesterov)
+  switch (kinds) {
+    case 1: MLC_MOM(1); break;
+    case 2: MLC_MOM(2); break;
+    case 4: MLC_MOM(4); break;
+    case 8: MLC_MOM(8); break;
+    case 10: MLC_MOM(10); break;        // rows that are a multiple of 8 throughout
+    default: MLC_MOM(15);
+  }
 #undef MLC_MOM
   return check_launch();
 }
@@ -375,8 +403,7 @@ static int launch_by_kind(const Desc* d, int n, Kind kind, Launch launch) {
 }
 
 int launch_momentum(const MomentumDesc* d, int n, float beta, int nesterov, hipStream_t stream) {
-  // groups of one dtype, orientation and row alignment share launches
-  auto kind = [](const MomentumDesc& x) { return x.grad_dtype * 4 + (x.transposed ? 2 : 0) + (x.n % 8 == 0 ? 1 : 0); };
+  auto kind = [](const MomentumDesc& x) { return x.grad_dtype; };      // groups of one dtype share launches
   return launch_by_kind(d, n, kind, [&](const MomentumDesc* const* pick, int np) {
     return pick[0]->grad_dtype == MLC_F32 ? launch_momentum_set<float, true>(pick, np, beta, nesterov, stream)
                                           : launch_momentum_set<bf16_t, true>(pick, np, beta, nesterov, stream);
@@ -392,24 +419,37 @@ int launch_ns_load(const void* in, int dtype, bf16_t* U, float* partials, int nb
   return launch_momentum_set<bf16_t, false>(&one, 1, 0.f, 0, stream);
 }
 
-int launch_norm_finalize(const float* partials, int nblk, float* scale, int64_t count, float eps,
-                         hipStream_t stream) {
-  LaunchScope scope(MLC_KERNEL_NORM, stream, 0.0, (double)count * nblk * 4);
-  hipLaunchKernelGGL(muon_norm_kernel, dim3((unsigned)count), dim3(EW_THREADS), 0, stream, partials,
-                     nblk, scale, eps);
-  return check_launch();
+int launch_norm_finalize(const NormDesc* d, int n, float eps, hipStream_t stream) {
+  return launch_by_kind(d, n, [](const NormDesc&) { return 0; }, [&](const NormDesc* const* pick, int np) -> int {
+    NormTable tab;
+    unsigned long blk = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < INNER_MAX_SEG; ++i) {
+      const NormDesc& x = *pick[i < np ? i : 0];
+      tab.s[i] = NormSeg{x.partials, x.scale, x.nblk, i < np ? (unsigned int)blk : 0xffffffffu};
+      if (i >= np) continue;
+      blk += (unsigned long)x.count;
+      bytes += (double)x.count * x.nblk * 4;
+    }
+    if (blk > 0x7fffffffUL) return MLC_ERR_SHAPE;
+    LaunchScope scope(MLC_KERNEL_NORM, stream, 0.0, bytes);
+    hipLaunchKernelGGL(muon_norm_kernel, dim3((unsigned)blk), dim3(EW_THREADS), 0, stream, tab, eps);
+    return check_launch();
+  });
 }
 
-// n (1 .. INNER_MAX_SEG) groups of one dtype and row alignment in one launch.
+// n (1 .. INNER_MAX_SEG) groups of one dtype in one launch.
 static int launch_update_set(const UpdateDesc* const* d, int n, float decay_factor, hipStream_t stream) {
   UpdateTable tab;
   unsigned long blk = 0;
   double bytes = 0.0;
   const int dtype = d[0]->dtype;
+  int kinds = 0;
   for (int i = 0; i < INNER_MAX_SEG; ++i) {
     const UpdateDesc& x = *d[i < n ? i : 0];
     const int nblk = grid_blocks(x.m * ((x.n + 7) / 8), 2048);
-    tab.s[i] = UpdateSeg{x.W, x.O, x.oscale, (int)x.m, (int)x.n, (int)x.mp, (int)x.ldx, x.step, nblk,
+    kinds |= x.n % 8 == 0 ? 2 : 1;
+    tab.s[i] = UpdateSeg{x.W, x.O, x.oscale, (int)x.m, (int)x.n, (int)x.mp, (int)x.ldx, x.step, nblk, x.n % 8 == 0,
                          i < n ? (unsigned int)blk : 0xffffffffu};
     if (i >= n) continue;
     blk += (unsigned long)nblk * (unsigned long)x.count;
@@ -417,17 +457,16 @@ static int launch_update_set(const UpdateDesc* const* d, int n, float decay_fact
     bytes += (double)x.count * x.m * x.n * (2 + 2 * (dtype == MLC_F32 ? 4 : 2));
   }
   LaunchScope scope(MLC_KERNEL_UPDATE, stream, 0.0, bytes);
-  const bool vec = d[0]->n % 8 == 0;
-#define MLC_UPD(WT, V) \
-  hipLaunchKernelGGL((muon_update_kernel<WT, V>), dim3((unsigned)blk), dim3(EW_THREADS), 0, stream, tab, decay_factor)
-  if (dtype == MLC_F32) { if (vec) MLC_UPD(float, true); else MLC_UPD(float, false); }
-  else { if (vec) MLC_UPD(bf16_t, true); else MLC_UPD(bf16_t, false); }
+#define MLC_UPD(WT, KINDS) \
+  hipLaunchKernelGGL((muon_update_kernel<WT, KINDS>), dim3((unsigned)blk), dim3(EW_THREADS), 0, stream, tab, decay_factor)
+  if (dtype == MLC_F32) { if (kinds == 3) MLC_UPD(float, 3); else if (kinds == 2) MLC_UPD(float, 2); else MLC_UPD(float, 1); }
+  else { if (kinds == 3) MLC_UPD(bf16_t, 3); else if (kinds == 2) MLC_UPD(bf16_t, 2); else MLC_UPD(bf16_t, 1); }
 #undef MLC_UPD
   return check_launch();
 }
 
 int launch_param_update(const UpdateDesc* d, int n, float decay_factor, hipStream_t stream) {
-  auto kind = [](const UpdateDesc& x) { return x.dtype * 2 + (x.n % 8 == 0 ? 1 : 0); };
+  auto kind = [](const UpdateDesc& x) { return x.dtype; };
   return launch_by_kind(d, n, kind, [&](const UpdateDesc* const* pick, int np) {
     return launch_update_set(pick, np, decay_factor, stream);
   });

@@ -61,6 +61,7 @@ constexpr int NTHREADS = 256;
 constexpr int NUM_XCD = 8;
 constexpr int GROUP_M = 8;        // most tile rows per group of the tile order
 constexpr size_t CU_LDS = 160 * 1024;
+constexpr int SC1 = 16;           // of a buffer store: write through
 
 struct GemmArgs {
   const bf16_t* A; long lda, strideA;
@@ -184,19 +185,19 @@ constexpr unsigned int BUFFER_END = 0xfffffff0u;
 struct TileCoord { int b, m0, n0, mirror, diag, edge; };
 
 // TI adjacent bf16 values of a row <-> TI / 2 words.
-template <int TI>
+template <int TI, int AUX>
 __device__ __forceinline__ void store_words(const unsigned int (&w)[TI / 2], __amdgpu_buffer_rsrc_t r,
                                             unsigned int voff, unsigned int soff) {
   if constexpr (TI == 8) {
     u32x4 v;
     v.x = w[0]; v.y = w[1]; v.z = w[2]; v.w = w[3];
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, AUX);
   } else if constexpr (TI == 2) {
-    __builtin_amdgcn_raw_buffer_store_b32(w[0], r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(w[0], r, voff, soff, AUX);
   } else {
     u32x2 v;
     v.x = w[0]; v.y = w[1];
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, AUX);
   }
 }
 
@@ -215,7 +216,7 @@ constexpr int epilogue_stores(int ti, bool mirror) {      // what store_tile lea
   const int plain = ti == 8 ? 16 : ti == 4 ? 8 : 2, transposed = ti == 2 ? 8 : 16;
   return mirror ? plain + transposed : plain;
 }
-template <int TI, int TJ, bool HAS_C, bool MIRROR, bool TOUT, bool DIAG, bool UNIT>
+template <int TI, int TJ, int AUX, bool HAS_C, bool MIRROR, bool TOUT, bool DIAG, bool UNIT>
 __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)[TI][TJ],
                                            const TileCoord& tc, float alpha, int wbase_m, int wbase_n,
                                            int lane, bool drop, u32x4 (&pend)[TI == 8 ? 16 : 1]) {
@@ -287,7 +288,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
           if constexpr (TI == 8) {
             if (P > 0) { pend[x] = u32x4{w[e][0], w[e][1], w[e][2], w[e][3]}; continue; }
           }
-          store_words<TI>(w[e], rd, voff_m, (unsigned int)(32 * (x / 8) + x % 8) * ldd2);
+          store_words<TI, AUX>(w[e], rd, voff_m, (unsigned int)(32 * (x / 8) + x % 8) * ldd2);
         }
       }
   } else {
@@ -330,12 +331,12 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
           if (P > 0) { pend[2 * i] = packed[0]; pend[2 * i + 1] = packed[1]; continue; }
         }
         if constexpr (NH == 1) {          // a wavefront's rows are 64 bytes: nothing to gather
-          __builtin_amdgcn_raw_buffer_store_b128(packed[0], rd, voff_n, (unsigned int)i * ldd2, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(packed[0], rd, voff_n, (unsigned int)i * ldd2, AUX);
         } else {
           u32x4 x, y;
           pair_rows(packed[0], packed[1], odd, x, y);
-          __builtin_amdgcn_raw_buffer_store_b128(x, rd, voff_n, (unsigned int)i * ldd2, 0);
-          __builtin_amdgcn_raw_buffer_store_b128(y, rd, voff_n, (unsigned int)(TI + i) * ldd2, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(x, rd, voff_n, (unsigned int)i * ldd2, AUX);
+          __builtin_amdgcn_raw_buffer_store_b128(y, rd, voff_n, (unsigned int)(TI + i) * ldd2, AUX);
         }
 #pragma unroll
         for (int h = 0; h < NH; ++h) first[i][h] = packed[h];
@@ -351,7 +352,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
           for (int i = 0; i < TI; i += 2)
             w[i / 2] = (e & 1) ? pair_hi(first[i][h][e / 2], first[i + 1][h][e / 2])
                                : pair_lo(first[i][h][e / 2], first[i + 1][h][e / 2]);
-          store_words<TI>(w, rd, voff_m, (unsigned int)(32 * h + e) * ldd2);
+          store_words<TI, AUX>(w, rd, voff_m, (unsigned int)(32 * h + e) * ldd2);
         }
     }
   }
@@ -546,8 +547,8 @@ __device__ __forceinline__ void store_triangle(const GemmArgs& g, const f32x4 (&
 // Workgroups are dealt round-robin to the 8 XCDs, so XCD x owns the contiguous range of
 // tiles [x * tiles_per_xcd, (x + 1) * tiles_per_xcd) and its workgroups take them in
 // order: tiles that share operand panels run at the same time behind the same L2.
-// BKS: operand B is K-strided.  NB: buffers of the ring; K >= 64 * (NB - 1) / 2.
-template <int BM, int BN, bool BKS, int NB>
+// BKS: operand B is K-strided.  NB: buffers of the ring; K >= 64 * (NB - 1) / 2.  WT: results are written through.
+template <int BM, int BN, bool BKS, int NB, bool WT>
 __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
   static_assert(BM == BN && NB % 2 == 1, "one buffer size, an odd ring");
   constexpr int TI = BM / 32, TJ = BN / 32;          // accumulator tiles per wavefront
@@ -1023,7 +1024,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
       alpha *= (g.bscale_pow == 2) ? sc * sc : sc;
     }
 #define MLC_STORE(C, M, T, DG, U) \
-  store_tile<TI, TJ, C, M, T, DG, U>(g, acc, tc, alpha, wbase_m, wbase_n, lane, drop, pend)
+  store_tile<TI, TJ, WT ? SC1 : 0, C, M, T, DG, U>(g, acc, tc, alpha, wbase_m, wbase_n, lane, drop, pend)
     // Symmetric products (Gram, polynomial) are those with a K-contiguous B, the apply products
     // those with a K-strided one: each kernel holds only the forms its products have.
     if constexpr (!BKS) {
@@ -1089,12 +1090,14 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
 constexpr int MAX_MULTI = 3;
 struct MultiArgs { GemmArgs seg[MAX_MULTI]; int nseg, mixed; };
 
-template <int BM, int BN, bool BKS, int NB>
+template <int BM, int BN, bool BKS, int NB, bool WT>
 __global__ __launch_bounds__(NTHREADS, 1) void ns_gemm_bf16_kernel(MultiArgs m) {
   const int xcd = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD;
   const int W = (int)(gridDim.x / NUM_XCD);
   int first = 0;                       // of equal depth: the workgroup whose turn it is
-  Dealer dealer{W, slot, 0, 0};        // of different depth, which only the large tile's launches mix
+  // Of different depth.  Small tiles are dealt as if of equal depth: the arithmetic alone, whether used or not, makes each of their
+  // launches 0.8 us longer (of about 4 to 8).
+  Dealer dealer{W, slot, 0, 0};
 #pragma unroll 1
   for (int j = 0; j < m.nseg; ++j) {
     const GemmArgs g = m.seg[j];
@@ -1109,7 +1112,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ns_gemm_bf16_kernel(MultiArgs m) 
       deal = Deal{lo + (pos < 0 ? pos + W : pos), hi, W, hi, hi, W};
       if (more) first = (int)((unsigned)(first + hi - lo) % (unsigned)W);
     }
-    run_tiles<BM, BN, BKS, NB>(g, deal);
+    run_tiles<BM, BN, BKS, NB, WT>(g, deal);
     // the next product's first transfers overwrite the ring: every wavefront must have left it
     __syncthreads();
   }
@@ -1183,7 +1186,7 @@ bool valid_desc(const GemmDesc& d) {
 }
 
 // n (1 .. MAX_MULTI) products of one layout in one launch, in descending order of depth.
-template <int BM, int BN, bool BKS, int NB>
+template <int BM, int BN, bool BKS, int NB, bool WT>
 int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   MultiArgs m;
   m.nseg = n;
@@ -1210,7 +1213,7 @@ int launch_cfg(const GemmDesc* const* d, int n, hipStream_t stream) {
   }
   if (most < W) W = most;    // fewer tiles than compute units
   static_assert((size_t)NB * BM * BK * 2 <= CU_LDS, "the ring fits a CU");
-  auto kern = ns_gemm_bf16_kernel<BM, BN, BKS, NB>;
+  auto kern = ns_gemm_bf16_kernel<BM, BN, BKS, NB, WT>;
   static std::atomic<bool> attr_set[MAX_DEVICES];
   const int rc = raise_lds_limit(kern, attr_set, slot, CU_LDS);
   if (rc != MLC_OK) return rc;
@@ -1240,6 +1243,7 @@ long tiles_of(const GemmDesc& d, int tile) {
 // that fits, nine in ten launches now take 0.83 to 1.09 of this, the median 0.91 with 64 x 64 tiles and 0.95
 // with the others.
 enum { FORM_GRAM, FORM_POLY, FORM_APPLY };
+int form_of(const GemmDesc& d) { return !d.symmetric ? FORM_APPLY : d.C ? FORM_POLY : FORM_GRAM; }
 double estimate_us(int tile, int form, long tiles, int kt, int cus) {
   const long full = tiles / cus, rest = tiles - full * cus;
   if (tile == 256) {
@@ -1275,7 +1279,7 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
     for (int t = 0; t < 3; ++t) tiles[t] += tiles_of(*d[j], 256 >> t);
   }
   const int kt = d[0]->K / BK;
-  const int form = !d[0]->symmetric ? FORM_APPLY : d[0]->C ? FORM_POLY : FORM_GRAM;
+  const int form = form_of(*d[0]);
   int small = 128;
   double us = estimate_us(128, form, tiles[1], kt, cus);
   const double e64 = estimate_us(64, form, tiles[2], kt, cus);
@@ -1286,6 +1290,52 @@ int pick_tile(const GemmDesc* const* d, int n, int cus) {
 
 // Products of one layout, at first of one depth, and the kernel that they run in.
 struct GemmSet { const GemmDesc* d[MAX_MULTI]; int n, tile, ring; };
+
+long tiles_in(const GemmSet& s, int tile) {
+  long tiles = 0;
+  for (int j = 0; j < s.n; ++j) tiles += tiles_of(*s.d[j], tile);
+  return tiles;
+}
+double set_us(const GemmSet& s, int cus) {
+  return estimate_us(s.tile, form_of(*s.d[0]), tiles_in(s, s.tile), s.d[0]->K / BK, cus);
+}
+
+// Do set t's products go out with those of set s, which are as deep or deeper?  If so s is left with the kernel for both.  Large
+// tiles always do (a tile that is small because there are few of them stays apart from them: its launch is shorter than a large
+// tile).  Small ones do where their results are of one size (a layer's square and rectangular matrices: Gram products) or the
+// depth is the same, and where the two leave much of the chip idle: together less than 1.75 rounds (1.5 of 64 x 64 tiles), or one
+// of them at most three quarters (half) of one; others keep launches of their own.  Sets that run different small tiles take one
+// if that makes one round of all and the estimate is lower.  A launch costs 2.7 us however little it does, its first transfers and
+// last stores as much again, and a partly empty round more: inner steps of three groups, 4 c of d x d, c of d x f and f x d, with sets
+// of different depth and divisors apart and together (6 to 10 us of it are launches of elementwise kernels): 4, 256 / 1000: 151 -> 119 us;
+// 2, 303 / 640: 179 -> 146; 1, 512 / 1536: 167 -> 133; 4, 768 / 2449: 645 -> 577; 3, 896 / 2944: 725 -> 645; 10, 512 / 640: 481 -> 465.
+bool join_sets(GemmSet& s, const GemmSet& t, int cus) {
+  if (s.n + t.n > MAX_MULTI || (t.d[0]->b_kstrided != 0) != (s.d[0]->b_kstrided != 0)) return false;
+  if (s.tile == 256 || t.tile == 256) return s.tile == t.tile;
+  int tile = s.tile;
+  const int64_t deep = s.d[0]->K, shallow = t.d[0]->K;
+  if (s.tile == t.tile) {
+    const long a = tiles_in(s, tile), b = tiles_in(t, tile);
+    const int quarters = tile == 64 ? 2 : 3;
+    if (deep != shallow && s.d[0]->M != t.d[0]->M && (a + b) * 4 > (quarters + 4L) * cus && std::min(a, b) * 4 > quarters * cus)
+      return false;
+  } else {
+    double us = set_us(s, cus) + set_us(t, cus);
+    tile = 0;
+    for (int x = 128; x >= 64; x /= 2) {
+      const long tiles = tiles_in(s, x) + tiles_in(t, x);
+      if (tiles > cus || (x == 64 && shallow < 4 * BK)) continue;
+      const double e = estimate_us(x, form_of(*s.d[0]), tiles, (int)(deep / BK), cus);
+      if (e < us) { us = e; tile = x; }
+    }
+    if (!tile) return false;
+  }
+  const bool nine = tile == 64 || deep > 640 || (s.tile == 128 && s.ring == 9) || (t.tile == 128 && t.ring == 9);
+  if (nine && shallow < 4 * BK) return false;       // the long ring needs four K tiles
+  s.tile = tile;
+  s.ring = nine ? 9 : 5;
+  return true;
+}
 
 void choose_kernel(GemmSet& s) {
   const int cus = cus_per_xcd(device_slot()) * NUM_XCD;
@@ -1307,10 +1357,10 @@ void choose_kernel(GemmSet& s) {
 
 template <bool BKS>
 int launch_set(const GemmSet& s, hipStream_t stream) {
-  if (s.tile == 256) return launch_cfg<256, 256, BKS, 5>(s.d, s.n, stream);
-  if (s.tile == 64) return launch_cfg<64, 64, BKS, 9>(s.d, s.n, stream);
-  if (s.ring == 5) return launch_cfg<128, 128, BKS, 5>(s.d, s.n, stream);
-  return launch_cfg<128, 128, BKS, 9>(s.d, s.n, stream);
+  if (s.tile == 256) return launch_cfg<256, 256, BKS, 5, false>(s.d, s.n, stream);
+  if (s.tile == 64) return launch_cfg<64, 64, BKS, 9, false>(s.d, s.n, stream);
+  if (s.ring == 5) return launch_cfg<128, 128, BKS, 5, false>(s.d, s.n, stream);
+  return launch_cfg<128, 128, BKS, 9, false>(s.d, s.n, stream);
 }
 
 }  // namespace
@@ -1320,6 +1370,7 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
   bool done[64] = {};
   for (int i = 0; i < n; ++i)
     if (!valid_desc(d[i])) return MLC_ERR_SHAPE;
+  const int cus = cus_per_xcd(device_slot()) * NUM_XCD;
   GemmSet sets[64];
   int n_sets = 0;
   for (int i = 0; i < n; ++i) {
@@ -1338,15 +1389,14 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
     }
     choose_kernel(s);
   }
-  // Sets of large tiles share launches as well, the deeper ones first.  (A tile that is small because
-  // there are few of them stays alone: its launch is shorter than a large tile.)
+  // Sets share launches as well, the deeper ones first
   std::stable_sort(sets, sets + n_sets, [](const GemmSet& a, const GemmSet& b) { return a.d[0]->K > b.d[0]->K; });
   for (int i = 0; i < n_sets; ++i) {
     GemmSet& s = sets[i];
     if (s.n == 0) continue;            // went out with an earlier one
-    for (int j = i + 1; j < n_sets && s.tile == 256; ++j) {
+    for (int j = i + 1; j < n_sets; ++j) {
       GemmSet& t = sets[j];
-      if (t.n == 0 || t.tile != 256 || s.n + t.n > MAX_MULTI || (t.d[0]->b_kstrided != 0) != (s.d[0]->b_kstrided != 0)) continue;
+      if (t.n == 0 || !join_sets(s, t, cus)) continue;
       for (int k = 0; k < t.n; ++k) s.d[s.n++] = t.d[k];
       t.n = 0;
     }

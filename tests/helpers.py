@@ -162,42 +162,68 @@ def ns_tiles(groups, cus=256):
         if not (s == 128 and l <= 512):
             jobs.append((i, c, s, l))
     out = [None if i not in [j[0] for j in jobs] else [0, 0, 0] for i in range(len(groups))]
-    for form in range(3):
-        todo = list(jobs)
-        while todo:
-            def shape(j):
-                _, c, s, l = j
-                return c, s, (l if form == 2 else s), (l if form == 0 else s)       # batch, M, N, K
-            first = shape(todo[0])
+    def estimate(t, form, tiles, kt):
+        full, rest = divmod(tiles, cus)
+        if t == 256:
+            f = rest / cus
+            return 3.5 + full * (kt * 1.40 + k["E"][form]) + (
+                kt * (1.02 + 0.38 * f) + k["R"][form] + k["F"][form] * f if rest else 0.0)
+        base, one, more, epi = k[t][4 * form:4 * form + 4]
+        return base + one * kt + (full + (rest > 0) - 1) * (more * kt + epi)
 
-            def large(M, N):     # sides that the 256 x 256 tile divides, or long enough for half a tile twice
-                return all(d >= 256 and (d % 256 == 0 or d >= 896) for d in (M, N))
+    for form in range(3):
+        def shape(j):
+            _, c, s, l = j
+            return c, s, (l if form == 2 else s), (l if form == 0 else s)       # batch, M, N, K
+
+        def count(some, t):
+            return sum(c * (-(-M // t) * (-(-M // t) + 1) // 2 if form < 2 else -(-M // t) * -(-N // t))
+                       for c, M, N, K in map(shape, some))
+
+        def large(M, N):     # sides that the 256 x 256 tile divides, or long enough for half a tile twice
+            return all(d >= 256 and (d % 256 == 0 or d >= 896) for d in (M, N))
+        todo, sets = list(jobs), []
+        while todo:
+            first = shape(todo[0])
             fits = large(*first[1:3])
             some = [j for j in todo if shape(j)[3] == first[3] and large(*shape(j)[1:3]) == fits][:3]
             todo = [j for j in todo if j not in some]
             kt = first[3] // 64
-            tiles, nbytes = {}, 0
-            for t in (64, 128, 256):
-                tiles[t] = sum(c * (-(-M // t) * (-(-M // t) + 1) // 2 if form < 2 else -(-M // t) * -(-N // t))
-                               for c, M, N, K in map(shape, some))
-            for c, M, N, K in map(shape, some):
-                nbytes += 2 * c * K * (M + (N if form == 2 else 0))
-
-            def estimate(t):
-                full, rest = divmod(tiles[t], cus)
-                if t == 256:
-                    f = rest / cus
-                    return 3.5 + full * (kt * 1.40 + k["E"][form]) + (
-                        kt * (1.02 + 0.38 * f) + k["R"][form] + k["F"][form] * f if rest else 0.0)
-                base, one, more, epi = k[t][4 * form:4 * form + 4]
-                return base + one * kt + (full + (rest > 0) - 1) * (more * kt + epi)
-            tile, us = 128, estimate(128)
-            if kt >= 4 and estimate(64) < 0.95 * us:
-                tile, us = 64, estimate(64)
-            if fits and not us < (0.85 if nbytes > 64e6 else 0.95) * estimate(256):
+            nbytes = sum(2 * c * K * (M + (N if form == 2 else 0)) for c, M, N, K in map(shape, some))
+            tile, us = 128, estimate(128, form, count(some, 128), kt)
+            e64 = estimate(64, form, count(some, 64), kt)
+            if kt >= 4 and e64 < 0.95 * us:
+                tile, us = 64, e64
+            if fits and kt >= 4 and not us < (0.85 if nbytes > 64e6 else 0.95) * estimate(256, form, count(some, 256), kt):
                 tile = 256
-            for j in some:
-                out[j[0]][form] = tile
+            sets.append([some, tile, kt])
+        # sets that run different small tiles and make one round together take one tile
+        sets.sort(key=lambda x: -x[2])
+        for i, a in enumerate(sets):
+            for b in sets[i + 1:]:
+                if not a[0] or not b[0] or len(a[0]) + len(b[0]) > 3 or (a[1] == 256) != (b[1] == 256):
+                    continue
+                if a[1] == b[1]:
+                    ca, cb = count(a[0], a[1]), count(b[0], b[1])
+                    q = 2 if a[1] == 64 else 3
+                    several = (ca + cb) * 4 > (q + 4) * cus and min(ca, cb) * 4 > q * cus
+                    if a[1] != 256 and a[2] != b[2] and shape(a[0][0])[1] != shape(b[0][0])[1] and several:
+                        continue
+                    tile = a[1]
+                else:
+                    us = sum(estimate(x[1], form, count(x[0], x[1]), x[2]) for x in (a, b))
+                    tile = 0
+                    for t in (128, 64):
+                        n = count(a[0] + b[0], t)
+                        if n <= cus and (t == 128 or b[2] >= 4) and estimate(t, form, n, a[2]) < us:
+                            tile, us = t, estimate(t, form, n, a[2])
+                    if not tile:
+                        continue
+                if tile == 128 and b[2] < 4 and a[2] > 10:       # the long ring needs four K tiles
+                    continue
+                a[0], a[1], b[0] = a[0] + b[0], tile, []
+            for j in a[0]:
+                out[j[0]][form] = a[1]
     return [None if o is None else tuple(o) for o in out]
 
 

@@ -485,3 +485,38 @@ def test_half_tiles_at_the_edge(shapes, tiles):
     (g, w), s = few[0], shapes[0]
     _check_group(w[:1].cpu(), g[:1].cpu(), torch.zeros((1, *s[1:])), groups[0].param[:1].cpu(), groups[0].momentum[:1].cpu(), hp,
                  0.7, f"{s}")
+
+
+# Products of several depths that share launches in small tiles: in one round, in more, sets that run different small tiles
+# and take one, a depth of two K tiles; momentum, norm and update launches of rows that are a multiple of 8 and others,
+# plain and transposed, and of more groups than share one
+JOINED = [([(4, 512, 512), (1, 512, 1536), (1, 1536, 512)], 15), ([(8, 303, 303), (2, 303, 640), (2, 640, 303)], 15),
+          ([(16, 256, 256), (4, 256, 1000), (4, 1000, 256)], 15), ([(16, 768, 768), (4, 768, 2449), (4, 2449, 768)], 15),
+          ([(8, 640, 640), (2, 640, 1192), (2, 1192, 640)], 15), ([(2, 384, 384), (3, 128, 640), (1, 512, 901)], 15),
+          ([(2, 200, 136), (1, 300, 77), (1, 77, 901), (2, 333, 512), (1, 1001, 384)], None)]
+
+
+@pytest.mark.parametrize("shapes,launches", JOINED)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_small_products_of_several_depths_share_launches(shapes, launches, dtype):
+    """The bits of one group after the other."""
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-2, beta=0.9)
+
+    def build():
+        host = [_make_group(c, m, n, dtype, torch.bfloat16, seed=60 + i) for i, (c, m, n) in enumerate(shapes)]
+        return host, [mlc.InnerGroup(*[t.to(DEV) for t in h], 0.5) for h in host]
+    (host, together), (_, apart) = build(), build()
+    ws = torch.empty(mlc.muloco_inner_workspace_bytes(together), dtype=torch.uint8, device=DEV)
+    mlc.muloco_timing_enable(True)
+    mlc.muloco_timing_read()
+    mlc.muloco_inner_step(together, hp, ws)
+    n = mlc.muloco_timing_read()["ns_gemm"]["launches"]
+    mlc.muloco_timing_enable(False)
+    assert launches in (n, None)
+    for g in apart:
+        mlc.muloco_inner_step([g], hp, ws)
+    torch.cuda.synchronize()
+    for a, b in zip(together, apart):
+        assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
+    for (W0, g, m0), grp, s in zip(host, together, shapes):
+        _check_group(W0[-1:], g[-1:], m0[-1:], grp.param[-1:].cpu(), grp.momentum[-1:].cpu(), hp, 0.5, f"group {s}")
