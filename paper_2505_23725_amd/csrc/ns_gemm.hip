@@ -1355,12 +1355,21 @@ void choose_kernel(GemmSet& s) {
   if (!(K < 256 || tiles <= (K == 256 ? 8 : K <= 640 ? 2 : 0) * cus)) s.ring = 9;
 }
 
+// The small tiles' results are written through to memory.  Their launches are short, and one ends only when the L2s
+// have written back what it left in them: inner steps of 12 x 401 x 401 and two groups of 3 beside it 190 -> 178 us, of
+// 24 x 512 x 512 and 6 346 -> 333, newton_schulz of 6 of 3001 x 1000 434 -> 421.  Of a few 64 x 64 tiles nothing is left to wait for
+// (a 256 x 256 matrix, ten and sixteen tiles: 73 to 76 us, written through 77 to 78; a 512 x 512 one, 36 and 64, alike).  In long
+// launches of large tiles it is worth nothing, in short ones it costs 1 %.
+constexpr long THROUGH_TILES = 64;
 template <bool BKS>
 int launch_set(const GemmSet& s, hipStream_t stream) {
   if (s.tile == 256) return launch_cfg<256, 256, BKS, 5, false>(s.d, s.n, stream);
-  if (s.tile == 64) return launch_cfg<64, 64, BKS, 9, false>(s.d, s.n, stream);
-  if (s.ring == 5) return launch_cfg<128, 128, BKS, 5, false>(s.d, s.n, stream);
-  return launch_cfg<128, 128, BKS, 9, false>(s.d, s.n, stream);
+  if (s.tile == 64) {
+    if (tiles_in(s, 64) < THROUGH_TILES) return launch_cfg<64, 64, BKS, 9, false>(s.d, s.n, stream);
+    return launch_cfg<64, 64, BKS, 9, true>(s.d, s.n, stream);
+  }
+  if (s.ring == 5) return launch_cfg<128, 128, BKS, 5, true>(s.d, s.n, stream);
+  return launch_cfg<128, 128, BKS, 9, true>(s.d, s.n, stream);
 }
 
 }  // namespace
