@@ -139,7 +139,18 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}; the library takes float32 or bfloat16")
 
 
+def _pointer(t):
+    """Address of a tensor that is plainly in order (csrc/marshal.cpp), else None."""
+    global _pointer
+    from . import _marshal              # built with the library; there is no fallback
+    _pointer = _marshal.pointer
+    return _pointer(t)
+
+
 def _dev_ptr(t: torch.Tensor, what: str) -> int:
+    p = _pointer(t)
+    if p is not None:
+        return p
     if not t.is_cuda:
         raise ValueError(f"{what} must live on the GPU")
     if not t.is_contiguous():
@@ -447,8 +458,13 @@ class AdamWHParams:
 
 def muloco_adamw_step(tensors: Sequence[tuple], hp: AdamWHParams, stream=None) -> None:
     """tensors: (param, grad, exp_avg, exp_avg_sq) tuples of equally sized device tensors."""
-    arr = (_AdamWGroup * max(1, len(tensors)))()
-    for i, (p_, g_, m_, v_) in enumerate(tensors):
+    from . import _marshal
+    ready = _marshal.adamw_groups(tensors) if tensors else None
+    if ready is not None:
+        arr = (_AdamWGroup * len(tensors)).from_buffer_copy(ready)
+    else:
+        arr = (_AdamWGroup * max(1, len(tensors)))()
+    for i, (p_, g_, m_, v_) in enumerate(tensors if ready is None else ()):
         n = p_.numel()
         if g_.numel() != n or m_.numel() != n or v_.numel() != n:
             raise ValueError("param, grad, exp_avg and exp_avg_sq must have the same size")

@@ -9,6 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libmuloco.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 MICROBENCH_PATH = os.path.join(HERE, "mlc_microbench")
 SOURCES = ["api.hip", "ns_gemm.hip", "ns_chain_small.hip", "inner_elementwise.hip", "outer.hip"]
 
@@ -41,8 +42,27 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
+    build_marshal(verbose)
     build_microbench(verbose)
     return LIB_PATH
+
+
+def build_marshal(verbose: bool = True) -> str:
+    """The binding's native part: reads tensors' addresses (host code only, against torch's headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[x for i in cpp_extension.include_paths() for x in ("-isystem", i)], "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "marshal.cpp"), "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL_PATH]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n" + res.stderr)
+    return MARSHAL_PATH
 
 
 def build_microbench(verbose: bool = True) -> str:
