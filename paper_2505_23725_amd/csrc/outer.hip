@@ -122,6 +122,94 @@ __device__ __forceinline__ float ef_input(float delta, float residual, float bet
   return __fadd_rn(__fmul_rn(beta, residual), delta);
 }
 
+// The level of a value without a division, where that is certain.  With i = 1 / scale to within 2^-24, fl(x i) is within
+// 3 * 2^-24 of fl(x / scale), relative to it; both round to the same integer unless that distance reaches from fl(x i) to a
+// half-integer, so unless |fl(x i) - rint(fl(x i))| >= 0.5 - (levels + 1) 2^-22.  Values closer to a tie (4 in 10^6 of 4-bit levels, 1 in 10^4
+// of 8-bit offset ones, more where data sit on a grid), and scales for which 1 / scale is no ordinary number, are divided.
+// Levels stay in floating point from there to the codes and to what is sent.  (Without an offset lo is 0, and to subtract
+// and add it changes nothing but the sign of a level -0, which counts as 0.)
+//
+// The one-pass kernels are bound by the memory stream and, from about three workers on, by vector instructions, of which each
+// value took 34 a worker, ten of them the division: with eight workers the SIMDs issued them for 0.7 of the time.  Now about 20.  4-bit
+// steps, us before and after: rows of 736 and 2432, eight workers, 182 -> 153; 528 and 1664, four, 267 -> 238, one, 293 -> 280; 1024 and
+// 4096, eight, 151 -> 134, one, 423 -> 420.
+struct Divider { float scale, lo, inv, limit, low, high; };
+// SCALAR: in scalar registers, for a range that a wavefront's lanes share.  (It frees vector registers where rows are alone in a
+// launch, rows of 2560 and 10240 with four workers 560 -> 552 us; beside others it only adds moves, 736 and 2432 with eight 153 -> 160.)
+template <bool SCALAR>
+__device__ __forceinline__ Divider make_divider(const Range& r, const QuantForm& f) {
+  auto uniform = [](float v) { return SCALAR ? __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))) : v; };
+  Divider d;
+  d.scale = uniform(r.scale);
+  d.lo = uniform(r.lo);
+  const float i = __builtin_amdgcn_rcpf(d.scale);
+  d.inv = uniform(fmaf(i, fmaf(-d.scale, i, 1.f), i));
+  const bool ordinary = d.scale >= 0x1p-100f && d.scale <= 0x1p100f;
+  d.limit = uniform(ordinary ? 0.5f - (f.levels + 1.f) * 0x1p-22f : -1.f);
+  d.low = f.offset ? 0.f : -f.levels;
+  d.high = f.levels;
+  return d;
+}
+__device__ __forceinline__ void quant_levels4(const float* v, const Divider& d, float (&q)[4]) {
+  float worst = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float t = __fmul_rn(__fsub_rn(v[j], d.lo), d.inv);
+    q[j] = rintf(t);
+    worst = fmaxf(worst, fabsf(__fsub_rn(t, q[j])));
+  }
+  if (worst >= d.limit) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = d.scale > 0.f ? rintf(__fsub_rn(v[j], d.lo) / d.scale) : 0.f;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) q[j] = __builtin_amdgcn_fmed3f(q[j], d.low, d.high);     // (a NaN becomes the lowest level)
+}
+__device__ __forceinline__ float dequant_level(float q, const Divider& d) {
+  return __fadd_rn(__fmul_rn(q, d.scale), d.lo);
+}
+// The codes of 4 levels, first one lowest: levels that take up to 16 bits are added up exactly in fp32, their bias with them.
+__device__ __forceinline__ unsigned int pack_levels4(const float (&q)[4], int bits, int bias) {
+  const float b = (float)bias;
+  if (bits == 4) return (unsigned int)fmaf(fmaf(fmaf(q[3] + b * (4369.f / 4096.f), 16.f, q[2]), 16.f, q[1]), 16.f, q[0]);
+  if (bits == 2) return (unsigned int)fmaf(fmaf(fmaf(q[3] + b * (85.f / 64.f), 4.f, q[2]), 4.f, q[1]), 4.f, q[0]);
+  const float c = b * (257.f / 256.f);
+  return (unsigned int)fmaf(q[1] + c, 256.f, q[0]) | (unsigned int)fmaf(q[3] + c, 256.f, q[2]) << 16;
+}
+__device__ __forceinline__ void store_packed8(uint8_t* crow, int c, const u32x2& p, int bits) {
+  if (bits == 4) *reinterpret_cast<unsigned int*>(crow + c / 2) = p.x;
+  else if (bits == 8) *reinterpret_cast<u32x2*>(crow + c) = p;
+  else *reinterpret_cast<unsigned short*>(crow + c / 4) = (unsigned short)p.x;
+}
+// The first cnt of 8 levels at an address aligned to a byte only (cnt * bits is a multiple of 8).
+__device__ __forceinline__ void store_packed8_part(uint8_t* crow, int c, const u32x2& p, int bits, int cnt) {
+  typedef unsigned short u16_u __attribute__((aligned(1)));
+  typedef unsigned int u32_u __attribute__((aligned(1)));
+  uint8_t* const at = crow + c * bits / 8;
+  if (cnt >= 8) {
+    if (bits == 2) *reinterpret_cast<u16_u*>(at) = (unsigned short)p.x;
+    else *reinterpret_cast<u32_u*>(at) = p.x;
+    if (bits == 8) *reinterpret_cast<u32_u*>(at + 4) = p.y;
+  } else {
+    const unsigned long w = p.x | (unsigned long)p.y << 32;
+    for (int j = 0; j < cnt * bits / 8; ++j) at[j] = (uint8_t)(w >> (8 * j));
+  }
+}
+// Largest value of a wavefront, in all its lanes, through lanes' neighbours in registers (six round trips through the LDS
+// otherwise, which every worker's row waits for).
+__device__ __forceinline__ float wave_max_dpp(float v) {
+#define MLC_DPP_MAX(CTRL) \
+  v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(v), __float_as_uint(v), CTRL, 0xf, 0xf, false)))
+  MLC_DPP_MAX(0xb1);        // the neighbour of a pair, the other pair of four, the mirrored half of 8, of 16
+  MLC_DPP_MAX(0x4e);
+  MLC_DPP_MAX(0x141);
+  MLC_DPP_MAX(0x140);
+  MLC_DPP_MAX(0x142);       // lane 15 of the row before, lane 31 of the half before
+  MLC_DPP_MAX(0x143);
+#undef MLC_DPP_MAX
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
+}
+
 // 8 adjacent levels of a row, first column c (a multiple of 8) <-> bits bytes of its codes
 __device__ __forceinline__ void store_codes8(uint8_t* crow, int c, const int (&q)[8], int bits, int bias) {
   if (bits == 4) {
@@ -142,24 +230,6 @@ __device__ __forceinline__ void store_codes8(uint8_t* crow, int c, const int (&q
 #pragma unroll
     for (int j = 0; j < 8; ++j) p |= (unsigned int)(q[j] + bias) << (2 * j);
     *reinterpret_cast<unsigned short*>(crow + c / 4) = (unsigned short)p;
-  }
-}
-
-// The first cnt of 8 levels at an address aligned to a byte only (cnt * bits is a multiple of 8).
-__device__ __forceinline__ void store_codes8_part(uint8_t* crow, int c, const int (&q)[8], int bits, int bias,
-                                                  int cnt) {
-  typedef unsigned short u16_u __attribute__((aligned(1)));
-  typedef unsigned int u32_u __attribute__((aligned(1)));
-  unsigned long p = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) p |= (unsigned long)(unsigned int)(q[j] + bias) << (bits * j);
-  uint8_t* const at = crow + c * bits / 8;
-  if (cnt >= 8) {
-    if (bits == 2) *reinterpret_cast<u16_u*>(at) = (unsigned short)p;
-    else *reinterpret_cast<u32_u*>(at) = (unsigned int)p;
-    if (bits == 8) *reinterpret_cast<u32_u*>(at + 4) = (unsigned int)(p >> 32);
-  } else {
-    for (int j = 0; j < cnt * bits / 8; ++j) at[j] = (uint8_t)(p >> (8 * j));
   }
 }
 
@@ -354,16 +424,18 @@ __global__ __launch_bounds__(OT_THREADS) void quantize_rows_kernel(
 // `blk` is the index of the workgroup among those that share these arguments; the pointer sets
 // may be the 32-wide ones of a single-group launch or the narrow ones of a launch that covers
 // several groups.
+// KC: the number of workers where it is known (1: nothing is requested ahead, which takes a third of the registers).
 // RAG: rows of any length, so neither the rows nor their codes are aligned and the last vector of
 // a row may be a part of one (24 / 6 / 6 matrices of 1001 x 1001, 1001 x 2730 and 2730 x 1001, two
 // workers, 8 bits with error feedback: 1500 us element by element in two passes, 516 like this).
-template <typename WT, typename GT, int NV, int G0, bool OUTER, bool RAG, typename PW, typename PC, typename PS,
+template <typename WT, typename GT, int NV, int G0, bool OUTER, bool RAG, int KC, bool SCALAR, typename PW, typename PC, typename PS,
           typename PO, typename PE>
 __device__ __forceinline__ void quantize_rows_reg_body(
     const PW& w, GT* __restrict__ theta_g, float* __restrict__ u, const PC& codes, const PS& scales,
-    const PO& offsets, const PE& ef, long rows, int n, int K, const QuantForm& form, float eta, float mu,
+    const PO& offsets, const PE& ef, long rows, int n, int workers, const QuantForm& form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
     float* mean_offsets, long blk) {
+  const int K = KC ? KC : workers;
   constexpr bool WHOLE = G0 == 0;
   const int G = WHOLE ? (int)blockDim.x : G0;
   constexpr int NW = WHOLE ? 16 : OT_THREADS / 64;
@@ -446,7 +518,7 @@ __device__ __forceinline__ void quantize_rows_reg_body(
     if (form.rows_per_range) {
       rg = stored_range(scales, offsets, k, grp, form);
     } else {
-      mn = wave_min(mn); mx = wave_max(mx);
+      mn = -wave_max_dpp(-mn); mx = wave_max_dpp(mx);
       if constexpr (WHOLE || G0 > 64) {
         if ((threadIdx.x & 63) == 0) { red[k & 1][0][threadIdx.x >> 6] = mn; red[k & 1][1][threadIdx.x >> 6] = mx; }
         __syncthreads();
@@ -458,23 +530,29 @@ __device__ __forceinline__ void quantize_rows_reg_body(
         if (form.offset) offsets.p[k][row] = rg.lo;
       }
     }
+    const Divider dv = make_divider<SCALAR>(rg, form);
     uint8_t* crow = codes.p[k] + row * row_bytes;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int c = (t + i * G) * 8;
       if (live && c < n) {
-        int q[8];
-        float e[8];
+        unsigned int h4[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          q[j] = quant_level(d[i][j], rg, form);
-          const float sent = dequant_level(q[j], rg, form);
-          e[j] = __fsub_rn(d[i][j], sent);
-          if constexpr (OUTER) acc[i][j] += sent;
+        for (int h = 0; h < 2; ++h) {          // (four at a time: registers)
+          float q[4];
+          quant_levels4(&d[i][4 * h], dv, q);
+          h4[h] = pack_levels4(q, bits, form.code_bias);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float sent = dequant_level(q[j], dv);
+            if constexpr (OUTER) acc[i][4 * h + j] += sent;
+            d[i][4 * h + j] = __fsub_rn(d[i][4 * h + j], sent);
+          }
         }
-        if constexpr (RAG) store_codes8_part(crow, c, q, bits, form.code_bias, n - c);
-        else store_codes8(crow, c, q, bits, form.code_bias);
-        if (res) store8<float, RAG>(res + c, e, n - c);
+        const u32x2 packed = {bits == 8 ? h4[0] : h4[0] | h4[1] << (4 * bits), h4[1]};
+        if constexpr (RAG) store_packed8_part(crow, c, packed, bits, n - c);
+        else store_packed8(crow, c, packed, bits);
+        if (res) store8<float, RAG>(res + c, d[i], n - c);
       }
     }
   }
@@ -549,7 +627,7 @@ __global__ __launch_bounds__(G ? OT_THREADS : 1024, quant_min_waves(NV, OUTER)) 
     OffsetPtrs offsets, ResidualPtrs ef, long rows, int n, int K, QuantForm form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
     float* mean_offsets) {
-  quantize_rows_reg_body<WT, GT, NV, G, OUTER, RAG>(w, theta_g, u, codes, scales, offsets, ef, rows, n, K, form,
+  quantize_rows_reg_body<WT, GT, NV, G, OUTER, RAG, 0, true>(w, theta_g, u, codes, scales, offsets, ef, rows, n, K, form,
                                                eta, mu, inv_k, nesterov, write_back, requant, mean_codes,
                                                mean_scales, mean_offsets, (long)blockIdx.x);
 }
@@ -581,8 +659,9 @@ __host__ __device__ constexpr RegCfg reg_cfg(int idx) {
        : idx == 3 ? RegCfg{2, 256} : RegCfg{4, 256};
 }
 
-template <typename WT, typename GT, bool RAG>
-__global__ __launch_bounds__(OT_THREADS, 3) void quantize_outer_multi_kernel(
+// (Three wavefronts a SIMD: more of them, which one worker's registers would allow, make its long rows 1 to 2 % slower.)
+template <typename WT, typename GT, bool RAG, int KC>
+__global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void quantize_outer_multi_kernel(
     QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
   int si = 0;
 #pragma unroll
@@ -591,7 +670,7 @@ __global__ __launch_bounds__(OT_THREADS, 3) void quantize_outer_multi_kernel(
   const QuantSeg& sg = tab.s[si];
   const long blk = (long)(blockIdx.x - sg.blk0);
 #define MLC_SEG_BODY(IDX)                                                                              \
-  quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG>(                             \
+  quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG, KC, false>(                             \
       sg.w, (GT*)sg.theta_g, sg.u, sg.codes, sg.scales, sg.offsets, sg.ef, sg.rows, sg.n, K, form, eta, \
       mu, inv_k, nesterov, write_back, 0, nullptr, nullptr, nullptr, blk)
   switch (sg.cfg) {      // uniform over the workgroup
@@ -1736,10 +1815,15 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
   }
   LaunchScope scope(MLC_KERNEL_DEQUANT_OUTER, stream, 0.0, bytes);
   const float inv_k = 1.0f / (float)K;
-#define MLC_QM_R(WT, GT, RAG)                                                                      \
-  hipLaunchKernelGGL((quantize_outer_multi_kernel<WT, GT, RAG>), dim3((unsigned)blk), dim3(OT_THREADS), \
+#define MLC_QM_R(WT, GT, RAG, KC)                                                                      \
+  hipLaunchKernelGGL((quantize_outer_multi_kernel<WT, GT, RAG, KC>), dim3((unsigned)blk), dim3(OT_THREADS), \
                      0, stream, tab, K, form, eta_out, mu, inv_k, nesterov, write_back)
-#define MLC_QM(WT, GT) do { if (quant_ragged(gs[0].n)) MLC_QM_R(WT, GT, true); else MLC_QM_R(WT, GT, false); } while (0)
+#define MLC_QM(WT, GT)                                                                            \
+  do {                                                                                            \
+    if (K == 1) { if (quant_ragged(gs[0].n)) MLC_QM_R(WT, GT, true, 1); else MLC_QM_R(WT, GT, false, 1); }   \
+    else if (quant_ragged(gs[0].n)) MLC_QM_R(WT, GT, true, 0);                                    \
+    else MLC_QM_R(WT, GT, false, 0);                                                              \
+  } while (0)
   if (worker_dtype == MLC_BF16 && global_dtype == MLC_F32) MLC_QM(bf16_t, float);
   else if (worker_dtype == MLC_BF16) MLC_QM(bf16_t, bf16_t);
   else MLC_QM(float, float);
