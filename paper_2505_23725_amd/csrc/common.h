@@ -169,6 +169,24 @@ __device__ __forceinline__ float wave_min(float v) {
   return v;
 }
 
+// Word k of lane p of every four lanes becomes word p of lane k.
+__device__ __forceinline__ u32x4 transpose_quad(u32x4 w, int p) {
+  const bool p1 = p & 1, p2 = p & 2;
+#pragma unroll
+  for (int x = 0; x < 4; x += 2) {
+    const unsigned int got = (unsigned int)__builtin_amdgcn_mov_dpp((int)(p1 ? w[x] : w[x + 1]), 0xb1, 0xf, 0xf, true);
+    w[x + 1] = p1 ? w[x + 1] : got;
+    w[x] = p1 ? got : w[x];
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const unsigned int got = (unsigned int)__builtin_amdgcn_mov_dpp((int)(p2 ? w[x] : w[x + 2]), 0x4e, 0xf, 0xf, true);
+    w[x + 2] = p2 ? w[x + 2] : got;
+    w[x] = p2 ? got : w[x];
+  }
+  return w;
+}
+
 static inline int64_t round_up(int64_t x, int64_t to) { return (x + to - 1) / to * to; }
 
 // Per-device host-side caches (kernel attributes, unit counts) are arrays of this many slots.

@@ -81,6 +81,15 @@ __device__ __forceinline__ void settle(f32x4 (&acc)[M][N]) {
 #pragma unroll
   for (int n = 0; n < M * N; ++n) asm volatile("" : "+a"(acc[n / N][n % N]));
 }
+// of a part of a symmetric product (DG: on the diagonal)
+template <bool DG>
+__device__ __forceinline__ void settle_part(f32x4 (&acc)[4][4]) {
+  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < (DG ? 2 * (i / 2) + 2 : 2); ++j) asm volatile("" : "+a"(acc[i][j]));
+}
 __device__ __forceinline__ f32x4 acc_read(f32x4 a) {
   asm volatile("" : "+v"(a));
   return a;
@@ -135,12 +144,12 @@ __device__ __forceinline__ u32x4 pack8(const f32x4& x, const f32x4& y) {
 
 // The whole chain of matrix `mat` of a batch, by one workgroup.
 //
-// Bound by what cannot overlap in one wavefront per SIMD: a phase's conversions and its barriers, and
-// in the Gram product the LDS, which takes as long to read 64 x 64 blocks as their MFMAs to run.  Cycles of
-// an iteration on 128 x 512: Gram 5200 (MFMAs 4100), its result 900, square 1750, polynomial 2400, product
-// with X 4900 (4100), its result 3000.  Kernel times: an iteration took 8.6 us and takes 7.4 (128 x 128: 5.1
-// and 3.9), the launch around five of them 13.7 and 7.1 us (6.9 and 4.6), since fragments are read ahead of their
-// use, K-strided ones with the transposing read, and all loads of X are in flight at once.
+// Bound by what cannot overlap in one wavefront per SIMD: a phase's conversions and its barriers.  The Gram matrix and the square are
+// symmetric, and only blocks on and below their diagonals are computed, 12 or 8 MFMAs a slice instead of 16, with 20 KB of fragments instead
+// of 24.  (Cycles of an iteration on 128 x 512 before that: Gram 5200, its result 900, square 1750, polynomial 2400, product with
+// X 4900, its result 3000; MFMAs 4100, 1000 and 4100.)  An iteration took 7.5 us and takes 7.1 (128 x 256: 5.2 and 4.9; 128 x 128:
+// 3.96 and 3.88, and with more matrices than compute units 5.6 and 5.3), the launch around five of them 7.1 us (128 x 128: 4.6): fragments are
+// read ahead of their use, K-strided ones with the transposing read, and all loads of X are in flight at once.
 template <int TT>
 __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   constexpr int LP = 128 * TT;
@@ -209,7 +218,10 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   const float s = sumsq > 0.f ? 1.0f / (sqrtf(sumsq) + g.eps) : 0.f;   // all-zero matrix: 0, also when eps = 0
   __syncthreads();
 
-  const int rm = (wave >> 1) * 64, rn = (wave & 1) * 64;     // 2 x 2 wavefronts over the 128 x 128 products
+  // The products of a matrix with its own transpose: wavefronts 0 and 3 take the 64 x 64 blocks on the diagonal, of their four
+  // 32 x 32 blocks the three on and below it, 1 and 2 half of the lower left block each.
+  const bool dg = wave == 0 || wave == 3;
+  const int rm = wave ? 64 : 0, rn = wave == 3 ? 64 : wave == 2 ? 32 : 0;     // first row and column
   constexpr int NT = 2 * TT;                                 // column tiles of the wavefront's block of X
   const int cb = wave * 32 * TT;                             // and its first column
 
@@ -218,97 +230,125 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
   int ix = idx, gx = lg;
   auto fresh = [&] { asm volatile("" : "+v"(ix), "+v"(gx)); };
 
-  // A 64 x 64 block of m m^T over `bytes` of a row, 32-deep slices.  A slice's 16 MFMAs take about as long as
-  // an LDS read, so fragments are read two slices ahead, into the set of four that the last slice but
-  // one has left.  DIAG: both operands are the same rows, read once.
+  // This wavefront's part of m m^T over `bytes` of a row, 32-deep slices: 12 MFMAs a slice on the diagonal (DG, from one set of
+  // fragments, since rows and columns are the same), 8 elsewhere.  They take about as long as an LDS read, so fragments are
+  // read two slices ahead, into the set of four that the last slice but one has left.
   u32x4 fa[4][4], fb[4][4];
+  f32x4 sq[4][4];
   LanePos pr, pc;
-  auto read64 = [&](auto diag, const unsigned char* m, int pitch, int set, int r, int at) {
-    if (r < 4) fb[set][r] = frag_col(m, pitch, pc, r, at);
-    else if (!decltype(diag)::value) fa[set][r - 4] = frag_col(m, pitch, pr, r - 4, at);
+  auto read_sq = [&](auto diag, const unsigned char* m, int pitch, int set, int r, int at) {
+    constexpr int NB = decltype(diag)::value ? 4 : 2;
+    if (r < NB) fb[set][r] = frag_col(m, pitch, pc, r, at);
+    else fa[set][r - NB] = frag_col(m, pitch, pr, r - NB, at);
   };
-  auto group64 = [&](auto diag, auto first, f32x4 (&acc)[4][4], const unsigned char* m, int pitch, int c, int last) {
-    constexpr bool DIAG = decltype(diag)::value;
+  auto group_sq = [&](auto diag, auto first, const unsigned char* m, int pitch, int c, int last) {
+    constexpr bool DG = decltype(diag)::value;
+    constexpr int NR = DG ? 4 : 6;
 #pragma unroll
     for (int sl = 0; sl < 4; ++sl) {
       const int next = sl < 2 ? c + 64 * (sl + 2) : last + 64 * (sl - 2);
 #pragma unroll
-      for (int n = 0; n < 16; ++n) {
-        const u32x4& a = DIAG ? fb[sl][n / 4] : fa[sl][n / 4];
-        if (decltype(first)::value && sl == 0) mfma<true>(acc[n / 4][n % 4], fb[sl][n % 4], a);
-        else mfma<false>(acc[n / 4][n % 4], fb[sl][n % 4], a);
-        if (n % 2 == 0) read64(diag, m, pitch, (sl + 2) & 3, n / 2, next);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < (DG ? 2 * (i / 2) + 2 : 2); ++j) {
+          const int n = DG ? (i < 2 ? 2 * i : 4 * (i - 1)) + j : 2 * i + j;
+          const u32x4& a = DG ? fb[sl][i] : fa[sl][i];
+          if (decltype(first)::value && sl == 0) mfma<true>(sq[i][j], fb[sl][j], a);
+          else mfma<false>(sq[i][j], fb[sl][j], a);
+          if (DG ? n % 2 == 0 && n / 2 < NR : n < NR) read_sq(diag, m, pitch, (sl + 2) & 3, DG ? n / 2 : n, next);
+          __builtin_amdgcn_sched_barrier(0);
+        }
     }
   };
-  auto product64 = [&](auto diag, f32x4 (&acc)[4][4], const unsigned char* m, int pitch, int bytes) {
+  auto product_sq = [&](auto diag, const unsigned char* m, int pitch, int bytes) {
+    constexpr bool DG = decltype(diag)::value;
+    constexpr int NR = DG ? 4 : 6;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) read64(diag, m, pitch, r / 8, r % 8, 64 * (r / 8));
+    for (int r = 0; r < 2 * NR; ++r) read_sq(diag, m, pitch, r / NR, r % NR, 64 * (r / NR));
     // (after the last group the reads ahead are of the first slices again, and not used)
-    group64(diag, std::true_type{}, acc, m, pitch, 0, bytes > 256 ? 256 : 0);
+    group_sq(diag, std::true_type{}, m, pitch, 0, bytes > 256 ? 256 : 0);
 #pragma unroll 1
-    for (int c = 256; c < bytes; c += 256) group64(diag, std::false_type{}, acc, m, pitch, c, c + 256 < bytes ? c + 256 : 0);
+    for (int c = 256; c < bytes; c += 256) group_sq(diag, std::false_type{}, m, pitch, c, c + 256 < bytes ? c + 256 : 0);
+    settle_part<DG>(sq);
   };
-  auto square64 = [&](f32x4 (&acc)[4][4], const unsigned char* m, int pitch, int bytes) {
-    fresh();
-    pr = lane_cols(pitch, rm, ix, gx);
-    pc = lane_cols(pitch, rn, ix, gx);
-    if (rm == rn) product64(std::true_type{}, acc, m, pitch, bytes);
-    else product64(std::false_type{}, acc, m, pitch, bytes);
-    settle(acc);
-    fresh();
-  };
-  // this lane's 16 bytes of a 64 x 64 block of A: tile row i, columns 32 J + 8 lg .. + 7
+  // this lane's 16 bytes of the wavefront's part of A: tile row i, columns 32 J + 8 lg .. + 7
   auto a_at = [&](int i, int J) -> u32x4* {
     const LanePos p = lane_cols(A_PITCH, rm, ix, gx);
     return reinterpret_cast<u32x4*>(as + p.row + (p.x ^ (2 * rn) ^ (64 * J) ^ ((i & 1) * SWZ_ROW4)) +
                                     (32 * (i >> 1) + 4 * (i & 1)) * A_PITCH);
   };
 
+  // A block of 32 x 32 of the part, rows from 32 I, columns from 32 J, turned over to the other side of the diagonal: four lanes hold a
+  // column's 8 adjacent rows between them.
+  auto put_turned = [&](int I, int J, const u32x4& v0, const u32x4& v1) {
+    const int p = ix & 3;
+    const u32x4 r0 = transpose_quad(v0, p), r1 = transpose_quad(v1, p);
+    const int row = rn + 32 * J + 8 * gx + 2 * p, chunk = (rm + 32 * I) / 8 + (ix >> 2);
+    *reinterpret_cast<u32x4*>(as + chunk_pos(row, chunk, A_PITCH)) =
+        u32x4{halves_lo(r0[0], r0[1]), halves_lo(r0[2], r0[3]), halves_lo(r1[0], r1[1]), halves_lo(r1[2], r1[3])};
+    *reinterpret_cast<u32x4*>(as + chunk_pos(row + 1, chunk, A_PITCH)) =
+        u32x4{halves_hi(r0[0], r0[1]), halves_hi(r0[2], r0[3]), halves_hi(r1[0], r1[1]), halves_hi(r1[2], r1[3])};
+  };
+  // This wavefront's part of m m^T, and its values, value(i, J) as they are stored, to both sides of the diagonal of A.  `wait` stands
+  // between the last value and the first store.
+  auto square_part = [&](auto diag, const unsigned char* m, int pitch, int bytes, auto&& value, auto&& wait) {
+    constexpr bool DG = decltype(diag)::value;
+    fresh();
+    pr = lane_cols(pitch, rm, ix, gx);
+    pc = lane_cols(pitch, rn, ix, gx);
+    product_sq(diag, m, pitch, bytes);
+    fresh();
+    u32x4 v[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int J = 0; J < (DG ? i / 2 + 1 : 1); ++J) v[i][J] = value(i, J);
+    wait();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int J = 0; J < (DG ? i / 2 + 1 : 1); ++J) *a_at(i, J) = v[i][J];
+    if (DG) {
+      put_turned(1, 0, v[2][0], v[3][0]);
+    } else {
+      put_turned(0, 0, v[0][0], v[1][0]);
+      put_turned(1, 0, v[2][0], v[3][0]);
+    }
+  };
+  auto square = [&](const unsigned char* m, int pitch, int bytes, auto&& value, auto&& wait) {
+    if (dg) square_part(std::true_type{}, m, pitch, bytes, value, wait);
+    else square_part(std::false_type{}, m, pitch, bytes, value, wait);
+  };
+
   for (int it = 0; it < g.iters; ++it) {
     const float alpha_a = it == 0 ? s * s : 1.f;
 
-    // ---- A = alpha_a X X^T : each wavefront one 64 x 64 block -------------------------
+    // ---- A = alpha_a X X^T ---------------------------------------------------------------
     {
-      f32x4 acc[4][4];
-      square64(acc, xs, X_PITCH, 2 * L);                       // L is a multiple of 128
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int J = 0; J < 2; ++J) *a_at(i, J) = pack8(alpha_a * acc_read(acc[i][2 * J]), alpha_a * acc_read(acc[i][2 * J + 1]));
+      auto value = [&](int i, int J) { return pack8(alpha_a * acc_read(sq[i][2 * J]), alpha_a * acc_read(sq[i][2 * J + 1])); };
+      square(xs, X_PITCH, 2 * L, value, [] {});                // L is a multiple of 128
     }
     __syncthreads();
 
     // ---- B' = c A A + b A + a I, in place over A (a column of A is its row) -------------
     {
-      f32x4 acc[4][4];
-      square64(acc, as, A_PITCH, A_PITCH);
-      u32x4 res[4][2];
+      auto value = [&](int i, int J) {
+        const u32x4 av = *a_at(i, J);
+        f32x4 v[2] = {acc_read(sq[i][2 * J]), acc_read(sq[i][2 * J + 1])};
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int J = 0; J < 2; ++J) {
-          const u32x4 av = *a_at(i, J);
-          f32x4 v[2] = {acc_read(acc[i][2 * J]), acc_read(acc[i][2 * J + 1])};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float ae = (e & 1) ? bf16hi(av[e / 2]) : bf16lo(av[e / 2]);
-            v[e / 4][e % 4] = g.c * v[e / 4][e % 4] + g.b * ae;
-          }
-          if (J == i / 2 && rm == rn) {                        // the diagonal crosses this tile
-            const int d = 8 * (ix >> 2) + 4 * (i & 1) + (ix & 3) - 8 * gx;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (e == d) v[e / 4][e % 4] += g.a;
-          }
-          res[i][J] = pack8(v[0], v[1]);
+        for (int e = 0; e < 8; ++e) {
+          const float ae = (e & 1) ? bf16hi(av[e / 2]) : bf16lo(av[e / 2]);
+          v[e / 4][e % 4] = g.c * v[e / 4][e % 4] + g.b * ae;
         }
-      __syncthreads();            // every wavefront is done reading A
+        if (J == i / 2 && dg) {                                // the diagonal crosses this tile
+          const int d = 8 * (ix >> 2) + 4 * (i & 1) + (ix & 3) - 8 * gx;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int J = 0; J < 2; ++J) *a_at(i, J) = res[i][J];
+          for (int e = 0; e < 8; ++e)
+            if (e == d) v[e / 4][e % 4] += g.a;
+        }
+        return pack8(v[0], v[1]);
+      };
+      square(as, A_PITCH, A_PITCH, value, [] { __syncthreads(); });      // every wavefront is done reading A
     }
     __syncthreads();
 
@@ -391,8 +431,8 @@ __global__ __launch_bounds__(256) void ns_chain_small_kernel(ChainArgs g) {
 }
 
 // Batches of several shapes in one launch.  A chain is a serial walk of one workgroup (24 us for
-// 128 x 128, 44 for 128 x 512, 47 for 512 x 128) that leaves the other compute units idle, so batches
-// that fit the chip together go side by side: 8 / 2 / 2 matrices of these shapes take 47 us instead of
+// 128 x 128, 43 for 128 x 512, 45 for 512 x 128) that leaves the other compute units idle, so batches
+// that fit the chip together go side by side: 8 / 2 / 2 matrices of these shapes take 45 us instead of
 // 115 one after the other.
 struct ChainTable { ChainArgs s[MAX_CHAINS]; unsigned int blk0[MAX_CHAINS]; int n; };
 __global__ __launch_bounds__(256) void ns_chain_multi_kernel(ChainTable tab) {
@@ -408,9 +448,9 @@ __global__ __launch_bounds__(256) void ns_chain_multi_kernel(ChainTable tab) {
 
 constexpr size_t chain_lds(int tt) { return (size_t)S * 128 * tt * 2 + (size_t)S * A_PITCH; }
 int chain_tt(const ChainArgs& g) { return g.L <= 128 ? 1 : g.L <= 256 ? 2 : 4; }
-// executed: the full Gram matrix and square (no triangle saving), all LP columns of X
+// executed: 40 of 64 MFMAs of the Gram matrix and the square, all LP columns of X
 double chain_flops(const ChainArgs& g) {
-  return (2.0 * S * S * (double)g.L + 2.0 * S * S * S + 2.0 * S * S * (128.0 * chain_tt(g))) * g.iters;
+  return ((2.0 * S * S * (double)g.L + 2.0 * S * S * S) * 40 / 64 + 2.0 * S * S * (128.0 * chain_tt(g))) * g.iters;
 }
 // raised once per kernel and device; the call is idempotent
 int raise_lds_limit(const void* kern, std::atomic<bool>* done, size_t lds) {

@@ -358,24 +358,6 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
   }
 }
 
-// Word k of lane p of every four lanes becomes word p of lane k.
-__device__ __forceinline__ u32x4 transpose_quad(u32x4 w, int p) {
-  const bool p1 = p & 1, p2 = p & 2;
-#pragma unroll
-  for (int x = 0; x < 4; x += 2) {
-    const unsigned int got = (unsigned int)__builtin_amdgcn_mov_dpp((int)(p1 ? w[x] : w[x + 1]), 0xb1, 0xf, 0xf, true);
-    w[x + 1] = p1 ? w[x + 1] : got;
-    w[x] = p1 ? got : w[x];
-  }
-#pragma unroll
-  for (int x = 0; x < 2; ++x) {
-    const unsigned int got = (unsigned int)__builtin_amdgcn_mov_dpp((int)(p2 ? w[x] : w[x + 2]), 0x4e, 0xf, 0xf, true);
-    w[x + 2] = p2 ? w[x + 2] : got;
-    w[x] = p2 ? got : w[x];
-  }
-  return w;
-}
-
 // Epilogue of a tile on the diagonal of a symmetric product, in which a lane holds rows 32 (i / 2) + 8 (idx / 4) + 4 (i % 2)
 // + idx % 4 in accumulator tile i, and columns as everywhere.  DG: a quarter on the diagonal, of which the
 // blocks (I, J) of 32 x 32 with J <= I have been computed; its diagonal is the matrix's.  Otherwise 128 x 64 of the
