@@ -314,11 +314,12 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
 constexpr int TOPK_BINS = 2048;     // widest digit of the radix select: 11 bits
 struct TopkState { unsigned int hist[TOPK_BINS]; unsigned int lo, width, rank, ctl; };
 size_t topk_workspace_bytes(int64_t count, int K);
-// thresholds: per worker [count] floats (may be null): the k-th largest magnitude found.
-int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype, float* u,
-                      const ResidualPtrs& ef, const ScalePtrs& thresholds, int64_t count, int64_t m,
-                      int64_t n, int K, unsigned int kcount, float ef_beta, float eta_out, float mu,
-                      int nesterov, int write_back, void* workspace, hipStream_t stream);
+// One group, or two of equally large matrices, types and use of error feedback that share no memory; `workspace` holds the states of
+// both.  thresholds: per worker [count] floats (may be null): the k-th largest magnitude found.
+struct TopkGroup { WorkerPtrs w; void* theta_g; float* u; ResidualPtrs ef; ScalePtrs thresholds; int64_t count; };
+int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, int global_dtype, int64_t elems, int K,
+                      unsigned int kcount, float ef_beta, float eta_out, float mu, int nesterov, int write_back,
+                      void* workspace, hipStream_t stream);
 // Form of the linear quantiser (see muloco.h).
 struct QuantForm {
   int bits;              // 2, 4 or 8

@@ -791,6 +791,15 @@ constexpr int TOPK_SAMPLE_PER = 2;                 // runs of 8 values that a th
 
 __device__ __forceinline__ unsigned int magnitude_key(float v) { return __float_as_uint(fabsf(v)); }
 
+// Pointers of the groups of a launch, one or two of equally large matrices, which are numbered through: those of the second
+// group are the addresses that matrix 0 would have, so that matrix b's are found alike in both.
+struct TopkPtrs { WorkerPtrs w; ResidualPtrs ef; ScalePtrs thresholds; void* theta_g; float* u; };
+struct TopkArgs {
+  TopkPtrs g[2];
+  int split;                         // first matrix of the second group
+  __device__ __forceinline__ const TopkPtrs& of(long b) const { return g[b >= split ? 1 : 0]; }
+};
+
 __global__ void topk_init_kernel(TopkState* st, unsigned int kcount) {
   TopkState& s = st[blockIdx.x];
   for (int i = threadIdx.x; i < TOPK_BINS; i += blockDim.x) s.hist[i] = 0u;
@@ -827,8 +836,7 @@ __device__ __forceinline__ unsigned int sample_bin(unsigned int key) {
 // that (replicas that did not move), the interval is one key and the pass over the window settles it.
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(TOPK_SAMPLE_THREADS) void topk_sample_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count,
-    unsigned int kcount, float ef_beta) {
+    TopkArgs args, TopkState* st, long elems, int count, unsigned int kcount, float ef_beta) {
   constexpr int WAVES = TOPK_SAMPLE_THREADS / 64, RUNS = TOPK_SAMPLE_THREADS * TOPK_SAMPLE_PER;
   static_assert(TOPK_BINS == 2 * TOPK_SAMPLE_THREADS, "a thread owns two bins");
   __shared__ unsigned int hist[TOPK_BINS];
@@ -836,9 +844,10 @@ __global__ __launch_bounds__(TOPK_SAMPLE_THREADS) void topk_sample_kernel(
   const long b = blockIdx.x;
   const int k = blockIdx.y, t = threadIdx.x;
   TopkState& s = st[(long)k * count + b];
-  const GT* tg = theta_g + b * elems;
-  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
-  const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
+  const TopkPtrs& g = args.of(b);
+  const GT* tg = reinterpret_cast<const GT*>(g.theta_g) + b * elems;
+  const WT* tk = reinterpret_cast<const WT*>(g.w.p[k]) + b * elems;
+  const float* res = g.ef.p[k] ? g.ef.p[k] + b * elems : nullptr;
   const unsigned int stretch = (unsigned int)(elems / 8 / RUNS);           // >= 1, below 2^18
   hist[t] = 0u; hist[t + TOPK_SAMPLE_THREADS] = 0u;
   s.hist[t] = 0u; s.hist[t + TOPK_SAMPLE_THREADS] = 0u;
@@ -1002,22 +1011,24 @@ __device__ __forceinline__ void topk_narrow(TopkState& s, int nbins, int shift, 
 // 4 bytes an element instead of 6 and needs no worker parameters.  A few per cent of the values fall
 // into the window, so one histogram a workgroup takes them; 16 wavefronts share it, since its
 // bins leave as one atomic each at the end (4 wavefronts: 0 to 3 % slower).  14 bytes an element at 4.8 TB/s.
-template <typename WT, typename GT, bool VEC>
+// TURN: the grid's first dimension is the workers, otherwise the pieces of a matrix (topk_turn).
+template <typename WT, typename GT, bool VEC, bool TURN>
 __global__ __launch_bounds__(TOPK_WINDOW_THREADS) void topk_window_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, float ef_beta) {
+    TopkArgs args, TopkState* st, long elems, int count, float ef_beta) {
   __shared__ unsigned int lh[TOPK_BINS];
-  const long b = blockIdx.y;
-  const int k = blockIdx.z;
+  const long b = TURN ? blockIdx.z : blockIdx.y;
+  const int k = TURN ? blockIdx.x : blockIdx.z, blk = TURN ? blockIdx.y : blockIdx.x, nblk = TURN ? gridDim.y : gridDim.x;
   TopkState& s = st[(long)k * count + b];
   const unsigned int lo = s.lo, shift = s.width;
   for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_WINDOW_THREADS) lh[i] = 0u;
   __syncthreads();
-  const GT* tg = theta_g + b * elems;
-  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
-  float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
+  const TopkPtrs& g = args.of(b);
+  const GT* tg = reinterpret_cast<const GT*>(g.theta_g) + b * elems;
+  const WT* tk = reinterpret_cast<const WT*>(g.w.p[k]) + b * elems;
+  float* res = g.ef.p[k] ? g.ef.p[k] + b * elems : nullptr;
   unsigned int above = 0u;
-  for (long i = ((long)blockIdx.x * TOPK_WINDOW_THREADS + threadIdx.x) * 8; i < elems;
-       i += (long)gridDim.x * TOPK_WINDOW_THREADS * 8) {
+  for (long i = ((long)blk * TOPK_WINDOW_THREADS + threadIdx.x) * 8; i < elems;
+       i += (long)nblk * TOPK_WINDOW_THREADS * 8) {
     float vals[8];
     const int left = (int)min(elems - i, 8L);
     topk_values<WT, GT, VEC>(tg, tk, res, i, left, ef_beta, vals);
@@ -1045,7 +1056,7 @@ __global__ __launch_bounds__(TOPK_WINDOW_THREADS) void topk_window_kernel(
   __syncthreads();
   for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_WINDOW_THREADS)
     if (lh[i]) __hip_atomic_fetch_add(&s.hist[i], lh[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (last_of_state(s, gridDim.x)) topk_narrow<WINDOW_LAST>(s, TOPK_BINS, (int)shift, st);
+  if (last_of_state(s, nblk)) topk_narrow<WINDOW_LAST>(s, TOPK_BINS, (int)shift, st);
 }
 
 // The first digits (bits from `shift` up) of a lane's first cnt of 8 values.  They mostly change
@@ -1222,12 +1233,12 @@ __device__ __forceinline__ void topk_count(const WorkerPtrs& w, const GT* __rest
 
 template <typename WT, typename GT, bool VEC, bool FIRST>
 __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, TopkState* st, long elems, int count, float ef_beta,
-    int pick) {
+    TopkArgs args, TopkState* st, long elems, int count, float ef_beta, int pick) {
   __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];     // one histogram per wavefront
   const long b = blockIdx.y;
   const int k = blockIdx.z;
-  topk_count<WT, GT, VEC, FIRST>(w, theta_g, ef, st[(long)k * count + b], lh, elems, b, k, ef_beta, blockIdx.x,
+  const TopkPtrs& g = args.of(b);
+  topk_count<WT, GT, VEC, FIRST>(g.w, (const GT*)g.theta_g, g.ef, st[(long)k * count + b], lh, elems, b, k, ef_beta, blockIdx.x,
                                  gridDim.x, pick != 0);
 }
 
@@ -1334,9 +1345,7 @@ __device__ __forceinline__ void topk_update(
 // listed, built bit by bit from counts that ballots give.  The interval becomes that key.  Bound by latency: a lane
 // requests four entries and their values at a time.
 template <typename WT, typename GT>
-__device__ __forceinline__ void topk_threshold(const WorkerPtrs& w, const GT* __restrict__ theta_g,
-                                               const ResidualPtrs& ef, const ScalePtrs& thresholds, TopkState& s,
-                                               long elems, long b, int k) {
+__device__ __forceinline__ void topk_threshold(const TopkPtrs& g, TopkState& s, long elems, long b, int k) {
   constexpr int PER = (TOPK_LIST + 63) / 64, SIDE = 4;
   static_assert(PER % SIDE == 0, "whole batches");
   const int lane = threadIdx.x & 63;
@@ -1344,9 +1353,9 @@ __device__ __forceinline__ void topk_threshold(const WorkerPtrs& w, const GT* __
   const int width = (int)s.width;
   const int first = width ? (int)min(s.hist[TOPK_BINS - 2], (unsigned int)TOPK_LIST) : 0;
   const int n = width ? (int)min(first + s.hist[TOPK_BINS - 1], (unsigned int)TOPK_LIST) : 0;
-  const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
-  const GT* tg = theta_g + b * elems;
-  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
+  const float* res = g.ef.p[k] ? g.ef.p[k] + b * elems : nullptr;
+  const GT* tg = reinterpret_cast<const GT*>(g.theta_g) + b * elems;
+  const WT* tk = reinterpret_cast<const WT*>(g.w.p[k]) + b * elems;
   unsigned int key[PER];                  // distance from lo, plus one: 0 is no entry
 #pragma unroll
   for (int i = 0; i < PER; i += SIDE) {
@@ -1383,7 +1392,7 @@ __device__ __forceinline__ void topk_threshold(const WorkerPtrs& w, const GT* __
   if (lane == 0) {
     s.lo = lo + best;
     s.width = 0u;
-    if (thresholds.p[k]) thresholds.p[k][b] = __uint_as_float(lo + best);
+    if (g.thresholds.p[k]) g.thresholds.p[k][b] = __uint_as_float(lo + best);
   }
 }
 
@@ -1393,8 +1402,8 @@ __device__ __forceinline__ void topk_threshold(const WorkerPtrs& w, const GT* __
 // bf16 global copy, took 445 us, 167 like this, and on 24 of 2048 x 2048, eight workers with lists of 60, 43 us of it and 17.)
 template <typename WT, typename GT>
 __device__ __forceinline__ void topk_settle(
-    const WorkerPtrs& w, GT* __restrict__ theta_g, float* __restrict__ u, const ResidualPtrs& ef, const TopkState* st,
-    long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back, long b, int blk,
+    const TopkPtrs& g, const TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov,
+    int write_back, long b, int blk,
     int nblk) {
   __shared__ unsigned int tau[MLC_MAX_WORKERS], primaries[MLC_MAX_WORKERS];
   constexpr int SIDE = 4;
@@ -1404,8 +1413,10 @@ __device__ __forceinline__ void topk_settle(
     primaries[threadIdx.x] = min(s.hist[TOPK_BINS - 2], (unsigned int)TOPK_LIST);
   }
   __syncthreads();
-  GT* tg = theta_g + b * elems;
-  float* ub = u + b * elems;
+  const WorkerPtrs& w = g.w;
+  const ResidualPtrs& ef = g.ef;
+  GT* tg = reinterpret_cast<GT*>(g.theta_g) + b * elems;
+  float* ub = g.u + b * elems;
   int k0 = 0;
   unsigned int before = 0u;                 // primary entries of the workers before k0
   for (unsigned int e = blk * OT_THREADS + threadIdx.x;; e += nblk * OT_THREADS) {
@@ -1444,8 +1455,7 @@ __device__ __forceinline__ void topk_settle(
 // first of these launches, the thresholds of the others.
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ResidualPtrs ef, ScalePtrs thresholds, TopkState* st, long elems,
-    int count, int K, float ef_beta, int most, int first) {
+    TopkArgs args, TopkState* st, long elems, int count, int K, float ef_beta, int most, int first) {
   __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];
   const bool none_open = topk_all_early(st);
   if (first)
@@ -1454,43 +1464,44 @@ __global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
       const int k = (int)(i / count), lane = threadIdx.x & 63;
       const long b = i - (long)k * count;
       if (none_open || __all(lane >= K || state_early(st[(long)min(lane, K - 1) * count + b])))
-        topk_threshold<WT, GT>(w, theta_g, ef, thresholds, st[i], elems, b, k);
+        topk_threshold<WT, GT>(args.of(b), st[i], elems, b, k);
     }
   if (none_open) return;
   topk_each_open(st, count, K, K, most, [&](long b, int k, int blk, int nblk) {
     TopkState& s = st[(long)k * count + b];
-    if (s.width) topk_count<WT, GT, VEC, false>(w, theta_g, ef, s, lh, elems, b, k, ef_beta, blk, nblk, true);
+    const TopkPtrs& g = args.of(b);
+    if (s.width) topk_count<WT, GT, VEC, false>(g.w, (const GT*)g.theta_g, g.ef, s, lh, elems, b, k, ef_beta, blk, nblk, true);
   });
 }
 
 // The update behind the pass over the window.
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(OT_THREADS) void topk_early_kernel(
-    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
-    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+    TopkArgs args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+  const TopkPtrs& g = args.of(blockIdx.y);
   if (topk_early(st, blockIdx.y, count, K))
-    topk_update<WT, GT, VEC, true>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+    topk_update<WT, GT, VEC, true>(g.w, (GT*)g.theta_g, g.u, g.ef, g.thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
                                    write_back, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
 // What is left of the matrices that the window settled, and the update of those that it left open.
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(OT_THREADS) void topk_finish_kernel(
-    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
-    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
+    TopkArgs args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
     int most) {
   const bool none_open = topk_all_early(st);
   const int parts = max(min(TOPK_SETTLE_GRID / count, TOPK_SETTLE_MOST), 1);
   for (int i = blockIdx.x; i < count * parts; i += gridDim.x) {
     const long b = i / parts;
     if (none_open || topk_early(st, b, count, K))
-      topk_settle<WT, GT>(w, theta_g, u, ef, st, elems, count, K, eta, mu, inv_k, nesterov, write_back, b,
+      topk_settle<WT, GT>(args.of(b), st, elems, count, K, eta, mu, inv_k, nesterov, write_back, b,
                           i - (int)b * parts, parts);
     __syncthreads();                        // its shared memory may be written again
   }
   if (none_open) return;
   topk_each_open(st, count, K, 1, most, [&](long b, int, int blk, int nblk) {
-    topk_update<WT, GT, VEC, false>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+    const TopkPtrs& g = args.of(b);
+    topk_update<WT, GT, VEC, false>(g.w, (GT*)g.theta_g, g.u, g.ef, g.thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
                                     write_back, b, blk, nblk);
   });
 }
@@ -1498,9 +1509,9 @@ __global__ __launch_bounds__(OT_THREADS) void topk_finish_kernel(
 // The update of groups that went through the three passes from the start.
 template <typename WT, typename GT, bool VEC>
 __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
-    WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, ResidualPtrs ef, ScalePtrs thresholds,
-    TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
-  topk_update<WT, GT, VEC, false>(w, theta_g, u, ef, thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
+    TopkArgs args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+  const TopkPtrs& g = args.of(blockIdx.y);
+  topk_update<WT, GT, VEC, false>(g.w, (GT*)g.theta_g, g.u, g.ef, g.thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
                                   write_back, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
@@ -1834,6 +1845,13 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
 
 size_t topk_workspace_bytes(int64_t count, int K) { return (size_t)count * K * sizeof(TopkState); }
 
+// Does the window's pass take the workers of a piece in turn?  All of them read the same global parameters: worker by worker
+// the second reads them from the memory-side cache, but only if what one worker touches, `bytes` a value, fits into it.  Two groups of
+// 2 x 2048 x 4096, 4 workers, error feedback (470 MB a worker), call of the whole step: 1615 us worker by worker, 1508 in turn; eight
+// workers 2973 and 2676.  Where it fits, in turn has more streams in flight and is up to 4 % slower: groups of
+// 4 x 1024 x 4096 without feedback (201 MB), four workers, 638 and 660.
+static bool topk_turn(long elems, int64_t count, double bytes) { return (double)elems * (double)count * bytes > (double)(1 << 28); }
+
 // Does the workgroup that ends a counting pass last pick the digit?  Against a launch of its own after every pass, 0.75 of a
 // call's time with up to 250 workgroups, 0.78 to 0.99 with 512, 0.83 to 0.96 with 700; with 1024 0.97 to 1.04 where a matrix has 32 of them
 // and more, 1.06 to 1.15 with 2 to 20, and with 4096 1.1 to 1.7.
@@ -1856,20 +1874,37 @@ static bool topk_window(long elems, int64_t count, int K, int blocks, bool feedb
   return 0.77 * values + 0.0048 * workgroups > 10.0 + 0.7 * K + 0.35 * K / count + 0.11 * states;
 }
 
-int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype, float* u,
-                      const ResidualPtrs& ef, const ScalePtrs& thresholds, int64_t count, int64_t m,
-                      int64_t n, int K, unsigned int kcount, float ef_beta, float eta_out, float mu,
-                      int nesterov, int write_back, void* workspace, hipStream_t stream) {
+int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, int global_dtype, int64_t elems_, int K,
+                      unsigned int kcount, float ef_beta, float eta_out, float mu, int nesterov, int write_back,
+                      void* workspace, hipStream_t stream) {
+  const long elems = elems_;
+  const int64_t first = groups[0].count, count = first + (n_groups > 1 ? groups[1].count : 0);
+  TopkArgs args;
+  args.split = (int)first;
+  for (int i = 0; i < 2; ++i) {
+    const TopkGroup& g = groups[i < n_groups ? i : 0];
+    TopkPtrs& p = args.g[i];
+    const long back = i && i < n_groups ? (long)first : 0;         // matrices before the group
+    auto at = [&](const void* x, double size) { return x ? (uintptr_t)x - (uintptr_t)back * (uintptr_t)(elems * (long)size) : 0; };
+    for (int k = 0; k < MLC_MAX_WORKERS; ++k) {
+      p.w.p[k] = (void*)at(g.w.p[k], esize(worker_dtype));
+      p.ef.p[k] = (float*)at(g.ef.p[k], 4.0);
+      p.thresholds.p[k] = g.thresholds.p[k] ? (float*)((uintptr_t)g.thresholds.p[k] - (uintptr_t)back * 4) : nullptr;
+    }
+    p.theta_g = (void*)at(g.theta_g, esize(global_dtype));
+    p.u = (float*)at(g.u, 4.0);
+  }
   if (count > 65535) return MLC_ERR_SHAPE;
   TopkState* st = (TopkState*)workspace;
-  const long elems = m * n;
   const bool vec = elems % 8 == 0;
   const long full = ((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS;      // a workgroup meets each element once
   const int full_grid = cap_blocks(full, 256);
   const int window_grid = cap_blocks((full * OT_THREADS + TOPK_WINDOW_THREADS - 1) / TOPK_WINDOW_THREADS, 256);
   const int n_states = (int)(count * K);
-  const bool fb = has_residuals(ef);
+  const bool fb = has_residuals(groups[0].ef);
   const double inputs = K * (esize(worker_dtype) + esize(global_dtype));
+  // one worker: nothing to share
+  const bool turn = K > 1 && topk_turn(elems, count, esize(worker_dtype) + esize(global_dtype) + (fb ? 8.0 : 0.0));
   const bool window = topk_window(elems, count, K, full_grid, fb,
                                   worker_dtype == MLC_BF16 && global_dtype == MLC_BF16);
   // the values once (or, small matrices, three times: with error feedback the inputs, then the residuals), the update
@@ -1879,23 +1914,24 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
   LaunchScope scope(MLC_KERNEL_TOPK, stream, 0.0, (double)count * elems * (passes + last));
   const float inv_k = 1.0f / (float)K;
 #define MLC_UPDATE(KERNEL, WT, GT, V, GRID, ...)                                                    \
-  hipLaunchKernelGGL((KERNEL<WT, GT, V>), GRID, dim3(OT_THREADS), 0, stream, w, (GT*)theta_g, u, ef, \
-                     thresholds, st, elems, (int)count, K, eta_out, mu, inv_k, nesterov, write_back, ##__VA_ARGS__)
+  hipLaunchKernelGGL((KERNEL<WT, GT, V>), GRID, dim3(OT_THREADS), 0, stream, args, st, elems, \
+                     (int)count, K, eta_out, mu, inv_k, nesterov, write_back, ##__VA_ARGS__)
   const dim3 all(full_grid, (unsigned)count);
   if (window) {
 #define MLC_SAMPLE(WT, GT, V)                                                                     \
   hipLaunchKernelGGL((topk_sample_kernel<WT, GT, V>), dim3((unsigned)count, K), dim3(TOPK_SAMPLE_THREADS), 0, \
-                     stream, w, (const GT*)theta_g, ef, st, elems, (int)count, kcount, ef_beta)
-#define MLC_WINDOW(WT, GT, V)                                                                     \
-  hipLaunchKernelGGL((topk_window_kernel<WT, GT, V>), dim3(window_grid, (unsigned)count, K),                  \
-                     dim3(TOPK_WINDOW_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta)
+                     stream, args, st, elems, (int)count, kcount, ef_beta)
+#define MLC_WINDOW(WT, GT, V, T, ...)                                                             \
+  hipLaunchKernelGGL((topk_window_kernel<WT, GT, V, T>), dim3(__VA_ARGS__), dim3(TOPK_WINDOW_THREADS), 0, stream, args, \
+                     st, elems, (int)count, ef_beta)
 #define MLC_LATE(WT, GT, V)                                                                       \
-  hipLaunchKernelGGL((topk_late_kernel<WT, GT, V>), dim3(TOPK_LATE_GRID), dim3(OT_THREADS), 0, stream, w,     \
-                     (const GT*)theta_g, ef, thresholds, st, elems, (int)count, K, ef_beta, late_most, (int)(pass == 0))
+  hipLaunchKernelGGL((topk_late_kernel<WT, GT, V>), dim3(TOPK_LATE_GRID), dim3(OT_THREADS), 0, stream, args,  \
+                     st, elems, (int)count, K, ef_beta, late_most, (int)(pass == 0))
 #define MLC_WINDOWED(WT, GT, V)                                                                   \
   do {                                                                                            \
     MLC_SAMPLE(WT, GT, V);                                                                        \
-    MLC_WINDOW(WT, GT, V);                                                                        \
+    if (turn) MLC_WINDOW(WT, GT, V, true, K, window_grid, (unsigned)count);                       \
+    else MLC_WINDOW(WT, GT, V, false, window_grid, (unsigned)count, K);                           \
     MLC_UPDATE(topk_early_kernel, WT, GT, V, all);                                                \
     for (int pass = 0; pass < 3; ++pass) MLC_LATE(WT, GT, V);                                     \
     MLC_UPDATE(topk_finish_kernel, WT, GT, V, dim3(TOPK_FINISH_GRID), finish_most);               \
@@ -1913,7 +1949,7 @@ int launch_topk_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, int 
     const bool last_picks = topk_last_picks(full_grid, n_states);
 #define MLC_HIST(WT, GT, V, F)                                                                    \
   hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(full_grid, (unsigned)count, K),        \
-                     dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, ef, st, elems, (int)count, ef_beta, (int)last_picks);   \
+                     dim3(OT_THREADS), 0, stream, args, st, elems, (int)count, ef_beta, (int)last_picks);   \
   if (!last_picks) hipLaunchKernelGGL(topk_pick_kernel, dim3(n_states), dim3(OT_THREADS), 0, stream, st)
 #define MLC_PASSES(WT, GT, V)                                                                     \
   do {                                                                                            \

@@ -442,3 +442,51 @@ def test_topk_long_lists_do_not_hold_a_call_up():
     (0.7 when one workgroup settled all of them)."""
     grp = _misled(1, 768, 3072, 16, torch.bfloat16, torch.bfloat16, False, lambda k, i: False)
     assert _terabytes_per_second(grp, 16, 0.05, False) > 1.3
+
+
+# Two groups of equally large matrices share launches where the work space holds the states of both (here a third group's), and give
+# the bits of a call each: by the passes, from a sample, with odd sizes, and where the pass of the window takes the workers in turn
+# (both groups past the memory-side cache).  Groups that share memory, of other sizes or types, or whose states do not fit, follow
+# each other.
+@pytest.mark.parametrize("c0,c1,m,n,K,wd,gd,ef,together", [
+    (2, 1, 64, 128, 3, torch.bfloat16, torch.float32, True, True),
+    (1, 3, 33, 7, 2, torch.float32, torch.float32, False, True),
+    (5, 3, 512, 1024, 2, torch.bfloat16, torch.bfloat16, True, True),
+    (2, 2, 2048, 4096, 2, torch.bfloat16, torch.float32, True, True),
+    (2, 2, 1449, 1451, 8, torch.bfloat16, torch.float32, False, True),
+    (40, 40, 313, 315, 3, torch.float32, torch.float32, True, True),
+    (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, True, "shared memory"),
+    (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, True, "states"),
+    (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, False, "size"),
+    (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, False, "type"),
+])
+def test_topk_groups_of_equal_matrices_share_launches(c0, c1, m, n, K, wd, gd, ef, together):
+    quiet = lambda k, i: False  # noqa: E731
+    first = _misled(c0, m, n, K, wd, gd, ef, quiet)
+    second = _misled(c1, n, m + (together == "size"), K, wd, torch.bfloat16 if together == "type" else gd, ef, quiet)
+    for t in second.worker_params:                                  # not the first group's values over again
+        t.mul_(1.01)
+    if together == "shared memory":
+        first.residuals, second.residuals = ([t for t in first.residuals],
+                                             [t.reshape(c1, n, m) for t in first.residuals])
+    groups = [first, second]
+    if together != "states":
+        groups.append(_misled(c0 + c1, 16, 24, K, wd, gd, ef, quiet))
+    shared = _clone(first), _clone(second)
+    if together == "shared memory":
+        shared[1].residuals = [t.reshape(c1, n, m) for t in shared[0].residuals]
+    for grp in shared:
+        _topk([grp], K, 0.05, ef)
+    mlc.muloco_timing_enable(True)
+    try:
+        mlc.muloco_timing_read()
+        _topk(groups, K, 0.05, ef)
+        torch.cuda.synchronize()
+        assert mlc.muloco_timing_read()["topk"]["launches"] == len(groups) - (together is True)
+    finally:
+        mlc.muloco_timing_enable(False)
+    for got, want in zip(groups, shared):
+        assert torch.equal(got.global_param, want.global_param) and torch.equal(got.outer_momentum, want.outer_momentum)
+        for k in range(K):
+            assert torch.equal(got.scales[k], want.scales[k]) and torch.equal(got.worker_params[k], want.worker_params[k])
+            assert not ef or torch.equal(got.residuals[k], want.residuals[k])
