@@ -645,6 +645,34 @@ static void gather_ptrs(const mlc_outer_group& g, const mlc_outer_hparams& hp, O
   }
 }
 
+static OuterGroupArgs group_args(const mlc_outer_group& g, const OuterPtrs& p) {
+  OuterGroupArgs a;
+  a.w = p.w; a.codes = p.c; a.scales = p.s; a.offsets = p.o; a.ef = p.e;
+  a.theta_g = g.global_param; a.u = g.outer_momentum;
+  a.rows = g.count * g.m; a.m = g.m; a.n = g.n;
+  return a;
+}
+
+// Does any memory that these groups' step reads or writes, with a range or threshold a matrix, overlap another part of it?
+static bool outer_overlap(const mlc_outer_group* groups, int n_groups, const mlc_outer_hparams& hp) {
+  Span s[OUTER_MAX_SEG * (2 + 5 * MLC_MAX_WORKERS)];
+  int n = 0;
+  for (int i = 0; i < n_groups; ++i) {
+    const mlc_outer_group& g = groups[i];
+    const size_t elems = (size_t)g.count * g.m * g.n, ranges = (size_t)g.count * 4;     // one a matrix
+    s[n++] = span(g.global_param, elems * elem_size(g.global_dtype));
+    s[n++] = span(g.outer_momentum, elems * 4);
+    for (int k = 0; k < hp.K; ++k) {
+      s[n++] = span(g.worker_params[k], elems * elem_size(g.worker_dtype));
+      if (hp.error_feedback) s[n++] = span(g.residuals[k], elems * 4);
+      if (hp.quant_bits && g.codes) s[n++] = span(g.codes[k], elems * hp.quant_bits / 8);
+      if (g.scales) s[n++] = span(g.scales[k], ranges);
+      if (hp.quant_offset) s[n++] = span(g.offsets[k], ranges);
+    }
+  }
+  return any_overlap(s, n);
+}
+
 static QuantForm form_of(const mlc_outer_group& g, const mlc_outer_hparams& hp) {
   return make_quant_form(hp.quant_bits, hp.quant_offset, hp.quant_per_matrix ? g.m : 0, hp.ef_beta);
 }
@@ -661,8 +689,8 @@ int muloco_quantize_delta(const mlc_outer_group* groups, int n_groups, const mlc
     gather_ptrs(g, *hp, p);
     const QuantForm form = form_of(g, *hp);
     if (hp->quant_per_matrix) {
-      rc = launch_matrix_ranges(p.w, g.worker_dtype, g.global_param, g.global_dtype, p.s, p.o, p.e, g.count,
-                                g.m, g.n, hp->K, form, stream);
+      const OuterGroupArgs a = group_args(g, p);
+      rc = launch_matrix_ranges(&a, 1, g.worker_dtype, g.global_dtype, hp->K, form, stream);
       if (rc != MLC_OK) return rc;
     }
     rc = launch_quantize(p.w, g.worker_dtype, g.global_param, g.global_dtype, p.c, p.s, p.o, p.e,
@@ -674,7 +702,7 @@ int muloco_quantize_delta(const mlc_outer_group* groups, int n_groups, const mlc
 
 // Can this group go into a launch that covers several groups?
 static bool multi_launch_covers(const mlc_outer_group& g, const mlc_outer_hparams& hp) {
-  if (hp.K > OUTER_MAX_SEG_K || hp.second_quantisation || hp.quant_per_matrix) return false;
+  if (hp.K > OUTER_MAX_SEG_K || hp.second_quantisation) return false;
   if (hp.quant_bits == 0) return true;
   return quant_reg_cfg(g.n) >= 0 && !quant_two_pass(g.count * g.m, g.n, hp.quant_bits) &&
          !(g.worker_dtype == MLC_F32 && g.global_dtype == MLC_BF16);
@@ -693,15 +721,19 @@ int muloco_outer_step(const mlc_outer_group* groups, int n_groups, const mlc_out
            groups[i + run].global_dtype == groups[i].global_dtype && multi_launch_covers(groups[i + run], *hp) &&
            (hp->quant_bits == 0 || quant_ragged(groups[i + run].n) == quant_ragged(groups[i].n)))
       ++run;
-    if (run >= 2) {
+    // (ranges per matrix are those of the parameters before any of these groups' updates: their memory must be apart)
+    if (run >= 2 && !(hp->quant_per_matrix && outer_overlap(groups + i, run, *hp))) {
       OuterGroupArgs args[OUTER_MAX_SEG];
       for (int j = 0; j < run; ++j) {
         const mlc_outer_group& g = groups[i + j];
         OuterPtrs p;
         gather_ptrs(g, *hp, p);
-        args[j].w = p.w; args[j].codes = p.c; args[j].scales = p.s; args[j].offsets = p.o; args[j].ef = p.e;
-        args[j].theta_g = g.global_param; args[j].u = g.outer_momentum;
-        args[j].rows = g.count * g.m; args[j].n = g.n;
+        args[j] = group_args(g, p);
+      }
+      if (hp->quant_per_matrix) {
+        rc = launch_matrix_ranges(args, run, groups[i].worker_dtype, groups[i].global_dtype, hp->K,
+                                  form_of(groups[i], *hp), stream);
+        if (rc != MLC_OK) return rc;
       }
       if (hp->quant_bits)
         rc = launch_quantize_outer_multi(args, run, groups[i].worker_dtype, groups[i].global_dtype, hp->K,
@@ -720,8 +752,8 @@ int muloco_outer_step(const mlc_outer_group* groups, int n_groups, const mlc_out
     if (hp->quant_bits) {
       const QuantForm form = form_of(g, *hp);
       if (hp->quant_per_matrix) {
-        rc = launch_matrix_ranges(p.w, g.worker_dtype, g.global_param, g.global_dtype, p.s, p.o, p.e,
-                                  g.count, g.m, g.n, hp->K, form, stream);
+        const OuterGroupArgs a = group_args(g, p);
+        rc = launch_matrix_ranges(&a, 1, g.worker_dtype, g.global_dtype, hp->K, form, stream);
         if (rc != MLC_OK) return rc;
       }
       // one pass when the row fits in registers, else quantise and then consume the codes
@@ -768,19 +800,8 @@ size_t muloco_topk_workspace_bytes(const mlc_outer_group* groups, int n_groups, 
 static bool topk_pair(const mlc_outer_group& a, const mlc_outer_group& b, const mlc_outer_hparams& hp, size_t workspace_bytes) {
   if (a.m * a.n != b.m * b.n || a.worker_dtype != b.worker_dtype || a.global_dtype != b.global_dtype) return false;
   if (a.count + b.count > 65535 || topk_workspace_bytes(a.count + b.count, hp.K) > workspace_bytes) return false;
-  Span s[2 * (2 + 3 * MLC_MAX_WORKERS)];
-  int n = 0;
-  for (const mlc_outer_group* g : {&a, &b}) {
-    const size_t elems = (size_t)g->count * g->m * g->n;
-    s[n++] = span(g->global_param, elems * elem_size(g->global_dtype));
-    s[n++] = span(g->outer_momentum, elems * 4);
-    for (int k = 0; k < hp.K; ++k) {
-      s[n++] = span(g->worker_params[k], elems * elem_size(g->worker_dtype));
-      if (hp.error_feedback) s[n++] = span(g->residuals[k], elems * 4);
-      if (g->scales) s[n++] = span(g->scales[k], (size_t)g->count * 4);
-    }
-  }
-  return !any_overlap(s, n);
+  const mlc_outer_group both[2] = {a, b};
+  return !outer_overlap(both, 2, hp);
 }
 
 int muloco_topk_outer_step(const mlc_outer_group* groups, int n_groups, const mlc_outer_hparams* hp,

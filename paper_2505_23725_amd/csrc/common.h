@@ -289,7 +289,7 @@ constexpr int OUTER_MAX_SEG = 4;
 constexpr int OUTER_MAX_SEG_K = 8;
 struct OuterGroupArgs {
   WorkerPtrs w; CodePtrs codes; ScalePtrs scales; ScalePtrs offsets; ResidualPtrs ef;
-  void* theta_g; float* u; int64_t rows, n;
+  void* theta_g; float* u; int64_t rows, m, n;      // m: rows of a matrix
 };
 // >= 0 when groups with rows of length n can share a launch of the one-pass quantiser (up to 8192 columns; longer rows
 // would need so many registers of its 256 threads that they would halve the occupancy of the whole launch).
@@ -333,9 +333,7 @@ QuantForm make_quant_form(int bits, int offset, int64_t rows_per_range, float ef
 // per-worker lower ends of the ranges (offset form); all null otherwise
 typedef ScalePtrs OffsetPtrs;
 // Ranges per matrix, written to scales (and offsets) ahead of the quantiser proper.
-int launch_matrix_ranges(const WorkerPtrs& w, int worker_dtype, const void* theta_g, int global_dtype,
-                         const ScalePtrs& scales, const OffsetPtrs& offsets, const ResidualPtrs& ef,
-                         int64_t count, int64_t m, int64_t n, int K, const QuantForm& form,
+int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K, const QuantForm& form,
                          hipStream_t stream);
 int launch_quantize(const WorkerPtrs& w, int worker_dtype, const void* theta_g, int global_dtype,
                     const CodePtrs& codes, const ScalePtrs& scales, const OffsetPtrs& offsets,

@@ -273,67 +273,95 @@ __device__ __forceinline__ float key_float(unsigned int k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-__global__ void matrix_range_init_kernel(ScalePtrs scales, OffsetPtrs offsets, long count, int offset) {
+// Up to OUTER_MAX_SEG groups and OUTER_MAX_SEG_K workers a launch.
+template <typename T> struct SegPtrs { T p[OUTER_MAX_SEG_K]; };
+struct RangeSeg {
+  SegPtrs<void*> w;
+  SegPtrs<float*> ef, scales, offsets;
+  const void* theta_g;
+  long elems;
+  unsigned int count, nblk, blk0;      // matrices; workgroups a matrix; first workgroup of the group
+};
+struct RangeTable { RangeSeg s[OUTER_MAX_SEG]; int nseg; };
+
+__global__ void matrix_range_init_kernel(RangeTable tab, int offset) {
+  const RangeSeg& sg = tab.s[blockIdx.z];
   const long b = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int k = blockIdx.y;
-  if (b >= count) return;
-  reinterpret_cast<unsigned int*>(scales.p[k])[b] = 0u;                    // below every key
-  if (offset) reinterpret_cast<unsigned int*>(offsets.p[k])[b] = 0xffffffffu;   // above every key
+  if (b >= sg.count) return;
+  reinterpret_cast<unsigned int*>(sg.scales.p[k])[b] = 0u;                      // below every key
+  if (offset) reinterpret_cast<unsigned int*>(sg.offsets.p[k])[b] = 0xffffffffu;   // above every key
 }
 
-template <typename WT, typename GT, bool VEC>
-__global__ __launch_bounds__(OT_THREADS) void matrix_range_kernel(
-    WorkerPtrs w, const GT* __restrict__ theta_g, ScalePtrs scales, OffsetPtrs offsets, ResidualPtrs ef,
-    long elems, QuantForm form) {
-  __shared__ float red[2][OT_THREADS / 64];
-  const long b = blockIdx.y;
-  const int k = blockIdx.z;
-  const GT* tg = theta_g + b * elems;
-  const WT* tk = reinterpret_cast<const WT*>(w.p[k]) + b * elems;
-  const float* res = ef.p[k] ? ef.p[k] + b * elems : nullptr;
-  float mn = INFINITY, mx = -INFINITY;
-  for (long i = ((long)blockIdx.x * OT_THREADS + threadIdx.x) * 8; i < elems;
-       i += (long)gridDim.x * OT_THREADS * 8) {
-    float a[8], c[8], e[8];
-    const int left = (int)min(elems - i, 8L);
-    load8<GT, !VEC>(tg + i, left, a); load8<WT, !VEC>(tk + i, left, c);
-    if (res) load8<float, !VEC>(res + i, left, e);
+// The ranges of all workers of a piece, so that theta_g is read once and not once a worker: all their loads are under way
+// together (KM: their number, or the next power of two above it).  Whole steps with error feedback, eight workers, a grid
+// dimension for the workers and now, us: 2 x 3560 x 5504 and its square 3611 and 3200; without feedback 12 x 512 x 1024 with bf16 workers
+// 782 and 470.
+template <typename WT, typename GT, bool VEC, int KM>
+__global__ __launch_bounds__(OT_THREADS) void matrix_range_kernel(RangeTable tab, int K, QuantForm form) {
+  __shared__ float red[2][KM][OT_THREADS / 64];
+  int si = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float d = a[j] - c[j];
-      const float v = res ? ef_input(d, e[j], form.ef_beta) : d;
-      if (VEC || j < left) { mn = fminf(mn, v); mx = fmaxf(mx, v); }
-    }
-  }
-  mn = wave_min(mn); mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = mn; red[1][threadIdx.x >> 6] = mx; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    mn = fminf(fminf(red[0][0], red[0][1]), fminf(red[0][2], red[0][3]));
-    mx = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
-    if (mn <= mx) {          // this workgroup saw at least one element
-      if (form.offset) {
-        atomicMax(reinterpret_cast<unsigned int*>(scales.p[k]) + b, float_key(mx));
-        atomicMin(reinterpret_cast<unsigned int*>(offsets.p[k]) + b, float_key(mn));
-      } else {               // amax >= 0: its bit pattern is ordered like an unsigned
-        atomicMax(reinterpret_cast<unsigned int*>(scales.p[k]) + b, __float_as_uint(fmaxf(mx, -mn)));
+  for (int i = 1; i < OUTER_MAX_SEG; ++i)
+    if (i < tab.nseg && blockIdx.x >= tab.s[i].blk0) si = i;
+  const RangeSeg& sg = tab.s[si];
+  const unsigned int at = blockIdx.x - sg.blk0, blk = at % sg.nblk;
+  const long b = at / sg.nblk, elems = sg.elems;
+  const GT* tg = reinterpret_cast<const GT*>(sg.theta_g) + b * elems;
+  const bool fb = sg.ef.p[0] != nullptr;                  // all workers have residuals, or none
+  float mn[KM], mx[KM];
+#pragma unroll
+  for (int k = 0; k < KM; ++k) { mn[k] = INFINITY; mx[k] = -INFINITY; }
+  for (long i = ((long)blk * OT_THREADS + threadIdx.x) * 8; i < elems; i += (long)sg.nblk * OT_THREADS * 8) {
+    float a[8];
+    const int left = (int)min(elems - i, 8L);
+    load8<GT, !VEC>(tg + i, left, a);
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+      if (k >= K) break;
+      float c[8], e[8];
+      load8<WT, !VEC>(reinterpret_cast<const WT*>(sg.w.p[k]) + b * elems + i, left, c);
+      if (fb) load8<float, !VEC>(sg.ef.p[k] + b * elems + i, left, e);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float d = a[j] - c[j];
+        const float v = fb ? ef_input(d, e[j], form.ef_beta) : d;
+        if (VEC || j < left) { mn[k] = fminf(mn[k], v); mx[k] = fmaxf(mx[k], v); }
       }
     }
   }
+#pragma unroll
+  for (int k = 0; k < KM; ++k) {
+    const float lo = -wave_max_dpp(-mn[k]), hi = wave_max_dpp(mx[k]);
+    if ((threadIdx.x & 63) == 0) { red[0][k][threadIdx.x >> 6] = lo; red[1][k][threadIdx.x >> 6] = hi; }
+  }
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k >= K) return;
+  const float lo = fminf(fminf(red[0][k][0], red[0][k][1]), fminf(red[0][k][2], red[0][k][3]));
+  const float hi = fmaxf(fmaxf(red[1][k][0], red[1][k][1]), fmaxf(red[1][k][2], red[1][k][3]));
+  if (!(lo <= hi)) return;   // not a single element was a number
+  if (form.offset) {
+    atomicMax(reinterpret_cast<unsigned int*>(sg.scales.p[k]) + b, float_key(hi));
+    atomicMin(reinterpret_cast<unsigned int*>(sg.offsets.p[k]) + b, float_key(lo));
+  } else {                   // amax >= 0: its bit pattern is ordered like an unsigned
+    atomicMax(reinterpret_cast<unsigned int*>(sg.scales.p[k]) + b, __float_as_uint(fmaxf(hi, -lo)));
+  }
 }
 
-__global__ void matrix_range_finish_kernel(ScalePtrs scales, OffsetPtrs offsets, long count, QuantForm form) {
+__global__ void matrix_range_finish_kernel(RangeTable tab, QuantForm form) {
+  const RangeSeg& sg = tab.s[blockIdx.z];
   const long b = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int k = blockIdx.y;
-  if (b >= count) return;
+  if (b >= sg.count) return;
+  float* scale = sg.scales.p[k] + b;
   if (form.offset) {
-    const float mx = key_float(reinterpret_cast<unsigned int*>(scales.p[k])[b]);
-    const float mn = key_float(reinterpret_cast<unsigned int*>(offsets.p[k])[b]);
-    const Range r = make_range(mn, mx, form);
-    scales.p[k][b] = r.scale;
-    offsets.p[k][b] = r.lo;
+    float* lo = sg.offsets.p[k] + b;
+    const Range r = make_range(key_float(__float_as_uint(*lo)), key_float(__float_as_uint(*scale)), form);
+    *scale = r.scale;
+    *lo = r.lo;
   } else {
-    scales.p[k][b] = scales.p[k][b] / form.levels;     // the array holds amax
+    *scale = *scale / form.levels;     // the array holds amax
   }
 }
 
@@ -637,7 +665,6 @@ __global__ __launch_bounds__(G ? OT_THREADS : 1024, quant_min_waves(NV, OUTER)) 
 // three launches of 70-80 us each spend a good part of their time filling and draining the
 // chip; here the workgroups of one launch are dealt to the groups of a table that travels in
 // the kernel arguments (up to OUTER_MAX_SEG groups, OUTER_MAX_SEG_K workers).
-template <typename T> struct SegPtrs { T p[OUTER_MAX_SEG_K]; };
 struct QuantSeg {
   SegPtrs<void*> w;
   SegPtrs<uint8_t*> codes;
@@ -646,6 +673,7 @@ struct QuantSeg {
   float* u;
   long rows;
   int n;
+  int rows_per_range;       // as in QuantForm
   int cfg;                  // index into the (vectors per thread, threads per row) table below
   unsigned int blk0;        // first workgroup of this group
 };
@@ -668,6 +696,7 @@ __global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3
   for (int i = 1; i < OUTER_MAX_SEG; ++i)
     if (i < tab.nseg && blockIdx.x >= tab.s[i].blk0) si = i;
   const QuantSeg& sg = tab.s[si];
+  form.rows_per_range = sg.rows_per_range;
   const long blk = (long)(blockIdx.x - sg.blk0);
 #define MLC_SEG_BODY(IDX)                                                                              \
   quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG, KC, false>(                             \
@@ -1567,36 +1596,66 @@ QuantForm make_quant_form(int bits, int offset, int64_t rows_per_range, float ef
   return f;
 }
 
-int launch_matrix_ranges(const WorkerPtrs& w, int worker_dtype, const void* theta_g, int global_dtype,
-                         const ScalePtrs& scales, const OffsetPtrs& offsets, const ResidualPtrs& ef,
-                         int64_t count, int64_t m, int64_t n, int K, const QuantForm& form,
+// Workgroups a matrix at most: each ends with the reduction of its ranges, so no more than fill the chip (512 whatever the count, with
+// one worker: 18 layers of 848 and 2368 718 us, now 637; 9 of 1280 and 1888, two workers, 732 and 685).
+static long range_blocks(long count) { return count < 4 ? 2048 / count : max(1L, 1536 / count); }
+
+int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K, const QuantForm& form,
                          hipStream_t stream) {
-  if (count > 65535 || K > 65535) return MLC_ERR_SHAPE;
-  const long elems = m * n;
-  const bool vec = elems % 8 == 0;
-  const int nblk = cap_blocks(((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, 512);
-  const double bytes = (double)count * elems * (K * esize(worker_dtype) + K * esize(global_dtype) +
-                                                (has_residuals(ef) ? 4.0 * K : 0.0));
-  LaunchScope scope(MLC_KERNEL_QUANTIZE, stream, 0.0, bytes);
-  const dim3 small((unsigned)((count + 255) / 256), (unsigned)K);
-  hipLaunchKernelGGL(matrix_range_init_kernel, small, dim3(256), 0, stream, scales, offsets, (long)count,
-                     form.offset);
-#define MLC_CALL(WT, GT)                                                                          \
+  if (ng < 1 || ng > OUTER_MAX_SEG) return MLC_ERR_UNSUPPORTED;
+  const bool fb = has_residuals(gs[0].ef);
+  for (int k0 = 0; k0 < K; k0 += OUTER_MAX_SEG_K) {
+    const int workers = min(K - k0, OUTER_MAX_SEG_K);
+    RangeTable tab;
+    tab.nseg = ng;
+    long blk = 0, most = 0;
+    bool vec = true;
+    double bytes = 0.0;
+    for (int i = 0; i < OUTER_MAX_SEG; ++i) {
+      RangeSeg& sg = tab.s[i];
+      if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
+      const OuterGroupArgs& g = gs[i];
+      const long count = g.rows / g.m;
+      if (count > 65535) return MLC_ERR_SHAPE;
+      for (int k = 0; k < OUTER_MAX_SEG_K; ++k) {
+        const bool there = k < workers;
+        sg.w.p[k] = there ? g.w.p[k0 + k] : nullptr;
+        sg.ef.p[k] = there ? g.ef.p[k0 + k] : nullptr;
+        sg.scales.p[k] = there ? g.scales.p[k0 + k] : nullptr;
+        sg.offsets.p[k] = there ? g.offsets.p[k0 + k] : nullptr;
+      }
+      sg.theta_g = g.theta_g;
+      sg.elems = g.m * g.n;
+      vec = vec && sg.elems % 8 == 0;
+      sg.count = (unsigned int)count;
+      sg.nblk = (unsigned int)cap_blocks(((sg.elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, range_blocks(count));
+      sg.blk0 = (unsigned int)blk;
+      blk += (long)sg.nblk * count;
+      most = max(most, count);
+      bytes += (double)g.rows * g.n * (workers * esize(worker_dtype) + esize(global_dtype) + (fb ? 4.0 * workers : 0.0));
+    }
+    LaunchScope scope(MLC_KERNEL_QUANTIZE, stream, 0.0, bytes);
+    const dim3 small((unsigned)((most + 255) / 256), (unsigned)workers, (unsigned)ng);
+    hipLaunchKernelGGL(matrix_range_init_kernel, small, dim3(256), 0, stream, tab, form.offset);
+#define MLC_RANGE(WT, GT, V, KM)                                                                  \
+  hipLaunchKernelGGL((matrix_range_kernel<WT, GT, V, KM>), dim3((unsigned)blk), dim3(OT_THREADS), 0, stream, tab, workers, form)
+#define MLC_RANGE_K(WT, GT, V)                                                                    \
   do {                                                                                            \
-    if (vec)                                                                                      \
-      hipLaunchKernelGGL((matrix_range_kernel<WT, GT, true>), dim3(nblk, (unsigned)count, K),      \
-                         dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, scales, offsets, ef,  \
-                         elems, form);                                                            \
-    else                                                                                          \
-      hipLaunchKernelGGL((matrix_range_kernel<WT, GT, false>), dim3(nblk, (unsigned)count, K),     \
-                         dim3(OT_THREADS), 0, stream, w, (const GT*)theta_g, scales, offsets, ef,  \
-                         elems, form);                                                            \
+    if (workers == 1) MLC_RANGE(WT, GT, V, 1);                                                    \
+    else if (workers == 2) MLC_RANGE(WT, GT, V, 2);                                               \
+    else if (workers <= 4) MLC_RANGE(WT, GT, V, 4);                                               \
+    else MLC_RANGE(WT, GT, V, OUTER_MAX_SEG_K);                                                   \
   } while (0)
-  MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
+#define MLC_CALL(WT, GT) do { if (vec) MLC_RANGE_K(WT, GT, true); else MLC_RANGE_K(WT, GT, false); } while (0)
+    MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
-  hipLaunchKernelGGL(matrix_range_finish_kernel, small, dim3(256), 0, stream, scales, offsets, (long)count,
-                     form);
-  return check_launch();
+#undef MLC_RANGE_K
+#undef MLC_RANGE
+    hipLaunchKernelGGL(matrix_range_finish_kernel, small, dim3(256), 0, stream, tab, form);
+    const int rc = check_launch();
+    if (rc != MLC_OK) return rc;
+  }
+  return MLC_OK;
 }
 
 int launch_quantize(const WorkerPtrs& w, int worker_dtype, const void* theta_g, int global_dtype,
@@ -1789,7 +1848,7 @@ int quant_reg_cfg(int64_t n) {
 int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K,
                                 const QuantForm& form, float eta_out, float mu, int nesterov, int write_back,
                                 hipStream_t stream) {
-  if (ng < 1 || ng > OUTER_MAX_SEG || K > OUTER_MAX_SEG_K || form.rows_per_range != 0) return MLC_ERR_UNSUPPORTED;
+  if (ng < 1 || ng > OUTER_MAX_SEG || K > OUTER_MAX_SEG_K) return MLC_ERR_UNSUPPORTED;
   if (worker_dtype == MLC_F32 && global_dtype == MLC_BF16) return MLC_ERR_UNSUPPORTED;
   QuantSegTable tab;
   tab.nseg = ng;
@@ -1815,6 +1874,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     sg.u = gs[i].u;
     sg.rows = gs[i].rows;
     sg.n = (int)gs[i].n;
+    sg.rows_per_range = form.rows_per_range ? (int)gs[i].m : 0;
     sg.cfg = cfg;
     const long rpb = OT_THREADS / reg_cfg(cfg).g;
     sg.blk0 = (unsigned int)blk;

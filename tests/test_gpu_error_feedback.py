@@ -340,3 +340,44 @@ def test_ragged_and_aligned_groups_in_one_call_equal_one_call_per_group():
 def test_workgroups_of_one_row(n, K):
     bits = 4 if n % 16 else 8
     test_quantiser_forms_bit_exact(1, 5, n, K, torch.bfloat16, torch.float32, bits, K == 3, False, K == 2, K == 2)
+
+
+# Groups whose ranges are per matrix share their launches and give the bits of a call each: in one launch for all workers or, from
+# nine on, in slices; rows of any length; one matrix and many; next to a group of too long rows; and a group over the first one's
+# memory, which follows it.
+@pytest.mark.parametrize("shapes,K,wd,gd,bits,offset,ef,again", [
+    ([(3, 64, 128), (1, 128, 200), (2, 40, 2048)], 1, torch.bfloat16, torch.float32, 4, False, True, False),
+    ([(2, 50, 1000), (70, 8, 24)], 3, torch.float32, torch.float32, 4, True, True, False),
+    ([(2, 33, 131), (1, 77, 65), (5, 9, 203)], 2, torch.bfloat16, torch.bfloat16, 8, True, False, False),
+    ([(1, 300, 8192), (1, 16, 8200), (2, 64, 64), (2, 96, 64)], 8, torch.bfloat16, torch.float32, 2, False, False, False),
+    ([(2, 48, 96), (2, 96, 48)], 11, torch.bfloat16, torch.float32, 4, True, True, False),
+    ([(2, 48, 96), (2, 96, 48)], 2, torch.bfloat16, torch.float32, 4, True, True, True),
+])
+def test_groups_with_ranges_per_matrix(shapes, K, wd, gd, bits, offset, ef, again):
+    hp = mlc.OuterHParams(K=K, eta_out=0.9, mu=0.8, quant_bits=bits, error_feedback=ef, ef_beta=0.9, quant_offset=offset,
+                          quant_per_matrix=True)
+
+    def make():
+        groups = []
+        for i, (cnt, m, n) in enumerate(shapes):
+            tg0, ws0, u0 = _inputs(cnt, m, n, K, wd, gd, 100 * i + K)
+            f32 = lambda: [torch.full((cnt,), -1.0, device=DEV) for _ in range(K)]  # noqa: E731
+            groups.append(mlc.OuterGroup(
+                [w.to(DEV) for w in ws0], tg0.to(DEV), u0.to(DEV),
+                [torch.full((cnt * m, n * bits // 8), 0xAA, dtype=torch.uint8, device=DEV) for _ in range(K)], f32(),
+                [S.normal((cnt, m, n), 1e-3, 7 * i, 40 + k).to(DEV) for k in range(K)] if ef else None, None, None,
+                f32() if offset else None, None))
+        if again:
+            (c, _, _), (_, m, n) = shapes
+            groups[1].worker_params = [w.view(c, m, n) for w in groups[0].worker_params]
+        return groups
+
+    together, alone = make(), make()
+    mlc.muloco_outer_step(together, hp)
+    for grp in alone:
+        mlc.muloco_outer_step([grp], hp)
+    for got, want in zip(together, alone):
+        assert torch.equal(got.global_param, want.global_param) and torch.equal(got.outer_momentum, want.outer_momentum)
+        for name in ("worker_params", "codes", "scales", "offsets", "residuals"):
+            for a, b in zip(getattr(got, name) or [], getattr(want, name) or []):
+                assert torch.equal(a, b), name
