@@ -687,10 +687,10 @@ __host__ __device__ constexpr RegCfg reg_cfg(int idx) {
        : idx == 3 ? RegCfg{2, 256} : RegCfg{4, 256};
 }
 
-// (Three wavefronts a SIMD: more of them, which one worker's registers would allow, make its long rows 1 to 2 % slower.)
-template <typename WT, typename GT, bool RAG, int KC>
-__global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void quantize_outer_multi_kernel(
-    QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
+// TOP: the last entry of the table above that the groups use.
+template <typename WT, typename GT, bool RAG, int KC, int TOP>
+__device__ __forceinline__ void quantize_outer_multi_body(const QuantSegTable& tab, int K, QuantForm form, float eta, float mu,
+                                                          float inv_k, int nesterov, int write_back) {
   int si = 0;
 #pragma unroll
   for (int i = 1; i < OUTER_MAX_SEG; ++i)
@@ -702,14 +702,38 @@ __global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3
   quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG, KC, false>(                             \
       sg.w, (GT*)sg.theta_g, sg.u, sg.codes, sg.scales, sg.offsets, sg.ef, sg.rows, sg.n, K, form, eta, \
       mu, inv_k, nesterov, write_back, 0, nullptr, nullptr, nullptr, blk)
-  switch (sg.cfg) {      // uniform over the workgroup
-    case 0: MLC_SEG_BODY(0); break;
-    case 1: MLC_SEG_BODY(1); break;
-    case 2: MLC_SEG_BODY(2); break;
-    case 3: MLC_SEG_BODY(3); break;
-    default: MLC_SEG_BODY(4); break;
+  // uniform over the workgroup
+  if constexpr (TOP == 0) {
+    MLC_SEG_BODY(0);
+  } else if constexpr (TOP == 1) {
+    if (sg.cfg == 0) MLC_SEG_BODY(0);
+    else MLC_SEG_BODY(1);
+  } else {
+    switch (sg.cfg) {
+      case 0: MLC_SEG_BODY(0); break;
+      case 1: MLC_SEG_BODY(1); break;
+      case 2: MLC_SEG_BODY(2); break;
+      case 3: MLC_SEG_BODY(3); break;
+      default: MLC_SEG_BODY(4); break;
+    }
   }
 #undef MLC_SEG_BODY
+}
+
+// (Three wavefronts a SIMD: more of them, which one worker's registers would allow, make its long rows 1 to 2 % slower.)
+template <typename WT, typename GT, bool RAG, int KC>
+__global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void quantize_outer_multi_kernel(
+    QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
+  quantize_outer_multi_body<WT, GT, RAG, KC, 4>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
+}
+
+// Several workers, rows of up to 512 (TOP 0) or 1024 columns: as many wavefronts a SIMD as their registers allow, where the kernel of
+// all lengths has three.  160 / 40 / 40 matrices of 128 x 128, 128 x 256 and 256 x 128, 4 bits, us: two workers 53 to 39, eight 138 to 96, with
+// error feedback 273 to 173; 24 / 6 / 6 of 512 x 512 and 512 x 1024, eight workers 174 to 153, with error feedback 296 to 299.
+template <typename WT, typename GT, bool RAG, int TOP>
+__global__ __launch_bounds__(OT_THREADS, quant_min_waves(reg_cfg(TOP).nv, true)) void quantize_outer_narrow_kernel(
+    QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
+  quantize_outer_multi_body<WT, GT, RAG, 0, TOP>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
 }
 
 struct OuterSeg {
@@ -1855,6 +1879,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
   unsigned long blk = 0;
   double bytes = 0.0;
   bool ef_any = false;
+  int top = 0;
   for (int i = 0; i < OUTER_MAX_SEG; ++i) {
     QuantSeg& sg = tab.s[i];
     if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
@@ -1876,6 +1901,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     sg.n = (int)gs[i].n;
     sg.rows_per_range = form.rows_per_range ? (int)gs[i].m : 0;
     sg.cfg = cfg;
+    top = max(top, cfg);
     const long rpb = OT_THREADS / reg_cfg(cfg).g;
     sg.blk0 = (unsigned int)blk;
     blk += (unsigned long)((gs[i].rows + rpb - 1) / rpb);
@@ -1886,19 +1912,23 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
   }
   LaunchScope scope(MLC_KERNEL_DEQUANT_OUTER, stream, 0.0, bytes);
   const float inv_k = 1.0f / (float)K;
-#define MLC_QM_R(WT, GT, RAG, KC)                                                                      \
-  hipLaunchKernelGGL((quantize_outer_multi_kernel<WT, GT, RAG, KC>), dim3((unsigned)blk), dim3(OT_THREADS), \
-                     0, stream, tab, K, form, eta_out, mu, inv_k, nesterov, write_back)
-#define MLC_QM(WT, GT)                                                                            \
+#define MLC_QM_R(KERNEL, WT, GT, RAG, X)                                                          \
+  hipLaunchKernelGGL((KERNEL<WT, GT, RAG, X>), dim3((unsigned)blk), dim3(OT_THREADS), 0, stream, tab, K, form, eta_out, mu, \
+                     inv_k, nesterov, write_back)
+#define MLC_QM_K(WT, GT, RAG)                                                                     \
   do {                                                                                            \
-    if (K == 1) { if (quant_ragged(gs[0].n)) MLC_QM_R(WT, GT, true, 1); else MLC_QM_R(WT, GT, false, 1); }   \
-    else if (quant_ragged(gs[0].n)) MLC_QM_R(WT, GT, true, 0);                                    \
-    else MLC_QM_R(WT, GT, false, 0);                                                              \
+    if (K == 1) MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 1);                            \
+    else if (top == 0) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 0);                    \
+    else if (top == 1) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 1);                    \
+    else MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 0);                                   \
   } while (0)
+#define MLC_QM(WT, GT)                                                                            \
+  do { if (quant_ragged(gs[0].n)) MLC_QM_K(WT, GT, true); else MLC_QM_K(WT, GT, false); } while (0)
   if (worker_dtype == MLC_BF16 && global_dtype == MLC_F32) MLC_QM(bf16_t, float);
   else if (worker_dtype == MLC_BF16) MLC_QM(bf16_t, bf16_t);
   else MLC_QM(float, float);
 #undef MLC_QM
+#undef MLC_QM_K
 #undef MLC_QM_R
   return check_launch();
 }

@@ -344,7 +344,8 @@ def test_workgroups_of_one_row(n, K):
 
 # Groups whose ranges are per matrix share their launches and give the bits of a call each: in one launch for all workers or, from
 # nine on, in slices; rows of any length; one matrix and many; next to a group of too long rows; and a group over the first one's
-# memory, which follows it.
+# memory, which follows it.  The same of groups with ranges per row whose rows are narrow (512 and 1024 columns are the lines), for
+# which several workers have kernels of their own.
 @pytest.mark.parametrize("shapes,K,wd,gd,bits,offset,ef,again", [
     ([(3, 64, 128), (1, 128, 200), (2, 40, 2048)], 1, torch.bfloat16, torch.float32, 4, False, True, False),
     ([(2, 50, 1000), (70, 8, 24)], 3, torch.float32, torch.float32, 4, True, True, False),
@@ -352,16 +353,22 @@ def test_workgroups_of_one_row(n, K):
     ([(1, 300, 8192), (1, 16, 8200), (2, 64, 64), (2, 96, 64)], 8, torch.bfloat16, torch.float32, 2, False, False, False),
     ([(2, 48, 96), (2, 96, 48)], 11, torch.bfloat16, torch.float32, 4, True, True, False),
     ([(2, 48, 96), (2, 96, 48)], 2, torch.bfloat16, torch.float32, 4, True, True, True),
+    ([(3, 50, 512), (2, 33, 8)], 2, torch.bfloat16, torch.float32, 4, False, True, None),
+    ([(3, 50, 509), (2, 33, 505)], 3, torch.float32, torch.float32, 8, True, True, None),
+    ([(3, 50, 520), (2, 33, 1024)], 4, torch.bfloat16, torch.bfloat16, 2, True, False, None),
+    ([(3, 50, 1022), (2, 33, 70)], 2, torch.bfloat16, torch.float32, 4, False, True, None),
+    ([(3, 50, 1032), (2, 33, 64)], 8, torch.float32, torch.float32, 8, False, True, None),
 ])
-def test_groups_with_ranges_per_matrix(shapes, K, wd, gd, bits, offset, ef, again):
+def test_groups_that_share_launches(shapes, K, wd, gd, bits, offset, ef, again):
+    per_matrix = again is not None
     hp = mlc.OuterHParams(K=K, eta_out=0.9, mu=0.8, quant_bits=bits, error_feedback=ef, ef_beta=0.9, quant_offset=offset,
-                          quant_per_matrix=True)
+                          quant_per_matrix=per_matrix)
 
     def make():
         groups = []
         for i, (cnt, m, n) in enumerate(shapes):
             tg0, ws0, u0 = _inputs(cnt, m, n, K, wd, gd, 100 * i + K)
-            f32 = lambda: [torch.full((cnt,), -1.0, device=DEV) for _ in range(K)]  # noqa: E731
+            f32 = lambda: [torch.full((cnt if per_matrix else cnt * m,), -1.0, device=DEV) for _ in range(K)]  # noqa: E731
             groups.append(mlc.OuterGroup(
                 [w.to(DEV) for w in ws0], tg0.to(DEV), u0.to(DEV),
                 [torch.full((cnt * m, n * bits // 8), 0xAA, dtype=torch.uint8, device=DEV) for _ in range(K)], f32(),
