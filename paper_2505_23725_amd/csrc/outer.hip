@@ -644,13 +644,14 @@ __device__ __forceinline__ void quantize_rows_reg_body(
 
 // Wavefronts per SIMD the register allocation is held to: one more than the compiler reaches on
 // its own where that is a few registers away (these kernels wait on memory with little else to
-// do, so a resident wavefront more is worth more than the registers).
-constexpr int quant_min_waves(int nv, bool outer) {
-  return outer ? (nv <= 1 ? 6 : nv <= 2 ? 4 : nv <= 4 ? 3 : 1) : (nv <= 1 ? 7 : nv <= 2 ? 5 : nv <= 4 ? 3 : 1);
+// do, so a resident wavefront more is worth more than the registers).  Not so the update of ragged rows with four vectors, whose loop
+// over the workers spilt up to 57 of them (2 x 1402 x 4096 and its squares, eight workers of float32, 799 us, now 531).
+constexpr int quant_min_waves(int nv, bool outer, bool ragged) {
+  return outer ? (nv <= 1 ? 6 : nv <= 2 ? 4 : nv <= 4 ? (ragged ? 2 : 3) : 1) : (nv <= 1 ? 7 : nv <= 2 ? 5 : nv <= 4 ? 3 : 1);
 }
 
 template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG>
-__global__ __launch_bounds__(G ? OT_THREADS : 1024, quant_min_waves(NV, OUTER)) void quantize_rows_reg_kernel(
+__global__ __launch_bounds__(G ? OT_THREADS : 1024, quant_min_waves(NV, OUTER, RAG)) void quantize_rows_reg_kernel(
     WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, CodePtrs codes, ScalePtrs scales,
     OffsetPtrs offsets, ResidualPtrs ef, long rows, int n, int K, QuantForm form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
@@ -687,7 +688,7 @@ __host__ __device__ constexpr RegCfg reg_cfg(int idx) {
        : idx == 3 ? RegCfg{2, 256} : RegCfg{4, 256};
 }
 
-// TOP: the last entry of the table above that the groups use.
+// TOP: which entries of the table above the groups use: the first, the first two, those of four vectors (4) or any (5).
 template <typename WT, typename GT, bool RAG, int KC, int TOP>
 __device__ __forceinline__ void quantize_outer_multi_body(const QuantSegTable& tab, int K, QuantForm form, float eta, float mu,
                                                           float inv_k, int nesterov, int write_back) {
@@ -708,6 +709,9 @@ __device__ __forceinline__ void quantize_outer_multi_body(const QuantSegTable& t
   } else if constexpr (TOP == 1) {
     if (sg.cfg == 0) MLC_SEG_BODY(0);
     else MLC_SEG_BODY(1);
+  } else if constexpr (TOP == 4) {
+    if (sg.cfg == 2) MLC_SEG_BODY(2);
+    else MLC_SEG_BODY(4);
   } else {
     switch (sg.cfg) {
       case 0: MLC_SEG_BODY(0); break;
@@ -724,14 +728,17 @@ __device__ __forceinline__ void quantize_outer_multi_body(const QuantSegTable& t
 template <typename WT, typename GT, bool RAG, int KC>
 __global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void quantize_outer_multi_kernel(
     QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
-  quantize_outer_multi_body<WT, GT, RAG, KC, 4>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
+  quantize_outer_multi_body<WT, GT, RAG, KC, 5>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
 }
 
 // Several workers, rows of up to 512 (TOP 0) or 1024 columns: as many wavefronts a SIMD as their registers allow, where the kernel of
 // all lengths has three.  160 / 40 / 40 matrices of 128 x 128, 128 x 256 and 256 x 128, 4 bits, us: two workers 53 to 39, eight 138 to 96, with
 // error feedback 273 to 173; 24 / 6 / 6 of 512 x 512 and 512 x 1024, eight workers 174 to 153, with error feedback 296 to 299.
+// Or, TOP 4, ragged rows of four vectors a thread alone: two wavefronts a SIMD, since for three 60 and more registers of the loop over the
+// workers go to memory (8 / 2 / 2 of 1402 x 1402 and 1402 x 4098, eight workers of float32, 846 to 574; two of bf16 with error
+// feedback 442 to 383; next to rows of two vectors, 606 and 1818 columns, it would be 341 to 378).
 template <typename WT, typename GT, bool RAG, int TOP>
-__global__ __launch_bounds__(OT_THREADS, quant_min_waves(reg_cfg(TOP).nv, true)) void quantize_outer_narrow_kernel(
+__global__ __launch_bounds__(OT_THREADS, quant_min_waves(reg_cfg(TOP).nv, true, RAG)) void quantize_outer_narrow_kernel(
     QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
   quantize_outer_multi_body<WT, GT, RAG, 0, TOP>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
 }
@@ -1880,6 +1887,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
   double bytes = 0.0;
   bool ef_any = false;
   int top = 0;
+  bool four = true;
   for (int i = 0; i < OUTER_MAX_SEG; ++i) {
     QuantSeg& sg = tab.s[i];
     if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
@@ -1902,6 +1910,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     sg.rows_per_range = form.rows_per_range ? (int)gs[i].m : 0;
     sg.cfg = cfg;
     top = max(top, cfg);
+    four = four && reg_cfg(cfg).nv == 4;
     const long rpb = OT_THREADS / reg_cfg(cfg).g;
     sg.blk0 = (unsigned int)blk;
     blk += (unsigned long)((gs[i].rows + rpb - 1) / rpb);
@@ -1920,6 +1929,7 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
     if (K == 1) MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 1);                            \
     else if (top == 0) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 0);                    \
     else if (top == 1) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 1);                    \
+    else if (RAG && four) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, true, 4);                \
     else MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 0);                                   \
   } while (0)
 #define MLC_QM(WT, GT)                                                                            \

@@ -345,7 +345,7 @@ def test_workgroups_of_one_row(n, K):
 # Groups whose ranges are per matrix share their launches and give the bits of a call each: in one launch for all workers or, from
 # nine on, in slices; rows of any length; one matrix and many; next to a group of too long rows; and a group over the first one's
 # memory, which follows it.  The same of groups with ranges per row whose rows are narrow (512 and 1024 columns are the lines), for
-# which several workers have kernels of their own.
+# which several workers have kernels of their own, as they have for long ragged ones.
 @pytest.mark.parametrize("shapes,K,wd,gd,bits,offset,ef,again", [
     ([(3, 64, 128), (1, 128, 200), (2, 40, 2048)], 1, torch.bfloat16, torch.float32, 4, False, True, False),
     ([(2, 50, 1000), (70, 8, 24)], 3, torch.float32, torch.float32, 4, True, True, False),
@@ -357,6 +357,7 @@ def test_workgroups_of_one_row(n, K):
     ([(3, 50, 509), (2, 33, 505)], 3, torch.float32, torch.float32, 8, True, True, None),
     ([(3, 50, 520), (2, 33, 1024)], 4, torch.bfloat16, torch.bfloat16, 2, True, False, None),
     ([(3, 50, 1022), (2, 33, 70)], 2, torch.bfloat16, torch.float32, 4, False, True, None),
+    ([(3, 50, 1026), (2, 33, 2046), (1, 20, 4100), (1, 9, 8190)], 3, torch.bfloat16, torch.float32, 4, False, True, None),
     ([(3, 50, 1032), (2, 33, 64)], 8, torch.float32, torch.float32, 8, False, True, None),
 ])
 def test_groups_that_share_launches(shapes, K, wd, gd, bits, offset, ef, again):
