@@ -289,35 +289,34 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
     *reinterpret_cast<u32x4*>(as + chunk_pos(row + 1, chunk, A_PITCH)) =
         u32x4{halves_hi(r0[0], r0[1]), halves_hi(r0[2], r0[3]), halves_hi(r1[0], r1[1]), halves_hi(r1[2], r1[3])};
   };
-  // This wavefront's part of m m^T, and its values, value(i, J) as they are stored, to both sides of the diagonal of A.  `wait` stands
-  // between the last value and the first store.
-  auto square_part = [&](auto diag, const unsigned char* m, int pitch, int bytes, auto&& value, auto&& wait) {
+  // This wavefront's part of m m^T: in v its values, value(i, J) as they are stored.  Nothing that is called from here may wait for
+  // the other wavefronts, half of which take the other form of the code.
+  u32x4 v[4][2];
+  auto square_part = [&](auto diag, const unsigned char* m, int pitch, int bytes, auto&& value) {
     constexpr bool DG = decltype(diag)::value;
     fresh();
     pr = lane_cols(pitch, rm, ix, gx);
     pc = lane_cols(pitch, rn, ix, gx);
     product_sq(diag, m, pitch, bytes);
     fresh();
-    u32x4 v[4][2];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int J = 0; J < (DG ? i / 2 + 1 : 1); ++J) v[i][J] = value(i, J);
-    wait();
+  };
+  // They go to both sides of the diagonal of A.
+  auto put_part = [&](auto diag) {
+    constexpr bool DG = decltype(diag)::value;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int J = 0; J < (DG ? i / 2 + 1 : 1); ++J) *a_at(i, J) = v[i][J];
-    if (DG) {
-      put_turned(1, 0, v[2][0], v[3][0]);
-    } else {
-      put_turned(0, 0, v[0][0], v[1][0]);
-      put_turned(1, 0, v[2][0], v[3][0]);
-    }
+    if (!DG) put_turned(0, 0, v[0][0], v[1][0]);
+    put_turned(1, 0, v[2][0], v[3][0]);
   };
-  auto square = [&](const unsigned char* m, int pitch, int bytes, auto&& value, auto&& wait) {
-    if (dg) square_part(std::true_type{}, m, pitch, bytes, value, wait);
-    else square_part(std::false_type{}, m, pitch, bytes, value, wait);
+  auto either = [&](auto&& f) {
+    if (dg) f(std::true_type{});
+    else f(std::false_type{});
   };
 
   for (int it = 0; it < g.iters; ++it) {
@@ -326,7 +325,10 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
     // ---- A = alpha_a X X^T ---------------------------------------------------------------
     {
       auto value = [&](int i, int J) { return pack8(alpha_a * acc_read(sq[i][2 * J]), alpha_a * acc_read(sq[i][2 * J + 1])); };
-      square(xs, X_PITCH, 2 * L, value, [] {});                // L is a multiple of 128
+      either([&](auto diag) {
+        square_part(diag, xs, X_PITCH, 2 * L, value);          // L is a multiple of 128
+        put_part(diag);
+      });
     }
     __syncthreads();
 
@@ -334,21 +336,23 @@ __device__ __forceinline__ void ns_chain_body(const ChainArgs& g, long mat) {
     {
       auto value = [&](int i, int J) {
         const u32x4 av = *a_at(i, J);
-        f32x4 v[2] = {acc_read(sq[i][2 * J]), acc_read(sq[i][2 * J + 1])};
+        f32x4 b[2] = {acc_read(sq[i][2 * J]), acc_read(sq[i][2 * J + 1])};
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float ae = (e & 1) ? bf16hi(av[e / 2]) : bf16lo(av[e / 2]);
-          v[e / 4][e % 4] = g.c * v[e / 4][e % 4] + g.b * ae;
+          b[e / 4][e % 4] = g.c * b[e / 4][e % 4] + g.b * ae;
         }
         if (J == i / 2 && dg) {                                // the diagonal crosses this tile
           const int d = 8 * (ix >> 2) + 4 * (i & 1) + (ix & 3) - 8 * gx;
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            if (e == d) v[e / 4][e % 4] += g.a;
+            if (e == d) b[e / 4][e % 4] += g.a;
         }
-        return pack8(v[0], v[1]);
+        return pack8(b[0], b[1]);
       };
-      square(as, A_PITCH, A_PITCH, value, [] { __syncthreads(); });      // every wavefront is done reading A
+      either([&](auto diag) { square_part(diag, as, A_PITCH, A_PITCH, value); });
+      __syncthreads();            // every wavefront is done reading A
+      either(put_part);
     }
     __syncthreads();
 

@@ -181,6 +181,21 @@ def test_no_copy_of_an_accumulator_follows_its_mfma(tmp_path):
         assert not faults(ins, name not in SMALL), (name, faults(ins, name not in SMALL)[:5])
 
 
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+def test_all_wavefronts_of_a_chain_meet_at_the_same_barriers(tmp_path):
+    """Every barrier in the source stands once in the code of each form of the chain: none lies in a part that is
+    compiled for some of a workgroup's wavefronts and again for others."""
+    source = open(os.path.join(build.CSRC, "ns_chain_small.hip")).read()
+    body = source[source.index("ns_chain_body(const ChainArgs"):source.index("ns_chain_small_kernel(ChainArgs")]
+    barriers = body.count("__syncthreads();")
+    assert barriers
+    mlc.library()
+    code = listing(str(tmp_path))
+    for name in CHAINS:
+        forms = 3 if "multi" in name else 1
+        assert sum(i.op == "s_barrier" for i in code[name]) == forms * barriers, name
+
+
 MFMA = "v_mfma_f32_16x16x32_bf16 a[0:3], v[8:11], v[12:15], a[0:3]"
 LOAD = "buffer_load_dwordx4 v1, s[8:11], s12 offen lds"
 GOOD = [
