@@ -459,7 +459,7 @@ class AdamWHParams:
 def muloco_adamw_step(tensors: Sequence[tuple], hp: AdamWHParams, stream=None) -> None:
     """tensors: (param, grad, exp_avg, exp_avg_sq) tuples of equally sized device tensors."""
     from . import _marshal
-    ready = _marshal.adamw_groups(tensors) if tensors else None
+    ready = _marshal.adamw_groups(tensors) if len(tensors) else None
     if ready is not None:
         arr = (_AdamWGroup * len(tensors)).from_buffer_copy(ready)
     else:
