@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass, field
 from typing import List, Optional, Sequence
 
@@ -16,6 +17,7 @@ KERNEL_FAMILIES = ["ns_gemm", "momentum", "norm", "update", "outer", "quantize",
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmuloco.so")
 _lib = None
+_native = None          # csrc/marshal.cpp's module, once it was asked for; False: left out
 
 
 class MulocoError(RuntimeError):
@@ -139,11 +141,29 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}; the library takes float32 or bfloat16")
 
 
+def _marshal():
+    """The native readers of tensors (csrc/marshal.cpp), or None where they were not built or not for this torch, whose
+    structures they are compiled for.  The checks in Python then do the same work: no more than host time depends on them."""
+    global _native
+    if _native is None:
+        try:
+            from . import _marshal as native
+            built_for = getattr(native, "torch_version", None)
+            why = None if built_for == torch.__version__ else f"it was built for torch {built_for}"
+        except ImportError as e:
+            why = str(e)
+        if why:
+            warnings.warn(f"_marshal.so is left out ({why}): calls on many tensors take longer on the host; "
+                          "build it with `python -m paper_2505_23725_amd.build`", RuntimeWarning, stacklevel=2)
+        _native = False if why else native
+    return _native or None
+
+
 def _pointer(t):
     """Address of a tensor that is plainly in order (csrc/marshal.cpp), else None."""
     global _pointer
-    from . import _marshal              # built with the library; there is no fallback
-    _pointer = _marshal.pointer
+    native = _marshal()
+    _pointer = native.pointer if native else lambda t: None
     return _pointer(t)
 
 
@@ -458,8 +478,8 @@ class AdamWHParams:
 
 def muloco_adamw_step(tensors: Sequence[tuple], hp: AdamWHParams, stream=None) -> None:
     """tensors: (param, grad, exp_avg, exp_avg_sq) tuples of equally sized device tensors."""
-    from . import _marshal
-    ready = _marshal.adamw_groups(tensors) if len(tensors) else None
+    native = _marshal()
+    ready = native.adamw_groups(tensors) if native and len(tensors) else None
     if ready is not None:
         arr = (_AdamWGroup * len(tensors)).from_buffer_copy(ready)
     else:

@@ -42,8 +42,8 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
-    build_marshal(verbose)
     build_microbench(verbose)
+    build_marshal(verbose)              # last: the binding does without it
     return LIB_PATH
 
 
@@ -55,6 +55,7 @@ def build_marshal(verbose: bool = True) -> str:
     from torch.utils import cpp_extension
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DMLC_TORCH_VERSION="{torch.__version__}"',
            *[x for i in cpp_extension.include_paths() for x in ("-isystem", i)], "-I", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "marshal.cpp"), "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL_PATH]
     if verbose:

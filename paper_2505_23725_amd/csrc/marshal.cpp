@@ -89,4 +89,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal() {
+  PyObject* m = PyModule_Create(&module);
+  // the torch whose structures this was compiled for; the binding asks for the same
+  if (m && PyModule_AddStringConstant(m, "torch_version", MLC_TORCH_VERSION) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -55,3 +55,19 @@ def test_adamw_takes_the_sequences_it_took(wrap):
     mlc.muloco_adamw_step(wrap(b), hp)
     assert all(torch.equal(x, y) for s, t in zip(a, b) for x, y in zip(s, t))
     mlc.muloco_adamw_step([], hp)
+
+
+def test_calls_are_the_same_without_the_native_part(monkeypatch):
+    hp = mlc.AdamWHParams(lr=0.1, weight_decay=0.1)
+    x = torch.randn(3, 40, 72, generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
+
+    def both():
+        four, out = [_four(77), _four(4096)], torch.empty_like(x)
+        mlc.muloco_adamw_step(four, hp)
+        mlc.newton_schulz_static_scratch(x, out)
+        return [t for f in four for t in f] + [out]
+    assert binding._marshal() is not None
+    with_native = both()
+    monkeypatch.setattr(binding, "_native", False)
+    monkeypatch.setattr(binding, "_pointer", lambda t: None)
+    assert all(torch.equal(a, b) for a, b in zip(with_native, both()))
