@@ -481,6 +481,9 @@ def muloco_adamw_step(tensors: Sequence[tuple], hp: AdamWHParams, stream=None) -
     native = _marshal()
     ready = native.adamw_groups(tensors) if native and len(tensors) else None
     if ready is not None:
+        if len(ready) != len(tensors) * C.sizeof(_AdamWGroup):      # from_buffer_copy would take a longer one
+            raise RuntimeError("_marshal.so was built from another muloco.h; build it with "
+                               "`python -m paper_2505_23725_amd.build`")
         arr = (_AdamWGroup * len(tensors)).from_buffer_copy(ready)
     else:
         arr = (_AdamWGroup * max(1, len(tensors)))()

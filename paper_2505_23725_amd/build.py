@@ -57,7 +57,7 @@ def build_marshal(verbose: bool = True) -> str:
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            f'-DMLC_TORCH_VERSION="{torch.__version__}"',
            *[x for i in cpp_extension.include_paths() for x in ("-isystem", i)], "-I", sysconfig.get_paths()["include"],
-           os.path.join(CSRC, "marshal.cpp"), "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL_PATH]
+           "-I", os.path.join(HERE, "..", "include"), os.path.join(CSRC, "marshal.cpp"), "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL_PATH]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)

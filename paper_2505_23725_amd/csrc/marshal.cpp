@@ -2,9 +2,10 @@
 // and reading type, device, layout and address of each from Python takes longer than the kernels of a small step:
 // 3.4 us for the four tensors of an AdamW parameter.
 //
-// Only what is plainly in order is answered here: a torch.Tensor or Parameter, contiguous, on the current device, of a type that
-// the library takes.  For anything else the answer is None, and the caller's own checks say what is wrong with it (or, for a
-// subclass, ask its own methods).  Nothing is kept from one call to the next.
+// Only what is plainly in order is answered here: a torch.Tensor or Parameter, contiguous, on the current device (and, for
+// adamw_groups, of a type that the library takes; who asks for a single address looks at the type itself).  For anything else the
+// answer is None, and the caller's own checks say what is wrong with it (or, for a subclass, ask its own methods).  Nothing is
+// kept from one call to the next.
 #include <torch/csrc/python_headers.h>
 
 #include <ATen/core/Tensor.h>
@@ -15,6 +16,8 @@
 
 #include <cstdint>
 #include <cstring>
+
+#include "muloco.h"
 
 namespace {
 
@@ -28,10 +31,8 @@ const at::Tensor* plain(PyObject* o, int& device) {
   return t.get_device() == device ? &t : nullptr;
 }
 
-uint64_t address(const at::Tensor& t) { return (uint64_t)(uintptr_t)t.data_ptr(); }
-
 int type_code(const at::Tensor& t) {
-  return t.scalar_type() == at::kFloat ? 0 : t.scalar_type() == at::kBFloat16 ? 1 : -1;
+  return t.scalar_type() == at::kFloat ? MLC_F32 : t.scalar_type() == at::kBFloat16 ? MLC_BF16 : -1;
 }
 
 // pointer(tensor) -> address or None
@@ -40,19 +41,9 @@ PyObject* pointer(PyObject*, PyObject* arg) {
   int device = -1;
   const at::Tensor* t = plain(arg, device);
   if (!t) Py_RETURN_NONE;
-  return PyLong_FromUnsignedLongLong(address(*t));
+  return PyLong_FromUnsignedLongLong((unsigned long long)(uintptr_t)t->data_ptr());
   END_HANDLE_TH_ERRORS
 }
-
-// The C ABI's mlc_adamw_group.
-struct AdamWGroup {
-  int64_t count;
-  uint64_t param;
-  int32_t param_dtype, pad0;
-  uint64_t grad;
-  int32_t grad_dtype, pad1;
-  uint64_t exp_avg, exp_avg_sq;
-};
 
 // adamw_groups([(param, grad, exp_avg, exp_avg_sq), ...]) -> their mlc_adamw_group entries as bytes, or None
 PyObject* adamw_groups(PyObject*, PyObject* arg) {
@@ -60,11 +51,11 @@ PyObject* adamw_groups(PyObject*, PyObject* arg) {
   if (!PyList_CheckExact(arg)) Py_RETURN_NONE;
   const Py_ssize_t n = PyList_GET_SIZE(arg);
   int device = -1;
-  PyObject* out = PyBytes_FromStringAndSize(nullptr, n * (Py_ssize_t)sizeof(AdamWGroup));
+  PyObject* out = PyBytes_FromStringAndSize(nullptr, n * (Py_ssize_t)sizeof(mlc_adamw_group));
   if (!out) return nullptr;
   THPObjectPtr held(out);
   char* at = PyBytes_AS_STRING(out);
-  for (Py_ssize_t i = 0; i < n; ++i, at += sizeof(AdamWGroup)) {
+  for (Py_ssize_t i = 0; i < n; ++i, at += sizeof(mlc_adamw_group)) {
     PyObject* four = PyList_GET_ITEM(arg, i);
     if (!PyTuple_CheckExact(four) || PyTuple_GET_SIZE(four) != 4) Py_RETURN_NONE;
     const at::Tensor* t[4];
@@ -72,8 +63,17 @@ PyObject* adamw_groups(PyObject*, PyObject* arg) {
       t[k] = plain(PyTuple_GET_ITEM(four, k), device);
       if (!t[k] || t[k]->numel() != t[0]->numel()) Py_RETURN_NONE;
     }
-    AdamWGroup g{t[0]->numel(), address(*t[0]), type_code(*t[0]), 0, address(*t[1]), type_code(*t[1]), 0, address(*t[2]), address(*t[3])};
-    if (g.param_dtype < 0 || g.grad_dtype < 0 || type_code(*t[2]) != 0 || type_code(*t[3]) != 0) Py_RETURN_NONE;
+    const int param = type_code(*t[0]), grad = type_code(*t[1]);
+    if (param < 0 || grad < 0 || type_code(*t[2]) != MLC_F32 || type_code(*t[3]) != MLC_F32) Py_RETURN_NONE;
+    mlc_adamw_group g;
+    std::memset(&g, 0, sizeof g);
+    g.count = t[0]->numel();
+    g.param = t[0]->data_ptr();
+    g.param_dtype = param;
+    g.grad = t[1]->data_ptr();
+    g.grad_dtype = grad;
+    g.exp_avg = (float*)t[2]->data_ptr();
+    g.exp_avg_sq = (float*)t[3]->data_ptr();
     std::memcpy(at, &g, sizeof g);
   }
   return held.release();

@@ -59,3 +59,20 @@ def test_native_part_is_built_for_this_torch():
     from paper_2505_23725_amd import _marshal, binding
     assert _marshal.torch_version == torch.__version__
     assert binding._marshal() is _marshal
+
+
+def test_tables_of_another_layout_are_refused(monkeypatch):
+    """A table whose entries are longer than the binding's is from another header: none of it reaches the library."""
+    from paper_2505_23725_amd import binding
+    size = binding.C.sizeof(binding._AdamWGroup)
+    monkeypatch.setattr(binding, "_native", type("Longer", (), {"adamw_groups": staticmethod(lambda t: bytes(len(t) * (size + 8)))}))
+    with pytest.raises(RuntimeError, match="another muloco.h"):
+        mlc.muloco_adamw_step([(torch.zeros(8),) * 4] * 2, mlc.AdamWHParams(lr=0.1))
+
+
+def test_native_part_fills_the_header_s_structure():
+    """The entry is the header's own type, which the binding's is checked against (test_c_header.py), and no copy of it."""
+    source = open(os.path.join(ROOT, "paper_2505_23725_amd", "csrc", "marshal.cpp")).read()
+    assert '#include "muloco.h"' in source and "struct " not in source
+    for field in ("count", "param", "param_dtype", "grad", "grad_dtype", "exp_avg", "exp_avg_sq"):
+        assert f"g.{field} = " in source
