@@ -260,6 +260,12 @@ int muloco_quantize_delta(const mlc_outer_group* groups, int n_groups,
  * pointers to [count] floats.  workspace: device memory, 16-byte aligned, at least
  * muloco_topk_workspace_bytes(groups, n_groups, hp->K) bytes; its contents need not be
  * initialised and are not needed afterwards.
+ *
+ * That many bytes hold the states of the largest group, and groups then follow one another.
+ * More of them save time: two groups that follow each other in the list, with equal m * n and
+ * types, at most 65535 matrices together and no memory in common, share their kernel launches
+ * (1.02 to 1.6 times as fast) where the work space holds the states of both, which is what this
+ * query gives for one group with count = the sum of theirs.  The results are the same bits.
  */
 size_t muloco_topk_workspace_bytes(const mlc_outer_group* groups, int n_groups, int K);
 int muloco_topk_outer_step(const mlc_outer_group* groups, int n_groups, const mlc_outer_hparams* hp,

@@ -447,13 +447,16 @@ def muloco_quantize_delta(groups: Sequence[OuterGroup], hp: OuterHParams, stream
 
 
 def muloco_topk_workspace_bytes(groups: Sequence[OuterGroup], K: int) -> int:
+    """The least work space.  Neighbours of equally large matrices (d x f and f x d) share launches in one that holds the
+    states of both: what this gives for one group of as many matrices as the two have."""
     return int(library().muloco_topk_workspace_bytes(_outer_array(groups), len(groups), int(K)))
 
 
 def muloco_topk_outer_step(groups: Sequence[OuterGroup], hp: OuterHParams, fraction: float,
                            workspace: torch.Tensor, stream=None) -> None:
     """Outer step on top-k sparsified pseudogradients; group.scales (K tensors of `count`
-    floats), if given, receive the thresholds."""
+    floats), if given, receive the thresholds.  A work space larger than the least one can
+    save launches (muloco_topk_workspace_bytes)."""
     for g in groups:
         if len(g.worker_params) != hp.K:
             raise ValueError("every group needs K worker tensors")

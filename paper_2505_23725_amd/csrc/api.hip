@@ -824,7 +824,8 @@ int muloco_topk_outer_step(const mlc_outer_group* groups, int n_groups, const ml
   for (int i = 0; i < n_groups; ++i) {
     const mlc_outer_group& g = groups[i];
     // Two groups that follow each other share every launch where their matrices are equally large (d x f and f x d: only
-    // the number of values counts) and the work space holds the states of both: the 4 to 8 launches of a group cost 2.7 us each
+    // the number of values counts) and the work space holds the states of both (muloco.h says how a caller gets one that does; the
+    // query stays at the least, so that sizes kept from before serve as they did): the 4 to 8 launches of a group cost 2.7 us each
     // and leave the chip partly idle at either end, a single large matrix all the time.  Steps of 4 L matrices d x d, L d x f, L f x d,
     // us apart and together: d 256, f 448, L 2, two workers 91 and 65; 288, 981, 4, four 178 and 137; 640, 2491, 9, two 430 and 388;
     // 2048, 8192, 6, one 2514 and 2462; 4096, 8192, 1, four, no error feedback 1761 and 1428.

@@ -455,6 +455,7 @@ def test_topk_long_lists_do_not_hold_a_call_up():
     (2, 2, 2048, 4096, 2, torch.bfloat16, torch.float32, True, True),
     (2, 2, 1449, 1451, 8, torch.bfloat16, torch.float32, False, True),
     (40, 40, 313, 315, 3, torch.float32, torch.float32, True, True),
+    (3, 3, 1811, 1813, 2, torch.bfloat16, torch.float32, True, True),           # in turn, element by element
     (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, True, "shared memory"),
     (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, True, "states"),
     (2, 2, 64, 128, 2, torch.bfloat16, torch.float32, False, "size"),
@@ -490,3 +491,30 @@ def test_topk_groups_of_equal_matrices_share_launches(c0, c1, m, n, K, wd, gd, e
         for k in range(K):
             assert torch.equal(got.scales[k], want.scales[k]) and torch.equal(got.worker_params[k], want.worker_params[k])
             assert not ef or torch.equal(got.residuals[k], want.residuals[k])
+
+
+def test_topk_pair_shares_launches_in_a_work_space_for_both():
+    """Two groups and nothing else: the query's bytes serve them one after the other, those of one group with the matrices of
+    both together, the same bits."""
+    K, first = 2, _misled(2, 64, 128, 2, torch.bfloat16, torch.float32, True, lambda k, i: False)
+    second = _misled(3, 128, 64, K, torch.bfloat16, torch.float32, True, lambda k, i: False)
+    whole = mlc.OuterGroup([torch.cat([a.flatten(1), b.flatten(1)]).view(5, 64, 128) for a, b in
+                            zip(first.worker_params, second.worker_params)], torch.empty(5, 64, 128, device=DEV), None)
+    least = mlc.muloco_topk_workspace_bytes([first, second], K)
+    both = mlc.muloco_topk_workspace_bytes([whole], K)
+    assert both == least // 3 * 5
+    hp = mlc.OuterHParams(K=K, eta_out=0.9, mu=0.8, error_feedback=True, ef_beta=0.9)
+    done = []
+    for size, launches in ((least, 2), (both - 1, 2), (both, 1)):
+        groups = [_clone(first), _clone(second)]
+        mlc.muloco_timing_enable(True)
+        try:
+            mlc.muloco_timing_read()
+            mlc.muloco_topk_outer_step(groups, hp, 0.05, torch.full((size,), 0xCD, dtype=torch.uint8, device=DEV))
+            torch.cuda.synchronize()
+            assert mlc.muloco_timing_read()["topk"]["launches"] == launches
+        finally:
+            mlc.muloco_timing_enable(False)
+        done.append([t for g in groups for t in [g.global_param, g.outer_momentum, *g.worker_params, *g.scales, *g.residuals]])
+    for other in done[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(done[0], other))
