@@ -475,15 +475,22 @@ static bool any_overlap(Span* s, int n) {
   return false;
 }
 
-// Do any two of what the groups write (weights, momenta) share memory?
+// Do any two of what the groups write (weights, momenta) share memory, or a group's gradients and another's momenta, of which one
+// momentum pass would read and write at the same time?
 static bool inner_overlap(const mlc_inner_group* g, int n) {
   Span s[2 * MAX_NS_JOBS];
+  auto elems = [&](int i) { return (size_t)g[i].count * g[i].m * g[i].n; };
   for (int i = 0; i < n; ++i) {
-    const size_t elems = (size_t)g[i].count * g[i].m * g[i].n;
-    s[2 * i] = span(g[i].param, elems * elem_size(g[i].param_dtype));
-    s[2 * i + 1] = span(g[i].momentum, elems * 4);
+    s[2 * i] = span(g[i].param, elems(i) * elem_size(g[i].param_dtype));
+    s[2 * i + 1] = span(g[i].momentum, elems(i) * 4);
   }
-  return any_overlap(s, 2 * n);
+  if (any_overlap(s, 2 * n)) return true;
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j) {
+      const Span grad = span(g[i].grad, elems(i) * elem_size(g[i].grad_dtype)), mom = span(g[j].momentum, elems(j) * 4);
+      if (i != j && grad.lo < mom.hi && mom.lo < grad.hi) return true;
+    }
+  return false;
 }
 
 int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muon_hparams* hp,
@@ -499,8 +506,8 @@ int muloco_inner_step(const mlc_inner_group* groups, int n_groups, const mlc_muo
   const float decay_factor = 1.0f - hp->eta * hp->weight_decay;
   // With room for every group at once the groups go through Newton-Schulz side by side, so that
   // their products share launches; otherwise one group after the other, in chunks that fit.  Both give
-  // the same bits.  Groups that write the same memory also go one after the other: side by side their
-  // momentum passes, last products (which write bf16 weights) or updates would be in one launch.
+  // the same bits.  Groups that write the same memory, or read what another's momentum pass writes, also go one after the other: side
+  // by side their momentum passes, last products (which write bf16 weights) or updates would be in one launch.
   const size_t all = (n_groups >= 2 && n_groups <= MAX_NS_JOBS) ? inner_workspace_all(groups, n_groups) : 0;
   if (all && workspace_bytes >= all && !inner_overlap(groups, n_groups)) {
     NsJob jobs[MAX_NS_JOBS];

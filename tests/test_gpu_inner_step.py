@@ -380,6 +380,34 @@ def test_groups_that_write_the_same_memory_go_one_after_the_other(shapes, tile, 
         assert torch.equal(a.param.view(torch.int16), b.param.view(torch.int16)) and torch.equal(a.momentum, b.momentum)
 
 
+# A group whose gradients are another's momentum, before or after it: rows of several kinds, which share a momentum pass
+@pytest.mark.parametrize("reader,writer", [(0, 1), (1, 0), (2, 1)])
+def test_groups_that_read_another_s_momentum_go_one_after_the_other(reader, writer):
+    """The bits and the momentum passes of one call per group."""
+    hp = mlc.MuonHParams(eta=0.05, weight_decay=1e-3, beta=0.9)
+    shapes = [(2, 256, 384), (2, 384, 256), (4, 128, 384)]
+
+    def groups():
+        out = [mlc.InnerGroup(*[S.normal(s, std, 37, 10 * i + j).to(DEV) for j, std in enumerate((S.PARAM_STD, S.GRAD_STD, S.GRAD_STD))],
+                              0.5) for i, s in enumerate(shapes)]
+        out[reader].grad = out[writer].momentum.view(shapes[reader])
+        return out
+
+    def run(gs):
+        ws = torch.empty(mlc.muloco_inner_workspace_bytes(gs), dtype=torch.uint8, device=DEV)
+        mlc.muloco_timing_enable(True)
+        mlc.muloco_timing_read()
+        mlc.muloco_inner_step(gs, hp, ws)
+        torch.cuda.synchronize()
+        n = mlc.muloco_timing_read()["momentum"]["launches"]
+        mlc.muloco_timing_enable(False)
+        return n
+    together, apart = groups(), groups()
+    assert run(together) == sum(run([g]) for g in apart) == len(shapes)
+    for a, b in zip(together, apart):
+        assert torch.equal(a.param, b.param) and torch.equal(a.momentum, b.momentum)
+
+
 # Gram products of two depths, both in 256 x 256 tiles: workgroups that are a tile short in the deeper one
 # take several of the shallower one's; few and many tiles of either, and more products than share a launch
 DEPTHS = [([(16, 1024, 2816), (32, 1024, 1024)], 15), ([(30, 512, 3072), (30, 3072, 512), (140, 512, 512)], 15),
