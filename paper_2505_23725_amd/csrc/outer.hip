@@ -851,13 +851,18 @@ constexpr int TOPK_SAMPLE_PER = 2;                 // runs of 8 values that a th
 
 __device__ __forceinline__ unsigned int magnitude_key(float v) { return __float_as_uint(fabsf(v)); }
 
-// Pointers of the groups of a launch, one or two of equally large matrices, which are numbered through: those of the second
+// Pointers of the G groups of a launch, one or two of equally large matrices, which are numbered through: those of the second
 // group are the addresses that matrix 0 would have, so that matrix b's are found alike in both.
+//
+// A group alone has kernels without the choice: its pointers are then requested with the other arguments, not in a second trip to
+// them, which every workgroup waits for (us with the choice and without, one worker and 48 of 32 x 32 and 12 of 32 x 34 45.4 and 43.8;
+// four and 4 of 128 x 128 and one of 128 x 232 51.1 and 46.8; four and 800 of 112 x 112 253 and 244).
 struct TopkPtrs { WorkerPtrs w; ResidualPtrs ef; ScalePtrs thresholds; void* theta_g; float* u; };
+template <int G>
 struct TopkArgs {
-  TopkPtrs g[2];
+  TopkPtrs g[G];
   int split;                         // first matrix of the second group
-  __device__ __forceinline__ const TopkPtrs& of(long b) const { return g[b >= split ? 1 : 0]; }
+  __device__ __forceinline__ const TopkPtrs& of(long b) const { return g[G > 1 && b >= split ? 1 : 0]; }
 };
 
 __global__ void topk_init_kernel(TopkState* st, unsigned int kcount) {
@@ -894,9 +899,9 @@ __device__ __forceinline__ unsigned int sample_bin(unsigned int key) {
 // columns again and again): the keys from five standard deviations of a sample's rank below
 // the rank sought to as many above, at the resolution of the bins.  Where so many magnitudes tie that they fill all of
 // that (replicas that did not move), the interval is one key and the pass over the window settles it.
-template <typename WT, typename GT, bool VEC>
+template <typename WT, typename GT, bool VEC, int G>
 __global__ __launch_bounds__(TOPK_SAMPLE_THREADS) void topk_sample_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, unsigned int kcount, float ef_beta) {
+    TopkArgs<G> args, TopkState* st, long elems, int count, unsigned int kcount, float ef_beta) {
   constexpr int WAVES = TOPK_SAMPLE_THREADS / 64, RUNS = TOPK_SAMPLE_THREADS * TOPK_SAMPLE_PER;
   static_assert(TOPK_BINS == 2 * TOPK_SAMPLE_THREADS, "a thread owns two bins");
   __shared__ unsigned int hist[TOPK_BINS];
@@ -1072,9 +1077,9 @@ __device__ __forceinline__ void topk_narrow(TopkState& s, int nbins, int shift, 
 // into the window, so one histogram a workgroup takes them; 16 wavefronts share it, since its
 // bins leave as one atomic each at the end (4 wavefronts: 0 to 3 % slower).  14 bytes an element at 4.8 TB/s.
 // TURN: the grid's first dimension is the workers, otherwise the pieces of a matrix (topk_turn).
-template <typename WT, typename GT, bool VEC, bool TURN>
+template <typename WT, typename GT, bool VEC, bool TURN, int G>
 __global__ __launch_bounds__(TOPK_WINDOW_THREADS) void topk_window_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, float ef_beta) {
+    TopkArgs<G> args, TopkState* st, long elems, int count, float ef_beta) {
   __shared__ unsigned int lh[TOPK_BINS];
   const long b = TURN ? blockIdx.z : blockIdx.y;
   const int k = TURN ? blockIdx.x : blockIdx.z, blk = TURN ? blockIdx.y : blockIdx.x, nblk = TURN ? gridDim.y : gridDim.x;
@@ -1291,9 +1296,9 @@ __device__ __forceinline__ void topk_count(const WorkerPtrs& w, const GT* __rest
   if (pick && last_of_state(s, (unsigned int)nblk)) topk_narrow<PASS_LAST>(s, nbins, shift, nullptr);
 }
 
-template <typename WT, typename GT, bool VEC, bool FIRST>
+template <typename WT, typename GT, bool VEC, bool FIRST, int G>
 __global__ __launch_bounds__(OT_THREADS) void topk_hist_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, float ef_beta, int pick) {
+    TopkArgs<G> args, TopkState* st, long elems, int count, float ef_beta, int pick) {
   __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];     // one histogram per wavefront
   const long b = blockIdx.y;
   const int k = blockIdx.z;
@@ -1513,9 +1518,9 @@ __device__ __forceinline__ void topk_settle(
 
 // What the window left: a pass over the matrices left open, except for workers whose interval is one key already, and, in the
 // first of these launches, the thresholds of the others.
-template <typename WT, typename GT, bool VEC>
+template <typename WT, typename GT, bool VEC, int G>
 __global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, int K, float ef_beta, int most, int first) {
+    TopkArgs<G> args, TopkState* st, long elems, int count, int K, float ef_beta, int most, int first) {
   __shared__ unsigned int lh[OT_THREADS / 64][TOPK_BINS];
   const bool none_open = topk_all_early(st);
   if (first)
@@ -1535,9 +1540,9 @@ __global__ __launch_bounds__(OT_THREADS) void topk_late_kernel(
 }
 
 // The update behind the pass over the window.
-template <typename WT, typename GT, bool VEC>
+template <typename WT, typename GT, bool VEC, int G>
 __global__ __launch_bounds__(OT_THREADS) void topk_early_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+    TopkArgs<G> args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
   const TopkPtrs& g = args.of(blockIdx.y);
   if (topk_early(st, blockIdx.y, count, K))
     topk_update<WT, GT, VEC, true>(g.w, (GT*)g.theta_g, g.u, g.ef, g.thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
@@ -1545,9 +1550,9 @@ __global__ __launch_bounds__(OT_THREADS) void topk_early_kernel(
 }
 
 // What is left of the matrices that the window settled, and the update of those that it left open.
-template <typename WT, typename GT, bool VEC>
+template <typename WT, typename GT, bool VEC, int G>
 __global__ __launch_bounds__(OT_THREADS) void topk_finish_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
+    TopkArgs<G> args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back,
     int most) {
   const bool none_open = topk_all_early(st);
   const int parts = max(min(TOPK_SETTLE_GRID / count, TOPK_SETTLE_MOST), 1);
@@ -1567,9 +1572,9 @@ __global__ __launch_bounds__(OT_THREADS) void topk_finish_kernel(
 }
 
 // The update of groups that went through the three passes from the start.
-template <typename WT, typename GT, bool VEC>
+template <typename WT, typename GT, bool VEC, int G>
 __global__ __launch_bounds__(OT_THREADS) void topk_outer_kernel(
-    TopkArgs args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
+    TopkArgs<G> args, TopkState* st, long elems, int count, int K, float eta, float mu, float inv_k, int nesterov, int write_back) {
   const TopkPtrs& g = args.of(blockIdx.y);
   topk_update<WT, GT, VEC, false>(g.w, (GT*)g.theta_g, g.u, g.ef, g.thresholds, st, elems, count, K, eta, mu, inv_k, nesterov,
                                   write_back, blockIdx.y, blockIdx.x, gridDim.x);
@@ -1974,17 +1979,17 @@ static bool topk_window(long elems, int64_t count, int K, int blocks, bool feedb
   return 0.77 * values + 0.0048 * workgroups > 10.0 + 0.7 * K + 0.35 * K / count + 0.11 * states;
 }
 
-int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, int global_dtype, int64_t elems_, int K,
-                      unsigned int kcount, float ef_beta, float eta_out, float mu, int nesterov, int write_back,
-                      void* workspace, hipStream_t stream) {
-  const long elems = elems_;
-  const int64_t first = groups[0].count, count = first + (n_groups > 1 ? groups[1].count : 0);
-  TopkArgs args;
+// With groups of one or two of them (G) in every launch.
+template <int G>
+static int launch_topk(const TopkGroup* groups, int worker_dtype, int global_dtype, long elems, int K, unsigned int kcount,
+                       float ef_beta, float eta_out, float mu, int nesterov, int write_back, void* workspace, hipStream_t stream) {
+  const int64_t first = groups[0].count, count = first + (G > 1 ? groups[G - 1].count : 0);
+  TopkArgs<G> args;
   args.split = (int)first;
-  for (int i = 0; i < 2; ++i) {
-    const TopkGroup& g = groups[i < n_groups ? i : 0];
+  for (int i = 0; i < G; ++i) {
+    const TopkGroup& g = groups[i];
     TopkPtrs& p = args.g[i];
-    const long back = i && i < n_groups ? (long)first : 0;         // matrices before the group
+    const long back = i ? (long)first : 0;         // matrices before the group
     auto at = [&](const void* x, double size) { return x ? (uintptr_t)x - (uintptr_t)back * (uintptr_t)(elems * (long)size) : 0; };
     for (int k = 0; k < MLC_MAX_WORKERS; ++k) {
       p.w.p[k] = (void*)at(g.w.p[k], esize(worker_dtype));
@@ -2014,18 +2019,18 @@ int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, i
   LaunchScope scope(MLC_KERNEL_TOPK, stream, 0.0, (double)count * elems * (passes + last));
   const float inv_k = 1.0f / (float)K;
 #define MLC_UPDATE(KERNEL, WT, GT, V, GRID, ...)                                                    \
-  hipLaunchKernelGGL((KERNEL<WT, GT, V>), GRID, dim3(OT_THREADS), 0, stream, args, st, elems, \
+  hipLaunchKernelGGL((KERNEL<WT, GT, V, G>), GRID, dim3(OT_THREADS), 0, stream, args, st, elems, \
                      (int)count, K, eta_out, mu, inv_k, nesterov, write_back, ##__VA_ARGS__)
   const dim3 all(full_grid, (unsigned)count);
   if (window) {
 #define MLC_SAMPLE(WT, GT, V)                                                                     \
-  hipLaunchKernelGGL((topk_sample_kernel<WT, GT, V>), dim3((unsigned)count, K), dim3(TOPK_SAMPLE_THREADS), 0, \
+  hipLaunchKernelGGL((topk_sample_kernel<WT, GT, V, G>), dim3((unsigned)count, K), dim3(TOPK_SAMPLE_THREADS), 0, \
                      stream, args, st, elems, (int)count, kcount, ef_beta)
 #define MLC_WINDOW(WT, GT, V, T, ...)                                                             \
-  hipLaunchKernelGGL((topk_window_kernel<WT, GT, V, T>), dim3(__VA_ARGS__), dim3(TOPK_WINDOW_THREADS), 0, stream, args, \
+  hipLaunchKernelGGL((topk_window_kernel<WT, GT, V, T, G>), dim3(__VA_ARGS__), dim3(TOPK_WINDOW_THREADS), 0, stream, args, \
                      st, elems, (int)count, ef_beta)
 #define MLC_LATE(WT, GT, V)                                                                       \
-  hipLaunchKernelGGL((topk_late_kernel<WT, GT, V>), dim3(TOPK_LATE_GRID), dim3(OT_THREADS), 0, stream, args,  \
+  hipLaunchKernelGGL((topk_late_kernel<WT, GT, V, G>), dim3(TOPK_LATE_GRID), dim3(OT_THREADS), 0, stream, args,  \
                      st, elems, (int)count, K, ef_beta, late_most, (int)(pass == 0))
 #define MLC_WINDOWED(WT, GT, V)                                                                   \
   do {                                                                                            \
@@ -2048,7 +2053,7 @@ int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, i
     hipLaunchKernelGGL(topk_init_kernel, dim3(n_states), dim3(256), 0, stream, st, kcount);
     const bool last_picks = topk_last_picks(full_grid, n_states);
 #define MLC_HIST(WT, GT, V, F)                                                                    \
-  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F>), dim3(full_grid, (unsigned)count, K),        \
+  hipLaunchKernelGGL((topk_hist_kernel<WT, GT, V, F, G>), dim3(full_grid, (unsigned)count, K),        \
                      dim3(OT_THREADS), 0, stream, args, st, elems, (int)count, ef_beta, (int)last_picks);   \
   if (!last_picks) hipLaunchKernelGGL(topk_pick_kernel, dim3(n_states), dim3(OT_THREADS), 0, stream, st)
 #define MLC_PASSES(WT, GT, V)                                                                     \
@@ -2066,6 +2071,13 @@ int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, i
   }
 #undef MLC_UPDATE
   return check_launch();
+}
+
+int launch_topk_outer(const TopkGroup* groups, int n_groups, int worker_dtype, int global_dtype, int64_t elems, int K,
+                      unsigned int kcount, float ef_beta, float eta_out, float mu, int nesterov, int write_back,
+                      void* workspace, hipStream_t stream) {
+  return (n_groups > 1 ? launch_topk<2> : launch_topk<1>)(groups, worker_dtype, global_dtype, elems, K, kcount, ef_beta, eta_out, mu,
+                                                          nesterov, write_back, workspace, stream);
 }
 
 }  // namespace mlc
