@@ -273,40 +273,42 @@ __device__ __forceinline__ float key_float(unsigned int k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// Up to OUTER_MAX_SEG groups and OUTER_MAX_SEG_K workers a launch.
+// Up to OUTER_MAX_SEG groups of OUTER_MAX_SEG_K workers a launch, or as many such parts of a group's workers, each in a layer of the
+// grid (12 workers, 4 bits, error feedback, two groups of 4 x 1053 x 128 and 18 x 96 x 1024: 145 us with three launches for each
+// part, 126 like this).
 template <typename T> struct SegPtrs { T p[OUTER_MAX_SEG_K]; };
+static_assert(OUTER_MAX_SEG * OUTER_MAX_SEG_K >= MLC_MAX_WORKERS, "any group's workers go into one launch");
 struct RangeSeg {
   SegPtrs<void*> w;
   SegPtrs<float*> ef, scales, offsets;
   const void* theta_g;
   long elems;
-  unsigned int count, nblk, blk0;      // matrices; workgroups a matrix; first workgroup of the group
+  unsigned int count, nblk;            // matrices; workgroups a matrix
+  int workers;
 };
-struct RangeTable { RangeSeg s[OUTER_MAX_SEG]; int nseg; };
+struct RangeTable { RangeSeg s[OUTER_MAX_SEG]; };
 
 __global__ void matrix_range_init_kernel(RangeTable tab, int offset) {
   const RangeSeg& sg = tab.s[blockIdx.z];
   const long b = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int k = blockIdx.y;
-  if (b >= sg.count) return;
+  if (b >= sg.count || k >= sg.workers) return;
   reinterpret_cast<unsigned int*>(sg.scales.p[k])[b] = 0u;                      // below every key
   if (offset) reinterpret_cast<unsigned int*>(sg.offsets.p[k])[b] = 0xffffffffu;   // above every key
 }
 
-// The ranges of all workers of a piece, so that theta_g is read once and not once a worker: all their loads are under way
-// together (KM: their number, or the next power of two above it).  Whole steps with error feedback, eight workers, a grid
+// The ranges of all workers of a piece, so that theta_g is read once and not once a worker (KM: their number, or the next power of two
+// above it; without residuals all their loads are under way together, with them a worker's at a time).  Whole steps with error feedback, eight workers, a grid
 // dimension for the workers and now, us: 2 x 3560 x 5504 and its square 3611 and 3200; without feedback 12 x 512 x 1024 with bf16 workers
 // 782 and 470.
 template <typename WT, typename GT, bool VEC, int KM>
-__global__ __launch_bounds__(OT_THREADS) void matrix_range_kernel(RangeTable tab, int K, QuantForm form) {
+__global__ __launch_bounds__(OT_THREADS) void matrix_range_kernel(RangeTable tab, QuantForm form) {
   __shared__ float red[2][KM][OT_THREADS / 64];
-  int si = 0;
-#pragma unroll
-  for (int i = 1; i < OUTER_MAX_SEG; ++i)
-    if (i < tab.nseg && blockIdx.x >= tab.s[i].blk0) si = i;
-  const RangeSeg& sg = tab.s[si];
-  const unsigned int at = blockIdx.x - sg.blk0, blk = at % sg.nblk;
-  const long b = at / sg.nblk, elems = sg.elems;
+  const RangeSeg& sg = tab.s[blockIdx.z];
+  const int K = sg.workers;
+  const unsigned int blk = blockIdx.x % sg.nblk;
+  const long b = blockIdx.x / sg.nblk, elems = sg.elems;
+  if (b >= sg.count) return;
   const GT* tg = reinterpret_cast<const GT*>(sg.theta_g) + b * elems;
   const bool fb = sg.ef.p[0] != nullptr;                  // all workers have residuals, or none
   float mn[KM], mx[KM];
@@ -353,7 +355,7 @@ __global__ void matrix_range_finish_kernel(RangeTable tab, QuantForm form) {
   const RangeSeg& sg = tab.s[blockIdx.z];
   const long b = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int k = blockIdx.y;
-  if (b >= sg.count) return;
+  if (b >= sg.count || k >= sg.workers) return;
   float* scale = sg.scales.p[k] + b;
   if (form.offset) {
     float* lo = sg.offsets.p[k] + b;
@@ -1634,27 +1636,27 @@ QuantForm make_quant_form(int bits, int offset, int64_t rows_per_range, float ef
 
 // Workgroups a matrix at most: each ends with the reduction of its ranges, so no more than fill the chip (512 whatever the count, with
 // one worker: 18 layers of 848 and 2368 718 us, now 637; 9 of 1280 and 1888, two workers, 732 and 685).
-static long range_blocks(long count) { return count < 4 ? 2048 / count : max(1L, 1536 / count); }
+static long range_blocks(long count, long full) { return cap_blocks(full, count < 4 ? 2048 / count : max(1L, 1536 / count)); }
 
 int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K, const QuantForm& form,
                          hipStream_t stream) {
   if (ng < 1 || ng > OUTER_MAX_SEG) return MLC_ERR_UNSUPPORTED;
   const bool fb = has_residuals(gs[0].ef);
-  for (int k0 = 0; k0 < K; k0 += OUTER_MAX_SEG_K) {
-    const int workers = min(K - k0, OUTER_MAX_SEG_K);
-    RangeTable tab;
-    tab.nseg = ng;
-    long blk = 0, most = 0;
-    bool vec = true;
-    double bytes = 0.0;
-    for (int i = 0; i < OUTER_MAX_SEG; ++i) {
-      RangeSeg& sg = tab.s[i];
-      if (i >= ng) { sg = tab.s[0]; sg.blk0 = 0xffffffffu; continue; }
-      const OuterGroupArgs& g = gs[i];
-      const long count = g.rows / g.m;
-      if (count > 65535) return MLC_ERR_SHAPE;
+  RangeTable tab;
+  int nseg = 0;
+  long most_blocks = 0, most = 0;
+  bool vec = true;
+  double bytes = 0.0;
+  for (int i = 0; i < ng; ++i) {
+    const OuterGroupArgs& g = gs[i];
+    const long count = g.rows / g.m;
+    if (count > 65535) return MLC_ERR_SHAPE;
+    for (int k0 = 0; k0 < K; k0 += OUTER_MAX_SEG_K) {
+      if (nseg == OUTER_MAX_SEG) return MLC_ERR_UNSUPPORTED;
+      RangeSeg& sg = tab.s[nseg++];
+      sg.workers = min(K - k0, OUTER_MAX_SEG_K);
       for (int k = 0; k < OUTER_MAX_SEG_K; ++k) {
-        const bool there = k < workers;
+        const bool there = k < sg.workers;
         sg.w.p[k] = there ? g.w.p[k0 + k] : nullptr;
         sg.ef.p[k] = there ? g.ef.p[k0 + k] : nullptr;
         sg.scales.p[k] = there ? g.scales.p[k0 + k] : nullptr;
@@ -1664,17 +1666,20 @@ int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int
       sg.elems = g.m * g.n;
       vec = vec && sg.elems % 8 == 0;
       sg.count = (unsigned int)count;
-      sg.nblk = (unsigned int)cap_blocks(((sg.elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, range_blocks(count));
-      sg.blk0 = (unsigned int)blk;
-      blk += (long)sg.nblk * count;
+      sg.nblk = (unsigned int)range_blocks(count, ((sg.elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS);
+      most_blocks = max(most_blocks, (long)sg.nblk * count);
       most = max(most, count);
-      bytes += (double)g.rows * g.n * (workers * esize(worker_dtype) + esize(global_dtype) + (fb ? 4.0 * workers : 0.0));
+      bytes += (double)g.rows * g.n * (sg.workers * esize(worker_dtype) + esize(global_dtype) + (fb ? 4.0 * sg.workers : 0.0));
     }
-    LaunchScope scope(MLC_KERNEL_QUANTIZE, stream, 0.0, bytes);
-    const dim3 small((unsigned)((most + 255) / 256), (unsigned)workers, (unsigned)ng);
-    hipLaunchKernelGGL(matrix_range_init_kernel, small, dim3(256), 0, stream, tab, form.offset);
+  }
+  for (int i = nseg; i < OUTER_MAX_SEG; ++i) tab.s[i] = tab.s[0];
+  const int workers = min(K, OUTER_MAX_SEG_K);
+  LaunchScope scope(MLC_KERNEL_QUANTIZE, stream, 0.0, bytes);
+  const dim3 small((unsigned)((most + 255) / 256), (unsigned)workers, (unsigned)nseg);
+  hipLaunchKernelGGL(matrix_range_init_kernel, small, dim3(256), 0, stream, tab, form.offset);
 #define MLC_RANGE(WT, GT, V, KM)                                                                  \
-  hipLaunchKernelGGL((matrix_range_kernel<WT, GT, V, KM>), dim3((unsigned)blk), dim3(OT_THREADS), 0, stream, tab, workers, form)
+  hipLaunchKernelGGL((matrix_range_kernel<WT, GT, V, KM>), dim3((unsigned)most_blocks, 1, (unsigned)nseg), dim3(OT_THREADS), 0, \
+                     stream, tab, form)
 #define MLC_RANGE_K(WT, GT, V)                                                                    \
   do {                                                                                            \
     if (workers == 1) MLC_RANGE(WT, GT, V, 1);                                                    \
@@ -1683,15 +1688,12 @@ int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int
     else MLC_RANGE(WT, GT, V, OUTER_MAX_SEG_K);                                                   \
   } while (0)
 #define MLC_CALL(WT, GT) do { if (vec) MLC_RANGE_K(WT, GT, true); else MLC_RANGE_K(WT, GT, false); } while (0)
-    MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
+  MLC_DISPATCH2(worker_dtype, global_dtype, MLC_CALL);
 #undef MLC_CALL
 #undef MLC_RANGE_K
 #undef MLC_RANGE
-    hipLaunchKernelGGL(matrix_range_finish_kernel, small, dim3(256), 0, stream, tab, form);
-    const int rc = check_launch();
-    if (rc != MLC_OK) return rc;
-  }
-  return MLC_OK;
+  hipLaunchKernelGGL(matrix_range_finish_kernel, small, dim3(256), 0, stream, tab, form);
+  return check_launch();
 }
 
 int launch_quantize(const WorkerPtrs& w, int worker_dtype, const void* theta_g, int global_dtype,

@@ -389,3 +389,9 @@ def test_groups_that_share_launches(shapes, K, wd, gd, bits, offset, ef, again):
         for name in ("worker_params", "codes", "scales", "offsets", "residuals"):
             for a, b in zip(getattr(got, name) or [], getattr(want, name) or []):
                 assert torch.equal(a, b), name
+
+
+# Ranges per matrix of more workers than an entry of the kernels' table holds (8): their parts, whole and not, share the launches
+@pytest.mark.parametrize("K,n,offset", [(8, 64, True), (9, 64, True), (16, 130, False), (17, 130, True), (32, 66, False)])
+def test_ranges_per_matrix_of_many_workers(K, n, offset):
+    test_quantiser_forms_bit_exact(3, 9, n, K, BF16, F32, 4, offset, True, K % 2 == 1, False)
