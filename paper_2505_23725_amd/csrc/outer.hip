@@ -1634,9 +1634,16 @@ QuantForm make_quant_form(int bits, int offset, int64_t rows_per_range, float ef
   return f;
 }
 
-// Workgroups a matrix at most: each ends with the reduction of its ranges, so no more than fill the chip (512 whatever the count, with
-// one worker: 18 layers of 848 and 2368 718 us, now 637; 9 of 1280 and 1888, two workers, 732 and 685).
-static long range_blocks(long count, long full) { return cap_blocks(full, count < 4 ? 2048 / count : max(1L, 1536 / count)); }
+// Workgroups a matrix.  Each ends with an atomic for every worker, and those of a worker meet in one line of memory, which takes
+// one in 20 ns: one matrix of 1024 x 4096, one worker, is ready in 30 us with 256 workgroups, 31 with 512, 36 with 1024, 47 with
+// 2048.  More of them are worth it where loads are slow, at element alignment from three workers without residuals on: eight of
+// 4001 x 4003 260 us with 512, 234 with 1024, of 120 x 511 x 511 618, 556 and with 1536 547.  In all, several matrices: 120 of 512 x 512
+// with one worker 134 us with 480 workgroups, 126 with 720 or 1440, 129 with 3000; 16 of 1024 x 1024 73, 76, 83 and 97 with 512 to 3072.
+static long range_blocks(long count, long elems, int K, bool fb) {
+  const bool many = elems % 8 && K > 2 && !fb;
+  const long all = count < 4 ? (many ? 1024 : 512) : (many ? 1536 : 768);
+  return cap_blocks(((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, all / count);
+}
 
 int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K, const QuantForm& form,
                          hipStream_t stream) {
@@ -1666,7 +1673,7 @@ int launch_matrix_ranges(const OuterGroupArgs* gs, int ng, int worker_dtype, int
       sg.elems = g.m * g.n;
       vec = vec && sg.elems % 8 == 0;
       sg.count = (unsigned int)count;
-      sg.nblk = (unsigned int)range_blocks(count, ((sg.elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS);
+      sg.nblk = (unsigned int)range_blocks(count, sg.elems, K, fb);
       most_blocks = max(most_blocks, (long)sg.nblk * count);
       most = max(most, count);
       bytes += (double)g.rows * g.n * (sg.workers * esize(worker_dtype) + esize(global_dtype) + (fb ? 4.0 * sg.workers : 0.0));
