@@ -733,9 +733,11 @@ __global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3
   quantize_outer_multi_body<WT, GT, RAG, KC, 5>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
 }
 
-// Several workers, rows of up to 512 (TOP 0) or 1024 columns: as many wavefronts a SIMD as their registers allow, where the kernel of
-// all lengths has three.  160 / 40 / 40 matrices of 128 x 128, 128 x 256 and 256 x 128, 4 bits, us: two workers 53 to 39, eight 138 to 96, with
-// error feedback 273 to 173; 24 / 6 / 6 of 512 x 512 and 512 x 1024, eight workers 174 to 153, with error feedback 296 to 299.
+// Rows of up to 512 (TOP 0) or 1024 columns: as many wavefronts a SIMD as their registers allow, where the kernel of
+// all lengths has three.  160 / 40 / 40 matrices of 128 x 128, 128 x 256 and 256 x 128, 4 bits, us: one worker 37 to 31, two 53 to 39, eight
+// 138 to 96, with error feedback 273 to 173; 24 / 6 / 6 of 512 x 512 and 512 x 1024, eight workers 174 to 153, with error feedback 296
+// to 299 (where the memory stream bounds both); 800 / 200 / 200 of 303 x 303 and 303 x 831, 8 bits, one worker 1097 to 988, which ranges per
+// matrix in launches of a group each, with registers for their own rows alone, would do in 899.
 // Or, TOP 4, ragged rows of four vectors a thread alone: two wavefronts a SIMD, since for three 60 and more registers of the loop over the
 // workers go to memory (8 / 2 / 2 of 1402 x 1402 and 1402 x 4098, eight workers of float32, 846 to 574; two of bf16 with error
 // feedback 442 to 383; next to rows of two vectors, 606 and 1818 columns, it would be 341 to 378).
@@ -1940,9 +1942,9 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
                      inv_k, nesterov, write_back)
 #define MLC_QM_K(WT, GT, RAG)                                                                     \
   do {                                                                                            \
-    if (K == 1) MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 1);                            \
-    else if (top == 0) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 0);                    \
+    if (top == 0) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 0);                         \
     else if (top == 1) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 1);                    \
+    else if (K == 1) MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 1);                       \
     else if (RAG && four) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, true, 4);                \
     else MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 0);                                   \
   } while (0)
