@@ -135,7 +135,9 @@ __device__ __forceinline__ float ef_input(float delta, float residual, float bet
 // 4096, eight, 151 -> 134, one, 423 -> 420.
 struct Divider { float scale, lo, inv, limit, low, high; };
 // SCALAR: in scalar registers, for a range that a wavefront's lanes share.  (It frees vector registers where rows are alone in a
-// launch, rows of 2560 and 10240 with four workers 560 -> 552 us; beside others it only adds moves, 736 and 2432 with eight 153 -> 160.)
+// launch, rows of 2560 and 10240 with four workers 560 -> 552 us, or have four vectors a thread, which go to memory by the dozen
+// otherwise: 8 of 1280 x 1280 and 2 of 1280 x 4416, eight workers of float32 with error feedback, 628 -> 587, 24 of 1024 x 1536 and 6 of
+// 1536 x 1024, two of bf16, 206 -> 199.  Fewer vectors beside others it only costs moves: 736 and 2432 with eight 153 -> 160.)
 template <bool SCALAR>
 __device__ __forceinline__ Divider make_divider(const Range& r, const QuantForm& f) {
   auto uniform = [](float v) { return SCALAR ? __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))) : v; };
@@ -702,7 +704,7 @@ __device__ __forceinline__ void quantize_outer_multi_body(const QuantSegTable& t
   form.rows_per_range = sg.rows_per_range;
   const long blk = (long)(blockIdx.x - sg.blk0);
 #define MLC_SEG_BODY(IDX)                                                                              \
-  quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG, KC, false>(                             \
+  quantize_rows_reg_body<WT, GT, reg_cfg(IDX).nv, reg_cfg(IDX).g, true, RAG, KC, (reg_cfg(IDX).nv == 4)>(                             \
       sg.w, (GT*)sg.theta_g, sg.u, sg.codes, sg.scales, sg.offsets, sg.ef, sg.rows, sg.n, K, form, eta, \
       mu, inv_k, nesterov, write_back, 0, nullptr, nullptr, nullptr, blk)
   // uniform over the workgroup
