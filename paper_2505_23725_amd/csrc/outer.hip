@@ -649,13 +649,14 @@ __device__ __forceinline__ void quantize_rows_reg_body(
 // Wavefronts per SIMD the register allocation is held to: one more than the compiler reaches on
 // its own where that is a few registers away (these kernels wait on memory with little else to
 // do, so a resident wavefront more is worth more than the registers).  Not so the update of ragged rows with four vectors, whose loop
-// over the workers spilt up to 57 of them (2 x 1402 x 4096 and its squares, eight workers of float32, 799 us, now 531).
+// over the workers spilt up to 57 of them (2 x 1402 x 4096 and its squares, eight workers of float32, 799 us, now 531), unless
+// three make do with one round of workgroups where two need another (quant_three_waves).
 constexpr int quant_min_waves(int nv, bool outer, bool ragged) {
   return outer ? (nv <= 1 ? 6 : nv <= 2 ? 4 : nv <= 4 ? (ragged ? 2 : 3) : 1) : (nv <= 1 ? 7 : nv <= 2 ? 5 : nv <= 4 ? 3 : 1);
 }
 
-template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG>
-__global__ __launch_bounds__(G ? OT_THREADS : 1024, quant_min_waves(NV, OUTER, RAG)) void quantize_rows_reg_kernel(
+template <typename WT, typename GT, int NV, int G, bool OUTER, bool RAG, int MW = quant_min_waves(NV, OUTER, RAG)>
+__global__ __launch_bounds__(G ? OT_THREADS : 1024, MW) void quantize_rows_reg_kernel(
     WorkerPtrs w, GT* __restrict__ theta_g, float* __restrict__ u, CodePtrs codes, ScalePtrs scales,
     OffsetPtrs offsets, ResidualPtrs ef, long rows, int n, int K, QuantForm form, float eta, float mu,
     float inv_k, int nesterov, int write_back, int requant, uint8_t* mean_codes, float* mean_scales,
@@ -743,8 +744,8 @@ __global__ __launch_bounds__(OT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3
 // Or, TOP 4, ragged rows of four vectors a thread alone: two wavefronts a SIMD, since for three 60 and more registers of the loop over the
 // workers go to memory (8 / 2 / 2 of 1402 x 1402 and 1402 x 4098, eight workers of float32, 846 to 574; two of bf16 with error
 // feedback 442 to 383; next to rows of two vectors, 606 and 1818 columns, it would be 341 to 378).
-template <typename WT, typename GT, bool RAG, int TOP>
-__global__ __launch_bounds__(OT_THREADS, quant_min_waves(reg_cfg(TOP).nv, true, RAG)) void quantize_outer_narrow_kernel(
+template <typename WT, typename GT, bool RAG, int TOP, int MW = quant_min_waves(reg_cfg(TOP).nv, true, RAG)>
+__global__ __launch_bounds__(OT_THREADS, MW) void quantize_outer_narrow_kernel(
     QuantSegTable tab, int K, QuantForm form, float eta, float mu, float inv_k, int nesterov, int write_back) {
   quantize_outer_multi_body<WT, GT, RAG, 0, TOP>(tab, K, form, eta, mu, inv_k, nesterov, write_back);
 }
@@ -1795,6 +1796,15 @@ int launch_dequant_outer(const WorkerPtrs& w, int worker_dtype, void* theta_g, i
   return check_launch();
 }
 
+// Do ragged rows of four vectors of bf16 take the kernel that is held to three wavefronts a SIMD?  `blocks` workgroups of four
+// wavefronts each are one round of it where two wavefronts a SIMD need a second, nearly empty one: n 1501, 8 bits, us with two
+// and three, two workers with error feedback, 500 workgroups 24.1 and 26.4, 540 36.3 and 29.2, 760 39.2 and 34.3, 800 40.1 and 47.3; eight workers
+// 42 and 47, 68 and 53, 70 and 55, 76 and 82.  (Of 1100 workgroups it is 0.93 to 1.05 of two, of float32 workers 1.18, of rows over
+// 2048 with a bf16 global copy, which spill most, 0.98 to 1.22.)
+static bool quant_three_waves(long blocks, int worker_dtype) {
+  return worker_dtype == MLC_BF16 && blocks > 2 * 256 && blocks <= 3 * 256;
+}
+
 // Returns MLC_ERR_UNSUPPORTED when the one-pass kernel does not cover the request (the
 // caller then runs the quantiser and the dequantising update as two launches).
 int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* theta_g, int global_dtype,
@@ -1825,25 +1835,29 @@ int launch_quantize_outer_fused(const WorkerPtrs& w, int worker_dtype, void* the
                                            2 * esize(global_dtype) + 8) + (double)rows * 4 * K;
   LaunchScope scope(MLC_KERNEL_DEQUANT_OUTER, stream, 0.0, bytes);
   const float inv_k = 1.0f / (float)K;
-#define MLC_QO_R(WT, GT, NV, G, RAG)                                                              \
-  hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, true, RAG>), dim3((unsigned)nblk),   \
+  const bool three = quant_ragged(n) && quant_three_waves(nblk, worker_dtype);
+#define MLC_QO_R(WT, GT, NV, G, ...)                                                              \
+  hipLaunchKernelGGL((quantize_rows_reg_kernel<WT, GT, NV, G, true, __VA_ARGS__>), dim3((unsigned)nblk), \
                      dim3(threads), 0, stream, w, (GT*)theta_g, u, codes, scales, offsets, ef,  \
                      (long)rows, (int)n, K, form, eta_out, mu, inv_k, nesterov, write_back, requant, \
                      mean_codes, mean_scales, mean_offsets)
 #define MLC_QO(WT, GT, NV, G)                                                                     \
   do { if (quant_ragged(n)) MLC_QO_R(WT, GT, NV, G, true); else MLC_QO_R(WT, GT, NV, G, false); } while (0)
+#define MLC_QO_4(WT, GT, G)                                                                       \
+  do { if (three) MLC_QO_R(WT, GT, 4, G, true, sizeof(WT) == 2 && (G == 64 || sizeof(GT) == 4) ? 3 : 2); else MLC_QO(WT, GT, 4, G); } while (0)
 #define MLC_QO_NV(WT, GT)                                                                         \
   do {                                                                                            \
     if (whole == 2) MLC_QO(WT, GT, 2, 0); else if (whole == 3) MLC_QO(WT, GT, 3, 0);              \
     else if (g == 64) { if (nv == 1) MLC_QO(WT, GT, 1, 64); else if (nv == 2) MLC_QO(WT, GT, 2, 64);   \
-                   else MLC_QO(WT, GT, 4, 64); }                                                  \
-    else { if (nv <= 2) MLC_QO(WT, GT, 2, 256); else if (nv == 4) MLC_QO(WT, GT, 4, 256);         \
+                   else MLC_QO_4(WT, GT, 64); }                                                   \
+    else { if (nv <= 2) MLC_QO(WT, GT, 2, 256); else if (nv == 4) MLC_QO_4(WT, GT, 256);          \
            else MLC_QO(WT, GT, 6, 256); }                                                         \
   } while (0)
   if (worker_dtype == MLC_BF16 && global_dtype == MLC_F32) MLC_QO_NV(bf16_t, float);
   else if (worker_dtype == MLC_BF16) MLC_QO_NV(bf16_t, bf16_t);
   else MLC_QO_NV(float, float);
 #undef MLC_QO_NV
+#undef MLC_QO_4
 #undef MLC_QO
 #undef MLC_QO_R
   return check_launch();
@@ -1939,14 +1953,16 @@ int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dty
   }
   LaunchScope scope(MLC_KERNEL_DEQUANT_OUTER, stream, 0.0, bytes);
   const float inv_k = 1.0f / (float)K;
-#define MLC_QM_R(KERNEL, WT, GT, RAG, X)                                                          \
-  hipLaunchKernelGGL((KERNEL<WT, GT, RAG, X>), dim3((unsigned)blk), dim3(OT_THREADS), 0, stream, tab, K, form, eta_out, mu, \
+#define MLC_QM_R(KERNEL, WT, GT, RAG, ...)                                                        \
+  hipLaunchKernelGGL((KERNEL<WT, GT, RAG, __VA_ARGS__>), dim3((unsigned)blk), dim3(OT_THREADS), 0, stream, tab, K, form, eta_out, mu, \
                      inv_k, nesterov, write_back)
 #define MLC_QM_K(WT, GT, RAG)                                                                     \
   do {                                                                                            \
     if (top == 0) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 0);                         \
     else if (top == 1) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, RAG, 1);                    \
     else if (K == 1) MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 1);                       \
+    else if (RAG && four && quant_three_waves((long)blk, worker_dtype))                           \
+      MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, true, 4, sizeof(WT) == 2 ? 3 : 2);           \
     else if (RAG && four) MLC_QM_R(quantize_outer_narrow_kernel, WT, GT, true, 4);                \
     else MLC_QM_R(quantize_outer_multi_kernel, WT, GT, RAG, 0);                                   \
   } while (0)

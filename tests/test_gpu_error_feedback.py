@@ -395,3 +395,16 @@ def test_groups_that_share_launches(shapes, K, wd, gd, bits, offset, ef, again):
 @pytest.mark.parametrize("K,n,offset", [(8, 64, True), (9, 64, True), (16, 130, False), (17, 130, True), (32, 66, False)])
 def test_ranges_per_matrix_of_many_workers(K, n, offset):
     test_quantiser_forms_bit_exact(3, 9, n, K, BF16, F32, 4, offset, True, K % 2 == 1, False)
+
+
+# Ragged rows of four vectors in 513 to 768 workgroups, which have kernels with a wavefront more a SIMD: a row to a wavefront, with an
+# incomplete last workgroup, and to a workgroup; alone and beside others
+@pytest.mark.parametrize("m,n,K,wd,gd", [(2055, 1041, 2, BF16, F32), (3071, 1030, 1, BF16, BF16), (520, 4106, 3, BF16, F32),
+                                         (520, 4106, 6, BF16, BF16), (2055, 1041, 1, F32, F32)])
+def test_ragged_rows_of_one_round(m, n, K, wd, gd):
+    test_quantiser_forms_bit_exact(1, m, n, K, wd, gd, 8, False, False, K != 3, False)
+
+
+@pytest.mark.parametrize("gd", [F32, BF16])
+def test_ragged_groups_of_one_round(gd):
+    test_groups_that_share_launches([(2, 400, 1402), (1, 350, 4098)], 2, BF16, gd, 4, True, True, None)
