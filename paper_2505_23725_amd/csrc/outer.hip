@@ -161,8 +161,13 @@ __device__ __forceinline__ void quant_levels4(const float* v, const Divider& d, 
     worst = fmaxf(worst, fabsf(__fsub_rn(t, q[j])));
   }
   if (worst >= d.limit) {
+    if (d.scale > 0.f) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = d.scale > 0.f ? rintf(__fsub_rn(v[j], d.lo) / d.scale) : 0.f;
+      for (int j = 0; j < 4; ++j) q[j] = rintf(__fsub_rn(v[j], d.lo) / d.scale);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) q[j] = 0.f;
+    }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) q[j] = __builtin_amdgcn_fmed3f(q[j], d.low, d.high);     // (a NaN becomes the lowest level)
