@@ -1649,9 +1649,11 @@ QuantForm make_quant_form(int bits, int offset, int64_t rows_per_range, float ef
 // 2048.  More of them are worth it where loads are slow, at element alignment from three workers without residuals on: eight of
 // 4001 x 4003 260 us with 512, 234 with 1024, of 120 x 511 x 511 618, 556 and with 1536 547.  In all, several matrices: 120 of 512 x 512
 // with one worker 134 us with 480 workgroups, 126 with 720 or 1440, 129 with 3000; 16 of 1024 x 1024 73, 76, 83 and 97 with 512 to 3072.
+// Hundreds of matrices have many such lines, and one workgroup each for several workers is too uneven a load: 800 of 128 x 256, eight
+// workers with residuals, 785 us with one, 744 and 733 with two and three; 1000 of 40 x 304 379, 364 and 360.
 static long range_blocks(long count, long elems, int K, bool fb) {
   const bool many = elems % 8 && K > 2 && !fb;
-  const long all = count < 4 ? (many ? 1024 : 512) : (many ? 1536 : 768);
+  const long all = count < 4 ? (many ? 1024 : 512) : count > 512 && K > 2 ? 2400 : many ? 1536 : 768;
   return cap_blocks(((elems + 7) / 8 + OT_THREADS - 1) / OT_THREADS, all / count);
 }
 
