@@ -1066,7 +1066,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& g, Deal deal) {
 // compute units pays for a partly empty last round; sharing a launch leaves one such round instead
 // of one per group.  XCD x still owns a contiguous range of every product's tile order; inside it
 // each product of one depth starts with the workgroup after the one that took the previous product's last
-// tile, and deal_tiles evens out the time of different depths.  (Gram products of 16 x 1024 x 2816, 0.6
+// tile, and so do small tiles of any depth; deal_tiles evens out the time of large tiles of different depths.  (Gram products of 16 x 1024 x 2816, 0.6
 // rounds, and 32 x 1024 x 1024, 1.25: 135 us in two launches, 100 in one; of a 15B-scale layer 1350
 // and 1240.  Launches apart cost about 7 us each beside what their rounds cost.)
 constexpr int MAX_MULTI = 3;
@@ -1220,10 +1220,10 @@ long tiles_of(const GemmDesc& d, int tile) {
 // Microseconds that a launch of `tiles` output tiles of kt K tiles takes: a first round of one tile per
 // compute unit, and further ones that overlap its ends.  The 256 x 256 tile runs faster in a round that
 // leaves compute units idle (the chip is power-limited).  Symmetric results pay for the transposed
-// copy, the polynomial for its C operand too.  Fitted to kernel traces of earlier forms of all three tiles,
-// whose epilogues were longer: over 194 batches (1 to 200 matrices of 128 to 2048, K to 4096) in each tile
-// that fits, nine in ten launches now take 0.83 to 1.09 of this, the median 0.91 with 64 x 64 tiles and 0.95
-// with the others.
+// copy, the polynomial for its C operand too.  Fitted to kernel traces of earlier forms of all three tiles, with longer
+// epilogues, no triangles on the diagonal, no half tiles at the edge and no results written through: over 194 batches (1 to
+// 200 matrices of 128 to 2048, K to 4096) in each tile that fits, nine in ten launches now take 0.82 to 1.01 of this with 256 x 256
+// tiles, 0.83 to 1.17 with 128 x 128 and 0.82 to 1.19 with 64 x 64, the medians 0.94, 0.92 and 0.95.
 enum { FORM_GRAM, FORM_POLY, FORM_APPLY };
 int form_of(const GemmDesc& d) { return !d.symmetric ? FORM_APPLY : d.C ? FORM_POLY : FORM_GRAM; }
 double estimate_us(int tile, int form, long tiles, int kt, int cus) {
@@ -1248,8 +1248,8 @@ double estimate_us(int tile, int form, long tiles, int kt, int cus) {
 // more than 64 MB, of which X, its next iterate, A and B' fill the 256 MB memory-side cache: the operand
 // bytes then decide (Gram products of 32 x 1024 x 1024, alone 56 us in tiles of 256 and 52 in tiles of
 // 128, took 62 and 68 beside 16 of 1024 x 2816, with earlier epilogues).  Over those 194 batches the choice takes
-// 1.006 of the time of the best tile for each; one launch in ten is over 1.03, the worst (apply product of 72 x 256 x
-// 1024) 1.30.  The tile is chosen before it is known whether sets of different depth will share a launch.  The 64 x 64
+// 1.007 of the time of the best tile for each; one launch in thirteen is over 1.03, the worst (polynomial of 148 x 1152 x
+// 1152, whose half tiles the 256 x 256 tile would do faster) 1.25.  The tile is chosen before it is known whether sets of different depth will share a launch.  The 64 x 64
 // tile's ring needs four K tiles.
 int pick_tile(const GemmDesc* const* d, int n, int cus) {
   long tiles[3] = {0, 0, 0};
@@ -1291,6 +1291,8 @@ double set_us(const GemmSet& s, int cus) {
 // last stores as much again, and a partly empty round more: inner steps of three groups, 4 c of d x d, c of d x f and f x d, with sets
 // of different depth and divisors apart and together (6 to 10 us of it are launches of elementwise kernels): 4, 256 / 1000: 151 -> 119 us;
 // 2, 303 / 640: 179 -> 146; 1, 512 / 1536: 167 -> 133; 4, 768 / 2449: 645 -> 577; 3, 896 / 2944: 725 -> 645; 10, 512 / 640: 481 -> 465.
+// The bounds on rounds are not sharp: over 110 steps of two and three groups, 256 to 1280 wide, sets of one tile take 0.93 of their time
+// apart (0.83 to 1.00), and with every such pair together 0.98 to 1.01 of that.  Which launches they give is in the tests' sizes.
 bool join_sets(GemmSet& s, const GemmSet& t, int cus) {
   if (s.n + t.n > MAX_MULTI || (t.d[0]->b_kstrided != 0) != (s.d[0]->b_kstrided != 0)) return false;
   if (s.tile == 256 || t.tile == 256) return s.tile == t.tile;
@@ -1368,7 +1370,7 @@ int launch_ns_gemm_set(const GemmDesc* d, int n, hipStream_t stream) {
     if (done[i]) continue;
     // products that share a launch with product i whatever their tile: same depth (a whole tile then takes the
     // same time in each, so dealing tiles out evenly balances the time but for triangles, which take 0.7 to 0.9 of
-    // it), same divisors, same layout
+    // it), both fit for the large tile or neither, same layout
     GemmSet& s = sets[n_sets++];
     s.n = 0;
     for (int j = i; j < n && s.n < MAX_MULTI; ++j) {

@@ -1914,7 +1914,7 @@ int quant_reg_cfg(int64_t n) {
 }
 
 // One launch for the quantised outer step (quantise + dequantise + mean + eq. 3 + write-back)
-// of up to OUTER_MAX_SEG groups; ranges per row, no second quantisation.
+// of up to OUTER_MAX_SEG groups; ranges per row, or per matrix and ready (launch_matrix_ranges); no second quantisation.
 int launch_quantize_outer_multi(const OuterGroupArgs* gs, int ng, int worker_dtype, int global_dtype, int K,
                                 const QuantForm& form, float eta_out, float mu, int nesterov, int write_back,
                                 hipStream_t stream) {
