@@ -22,7 +22,7 @@ namespace mlc {
 //    3073  bf16, ragged  1.00 1.01  1.04  1.05  1.06  1.06  1.08  1.10  1.12
 //    4104  bf16          .80   .91   .85   .93   .95   .92   .99  1.05  1.07
 //    5001  bf16, ragged  .90   .96  1.04  1.06  1.04  1.03  1.05  1.02  1.03
-//          f32, ragged   .76   .72   .70   .70   .67   .64   .64   .62   .61    (four vectors a thread spill there)
+//          f32, ragged   .76   .72   .70   .70   .67   .64   .64   .62   .61    (four vectors a thread spilt there)
 //    6152  bf16          .84   .93   .90   .97  1.04  1.01  1.05  1.04   .98
 //          bf16, ef      .90   .91   .93   .90   .96   .93   .95   .84   .85
 //    8001  bf16, ragged  .79   .82   .88   .90   .91   .94   .95  1.03  1.03
@@ -30,6 +30,9 @@ namespace mlc {
 //          bf16, ef      .92   .93   .97   .96   .94   .97  1.00  1.02  1.03
 //   12296  bf16          .80   .81   .79   .79   .79   .80   .79   .77   .81
 //   24576  bf16          .91   .82   .83   .79   .78   .79   .77   .77   .77    (three vectors)
+// Ragged rows of four vectors have two wavefronts a SIMD since and no longer spill: of float32 workers, or with a bf16 global copy,
+// the row-sized workgroup takes 0.91 to 1.09 of their time now (4201 to 5001 columns, four and eight replicas; 1.29 and 0.83 with
+// 16, as few rows fill the last round), and 0.83 to 0.90 with 16 replicas over 6144.
 // (The rows of 3073 and of 8192 without feedback are at 8 and 4 bits; rows over 6144 and four replicas take 0.95 of the
 // time at 4 bits, 1.00 to 1.03 at 8.)  The mean's second quantisation, another reduction over the row, costs a
 // larger workgroup more: 1.03 at each line's last number of replicas without it, 0.98 two below.
@@ -42,8 +45,8 @@ inline int quant_whole_row(const QuantRow& q) {
   int most;                                  // replicas
   if (q.n % 8 != 0) {
     if (q.n <= 4096) return q.n <= 3072 && !q.worker_f32 && q.K >= 3 && q.K <= 5 ? 2 : 0;
-    const bool spills = q.worker_f32 || q.global_bf16;
-    most = q.n <= 5120 ? (spills ? 32 : 2) : q.n <= 6144 ? 2 : spills ? 32 : 8;
+    const bool heavy = q.worker_f32 || q.global_bf16;
+    most = q.n <= 5120 ? (heavy ? 32 : 2) : q.n <= 6144 ? 2 : heavy ? 32 : 8;
   } else if (q.n <= 4096) {
     if (q.n > 3072 || q.worker_f32 || q.feedback || q.K <= 2) return 0;
     most = 16;
